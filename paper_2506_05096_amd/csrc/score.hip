@@ -1,14 +1,27 @@
 // astraea_score: selection metric S_token (paper Sec. 3.2 "Selection Metric"; Algorithm 1 steps 1-2).
 //
 // The score decides which tokens are selected, so its fp32 value is defined to the bit: per token
-// one accumulator walks the channels in ascending order.  To keep that order and still stream HBM
-// with coalesced 16-byte loads, a wavefront owns 64 consecutive tokens: it loads a
-// [64 tokens x 128 bytes] slab of both feature arrays (8 lanes cover one 128-byte row segment),
-// writes the fp32 differences into a wave-private LDS tile, and then lane t walks row t of the tile.
-// The next slab's loads are in flight while the current one is reduced.  No workgroup barrier is
-// needed: the tile is private to the wave and a wave's LDS operations complete in order.
+// one accumulator walks the channels in ascending order.  One lane owns a token's accumulator and the
+// rest of the design is about feeding it: both feature arrays are read in 16-byte vectors along the
+// rows, turned into fp32 differences, and handed over through an LDS tile whose row t the lane of
+// token t walks.  A chain step takes ~5 clocks, so 3072 channels are 6.5 us however many tokens there are.
+//
+// Two kernels, by the number of tokens:
+//  * score_kernel: a workgroup of two waves owns 16 tokens.  The first wave loads slabs of [16 tokens x 256
+//    bytes] of both arrays, four slabs in flight, and writes the differences; the second runs the chains, one
+//    slab behind, with one barrier per slab.  16 tokens per workgroup instead of 64 per wave is what a
+//    short sequence needs: at 17550 tokens 64 per wave make 275 waves, one per CU, and each slab's
+//    load latency, its conversion and its chain came one after the other.  Cold arrays, 64 per wave -> this
+//    kernel: 2025 x 3072 bf16 63 -> 14.5 us; 17550 x 3072 80 -> 41 us (5.3 TB/s); 16384 x 512 13.1 -> 8.8;
+//    4096 x 512 fp32 14.3 -> 8.5; 40000 x 1536 49 -> 42.  Tried: one wave for both jobs 22 and 49 us at
+//    2025 and 17550 tokens; slabs of 8 x 512 B the same, 32 x 128 B 20 us at 2025.
+//  * score_wide_kernel: a wave owns 64 tokens and does both jobs (a [64 x 128 byte] slab, the next one in flight).
+//    With three such waves per CU or more the latencies are covered and all 64 lanes run chains: 111 us
+//    (6.7 TB/s) at 60000 x 3072 and 217 us at 118800 x 3072, against 116 and 220 for the other kernel.
 //
 // HBM-bound: 2*C*sizeof(T) bytes read and 4 written per token.
+#include <type_traits>
+
 #include "common.h"
 
 #pragma clang fp contract(off)
@@ -18,10 +31,19 @@ namespace {
 
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
-constexpr int kWavesPerBlock = 4;
-constexpr int kTok = 64;            // tokens per wave (lane == token in the reduce phase)
-constexpr int kSegBytes = 128;      // bytes of each row handled per slab
-constexpr int kVecPerLane = 8;      // 64 rows * 8 vec16 per row / 64 lanes
+constexpr int kWideWavesPerBlock = 4;
+constexpr int kWideTok = 64;            // tokens per wave (lane == token in the reduce phase)
+constexpr int kWideSegBytes = 128;      // bytes of each row handled per slab
+constexpr int kWideVecPerLane = 8;      // 64 rows * 8 vec16 per row / 64 lanes
+// The wide kernel is for at least this many tokens: three waves per CU.
+constexpr int64_t kWideMinTokens = 3 * 256 * kWideTok;
+
+constexpr int kTok = 16;            // tokens per workgroup; lane t < kTok of the second wave reduces token t
+constexpr int kSegBytes = 256;      // bytes of each row handled per slab
+constexpr int kVecPerRow = kSegBytes / 16;
+constexpr int kRowsPerLoad = kWave / kVecPerRow;
+constexpr int kVecPerLane = kTok / kRowsPerLoad;
+constexpr int kDepth = 4;           // slabs in flight
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
@@ -61,6 +83,192 @@ template <> struct Elem<uint16_t> {
     }
 };
 
+// Delta from the channel sum, then the weights and the penalty of the metric.
+template <int MODE>
+__device__ __forceinline__ float finish_score(float acc, int64_t C, int64_t tok, const float *__restrict__ lse_weight,
+                                              const int32_t *__restrict__ skip_count,
+                                              const float *__restrict__ penalty_table, int32_t table_len, float w_alpha,
+                                              float w_beta)
+{
+    float delta = (MODE == ASTRAEA_DELTA_L2) ? sqrtf(acc) : acc / (float)C;
+    float sig = lse_weight ? delta * lse_weight[tok] : delta;
+    float sc = w_alpha * sig;
+    if (skip_count) {
+        int32_t n = skip_count[tok];
+        n = n < 0 ? 0 : n;
+        n = n > table_len - 1 ? table_len - 1 : n;
+        sc = __builtin_fmaf(w_beta, penalty_table[n], sc);
+    }
+    return sc;
+}
+
+// Publishes the loading wave's LDS writes to the reducing wave and its reads to the loading one.  Outstanding global
+// loads stay outstanding across it.
+__device__ __forceinline__ void publish()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+template <typename T, int MODE, bool VEC, bool NT>
+__global__ __launch_bounds__(2 * kWave) void score_kernel(
+    const T *__restrict__ x_cur, const T *__restrict__ x_prev, int64_t N, int64_t C, int64_t row_stride,
+    const float *__restrict__ lse_weight, const int32_t *__restrict__ skip_count,
+    const float *__restrict__ penalty_table, int32_t table_len, float w_alpha, float w_beta,
+    float *__restrict__ score_out)
+{
+    constexpr int EPV = Elem<T>::kPerVec;              // elements per 16-byte vector
+    constexpr int SEG = kSegBytes / (int)sizeof(T);    // channels per slab
+    constexpr int PLANES = EPV / 4;                    // a vector's floats are kept as 16-byte pieces, piece p in plane p
+    constexpr int PLANE = 4 * kVecPerRow;              // floats
+    constexpr int PITCH = SEG + 4;                     // floats; the 16 row reads of a piece hit distinct banks
+    __shared__ __attribute__((aligned(16))) float tile[2][kTok * PITCH];
+
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t tok0 = (int64_t)blockIdx.x * kTok;
+    const int32_t nslab = (int32_t)((C + SEG - 1) / SEG);
+
+    if (wave == 0) {
+        // load slot j of this lane: row j*kRowsPerLoad + lane/kVecPerRow of the slab, 16-byte vector lane%kVecPerRow
+        const int vrow = lane / kVecPerRow, vcol = lane % kVecPerRow;
+        const char *bc = reinterpret_cast<const char *>(x_cur + tok0 * row_stride);
+        const char *bp = reinterpret_cast<const char *>(x_prev + tok0 * row_stride);
+        uint32_t row_off[kVecPerLane];
+#pragma unroll
+        for (int j = 0; j < kVecPerLane; ++j) {
+            int64_t row = j * kRowsPerLoad + vrow;
+            if (tok0 + row > N - 1) row = N - 1 - tok0;   // ragged last workgroup: re-read a valid row, result unused
+            row_off[j] = (uint32_t)(row * row_stride * (int64_t)sizeof(T));
+        }
+        // Loads are unconditional, so that the wait for one slab never has to cover the next one's: past the last
+        // whole vector of the row a lane reads that vector again, and its difference counts as +0.
+        const int32_t c_lane = vcol * EPV, c_last = (int32_t)(C - C % EPV - EPV);
+        uint4v ra[kDepth][kVecPerLane], rb[kDepth][kVecPerLane];
+        auto issue = [&](int32_t s, auto buf_tag) __attribute__((always_inline)) {
+            constexpr int B = decltype(buf_tag)::value;
+            if (!VEC) return;
+            const uint32_t c = (s * SEG + c_lane < c_last ? s * SEG + c_lane : c_last) * (uint32_t)sizeof(T);
+#pragma unroll
+            for (int j = 0; j < kVecPerLane; ++j) {
+                ra[B][j] = load16<NT>(bc + (row_off[j] + c));
+                rb[B][j] = load16<NT>(bp + (row_off[j] + c));
+            }
+            __builtin_amdgcn_sched_barrier(0);         // the waits count on this order
+        };
+        // differences of slab s -> LDS tile
+        auto slab = [&](int32_t s, auto buf_tag) __attribute__((always_inline)) {
+            constexpr int B = decltype(buf_tag)::value;
+            const int32_t c0 = s * SEG;
+            auto differences = [&](auto whole_tag) __attribute__((always_inline)) {
+                const bool keep = decltype(whole_tag)::value || c0 + c_lane <= c_last;
+#pragma unroll
+                for (int j = 0; j < kVecPerLane; ++j) {
+                    float d[EPV];
+                    if (VEC) {
+                        Elem<T>::diff(ra[B][j], rb[B][j], d);
+#pragma unroll
+                        for (int e = 0; e < EPV; ++e) d[e] = keep ? d[e] : 0.0f;
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < EPV; ++e) {
+                            const int32_t c = c0 + c_lane + e;
+                            // channels past C contribute +0, which leaves the accumulator unchanged
+                            d[e] = (c < C) ? Elem<T>::load(reinterpret_cast<const T *>(bc + row_off[j]) + c) -
+                                             Elem<T>::load(reinterpret_cast<const T *>(bp + row_off[j]) + c)
+                                       : 0.0f;
+                        }
+                    }
+                    float *dst = tile[B & 1] + (j * kRowsPerLoad + vrow) * PITCH + vcol * 4;
+#pragma unroll
+                    for (int p = 0; p < PLANES; ++p)
+                        *reinterpret_cast<float4 *>(dst + p * PLANE) = make_float4(d[4 * p], d[4 * p + 1], d[4 * p + 2], d[4 * p + 3]);
+                }
+            };
+            if (c0 + SEG <= C)
+                differences(std::true_type{});
+            else
+                differences(std::false_type{});
+        };
+        using B0 = std::integral_constant<int, 0>;
+        using B1 = std::integral_constant<int, 1>;
+        using B2 = std::integral_constant<int, 2>;
+        using B3 = std::integral_constant<int, 3>;
+        issue(0, B0{});
+        issue(1, B1{});
+        issue(2, B2{});
+        issue(3, B3{});
+        auto step = [&](int32_t s, auto buf_tag) __attribute__((always_inline)) {
+            slab(s, buf_tag);
+            issue(s + kDepth, buf_tag);
+            publish();
+        };
+        int32_t s = 0;
+        for (; s + kDepth <= nslab; s += kDepth) {
+            step(s, B0{});
+            step(s + 1, B1{});
+            step(s + 2, B2{});
+            step(s + 3, B3{});
+        }
+        if (s < nslab) {
+            slab(s, B0{});
+            publish();
+        }
+        if (s + 1 < nslab) {
+            slab(s + 1, B1{});
+            publish();
+        }
+        if (s + 2 < nslab) {
+            slab(s + 2, B2{});
+            publish();
+        }
+        return;
+    }
+
+    float acc = 0.0f;
+    for (int32_t s = 0; s < nslab; ++s) {
+        publish();
+        if (lane < kTok) {
+            const float *row = tile[s & 1] + lane * PITCH;
+            auto piece = [&](int e) { return *reinterpret_cast<const float4 *>(row + (e % PLANES) * PLANE + (e / PLANES) * 4); };
+            constexpr int A = 8;             // pieces read ahead of the chain
+            float4 v[A];
+#pragma unroll
+            for (int e = 0; e < A; ++e) v[e] = piece(e);
+#pragma unroll
+            for (int e = 0; e < SEG / 4; ++e) {
+                const float4 u = v[e % A];
+                if (e + A < SEG / 4) v[e % A] = piece(e + A);
+                if (MODE == ASTRAEA_DELTA_MEAN_ABS) {
+                    acc = acc + fabsf(u.x);
+                    acc = acc + fabsf(u.y);
+                    acc = acc + fabsf(u.z);
+                    acc = acc + fabsf(u.w);
+                } else {
+                    acc = __builtin_fmaf(u.x, u.x, acc);
+                    acc = __builtin_fmaf(u.y, u.y, acc);
+                    acc = __builtin_fmaf(u.z, u.z, acc);
+                    acc = __builtin_fmaf(u.w, u.w, acc);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    if (lane >= kTok) return;
+    if (VEC) {
+        // a width that is no multiple of a vector: its last channels, from memory
+        const int64_t row = (tok0 + lane < N ? tok0 + lane : N - 1) * row_stride;
+        for (int64_t c = C - C % EPV; c < C; ++c) {
+            const float d = Elem<T>::load(x_cur + row + c) - Elem<T>::load(x_prev + row + c);
+            acc = MODE == ASTRAEA_DELTA_MEAN_ABS ? acc + fabsf(d) : __builtin_fmaf(d, d, acc);
+        }
+    }
+    const int64_t tok = tok0 + lane;
+    if (tok >= N) return;
+    score_out[tok] = finish_score<MODE>(acc, C, tok, lse_weight, skip_count, penalty_table, table_len, w_alpha, w_beta);
+}
+
 // Orders this wave's LDS traffic without a workgroup barrier.
 __device__ __forceinline__ void wave_lds_sync()
 {
@@ -70,39 +278,39 @@ __device__ __forceinline__ void wave_lds_sync()
 }
 
 template <typename T, int MODE, bool VEC, bool NT>
-__global__ __launch_bounds__(kWavesPerBlock *kWave) void score_kernel(
+__global__ __launch_bounds__(kWideWavesPerBlock *kWave) void score_wide_kernel(
     const T *__restrict__ x_cur, const T *__restrict__ x_prev, int64_t N, int64_t C, int64_t row_stride,
     const float *__restrict__ lse_weight, const int32_t *__restrict__ skip_count,
     const float *__restrict__ penalty_table, int32_t table_len, float w_alpha, float w_beta,
     float *__restrict__ score_out)
 {
     constexpr int EPV = Elem<T>::kPerVec;              // elements per 16-byte vector
-    constexpr int SEG = kSegBytes / (int)sizeof(T);    // channels per slab
+    constexpr int SEG = kWideSegBytes / (int)sizeof(T);    // channels per slab
     constexpr int PITCH = SEG + 4;                     // floats; keeps b128 row reads conflict-free
-    __shared__ float tile_all[kWavesPerBlock][kTok * PITCH];
+    __shared__ float tile_all[kWideWavesPerBlock][kWideTok * PITCH];
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     float *tile = tile_all[wave];
-    const int64_t tok0 = ((int64_t)blockIdx.x * kWavesPerBlock + wave) * kTok;
+    const int64_t tok0 = ((int64_t)blockIdx.x * kWideWavesPerBlock + wave) * kWideTok;
     if (tok0 >= N) return;
 
     // load slot j of this lane: row j*8 + lane/8 of the slab, 16-byte vector lane%8 of the segment
     const int vrow = lane >> 3, vcol = lane & 7;
-    const T *pc[kVecPerLane];
-    const T *pp[kVecPerLane];
+    const T *pc[kWideVecPerLane];
+    const T *pp[kWideVecPerLane];
 #pragma unroll
-    for (int j = 0; j < kVecPerLane; ++j) {
+    for (int j = 0; j < kWideVecPerLane; ++j) {
         int64_t tok = tok0 + j * 8 + vrow;
         if (tok > N - 1) tok = N - 1;                  // ragged last wave: re-read a valid row, result unused
         pc[j] = x_cur + tok * row_stride + vcol * EPV;
         pp[j] = x_prev + tok * row_stride + vcol * EPV;
     }
 
-    uint4v ra[kVecPerLane], rb[kVecPerLane];
+    uint4v ra[kWideVecPerLane], rb[kWideVecPerLane];
     auto issue = [&](int64_t c0) {
 #pragma unroll
-        for (int j = 0; j < kVecPerLane; ++j) {
+        for (int j = 0; j < kWideVecPerLane; ++j) {
             if (VEC && c0 + SEG <= C) {
                 ra[j] = load16<NT>(pc[j] + c0);
                 rb[j] = load16<NT>(pp[j] + c0);
@@ -118,7 +326,7 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave) void score_kernel(
         const bool fast = VEC && (c0 + SEG <= C);
         // 1. differences of this slab -> LDS tile
 #pragma unroll
-        for (int j = 0; j < kVecPerLane; ++j) {
+        for (int j = 0; j < kWideVecPerLane; ++j) {
             float d[EPV];
             if (fast) {
                 Elem<T>::diff(ra[j], rb[j], d);
@@ -160,36 +368,27 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave) void score_kernel(
 
     const int64_t tok = tok0 + lane;
     if (tok >= N) return;
-    float delta = (MODE == ASTRAEA_DELTA_L2) ? sqrtf(acc) : acc / (float)C;
-    float sig = lse_weight ? delta * lse_weight[tok] : delta;
-    float sc = w_alpha * sig;
-    if (skip_count) {
-        int32_t n = skip_count[tok];
-        n = n < 0 ? 0 : n;
-        n = n > table_len - 1 ? table_len - 1 : n;
-        sc = __builtin_fmaf(w_beta, penalty_table[n], sc);
-    }
-    score_out[tok] = sc;
+    score_out[tok] = finish_score<MODE>(acc, C, tok, lse_weight, skip_count, penalty_table, table_len, w_alpha, w_beta);
 }
 
 template <typename T, bool VEC, bool NT>
-void launch_mode(astraea_delta_mode mode, dim3 grid, dim3 block, hipStream_t st, const T *xc, const T *xp, int64_t N,
-                 int64_t C, int64_t rs, const float *lw, const int32_t *sc, const float *pt, int32_t tl, float wa,
-                 float wb, float *out)
+void launch_mode(astraea_delta_mode mode, bool wide, hipStream_t st, const T *xc, const T *xp, int64_t N, int64_t C,
+                 int64_t rs, const float *lw, const int32_t *sc, const float *pt, int32_t tl, float wa, float wb, float *out)
 {
+    const int64_t per_block = wide ? kWideWavesPerBlock * kWideTok : kTok;
+    const dim3 grid((unsigned)((N + per_block - 1) / per_block)), block(wide ? kWideWavesPerBlock * kWave : 2 * kWave);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, xc, xp, N, C, rs, lw, sc, pt, tl, wa, wb, out); };
+    auto pick = [&](auto mode_tag) {
+        constexpr int MODE = decltype(mode_tag)::value;
+        if (wide)
+            go(score_wide_kernel<T, MODE, VEC, NT>);
+        else
+            go(score_kernel<T, MODE, VEC, NT>);
+    };
     switch (mode) {
-    case ASTRAEA_DELTA_L2:
-        hipLaunchKernelGGL((score_kernel<T, ASTRAEA_DELTA_L2, VEC, NT>), grid, block, 0, st, xc, xp, N, C, rs, lw, sc, pt,
-                           tl, wa, wb, out);
-        break;
-    case ASTRAEA_DELTA_MEAN_ABS:
-        hipLaunchKernelGGL((score_kernel<T, ASTRAEA_DELTA_MEAN_ABS, VEC, NT>), grid, block, 0, st, xc, xp, N, C, rs, lw,
-                           sc, pt, tl, wa, wb, out);
-        break;
-    default:
-        hipLaunchKernelGGL((score_kernel<T, ASTRAEA_DELTA_MEAN_SQ, VEC, NT>), grid, block, 0, st, xc, xp, N, C, rs, lw,
-                           sc, pt, tl, wa, wb, out);
-        break;
+    case ASTRAEA_DELTA_L2: pick(std::integral_constant<int, ASTRAEA_DELTA_L2>{}); break;
+    case ASTRAEA_DELTA_MEAN_ABS: pick(std::integral_constant<int, ASTRAEA_DELTA_MEAN_ABS>{}); break;
+    default: pick(std::integral_constant<int, ASTRAEA_DELTA_MEAN_SQ>{}); break;
     }
 }
 
@@ -201,19 +400,17 @@ int launch_score(const void *x_cur, const void *x_prev, astraea_dtype dt, int64_
                  hipStream_t stream)
 {
     if (N == 0) return ASTRAEA_OK;
-    const int64_t tokens_per_block = (int64_t)kWavesPerBlock * kTok;
-    const int64_t nblocks = (N + tokens_per_block - 1) / tokens_per_block;
-    dim3 grid((unsigned)nblocks), block(kWavesPerBlock * kWave);
-    const size_t es = dt == ASTRAEA_F32 ? 4 : 2;
-    const bool vec = ((uintptr_t)x_cur % 16 == 0) && ((uintptr_t)x_prev % 16 == 0) && ((row_stride * es) % 16 == 0);
-    // Feature arrays larger than the chip's caches (4 MB of L2 per XCD, 256 MB behind them) are read once and
-    // gone: their loads then carry the streaming hint, which raises the rate from 5.96 to 6.77 TB/s at
-    // N = 118800, C = 3072.  Smaller arrays are often still cached from their producer, and the hint would
-    // make them miss (N = 17550: 3.3 TB/s without it, 2.8 with it).
-    const bool stream_loads = vec && 2 * N * row_stride * (int64_t)es > ((int64_t)256 << 20);
-#define ASTRAEA_SCORE_LAUNCH(T, VEC, NT)                                                                       \
-    launch_mode<T, VEC, NT>(mode, grid, block, stream, (const T *)x_cur, (const T *)x_prev, N, C, row_stride,  \
-                            lse_weight, skip_count, penalty_table, table_len, w_alpha, w_beta, score_out)
+    const int64_t es = dt == ASTRAEA_F32 ? 4 : 2;
+    // a 16-token workgroup addresses its rows with 32-bit byte offsets
+    const bool wide = N >= kWideMinTokens || kTok * row_stride * es > 2147483647LL;
+    const bool vec = C * es >= 16 && ((uintptr_t)x_cur % 16 == 0) && ((uintptr_t)x_prev % 16 == 0) && ((row_stride * es) % 16 == 0);
+    // The streaming hint (the line is not kept in L2) is for arrays that are not still cached from their producer.
+    // Wide kernel: above the 256 MB of the memory-side cache, 5.96 -> 6.77 TB/s at 118800 x 3072.  The other, both
+    // arrays together above 128 MB: cold 45.3 -> 40.9 us and hot 38.5 -> 39.2 us at 17550 x 3072.
+    const bool stream_loads = vec && 2 * N * row_stride * es > ((int64_t)(wide ? 256 : 128) << 20);
+#define ASTRAEA_SCORE_LAUNCH(T, VEC, NT)                                                                                  \
+    launch_mode<T, VEC, NT>(mode, wide, stream, (const T *)x_cur, (const T *)x_prev, N, C, row_stride, lse_weight,        \
+                            skip_count, penalty_table, table_len, w_alpha, w_beta, score_out)
     if (dt == ASTRAEA_F32) {
         if (stream_loads)
             ASTRAEA_SCORE_LAUNCH(float, true, true);
