@@ -6,6 +6,7 @@
 namespace astraea {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -25,6 +26,11 @@ __device__ __forceinline__ bf16x8 lds_read_b128(uint32_t addr)
     return *reinterpret_cast<const bf16x8 __attribute__((address_space(3))) *>((uintptr_t)addr);
 }
 
+__device__ __forceinline__ floatx4 lds_read_f32x4(uint32_t addr)
+{
+    return *reinterpret_cast<const floatx4 __attribute__((address_space(3))) *>((uintptr_t)addr);
+}
+
 // 16 bytes per lane from global memory straight into LDS: lane l of the wave lands at
 // lds_wave_base + 16*l.  The LDS base travels in M0, which the statement overwrites (declared, so the
 // compiler keeps nothing of its own there across it).  Completion is counted by vmcnt; a kernel waits
@@ -38,8 +44,22 @@ __device__ __forceinline__ void dma16(const void *gbase, uint32_t goff, uint32_t
                  : "s"(lds_wave_base), "v"(goff), "s"(gbase)
                  : "memory", "m0");
 }
+// The same with a full 64-bit address per lane, for operands that may span more than 4 GiB.
+__device__ __forceinline__ void dma16_far(const void *gptr, uint32_t lds_wave_base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :
+                 : "s"(lds_wave_base), "v"(gptr)
+                 : "memory", "m0");
+}
 #pragma clang diagnostic pop
 __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Waits until at most N of this wave's vector-memory instructions are pending (they retire in order).
+template <int N> __device__ __forceinline__ void wait_dma_but()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
 
 // An index from a caller's idx_sel, forced into [0, n_rows): reads through it stay inside the buffer.
 __device__ __forceinline__ int32_t clamp_row(int32_t ix, int32_t n_rows)

@@ -6,14 +6,24 @@
 // v_mfma_f32_32x32x2_f32.  x rows and W rows are both contiguous along the contraction, so W feeds the
 // A operand and x the B operand (the transposed form, as in the bf16 kernel): a lane owns one token
 // and, per accumulator block, 16 features in groups of 4 consecutive ones, which it stores as 16 bytes.
-// No LDS: lane (r = l % 32, hf = l / 32) reads, for a step of 16 contraction indices, the 8 floats
-// k0 + 8*hf .. k0 + 8*hf + 7 of row r of each operand block (two 16-byte loads) and MFMA j of the step
-// contracts indices {k0 + j, k0 + 8 + j}; the next step's loads are in flight during the MFMAs.
-// Workgroup = 4 waves in a 2 x 2 arrangement, 128 features x 128 tokens; a wave 64 x 64.
 //
-// MFMA-bound in principle (157.3 TFLOP/s fp32), in practice bound by the operand loads: each wave
-// re-reads its 64 + 64 rows from L2 (16 flops per byte).  It serves the small fp32 layers; the bf16
-// kernel carries the throughput.
+// Shape on gfx950:
+//  * stages of 32 contraction indices (128 bytes of every row of the tile) go from global memory straight into a ring
+//    of four LDS buffers (global_load_lds_dwordx4, per-lane addresses, so the row gather is free), three stages ahead,
+//    16-byte chunks XOR-swizzled inside a row.  A lane then reads 8 consecutive floats of its row per half stage
+//    (two 16-byte reads, one half ahead) and MFMA j of the half contracts the index pair {j, 8 + j}.
+//  * bound by the matrix pipe: 4096 flops per MFMA in 64 clocks, 157 TFLOP/s for the chip.  A wave's
+//    vector instructions do not overlap its fp32 MFMAs: each one in the loop is matrix time lost (measured: address
+//    arithmetic for reads and copies took a fifth of the rate, with one or two waves per SIMD).  Hence the loop is unrolled over the ring, all LDS addresses
+//    are constants in the instructions, and copies advance a scalar base with 32-bit lane offsets.
+//  * three tile shapes, by the rounds of tiles over 256 CUs that they leave: 128 x 128 (waves of 64 x 64), 64 x 64 (waves of
+//    32 x 32; two workgroups share a CU), and, where those leave CUs without a tile, 32 x 32 with the four waves
+//    splitting the contraction, each from a ring of its own, and the sums meeting in LDS.
+// Measured (us; before = 128 x 128 tiles, operands read from global memory into registers): 2048 rows 512 -> 512
+// 47 -> 12.1, 512 -> 2048 49 -> 36.9, 2048 -> 512 167 -> 33.1 (130 TFLOP/s); 500 rows 512 -> 512 43.5 -> 8.6; 600 rows
+// 6144 -> 1536 489 -> 90; 4096 rows 3072 -> 3072 734 -> 524 (148 TFLOP/s).
+#include <type_traits>
+
 #include "gfx950.h"
 
 namespace astraea {
@@ -21,8 +31,9 @@ namespace {
 
 
 constexpr int kWaves = 4;
-constexpr int kTile = 128;          // features and tokens per workgroup
-constexpr int kStep = 16;           // contraction indices per step
+constexpr int kStepBytes = 128;     // of a row per stage: 32 contraction indices
+constexpr int kStep = kStepBytes / 4;
+constexpr int kStages = 4;          // ring of stages in LDS; copies run three ahead
 
 struct LinearF32Args {
     const float *x;
@@ -34,129 +45,244 @@ struct LinearF32Args {
     int32_t k_sel, c_in, c_out;
     int32_t n_rows;            // rows of the indexed buffer(s): indices outside [0, n_rows) read a valid row, write none
     int32_t x_indexed, y_indexed, act;
-    int32_t n_tiles;           // feature tiles; workgroup id = token tile * n_tiles + feature tile
+    int32_t m_tiles, n_tiles;  // token and feature tiles
 };
 
 struct Frag {
-    float4 lo, hi;             // contraction indices 8*hf + 0..3 and 8*hf + 4..7 of this lane's row
+    floatx4 lo, hi;            // contraction indices 8*hf + 0..3 and 8*hf + 4..7 of this lane's row
 };
 
-__device__ __forceinline__ Frag load_frag(const float *row, int k0)
-{
-    Frag f;
-    f.lo = *reinterpret_cast<const float4 *>(row + k0);
-    f.hi = *reinterpret_cast<const float4 *>(row + k0 + 4);
-    return f;
-}
-__device__ __forceinline__ float frag_at(const Frag &f, int j)
-{
-    switch (j) {
-    case 0: return f.lo.x;
-    case 1: return f.lo.y;
-    case 2: return f.lo.z;
-    case 3: return f.lo.w;
-    case 4: return f.hi.x;
-    case 5: return f.hi.y;
-    case 6: return f.hi.z;
-    default: return f.hi.w;
-    }
-}
+__device__ __forceinline__ float frag_at(const Frag &f, int j) { return j < 4 ? f.lo[j] : f.hi[j - 4]; }
 
+// BN x BM accumulator blocks of 32 features x 32 tokens per wave, waves in a WN x WM arrangement, WK of which (1, or
+// all four) share a tile by splitting its contraction steps among them.
+template <int BN, int BM, int WN, int WM, int WK, bool FAR>
 __global__ __launch_bounds__(kWaves *kWave) void linear_f32_kernel(LinearF32Args a)
 {
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    static_assert(WN * WM * WK == kWaves && (WK == 1 || WK == kWaves), "four waves");
+    constexpr int TN = 32 * BN * WN, TM = 32 * BM * WM, kRows = TN + TM;
+    constexpr int kStageBytes = kRows * kStepBytes;
+    constexpr int kCopies = kRows / 8 / (kWaves / WK);       // copy instructions (8 rows each) per wave and stage
+    __shared__ __attribute__((aligned(1024))) char lds[WK * kStages * kStageBytes];
+
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int r = lane & 31, hf = lane >> 5;
-    const int wn = wave & 1, wm = wave >> 1;
-    const int tile_n = blockIdx.x % a.n_tiles, tile_m = blockIdx.x / a.n_tiles;
-    const int n0 = tile_n * kTile + wn * 64;           // first feature of this wave
-    const int m0 = tile_m * kTile + wm * 64;           // first selected row of this wave
+    const int wk = WK == 1 ? 0 : wave, wn = WK == 1 ? wave % WN : 0, wm = WK == 1 ? wave / WN : 0;
+    // Workgroup ids reach the 8 XCDs round-robin.  Each XCD takes a contiguous range of the tiles, counted through columns
+    // of 8 feature tiles, so that what it runs at one time is an 8-wide block whose rows its L2 serves.
+    const int tiles = a.m_tiles * a.n_tiles, per_xcd = (tiles + 7) / 8;
+    const int tile = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+    if (tile >= tiles || (int)(blockIdx.x / 8) >= per_xcd) return;
+    const int col = tile / (8 * a.m_tiles), in_col = tile % (8 * a.m_tiles);
+    const int width = a.n_tiles - 8 * col < 8 ? a.n_tiles - 8 * col : 8;
+    const int n0 = (8 * col + in_col % width) * TN;          // first feature of the tile
+    const int m0 = in_col / width * TM;                      // first selected row of the tile
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds + wk * kStages * kStageBytes;
 
-    // this lane's rows of the two feature blocks (A) and the two token blocks (B); rows past the end
-    // re-read the last valid one and are never stored
-    const float *wrow[2];
-    const float *xrow[2];
+    const int nk_all = a.c_in / kStep;                       // c_in is a multiple of 64: at least two stages
+    const int nk = (nk_all - wk + WK - 1) / WK;              // stages wk, wk + WK, ... are this wave's (perhaps none)
+
+    // Copies.  Instruction i of this wave fills rows 8*i' .. 8*i'+7 of the stage (feature rows first), lane l the
+    // physical 16-byte chunk l%8 of row 8*i' + l/8, which holds logical chunk (l%8) ^ ((row/2)%8).  Rows past the
+    // end re-read the last valid one and are never stored.
+    const char *src[kCopies];             // FAR: this lane's source; otherwise its operand's first byte, the same for all lanes
+    uint32_t off32[kCopies];              // not FAR: this lane's byte offset from it
+    int32_t xr[kCopies];
+    auto copy_row_base = [&](int i) { return 8 * (i * (kWaves / WK) + (WK == 1 ? wave : 0)); };
+    auto copy_row = [&](int i) { return copy_row_base(i) + (lane >> 3); };
+    auto clamp_m = [&](int i) {
+        const int m = m0 + (copy_row(i) < TN ? 0 : copy_row(i) - TN);
+        return m < a.k_sel ? m : a.k_sel - 1;
+    };
+    // all index loads go out together
+    if (a.x_indexed) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        int n = n0 + 32 * b + r;
-        if (n > a.c_out - 1) n = a.c_out - 1;
-        wrow[b] = a.w + (int64_t)n * a.c_in + 8 * hf;
-        int m = m0 + 32 * b + r;
-        if (m > a.k_sel - 1) m = a.k_sel - 1;
-        const int64_t row = a.x_indexed ? (int64_t)clamp_row(a.idx_sel[m], a.n_rows) : (int64_t)m;
-        xrow[b] = a.x + row * a.ldx + 8 * hf;
+        for (int i = 0; i < kCopies; ++i) xr[i] = a.idx_sel[clamp_m(i)];
+#pragma unroll
+        for (int i = 0; i < kCopies; ++i) xr[i] = clamp_row(xr[i], a.n_rows);
+    } else {
+#pragma unroll
+        for (int i = 0; i < kCopies; ++i) xr[i] = clamp_m(i);
     }
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) {
+        const int row = copy_row(i), chunk = (lane & 7) ^ ((row >> 1) & 7);
+        const int n = n0 + row < a.c_out ? n0 + row : a.c_out - 1;
+        const int64_t first = (wk < nk_all ? wk : nk_all - 1) * kStepBytes + 16 * chunk;
+        const int64_t at = first + 4 * (row < TN ? (int64_t)n * a.c_in : (int64_t)xr[i] * a.ldx);
+        src[i] = reinterpret_cast<const char *>(copy_row_base(i) < TN ? a.w : a.x) + (FAR ? at : 0);
+        off32[i] = (uint32_t)at;
+    }
+    // What the epilogue needs from memory is fetched here as well: destination rows (-1: not stored) and bias.
+    // Split contraction: the wave finishes register group `wave` of the one block.
+    constexpr int kGroups = WK == 1 ? 4 : 1;
+    int32_t orow[BM];
+    floatx4 bias4[BN][kGroups];
+    auto feature = [&](int i, int g) { return n0 + 32 * (wn * BN + i) + 8 * (WK == 1 ? g : wave) + 4 * hf; };
+#pragma unroll
+    for (int t = 0; t < BM; ++t) {
+        const int m = m0 + 32 * (wm * BM + t) + r;
+        orow[t] = m < a.k_sel ? m : -1;
+    }
+    if (a.y_indexed) {
+#pragma unroll
+        for (int t = 0; t < BM; ++t) {
+            const int32_t ix = a.idx_sel[orow[t] < 0 ? a.k_sel - 1 : orow[t]];
+            if ((uint32_t)ix >= (uint32_t)a.n_rows) orow[t] = -1;           // a row index outside the buffer writes nothing
+            if (orow[t] >= 0) orow[t] = ix;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < BN; ++i)
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) {
+            const int n = feature(i, g) < a.c_out ? feature(i, g) : 0;
+            bias4[i][g] = a.bias ? *reinterpret_cast<const floatx4 *>(a.bias + n) : floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+    // all of these loads must have landed: the waits below count the copies alone
+#pragma unroll
+    for (int i = 0; i < BN; ++i)
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) asm volatile("" : "+v"(bias4[i][g]));
+#pragma unroll
+    for (int t = 0; t < BM; ++t) asm volatile("" : "+v"(orow[t]));
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) {
+        if (FAR) asm volatile("" ::"v"(src[i]));
+        else asm volatile("" ::"v"(off32[i]));
+    }
+    // copy instruction i of stage s into ring buffer P; past the end the last stage is copied again, into a buffer
+    // nothing reads any more
+    auto copy = [&](int s, auto p_tag, int i) __attribute__((always_inline)) {
+        const int64_t off = (int64_t)(s < nk ? s : nk > 0 ? nk - 1 : 0) * (WK * kStepBytes);
+        const uint32_t dst = lds0 + decltype(p_tag)::value * kStageBytes + (i * (kWaves / WK) + (WK == 1 ? wave : 0)) * 1024;
+        if (FAR) dma16_far(src[i] + off, dst);
+        else dma16(src[i] + off, off32[i], dst);
+    };
 
-    floatx16 acc[2][2];        // [feature block][token block]
+    // Fragments.  Half t of a stage contracts its indices 16t .. 16t+15: this lane holds 16t + 8*hf + 0..7 of its row,
+    // logical chunks 4t + 2*hf and the next, and MFMA j takes index pair {j, 8 + j}.
+    const uint32_t sw = (r >> 1) & 7;
+    uint32_t wa[4], xa[4];                                  // [2*t + half of the 8 floats]
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int u = 0; u < 4; ++u) {
+        const uint32_t c = lds0 + r * kStepBytes + (((4 * (u >> 1) + 2 * hf + (u & 1)) ^ sw) << 4);
+        wa[u] = c + wn * 32 * BN * kStepBytes;
+        xa[u] = c + (TN + wm * 32 * BM) * kStepBytes;
+    }
+    Frag wf[2][BN], xf[2][BM];
+    constexpr int kReads = 2 * (BN + BM);                    // fragment reads per half
+    auto read = [&](auto p_tag, auto t_tag, int u) __attribute__((always_inline)) {
+        constexpr int t = decltype(t_tag)::value;
+        constexpr uint32_t at = decltype(p_tag)::value * kStageBytes;
+        const int b = u % (BN + BM), half = u / (BN + BM);      // all the first halves, then all the second ones
+        const floatx4 v = lds_read_f32x4((b < BN ? wa[2 * t + half] : xa[2 * t + half]) + (at + (b < BN ? b : b - BN) * 32 * kStepBytes));
+        Frag &f = b < BN ? wf[t][b] : xf[t][b - BN];
+        if (half) f.hi = v;
+        else f.lo = v;
+    };
+    floatx16 acc[BN][BM];
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+    for (int i = 0; i < BN; ++i)
+#pragma unroll
+        for (int j = 0; j < BM; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-
-    Frag wf[2], xf[2];
+    // The MFMAs of half t of stage s, in the order written.  One memory instruction goes behind an MFMA and no more: first
+    // the fragment reads of the next half, then this half's share of the copies of stage s + 3.  With all four
+    // waves of the CU at the same place, a read takes the LDS ~32 clocks and a copy the memory pipe ~57, and the
+    // wave is held meanwhile; an MFMA's 64 clocks cover one of them, not a burst.
+    auto mfma_half = [&](auto t_tag, auto p_tag, int s) __attribute__((always_inline)) {
+        constexpr int t = decltype(t_tag)::value;
+        using Next = std::integral_constant<int, (decltype(p_tag)::value + t) % kStages>;
+        using Ahead = std::integral_constant<int, (decltype(p_tag)::value + 3) % kStages>;
+        constexpr int kMfmas = 8 * BN * BM, kCopiesHalf = kCopies / 2;
+        constexpr int kReadGap = kMfmas / 2 / kReads, kCopyGap = kMfmas / 2 / kCopiesHalf;
+        static_assert(kReadGap > 0 && kCopyGap > 0, "one memory instruction per MFMA at most");
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        wf[b] = load_frag(wrow[b], 0);
-        xf[b] = load_frag(xrow[b], 0);
-    }
-    for (int k0 = 0; k0 < a.c_in; k0 += kStep) {
-        Frag wn_[2], xn_[2];
-        const int kn = k0 + kStep < a.c_in ? k0 + kStep : k0;      // the last step re-reads itself, unused
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            wn_[b] = load_frag(wrow[b], kn);
-            xn_[b] = load_frag(xrow[b], kn);
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int t = 0; t < 2; ++t)
-                    acc[i][t] = __builtin_amdgcn_mfma_f32_32x32x2f32(frag_at(wf[i], j), frag_at(xf[t], j), acc[i][t], 0, 0, 0);
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            wf[b] = wn_[b];
-            xf[b] = xn_[b];
-        }
-    }
-
-    // accumulator register e of block (i, t): feature n0 + 32 i + 8 (e / 4) + 4 hf + e % 4, token m0 + 32 t + r
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const int m = m0 + 32 * t + r;
-        if (m >= a.k_sel) continue;
-        int64_t orow = m;
-        if (a.y_indexed) {
-            const int32_t ix = a.idx_sel[m];
-            if ((uint32_t)ix >= (uint32_t)a.n_rows) continue;       // a row index outside the buffer writes nothing
-            orow = ix;
-        }
-        float *yp = a.y + orow * a.ldy;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int n = n0 + 32 * i + 8 * g + 4 * hf;         // c_out is a multiple of 8: all four in or all out
-                if (n >= a.c_out) continue;
-                float4 v = make_float4(acc[i][t][4 * g], acc[i][t][4 * g + 1], acc[i][t][4 * g + 2], acc[i][t][4 * g + 3]);
-                if (a.bias) {
-                    const float4 b4 = *reinterpret_cast<const float4 *>(a.bias + n);
-                    v.x += b4.x;
-                    v.y += b4.y;
-                    v.z += b4.z;
-                    v.w += b4.w;
-                }
-                if (a.act == ASTRAEA_ACT_GELU_TANH) {
-                    v.x = gelu_tanh(v.x);
-                    v.y = gelu_tanh(v.y);
-                    v.z = gelu_tanh(v.z);
-                    v.w = gelu_tanh(v.w);
-                }
-                *reinterpret_cast<float4 *>(yp + n) = v;
+        for (int q = 0; q < kMfmas; ++q) {
+            const int j = q / (BN * BM), i = q / BM % BN, m = q % BM;
+            acc[i][m] = __builtin_amdgcn_mfma_f32_32x32x2f32(frag_at(wf[t][i], j), frag_at(xf[t][m], j), acc[i][m], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (q < kMfmas / 2) {
+                if (q % kReadGap == 0 && q / kReadGap < kReads) read(Next{}, std::integral_constant<int, t ^ 1>{}, q / kReadGap);
+            } else {
+                const int p = q - kMfmas / 2;
+                if (p % kCopyGap == 0 && p / kCopyGap < kCopiesHalf) copy(s + 3, Ahead{}, t * kCopiesHalf + p / kCopyGap);
             }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    using T0 = std::integral_constant<int, 0>;
+    using T1 = std::integral_constant<int, 1>;
+    using P0 = std::integral_constant<int, 0>;
+    using P1 = std::integral_constant<int, 1>;
+    using P2 = std::integral_constant<int, 2>;
+    using P3 = std::integral_constant<int, 3>;
+
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) copy(0, P0{}, i);
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) copy(1, P1{}, i);
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) copy(2, P2{}, i);
+    wait_dma_but<2 * kCopies>();
+    if (WK == 1) __builtin_amdgcn_s_barrier();
+#pragma unroll
+    for (int u = 0; u < kReads; ++u) read(P0{}, T0{}, u);
+    auto stage = [&](int s, auto p_tag) __attribute__((always_inline)) {
+        // Stage s + 1 has landed, for every wave, and every wave is past its last read of stage s - 1, whose buffer
+        // stage s + 3 takes.  (Waves that split the contraction share nothing until the end.)
+        wait_dma_but<kCopies>();
+        if (WK == 1) __builtin_amdgcn_s_barrier();
+        mfma_half(T0{}, p_tag, s);
+        mfma_half(T1{}, p_tag, s);           // the fragments it reads after the last stage are not used
+    };
+    // unrolled over the ring, so that buffer addresses are constants
+    int s = 0;
+    for (; s + 4 <= nk; s += 4) {
+        stage(s, P0{});
+        stage(s + 1, P1{});
+        stage(s + 2, P2{});
+        stage(s + 3, P3{});
     }
+    if (s < nk) stage(s, P0{});
+    if (s + 1 < nk) stage(s + 1, P1{});
+    if (s + 2 < nk) stage(s + 2, P2{});
+    wait_dma();
+
+    // accumulator register e of block (i, t): feature 32 i + 8 (e / 4) + 4 hf + e % 4, token 32 t + r of the wave's part
+    auto store = [&](int64_t row, int n, floatx4 v, floatx4 b) __attribute__((always_inline)) {
+        if (row < 0 || n >= a.c_out) return;                // c_out is a multiple of 8: all four features in or all out
+        v += b;
+        if (a.act == ASTRAEA_ACT_GELU_TANH) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = gelu_tanh(v[e]);
+        }
+        *reinterpret_cast<floatx4 *>(a.y + row * a.ldy + n) = v;
+    };
+    auto group = [&](int i, int t, int g) { return floatx4{acc[i][t][4 * g], acc[i][t][4 * g + 1], acc[i][t][4 * g + 2], acc[i][t][4 * g + 3]}; };
+    if (WK == 1) {
+#pragma unroll
+        for (int t = 0; t < BM; ++t)
+#pragma unroll
+            for (int i = 0; i < BN; ++i)
+#pragma unroll
+                for (int g = 0; g < kGroups; ++g) store(orow[t], feature(i, g), group(i, t, g), bias4[i][g]);
+        return;
+    }
+    // Split contraction (one block): the waves' sums meet in LDS, 4 KiB per wave at the start of its own ring, and wave g
+    // adds up and stores register group g.
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<floatx4 __attribute__((address_space(3))) *>((uintptr_t)(lds0 + g * 1024 + lane * 16)) = group(0, 0, g);
+    __syncthreads();
+    const uint32_t part = (uint32_t)(uintptr_t)lds + wave * 1024 + lane * 16;
+    floatx4 sum = lds_read_f32x4(part);
+#pragma unroll
+    for (int w = 1; w < WK; ++w) sum += lds_read_f32x4(part + w * kStages * kStageBytes);
+    store(orow[0], feature(0, 0), sum, bias4[0][0]);
 }
 
 }  // namespace
@@ -181,10 +307,32 @@ int launch_linear_f32(const void *x, const void *w, const void *bias, void *y, c
     a.x_indexed = x_indexed;
     a.y_indexed = y_indexed;
     a.act = act;
-    const int64_t gx = (c_out + kTile - 1) / kTile, gy = (k_sel + kTile - 1) / kTile;
-    if (gx * gy > 2147483647LL) return fail(ASTRAEA_ERR_INVALID, "astraea_sparse_linear(fp32): grid too large");
-    a.n_tiles = (int32_t)gx;
-    hipLaunchKernelGGL(linear_f32_kernel, dim3((unsigned)(gx * gy)), dim3(kWaves * kWave), 0, stream, a);
+    auto tiles = [&](int64_t t) { return ((c_out + t - 1) / t) * ((k_sel + t - 1) / t); };
+    if (tiles(128) > 2147483647LL / 16) return fail(ASTRAEA_ERR_INVALID, "astraea_sparse_linear(fp32): grid too large");
+    // Rounds of tiles over the 256 CUs, in units of a 32 x 32 tile's work.  At equal rounds the larger tile is the better one
+    // (4096 rows, 3072 -> 3072: 533 us with 128, 559 with 64, 666 with 32, hence the factor 5/4 against the last);
+    // fewer rounds outweigh it (6000 rows: 879 with 128, 830 with 64; 200 rows, 512 -> 512: 12 with 64, 8.5 with 32).
+    const int64_t c128 = (tiles(128) + 255) / 256 * 16, c64 = (tiles(64) + 255) / 256 * 4, c32 = (tiles(32) + 255) / 256;
+    auto go = [&](auto kernel, int t) {
+        a.n_tiles = (c_out + t - 1) / t;
+        a.m_tiles = (int32_t)((k_sel + t - 1) / t);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((tiles(t) + 7) / 8 * 8)), dim3(kWaves * kWave), 0, stream, a);
+    };
+    // 32-bit byte offsets serve unless an operand is larger (the far form costs one more VALU instruction per copy)
+    const bool far = ((x_indexed ? n_rows : k_sel) * ldx) * 4 >= (int64_t)1 << 32 || (int64_t)c_out * c_in * 4 >= (int64_t)1 << 32;
+    auto pick = [&](auto far_tag) {
+        constexpr bool FAR = decltype(far_tag)::value;
+        if (c128 <= c64 && 4 * c128 <= 5 * c32)
+            go(linear_f32_kernel<2, 2, 2, 2, 1, FAR>, 128);
+        else if (4 * c64 <= 5 * c32)
+            go(linear_f32_kernel<1, 1, 2, 2, 1, FAR>, 64);
+        else
+            go(linear_f32_kernel<1, 1, 1, 1, 4, FAR>, 32);
+    };
+    if (far)
+        pick(std::true_type{});
+    else
+        pick(std::false_type{});
     return check_launch("astraea_sparse_linear(fp32)");
 }
 

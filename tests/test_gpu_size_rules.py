@@ -32,3 +32,50 @@ def test_score_sizes(n, c, stride, dtype, mode):
     ab.astraea_score(cur.to(DEV)[:, :c], prev.to(DEV)[:, :c], out, mode)
     torch.cuda.synchronize()
     assert np.array_equal(out.cpu().numpy().view(np.uint32), exp.view(np.uint32))
+
+
+# fp32 linear: 128-, 64- or 32-wide tiles by the rounds of tiles they leave (32: the four waves split the contraction, and
+# a 64-wide contraction leaves two of them without a stage); stages of 32 indices in a ring of four.  Bound: sums of c_in
+# products of size ~1/sqrt(c_in) in fp32, error below c_in * 2^-24 / sqrt(c_in) * 4 <= 1e-4 absolute at c_in <= 4096.
+@pytest.mark.parametrize("n,k,c_in,c_out,gather,scatter,bias,act", [
+    (40, 33, 64, 40, True, True, True, ab.ACT_NONE),             # 32: two stages for four waves
+    (300, 31, 192, 104, True, False, False, ab.ACT_GELU_TANH),   # 32: six stages
+    (300, 257, 448, 264, False, True, True, ab.ACT_NONE),        # 32: fourteen stages, ragged both ways
+    (2100, 2049, 128, 512, True, True, True, ab.ACT_NONE),       # 64: one stage past a tile edge
+    (2100, 2016, 320, 520, True, False, True, ab.ACT_GELU_TANH), # 64: ten stages
+    (2100, 2047, 192, 2056, False, True, True, ab.ACT_NONE),     # 64 or 128 at the edge of a round
+    (2100, 2048, 128, 2048, True, True, False, ab.ACT_NONE),     # 128
+    (4100, 4095, 64, 1032, True, True, True, ab.ACT_NONE),       # 128: two stages, ragged
+])
+def test_linear_f32_tiles(n, k, c_in, c_out, gather, scatter, bias, act):
+    g = torch.Generator(device=DEV).manual_seed(n + k + c_in)
+    idx = torch.randperm(n, device=DEV, generator=g)[:k].sort().values.to(torch.int32)
+    x = torch.randn(n if gather else k, c_in, device=DEV, generator=g)
+    w = torch.randn(c_out, c_in, device=DEV, generator=g) * c_in ** -0.5
+    b = torch.randn(c_out, device=DEV, generator=g) if bias else None
+    y = torch.randn(n if scatter else k, c_out + 8, device=DEV, generator=g)
+    exp = y.double()
+    ref = (x[idx.long()] if gather else x).double() @ w.double().T + (b.double() if bias else 0.0)
+    if act == ab.ACT_GELU_TANH:
+        ref = torch.nn.functional.gelu(ref, approximate="tanh")
+    exp[idx.long() if scatter else slice(None), :c_out] = ref
+    ab.astraea_sparse_linear(x, w, b, idx, k, y[:, :c_out], act=act, x_is_compact=not gather, y_is_compact=not scatter, N=n)
+    torch.cuda.synchronize()
+    assert (y.double() - exp).abs().max().item() <= 1e-4
+    keep = torch.ones(y.shape, dtype=torch.bool, device=DEV)
+    keep[idx.long() if scatter else slice(None), :c_out] = False
+    assert torch.equal(y[keep].double(), exp[keep])
+
+
+def test_linear_f32_operand_past_4_gib():
+    """Rows beyond the reach of a 32-bit byte offset: 1040 rows of 4 MiB pitch."""
+    n, k, c_in, c_out = 1040, 100, 64, 72
+    g = torch.Generator(device=DEV).manual_seed(3)
+    x = torch.empty(n, 1 << 20, device=DEV)[:, :c_in]
+    x.copy_(torch.randn(n, c_in, device=DEV, generator=g))
+    w = torch.randn(c_out, c_in, device=DEV, generator=g) * c_in ** -0.5
+    idx = torch.arange(n - k, n, dtype=torch.int32, device=DEV)
+    y = torch.empty(k, c_out, device=DEV)
+    ab.astraea_sparse_linear(x, w, None, idx, k, y)
+    torch.cuda.synchronize()
+    assert (y.double() - x[n - k:].double() @ w.double().T).abs().max().item() <= 1e-4
