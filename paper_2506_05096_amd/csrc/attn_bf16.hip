@@ -28,8 +28,9 @@
 //    kernel therefore fixes each row's offset at the max over the first key tile and takes no max in
 //    the sweep at all, which removes a fifth of the softmax arithmetic.  A row whose later logits
 //    outgrow that offset by more than 2^80 (or overflow) shows in its final row sum; its workgroup
-//    then flags itself, writes nothing, and a second launch of the same kernel in its exact form
-//    (a max per tile, lazy rescale when it grew by more than 2^kTau) redoes just the flagged ones.
+//    then sweeps its keys once more in the exact form (a max per tile, lazy rescale when it grew by
+//    more than 2^kTau).  Both forms are in the one kernel: as a launch of its own over the same grid the
+//    exact form cost 4 - 7 us a call with nothing to redo, and needed a flag per workgroup.
 //  * workgroup ids are mapped so that the workgroups resident on one XCD work on the same head and
 //    sweep the keys together; K/V tiles are then served from that XCD's L2.
 //  * the two waves that share a SIMD alternate: while one runs the MFMAs of a tile the other runs
@@ -49,8 +50,9 @@ constexpr int kBk = 64;                 // keys per LDS tile
 constexpr int kRowBytes = D * 2;        // 256 B per key row, unpadded
 constexpr int kTileBytes = kBk * kRowBytes;          // 16 KiB
 constexpr int kBufBytes = 2 * kTileBytes;            // K tile then V tile
+constexpr int kRowsBytes = 32 * kRowBytes;           // a wave's 32 query or output rows
 constexpr float kTau = 8.0f;            // exact form: lazy-rescale threshold, log2 units
-constexpr float kBig = 0x1p80f;         // fast form: a final row sum above this sends the workgroup to the exact form
+constexpr float kBig = 0x1p80f;         // fast form: after a final row sum above this the workgroup repeats its sweep in the exact form
 constexpr int kNumXcd = 8;
 
 __device__ __forceinline__ float xhalf_max(float x)
@@ -111,6 +113,19 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const __bf16 *__restri
     }
 }
 
+// 32 output rows of 256 bytes in LDS, 16-byte chunks XOR-swizzled, on their way from accumulators to whole rows:
+// registers 4g..4g+3 of block b of a lane are head-dim 32*b + 8*g + 4*(lane/32) + 0..3 of row lane%32.
+__device__ __forceinline__ void rows_put(uint32_t rows_lds, int b, int g, int lane, uint2v v)
+{
+    const int row = lane & 31;
+    *reinterpret_cast<uint2v __attribute__((address_space(3))) *>(
+        (uintptr_t)(rows_lds + row * kRowBytes + (((4 * b + g) ^ (row & 15)) << 4) + 8 * (lane >> 5))) = v;
+}
+__device__ __forceinline__ uint4v rows_get(uint32_t rows_lds, int row, int chunk)
+{
+    return __builtin_bit_cast(uint4v, lds_read_b128(rows_lds + row * kRowBytes + ((chunk ^ (row & 15)) << 4)));
+}
+
 // Budget-aware work split.  Work item = (head, tile of 256 selected queries), head-major; XCD x owns the
 // contiguous item range [x * items_per_xcd, (x+1) * items_per_xcd) and workgroups reach XCDs round-robin
 // by id.  With 32 CUs per XCD the items of an XCD run in rounds of 32.  The first `full_items` of each
@@ -127,6 +142,7 @@ struct AttnSchedule {
 };
 constexpr int kPartialFloats = kBq * D + 2 * kBq;    // O^T accumulators, then running max, then row sum
 constexpr int kMaxSharesPerXcd = 64;
+constexpr int kCuPerXcd = 32;
 
 constexpr int MFMA = 0x008, DSR = 0x100;
 #define SGB(mask, n) __builtin_amdgcn_sched_group_barrier(mask, n, 0)
@@ -139,22 +155,17 @@ constexpr int MFMA = 0x008, DSR = 0x100;
         __builtin_amdgcn_sched_barrier(0); \
     } while (0)
 
-// EXACT = false: the main launch (offset fixed by the first tile, no max in the sweep); every workgroup
-// writes redo[blockIdx.x] = 1 if one of its rows outgrew the offset (and then stores no result), else 0.
-// EXACT = true: the second launch over the same grid; a workgroup whose flag is 0 returns at once, the
-// others sweep their keys again with a max per tile and store their results.
-template <bool EXACT>
 __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
     const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const char *__restrict__ vt, int64_t N, int32_t H,
     int64_t q_stride_n, int64_t q_stride_h, int64_t kv_stride_n, int64_t kv_stride_h,
     const int32_t *__restrict__ idx_sel, int64_t k_sel, int q_is_compact, float scale_log2e,
     __bf16 *__restrict__ o_sel, int64_t o_stride_n, int o_scatter, float *__restrict__ lse_sel, AttnSchedule sch,
-    float *__restrict__ partial, uint32_t *__restrict__ redo)
+    float *__restrict__ partial)
 {
-    // [parity][K tile | V^T tile]; 64 KiB, one 8-wave workgroup per CU (two waves per SIMD)
-    __shared__ __attribute__((aligned(1024))) char lds[2 * kBufBytes];
+    // [parity][K tile | V^T tile], 64 KiB, then 8 KiB per wave for its query rows and later its output rows; one
+    // 8-wave workgroup per CU (two waves per SIMD)
+    __shared__ __attribute__((aligned(1024))) char lds[2 * kBufBytes + kWaves * kRowsBytes];
     __shared__ uint32_t wave_outgrew[kWaves];
-    if (EXACT && redo && redo[blockIdx.x] == 0) return;     // no flag array: the exact form runs alone
 
     const int64_t ntiles = (N + kBk - 1) / kBk;
     const int64_t total_items = (int64_t)H * sch.q_tiles;
@@ -179,23 +190,9 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
     const int64_t r0 = qt * kBq + wave * 32;
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
 
-    // ---- Q fragment: lane holds query column qc, head-dim 16*s + 8*hf + 0..7 (B operand of K Q^T)
-    int64_t r = r0 + qc;
-    if (r > k_sel - 1) r = k_sel - 1;               // ragged last tile: duplicate a valid row, never stored
-    // an index outside [0, N) reads a valid row instead
-    const int64_t qrow = q_is_compact ? r : (int64_t)clamp_row(idx_sel[r], (int32_t)N);
-    const __bf16 *qp = q + qrow * q_stride_n + (int64_t)head * q_stride_h + 8 * hf;
-    bf16x8 qf[D / 16];
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) qf[s] = *reinterpret_cast<const bf16x8 *>(qp + 16 * s);
-
     floatx16 oacc[4];
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) oacc[b][i] = 0.0f;
-    float m_c = -INFINITY;     // running max of scale*log2(e)*logit actually used as exponent offset
-    float l_run = 0.0f;        // this lane's share of the running sum
+    float m_c;                 // running max of scale*log2(e)*logit actually used as exponent offset
+    float l_run;               // this lane's share of the running sum
 
     // ---- tile DMA.  A wave instruction fills 1 KiB of a tile: lane l writes 16 bytes at 16*l.
     // K: block = 4 key rows; physical chunk p of row r holds logical chunk p ^ (r & 15).
@@ -236,6 +233,35 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
         }
     };
 
+    const int grp = wave >> 2, wig = wave & 3;
+    using W4 = std::integral_constant<int, 4>;
+    using W8 = std::integral_constant<int, 8>;
+    auto first_tiles = [&]() __attribute__((always_inline)) {
+        dma_k_tile(tile_begin, 0, wave, W8{});
+        dma_v_tile(tile_begin, 0, wave, W8{});
+        if (tile_begin + 1 < tile_end) dma_k_tile(tile_begin + 1, 1, wave, W8{});
+    };
+    first_tiles();
+
+    // ---- Q fragment: lane holds query column qc, head-dim 16*s + 8*hf + 0..7 (B operand of K Q^T).  The rows come
+    // through LDS in the K tile's layout, four whole rows per copy: fragments loaded straight from global memory take
+    // 16 bytes of each of 32 rows per instruction, and a short sweep waits for them.
+    const int64_t row_n = k_sel - r0 < 32 ? k_sel - r0 : 32;     // rows of this wave; at most 0: none
+    auto lane_row = [&](int n) { return (int64_t)n < row_n ? r0 + n : k_sel - 1; };    // ragged tile: a valid row, never stored
+    // an index outside [0, N) reads a valid row instead
+    const int32_t q_row = q_is_compact ? 0 : clamp_row(idx_sel[lane_row(qc)], (int32_t)N);
+    const uint32_t rows_lds = lds0 + 2 * kBufBytes + wave * kRowsBytes;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int n = 4 * i + d_row;
+        const int64_t row = q_is_compact ? lane_row(n) : (int64_t)__shfl(q_row, n);
+        dma16_far(q + row * q_stride_n + (int64_t)head * q_stride_h + 8 * (d_p ^ (n & 15)), rows_lds + i * 1024);
+    }
+    wait_dma();
+    bf16x8 qf[D / 16];
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) qf[s] = lds_read_b128(rows_lds + qc * kRowBytes + (((2 * s + hf) ^ (qc & 15)) << 4));
+
     // ---- LDS read offsets relative to a buffer pair; the buffer parity and the array's base are added where
     // the offsets are used (the tile loop is unrolled by two, so the parity is a compile-time constant there
     // and lands in the read's immediate offset)
@@ -264,7 +290,8 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
             for (int i = 0; i < 16; ++i) tm = fmaxf(tm, sacc[kb][i]);
         return xhalf_max(tm) * scale_log2e;
     };
-    auto softmax_tile = [&](int64_t j) __attribute__((always_inline)) {
+    auto softmax_tile = [&](int64_t j, auto exact_tag) __attribute__((always_inline)) {
+        constexpr bool EXACT = decltype(exact_tag)::value;
         if ((j + 1) * kBk > N) {                    // only the last tile can be ragged
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
@@ -375,89 +402,90 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
     // free (both groups are past the MFMA phase that read them), and the copies are waited for at the
     // end of its following MFMA phase, one phase before group 0 needs them.  Every wave executes the
     // same number of barriers: group 1 one more at the start, group 0 one more at the end.
-    const int grp = wave >> 2, wig = wave & 3;
-    using W4 = std::integral_constant<int, 4>;
-    using W8 = std::integral_constant<int, 8>;
-    dma_k_tile(tile_begin, 0, wave, W8{});
-    dma_v_tile(tile_begin, 0, wave, W8{});
-    if (tile_begin + 1 < tile_end) dma_k_tile(tile_begin + 1, 1, wave, W8{});
-    // The Q fragment must be resident before the loop starts: a load still counted as pending at the
-    // loop header would make the compiler wait on the vector-memory counter inside the loop.
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) asm volatile("" ::"v"(qf[s]));
-    wait_dma();
-    PHASE_BARRIER();
-    if (grp == 1) PHASE_BARRIER();
-    qk_mfmas();                    // S^T of the first tile (K buffer 0)
-    // fast form: the first tile's row max is the offset of the whole sweep (nothing is accumulated yet, so
-    // nothing needs rescaling; rows past the last key were filled with copies of it and cannot raise the max)
-    if (!EXACT) m_c = tile_row_max();
-    PHASE_BARRIER();
-
     using P0 = std::integral_constant<int, 0>;
     using P1 = std::integral_constant<int, 1>;
-    // One tile that has a successor: VALU phase of tile j, then the MFMA phase (second product of tile j from
-    // V buffer PAR, first product of tile j+1 from K buffer PAR ^ 1).
-    auto tile_step = [&](int64_t j, auto par_tag) __attribute__((always_inline)) {
-        constexpr int PAR = decltype(par_tag)::value;
-        if (grp == 1) {
-            dma_v_tile(j + 1, PAR ^ 1, wig, W4{});
-            if (j + 2 < tile_end) dma_k_tile(j + 2, PAR, wig, W4{});
-        }
-        softmax_tile(j);
-        PHASE_BARRIER();
-        // The wave in its MFMA phase gets issue priority over its SIMD neighbour, which is in its VALU phase.
-        __builtin_amdgcn_s_setprio(3);
-        mfma_phase(std::true_type{}, par_tag);
-        __builtin_amdgcn_s_setprio(0);
-        if (grp == 1) wait_dma();
-        PHASE_BARRIER();
-    };
-    // last tile: no next tile to prefetch or to start
-    auto last_step = [&](int64_t j, auto par_tag) __attribute__((always_inline)) {
-        softmax_tile(j);
-        PHASE_BARRIER();
-        mfma_phase(std::false_type{}, par_tag);
-        PHASE_BARRIER();
-    };
-    // the loop is unrolled by two so that the buffer parity is a constant in each copy
-    int64_t j = tile_begin;
-    for (; j + 2 < tile_end; j += 2) {
-        tile_step(j, P0{});
-        tile_step(j + 1, P1{});
-    }
-    if (j + 1 < tile_end) {
-        tile_step(j, P0{});
-        last_step(j + 1, P1{});
-    } else {
-        last_step(j, P0{});
-    }
-    if (grp == 0) PHASE_BARRIER();
-
-    const float l_tot = xhalf_sum(l_run);
-    if (!EXACT) {
-        // Did a row outgrow its offset?  Its row sum then passed 2^80, or is infinite or NaN (the comparison is
-        // written so that those fail it too).  The workgroup decides as one: it stores either all of its rows or
-        // none and leaves them to the exact launch.
-        const bool outgrew = __builtin_amdgcn_ballot_w64(!(l_tot <= kBig)) != 0;
-        if (lane == 0) wave_outgrew[wave] = outgrew ? 1u : 0u;
-        __syncthreads();
-        uint32_t any = 0;
+    // The whole sweep.  EXACT = false: offset fixed by the first tile, no max in the sweep.  EXACT = true: a max per tile.
+    auto sweep = [&](auto exact_tag) __attribute__((always_inline)) {
+        constexpr bool EXACT = decltype(exact_tag)::value;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) any |= wave_outgrew[w];
-        if (tid == 0) redo[blockIdx.x] = any;
-        if (any) return;
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) oacc[b][i] = 0.0f;
+        m_c = -INFINITY;
+        l_run = 0.0f;
+        PHASE_BARRIER();
+        if (grp == 1) PHASE_BARRIER();
+        qk_mfmas();                    // S^T of the first tile (K buffer 0)
+        // fast form: the first tile's row max is the offset of the whole sweep (nothing is accumulated yet, so
+        // nothing needs rescaling; rows past the last key were filled with copies of it and cannot raise the max)
+        if (!EXACT) m_c = tile_row_max();
+        PHASE_BARRIER();
+
+        // One tile that has a successor: VALU phase of tile j, then the MFMA phase (second product of tile j from
+        // V buffer PAR, first product of tile j+1 from K buffer PAR ^ 1).
+        auto tile_step = [&](int64_t j, auto par_tag) __attribute__((always_inline)) {
+            constexpr int PAR = decltype(par_tag)::value;
+            if (grp == 1) {
+                dma_v_tile(j + 1, PAR ^ 1, wig, W4{});
+                if (j + 2 < tile_end) dma_k_tile(j + 2, PAR, wig, W4{});
+            }
+            softmax_tile(j, exact_tag);
+            PHASE_BARRIER();
+            // The wave in its MFMA phase gets issue priority over its SIMD neighbour, which is in its VALU phase.
+            __builtin_amdgcn_s_setprio(3);
+            mfma_phase(std::true_type{}, par_tag);
+            __builtin_amdgcn_s_setprio(0);
+            if (grp == 1) wait_dma();
+            PHASE_BARRIER();
+        };
+        // last tile: no next tile to prefetch or to start
+        auto last_step = [&](int64_t j, auto par_tag) __attribute__((always_inline)) {
+            softmax_tile(j, exact_tag);
+            PHASE_BARRIER();
+            mfma_phase(std::false_type{}, par_tag);
+            PHASE_BARRIER();
+        };
+        // the loop is unrolled by two so that the buffer parity is a constant in each copy
+        int64_t j = tile_begin;
+        for (; j + 2 < tile_end; j += 2) {
+            tile_step(j, P0{});
+            tile_step(j + 1, P1{});
+        }
+        if (j + 1 < tile_end) {
+            tile_step(j, P0{});
+            last_step(j + 1, P1{});
+        } else {
+            last_step(j, P0{});
+        }
+        if (grp == 0) PHASE_BARRIER();
+    };
+    sweep(std::false_type{});
+    float l_tot = xhalf_sum(l_run);
+    // Did a row outgrow its offset?  Its row sum then passed 2^80, or is infinite or NaN (the comparison is
+    // written so that those fail it too).  The workgroup decides as one, since its waves share the tiles.
+    const bool outgrew = __builtin_amdgcn_ballot_w64(!(l_tot <= kBig)) != 0;
+    if (lane == 0) wave_outgrew[wave] = outgrew ? 1u : 0u;
+    __syncthreads();
+    uint32_t any = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) any |= wave_outgrew[w];
+    if (__builtin_amdgcn_readfirstlane(any) != 0) {
+        first_tiles();
+        wait_dma();
+        sweep(std::true_type{});
+        l_tot = xhalf_sum(l_run);
     }
     if (pslot >= 0) {
-        // a key-range share of an item: unnormalised accumulators, running max and row sum go to the
-        // workspace; merge_partials_kernel combines the shares
+        // a key-range share of an item: unnormalised accumulators, running max and row sum go to the workspace;
+        // merge_partials_kernel combines the shares.  The accumulators are stored as they lie, [wave][b][g][lane][4]:
+        // whole lines, where rows of head-dim would put 16 bytes on each of 64 lines.
         float *pp = partial + pslot * kPartialFloats;
         const int row = wave * 32 + qc;
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
             for (int g = 0; g < 4; ++g)
-                *reinterpret_cast<float4 *>(pp + row * D + 32 * b + 8 * g + 4 * hf) =
+                *reinterpret_cast<float4 *>(pp + (((wave * 4 + b) * 4 + g) * kWave + lane) * 4) =
                     make_float4(oacc[b][4 * g], oacc[b][4 * g + 1], oacc[b][4 * g + 2], oacc[b][4 * g + 3]);
         if (hf == 0) {
             pp[kBq * D + row] = m_c;
@@ -465,13 +493,11 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
         }
         return;
     }
+    // the lane number under another name: addresses the prologue had are computed again instead of held in registers
+    // through the sweep, which has none to spare
+    int el = lane;
+    asm volatile("" : "+v"(el));
     const float inv = 1.0f / l_tot;
-    const int64_t rr = r0 + qc;
-    if (rr >= k_sel) return;
-    // compact output row rr, or straight into the cached buffer's row of that token
-    const int64_t orow = o_scatter ? (int64_t)idx_sel[rr] : rr;
-    __bf16 *op = o_sel + orow * o_stride_n + (int64_t)head * D;
-    if (!o_scatter || (uint64_t)orow < (uint64_t)N)     // a row index outside the cached buffer writes nothing
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -480,80 +506,122 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
             uint2v o4;
             o4[0] = pack_bf16(oacc[b][4 * g] * inv, oacc[b][4 * g + 1] * inv);
             o4[1] = pack_bf16(oacc[b][4 * g + 2] * inv, oacc[b][4 * g + 3] * inv);
-            *reinterpret_cast<uint2v *>(op + 32 * b + 8 * g + 4 * hf) = o4;
+            rows_put(rows_lds, b, g, el, o4);
         }
-    if (lse_sel && hf == 0) lse_sel[rr * H + head] = (m_c + log2f(l_tot)) * 0.69314718055994530942f;
+    __builtin_amdgcn_s_waitcnt(0xc07f);              // lgkmcnt(0): this wave's rows are in LDS; no other wave reads them
+    // compact output row r0 + n, or straight into the cached buffer's row of that token
+    const int32_t o_row = o_scatter ? idx_sel[lane_row(el & 31)] : 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int n = 4 * i + (el >> 4);
+        const int64_t orow = o_scatter ? (int64_t)__shfl(o_row, n) : r0 + n;
+        const uint4v val = rows_get(rows_lds, n, (el & 15));
+        // a row index outside the cached buffer writes nothing
+        if ((int64_t)n < row_n && (!o_scatter || (uint64_t)orow < (uint64_t)N))
+            *reinterpret_cast<uint4v *>(o_sel + orow * o_stride_n + (int64_t)head * D + 8 * (el & 15)) = val;
+    }
+    if (lse_sel && el < 32 && (int64_t)el < row_n)
+        lse_sel[(r0 + el) * H + head] = (m_c + log2f(l_tot)) * 0.69314718055994530942f;
 }
 
 
 // Combines the key-range shares of the split items: with m* = max_s m_s and w_s = 2^(m_s - m*),
-// O = sum_s w_s O_s / sum_s w_s l_s.  Workgroup (x, y) handles rows 8*y .. 8*y+7 of split item x; a
-// thread handles one row and four head-dim elements.
+// O = sum_s w_s O_s / sum_s w_s l_s.  Workgroup (x, y) handles rows 32*y .. 32*y+31 of split item x, i.e. what wave y of
+// each share stored; its wave b takes head-dim 32*b .. 32*b+31.  Bound by reading the shares (4 KiB per wave and share).
 __global__ __launch_bounds__(256) void merge_partials_kernel(const float *__restrict__ partial, AttnSchedule sch,
                                                              int32_t H, int64_t k_sel, int64_t n_rows,
                                                              const int32_t *__restrict__ idx_sel, __bf16 *__restrict__ o_sel,
                                                              int64_t o_stride_n, int o_scatter,
                                                              float *__restrict__ lse_sel)
 {
+    __shared__ __attribute__((aligned(1024))) char rows[kRowsBytes];
     const int64_t left = sch.items_per_xcd - sch.full_items;
     const int64_t xcd = blockIdx.x / left, li = blockIdx.x % left;
     const int64_t item = xcd * sch.items_per_xcd + sch.full_items + li;
     if (item >= (xcd + 1) * sch.items_per_xcd || item >= (int64_t)H * sch.q_tiles) return;
     const int head = (int)(item / sch.q_tiles);
-    const int64_t qt = item % sch.q_tiles;
+    const int64_t r0 = (item % sch.q_tiles) * kBq + 32 * blockIdx.y;
+    if (r0 >= k_sel) return;
     const float *base = partial + (xcd * left + li) * sch.splits * (int64_t)kPartialFloats;
-    const int d4 = (threadIdx.x & 31) * 4;
-    {
-        const int row = (threadIdx.x >> 5) + 8 * blockIdx.y;
-        const int64_t rr = qt * kBq + row;
-        if (rr >= k_sel) return;
-        float m_star = -INFINITY;
-        for (int s = 0; s < sch.splits; ++s) m_star = fmaxf(m_star, base[s * (int64_t)kPartialFloats + kBq * D + row]);
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        float l = 0.0f;
-        for (int s = 0; s < sch.splits; ++s) {
-            const float *ps = base + s * (int64_t)kPartialFloats;
-            const float w = exp2f(ps[kBq * D + row] - m_star);
-            const float4 o = *reinterpret_cast<const float4 *>(ps + row * D + d4);
-            acc.x += w * o.x;
-            acc.y += w * o.y;
-            acc.z += w * o.z;
-            acc.w += w * o.w;
-            l += w * ps[kBq * D + kBq + row];
-        }
-        const float inv = 1.0f / l;
+    const int lane = threadIdx.x & (kWave - 1), b = threadIdx.x / kWave;
+    const int row = 32 * blockIdx.y + (lane & 31);
+    float m_star = -INFINITY;
+    for (int s = 0; s < sch.splits; ++s) m_star = fmaxf(m_star, base[s * (int64_t)kPartialFloats + kBq * D + row]);
+    floatx4 acc[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) acc[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+    float l = 0.0f;
+#pragma unroll 2
+    for (int s = 0; s < sch.splits; ++s) {
+        const float *ps = base + s * (int64_t)kPartialFloats;
+        const float w = exp2f(ps[kBq * D + row] - m_star);
+        l += w * ps[kBq * D + kBq + row];
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            acc[g] += w * *reinterpret_cast<const floatx4 *>(ps + (((blockIdx.y * 4 + b) * 4 + g) * kWave + lane) * 4);
+    }
+    const float inv = 1.0f / l;
+    const uint32_t rows_lds = (uint32_t)(uintptr_t)rows;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
         uint2v o4;
-        o4[0] = pack_bf16(acc.x * inv, acc.y * inv);
-        o4[1] = pack_bf16(acc.z * inv, acc.w * inv);
+        o4[0] = pack_bf16(acc[g][0] * inv, acc[g][1] * inv);
+        o4[1] = pack_bf16(acc[g][2] * inv, acc[g][3] * inv);
+        rows_put(rows_lds, b, g, lane, o4);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int n = 16 * i + (threadIdx.x >> 4), c = threadIdx.x & 15;
+        const int64_t rr = r0 + n;
+        if (rr >= k_sel) break;
         const int64_t orow = o_scatter ? (int64_t)idx_sel[rr] : rr;
         if (!o_scatter || (uint64_t)orow < (uint64_t)n_rows)
-            *reinterpret_cast<uint2v *>(o_sel + orow * o_stride_n + (int64_t)head * D + d4) = o4;
-        if (lse_sel && d4 == 0) lse_sel[rr * H + head] = (m_star + log2f(l)) * 0.69314718055994530942f;
+            *reinterpret_cast<uint4v *>(o_sel + orow * o_stride_n + (int64_t)head * D + 8 * c) = rows_get(rows_lds, n, c);
     }
+    if (lse_sel && threadIdx.x < 32 && r0 + lane < k_sel)
+        lse_sel[(r0 + lane) * H + head] = (m_star + log2f(l)) * 0.69314718055994530942f;
 }
 
 }  // namespace
+
+// Estimated microseconds of the last items of an XCD, `left` of them cut into s shares each.  Measured on shapes of 2 to
+// 625 key tiles with 90 to 12000 queries:
+//  * a key tile takes 0.72 + 0.027 n us with n of the XCD's 32 CUs at work: the chip is at its power limit and lowers its
+//    clock as CUs fill up (0.96 us at 9, 1.16 at 18, 1.56 at 30), so filling the idle ones gains less than the count of
+//    rounds says (1755 queries x 17550 keys x 24 heads, 21 items per XCD: 351 us whole, 320 us in 63 shares);
+//  * a workgroup costs 11 us besides its tiles, one that stores a share (128 KiB) 11 + 0.13 n;
+//  * merging costs 4 us and 0.2 us per share of an XCD.
+// So short sweeps stay whole: 7020 queries x 512 keys 66 us whole, 84 us in shares by the count of rounds alone; 608 x
+// 2025 takes 3 shares per item (37.7 us) instead of 7 (48.2).
+static double tail_us(int64_t left, int64_t s, int64_t ntiles)
+{
+    double us = s > 1 ? 4.0 + 0.2 * (double)(left * s) : 0.0;
+    for (int64_t n = left * s; n > 0; n -= kCuPerXcd) {
+        const double cus = (double)(n < kCuPerXcd ? n : kCuPerXcd);
+        us += 11.0 + (s > 1 ? 0.13 * cus : 0.0) + (double)((ntiles + s - 1) / s) * (0.72 + 0.027 * cus);
+    }
+    return us;
+}
 
 // The budget-aware split for k_sel selected queries of H heads over N keys; `slots` = workgroups per XCD.
 // False when the grid would not fit.
 static bool plan_attn(int64_t N, int32_t H, int64_t k_sel, AttnSchedule &sch, int64_t &slots)
 {
     const int64_t ntiles = (N + kBk - 1) / kBk;
-    constexpr int kCuPerXcd = 32;
     sch.q_tiles = (int32_t)((k_sel + kBq - 1) / kBq);
     const int64_t total = (int64_t)sch.q_tiles * H;
     sch.items_per_xcd = (total + kNumXcd - 1) / kNumXcd;
-    // Items that would run in a last, partly filled round are cut along the keys into `splits` shares
-    // each, chosen (up to 8 shares per item, 64 shares per XCD) so that the shares take the fewest
-    // rounds relative to their length: rounds(left * splits) / splits is the tail's cost in full sweeps.
+    // Items that would run in a last, partly filled round are cut along the keys into `splits` shares each (up to 8
+    // per item, 64 per XCD) where that is cheaper by the estimate below.
     int64_t left = sch.items_per_xcd % kCuPerXcd;
     int64_t splits = 1;
     if (left > 0) {
-        double best = 1.0;
+        double best = tail_us(left, 1, ntiles);
         for (int64_t s2 = 2; s2 <= 8 && left * s2 <= kMaxSharesPerXcd && s2 <= ntiles; ++s2) {
             if ((s2 - 1) * ((ntiles + s2 - 1) / s2) >= ntiles) continue;      // would leave an empty share
-            const double cost = (double)((left * s2 + kCuPerXcd - 1) / kCuPerXcd) / (double)s2;
-            if (cost < best - 1e-9) {
+            const double cost = tail_us(left, s2, ntiles);
+            if (cost < best) {
                 best = cost;
                 splits = s2;
             }
@@ -587,24 +655,17 @@ int attn_bf16_plan(int64_t N, int32_t H, int64_t k_sel, int64_t plan[8])
 }
 
 // Workspace of the bf16 path: the V^T tiles written by the pre-pass, then the partial results of the
-// split items (at most kMaxSharesPerXcd shares per XCD), then one redo flag per workgroup of the largest
-// grid a selection of up to N queries can launch.
+// split items (at most kMaxSharesPerXcd shares per XCD).
 static size_t vt_bytes(int64_t N, int32_t H)
 {
     const int64_t ntiles = (N + kBk - 1) / kBk;
     return (size_t)ntiles * (size_t)H * kTileBytes;
 }
 static size_t partial_bytes() { return (size_t)kNumXcd * kMaxSharesPerXcd * kPartialFloats * sizeof(float); }
-// Workgroups of a launch: 8 * (full items + shares) per XCD <= all items rounded up to the XCD count, plus the shares.
-static size_t redo_flags(int64_t N, int32_t H)
-{
-    const int64_t items = ((N + kBq - 1) / kBq) * (int64_t)H;
-    return (size_t)(((items + kNumXcd - 1) / kNumXcd) * kNumXcd + (int64_t)kNumXcd * kMaxSharesPerXcd);
-}
 size_t attn_bf16_workspace_bytes(int64_t N, int32_t H)
 {
     if (N <= 0 || H <= 0) return 0;
-    const size_t b = vt_bytes(N, H) + partial_bytes() + redo_flags(N, H) * sizeof(uint32_t);
+    const size_t b = vt_bytes(N, H) + partial_bytes();
     return (b + 255) & ~(size_t)255;
 }
 
@@ -626,32 +687,17 @@ int launch_attn_bf16_d128(const void *q, const void *k, const void *v, int64_t N
     const int64_t left = sch.items_per_xcd - sch.full_items;
     char *vt = (char *)workspace;
     float *partial = (float *)(vt + vt_bytes(N, H));
-    uint32_t *redo = (uint32_t *)((char *)partial + partial_bytes());
-    // compact queries may outnumber the keys (cross-attention of many rows over a short context): the flag
-    // area is sized for up to N queries, larger selections run the exact form alone, which needs no flags
-    const bool two_forms = (size_t)(slots * kNumXcd) <= redo_flags(N, H);
     hipLaunchKernelGGL(transpose_v_kernel, dim3((unsigned)ntiles, (unsigned)H), dim3(256), 0, stream,
                        (const __bf16 *)v, N, kv_stride_n, kv_stride_h, ntiles, vt);
     dim3 grid((unsigned)(slots * kNumXcd)), block(kWaves * kWave);
     const float c = scale * 1.44269504088896340736f;
     kernel_timer_begin(stream);
-    if (two_forms)
-        hipLaunchKernelGGL(attn_bf16_kernel<false>, grid, block, 0, stream, (const __bf16 *)q, (const __bf16 *)k,
-                           (const char *)vt, N, H, q_stride_n, q_stride_h, kv_stride_n, kv_stride_h, idx_sel, k_sel,
-                           q_is_compact, c, (__bf16 *)o_sel, o_stride_n, o_scatter, lse_sel, sch, partial, redo);
-    else
-        hipLaunchKernelGGL(attn_bf16_kernel<true>, grid, block, 0, stream, (const __bf16 *)q, (const __bf16 *)k,
-                           (const char *)vt, N, H, q_stride_n, q_stride_h, kv_stride_n, kv_stride_h, idx_sel, k_sel,
-                           q_is_compact, c, (__bf16 *)o_sel, o_stride_n, o_scatter, lse_sel, sch, partial,
-                           (uint32_t *)nullptr);
+    hipLaunchKernelGGL(attn_bf16_kernel, grid, block, 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const char *)vt,
+                       N, H, q_stride_n, q_stride_h, kv_stride_n, kv_stride_h, idx_sel, k_sel, q_is_compact, c,
+                       (__bf16 *)o_sel, o_stride_n, o_scatter, lse_sel, sch, partial);
     kernel_timer_end(stream);
-    // the exact form over the same grid: only workgroups that flagged themselves do anything
-    if (two_forms)
-        hipLaunchKernelGGL(attn_bf16_kernel<true>, grid, block, 0, stream, (const __bf16 *)q, (const __bf16 *)k,
-                           (const char *)vt, N, H, q_stride_n, q_stride_h, kv_stride_n, kv_stride_h, idx_sel, k_sel,
-                           q_is_compact, c, (__bf16 *)o_sel, o_stride_n, o_scatter, lse_sel, sch, partial, redo);
     if (left > 0)
-        hipLaunchKernelGGL(merge_partials_kernel, dim3((unsigned)(left * kNumXcd), kBq / 8), dim3(256), 0, stream, partial, sch,
+        hipLaunchKernelGGL(merge_partials_kernel, dim3((unsigned)(left * kNumXcd), kBq / 32), dim3(256), 0, stream, partial, sch,
                            H, k_sel, N, idx_sel, (__bf16 *)o_sel, o_stride_n, o_scatter, lse_sel);
     return check_launch("astraea_sparse_attn_fwd(bf16)");
 }

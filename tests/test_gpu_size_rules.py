@@ -79,3 +79,48 @@ def test_linear_f32_operand_past_4_gib():
     ab.astraea_sparse_linear(x, w, None, idx, k, y)
     torch.cuda.synchronize()
     assert (y.double() - x[n - k:].double() @ w.double().T).abs().max().item() <= 1e-4
+
+
+# bf16 attention: 256 queries per workgroup, 32 per wave (rows pass through LDS whole, four at a time), 64 keys per tile; the
+# items of a partly filled round are cut into key shares where the launch's estimate says so (last four cases: 8, 3, 2
+# and 1 shares).  `hot` plants one key whose logit overflows the first tile's offset, so that the workgroup repeats its
+# sweep; compact queries may outnumber the keys.  Oracle: fp64 softmax; bar: relative L2 1e-2 per row and head.
+@pytest.mark.parametrize("n,h,k,hot,scatter,splits", [
+    (1, 1, 1, False, True, 1), (63, 2, 31, False, True, 1), (64, 1, 33, True, False, 1), (65, 3, 65, True, True, 1),
+    (129, 2, 5000, True, False, 1), (300, 1, 255, False, True, 1), (512, 9, 257, True, True, 1),
+    (4000, 1, 30, True, True, 8), (2025, 24, 608, True, True, 3), (4100, 24, 1100, False, False, 2), (900, 24, 450, True, True, 1),
+])
+def test_attn_bf16_tiles(n, h, k, hot, scatter, splits):
+    if splits is not None:
+        assert ab.astraea_attn_plan(n, h, k)["splits"] == splits
+    g = torch.Generator(device=DEV).manual_seed(n + h + k)
+    q, kc, vc = (torch.randn(m, h, 128, device=DEV, generator=g).bfloat16() for m in (k, n, n))
+    if hot:
+        q[[0, k // 2, k - 1], :, 0] = 64.0
+        kc[n - 1, :, 0] = 64.0                               # 362 nats above the rest for those rows
+    idx = torch.randperm(max(n, k), device=DEV, generator=g)[:k].sort().values.to(torch.int32)
+    scale = 1.0 / math.sqrt(128)
+    lse = torch.full((k, h), math.nan, device=DEV)
+    ws = torch.full((ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, 128),), 255, dtype=torch.uint8, device=DEV)
+    out = torch.randn(n if scatter else k, h * 128 + 8, device=DEV, generator=g).bfloat16()
+    before = out.clone()
+    if scatter:
+        ab.astraea_sparse_attn_update_fwd(q, kc, vc, idx, k, out[:, :h * 128], scale, q_is_compact=True, lse_sel=lse, workspace=ws)
+        got = out[idx.long(), :h * 128]
+    else:
+        out = torch.empty(k, h, 128, dtype=torch.bfloat16, device=DEV)
+        ab.astraea_sparse_attn_fwd(q, kc, vc, None, k, out, scale, q_is_compact=True, lse_sel=lse, workspace=ws)
+        got = out
+    torch.cuda.synchronize()
+    for i in range(h):
+        logits = (q[:, i].double() @ kc[:, i].double().T.contiguous()) * scale
+        ref = torch.softmax(logits, 1) @ vc[:, i].double()
+        assert_rel_l2(got.view(k, h, 128)[:, i].double().cpu().numpy(), ref.cpu().numpy(), tag=f"head {i}")
+        want = torch.logsumexp(logits, 1)
+        # bf16 rounding of P averages out over the keys of a flat row and is absent where one key carries the row; single
+        # tiles of a handful of keys can show all of it, 2^-9
+        assert ((lse[:, i].double() - want).abs() / want.abs().clamp(min=1.0)).max().item() <= 2.0 ** -9
+    if scatter:
+        keep = torch.ones(out.shape, dtype=torch.bool, device=DEV)
+        keep[idx.long(), :h * 128] = False
+        assert torch.equal(out[keep], before[keep])
