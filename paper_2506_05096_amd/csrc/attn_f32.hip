@@ -8,8 +8,22 @@
 // (one exchange between lane l and lane l+32), and the S^T accumulator registers feed the second
 // product directly as its B operand.
 //
-// Workgroup = 4 waves x 32 queries; keys are swept in tiles of 32 staged in LDS.  This is the
-// accuracy-first path for small layers; the bf16 path carries the throughput.
+// Shape on gfx950:
+//  * workgroup = 4 waves x 32 queries, two workgroups per CU; keys are swept in tiles of 32.  K and V tiles go from global
+//    memory straight into two LDS stages (global_load_lds_dwordx4), one tile ahead, one barrier per tile; 16-byte
+//    chunks are XOR-swizzled inside a row, so that reads meet no bank conflicts.
+//  * the first product's contraction is permuted: a lane reads 8 consecutive floats of its key row (two 16-byte reads) and
+//    MFMA j of the step takes index pair {j, 8 + j}; the second product reads V by the float, 32 consecutive ones of a row.
+//  * bound by the matrix pipe (4096 flops per MFMA in 64 clocks, 157 TFLOP/s) plus the vector instructions, which do not
+//    overlap fp32 MFMAs.  So each row's exponent offset is fixed at its max over the first tile, and the sweep takes
+//    no max and rescales nothing: fma, exponential and add per logit.  A row that outgrows the offset by more than 2^80
+//    shows in its row sum; the workgroup then repeats its sweep in the exact form (running max).
+// Measured (call with merge; before: tiles staged through registers between two barriers, running max, 4-byte K reads):
+// 2048 queries x 4096 keys x 8 heads x 64 196 -> 146 us (118 TFLOP/s), 6000 x 6000 x 24 x 64 2303 -> 1786, 3000 x 6000 x 24 x
+// 128 3439 -> 2092, 250 x 2500 x 8 x 128 79 -> 51.  Error against 64 bits unchanged (6.7e-7 at the first).  Not the number
+// of workgroups per CU (forced to two: no change); with flat softmax rows, whose operands switch less, 136 us.
+#include <type_traits>
+
 #include "gfx950.h"
 
 namespace astraea {
@@ -19,6 +33,7 @@ namespace {
 constexpr int kWaves = 4;
 constexpr int kBq = 32 * kWaves;   // queries per workgroup
 constexpr int kBk = 32;            // keys per tile
+constexpr float kBig = 0x1p80f;    // a final row sum above this: the workgroup repeats its sweep in the exact form
 
 __device__ __forceinline__ float xhalf_max(float x)
 {
@@ -28,8 +43,14 @@ __device__ __forceinline__ float xhalf_max(float x)
 }
 __device__ __forceinline__ float xhalf_sum(float x) { return x + __shfl_xor(x, 32); }
 
-template <int D>
-__global__ __launch_bounds__(kWaves *kWave) void attn_f32_kernel(
+__device__ __forceinline__ float lds_read_f32(uint32_t addr)
+{
+    return *reinterpret_cast<const float __attribute__((address_space(3))) *>((uintptr_t)addr);
+}
+
+// FAR: 32 rows span 4 GiB or more, copies take 64-bit lane addresses.
+template <int D, bool FAR>
+__global__ __launch_bounds__(kWaves *kWave, 2) void attn_f32_kernel(
     const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v, int64_t N, int32_t H,
     int64_t q_stride_n, int64_t q_stride_h, int64_t kv_stride_n, int64_t kv_stride_h,
     const int32_t *__restrict__ idx_sel, int64_t k_sel, int q_is_compact, float scale_log2e,
@@ -37,106 +58,204 @@ __global__ __launch_bounds__(kWaves *kWave) void attn_f32_kernel(
     int64_t tiles_per_split, float *__restrict__ partial)
 {
     constexpr int kPartialPitch = D + 4;   // a share's row: D accumulators, running max, row sum (16-byte aligned)
-    constexpr int KP = D + 2;      // K tile pitch (floats): lanes (key, d-parity) hit 64 distinct banks
-    constexpr int VP = D + 8;      // V tile pitch: rows r and r+4 land 32 banks apart
-    constexpr int DB = D / 32;
-    __shared__ float k_lds[kBk * KP];
-    __shared__ float v_lds[kBk * VP];
+    constexpr int DB = D / 32, DS = D / 16;
+    constexpr int kRowBytes = D * 4, kTileBytes = kBk * kRowBytes, kStageBytes = 2 * kTileBytes;   // K tile, then V tile
+    constexpr int kRowsPerCopy = 1024 / kRowBytes;                   // a copy instruction fills 1 KiB of a tile
+    constexpr int kCopies = kTileBytes / 1024 / kWaves;              // per wave and tile, K and V each
+    __shared__ __attribute__((aligned(1024))) char lds[2 * kStageBytes];
+    __shared__ uint32_t wave_outgrew[kWaves];
 
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int qc = lane & 31, hf = lane >> 5;
     const int head = blockIdx.y;
     const int64_t r0 = (int64_t)blockIdx.x * kBq + wave * 32;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
 
-    // Q operand: lane holds query column qc, head-dim elements 2s + hf
-    int64_t r = r0 + qc;
-    if (r > k_sel - 1) r = k_sel - 1;                    // ragged last tile: duplicate a valid row, never stored
-    // an index outside [0, N) reads a valid row instead
-    const int64_t qrow = q_is_compact ? r : (int64_t)clamp_row(idx_sel[r], (int32_t)N);
-    const float *qp = q + qrow * q_stride_n + (int64_t)head * q_stride_h;
-    float qreg[D / 2];
-#pragma unroll
-    for (int s = 0; s < D / 2; ++s) qreg[s] = qp[2 * s + hf];
-
-    floatx16 oacc[DB];
-#pragma unroll
-    for (int b = 0; b < DB; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) oacc[b][i] = 0.0f;
-    float m_run = -INFINITY;   // running max of the scaled logits in log2 units
-    float l_run = 0.0f;        // this lane's share of the running sum
-
-    const float *kb = k + (int64_t)head * kv_stride_h;
-    const float *vb = v + (int64_t)head * kv_stride_h;
     // blockIdx.z takes one of `splits` consecutive key ranges (the budget-aware launch: a small selection
     // does not fill the chip with whole sweeps)
     const int64_t ntiles = (N + kBk - 1) / kBk;
     const int64_t t_begin = (int64_t)blockIdx.z * tiles_per_split;
     const int64_t t_end = t_begin + tiles_per_split < ntiles ? t_begin + tiles_per_split : ntiles;
-    for (int64_t t = t_begin; t < t_end; ++t) {
-        const int64_t key0 = t * kBk;
-        __syncthreads();
-        // stage the tile: 32 rows x D floats each for K and V, 16-byte global loads
-        for (int c = threadIdx.x; c < kBk * (D / 4); c += kWaves * kWave) {
-            const int row = c / (D / 4), c4 = c % (D / 4);
-            int64_t key = key0 + row;
-            if (key > N - 1) key = N - 1;
-            const float4 kv4 = *reinterpret_cast<const float4 *>(kb + key * kv_stride_n + c4 * 4);
-            const float4 vv4 = *reinterpret_cast<const float4 *>(vb + key * kv_stride_n + c4 * 4);
-            float *kd = k_lds + row * KP + c4 * 4;
-            kd[0] = kv4.x; kd[1] = kv4.y; kd[2] = kv4.z; kd[3] = kv4.w;
-            *reinterpret_cast<float4 *>(v_lds + row * VP + c4 * 4) = vv4;
+
+    // ---- tile copies.  Instruction i of this wave fills rows kRowsPerCopy * (wave + 4 i) .. of the K and of the V tile.
+    // Physical chunk p of row r holds logical chunk p ^ (r & 15) of K (a read takes one chunk of each of 32 rows) and
+    // p ^ 8 * ((r / 4) & 1) of V (a read takes 128 bytes of rows r and r + 4).
+    // Past the last tile of the range the last one is copied again, into a stage that nothing reads.
+    const int64_t row_pitch = kv_stride_n * 4, tile_pitch = row_pitch * kBk;
+    const char *kb = reinterpret_cast<const char *>(k + (int64_t)head * kv_stride_h);
+    const char *vb = reinterpret_cast<const char *>(v + (int64_t)head * kv_stride_h);
+    const int c_row = lane / (kRowBytes / 16), c_chunk = lane % (kRowBytes / 16);
+    using Off = std::conditional_t<FAR, int64_t, uint32_t>;
+    Off koff[kCopies], voff[kCopies];            // this lane's byte offsets inside a tile
+    auto offsets = [&](int64_t rows) __attribute__((always_inline)) {      // of a tile with this many valid rows: those past them re-read the last
+#pragma unroll
+        for (int i = 0; i < kCopies; ++i) {
+            const int r = kRowsPerCopy * (wave + kWaves * i) + c_row;
+            const int64_t from = (r < rows ? r : rows - 1) * row_pitch;
+            koff[i] = (Off)(from + ((c_chunk ^ (r & 15)) << 4));
+            voff[i] = (Off)(from + ((c_chunk ^ (((r >> 2) & 1) << 3)) << 4));
         }
-        __syncthreads();
+    };
+    auto copy = [&](const char *kt, const char *vt, uint32_t stage, int n) __attribute__((always_inline)) {       // copy n of 2 * kCopies of a tile
+        const int i = n >> 1;
+        const char *src = n & 1 ? vt : kt;
+        const Off off = n & 1 ? voff[i] : koff[i];
+        const uint32_t dst = lds0 + stage + (n & 1 ? kTileBytes : 0) + (wave + kWaves * i) * 1024;
+        if (FAR) dma16_far(src + off, dst);
+        else dma16(src, (uint32_t)off, dst);
+    };
+    auto rows_of = [&](int64_t t) { return N - t * kBk < kBk ? N - t * kBk : (int64_t)kBk; };
+    auto first_tile = [&]() __attribute__((always_inline)) {
+        offsets(rows_of(t_begin));
+#pragma unroll
+        for (int n = 0; n < 2 * kCopies; ++n) copy(kb + t_begin * tile_pitch, vb + t_begin * tile_pitch, 0, n);
+    };
+    first_tile();
+
+    // Q operand: lane holds query column qc, head-dim elements 16 s + 8 hf + j in qreg[8 s + j]
+    int64_t r = r0 + qc;
+    if (r > k_sel - 1) r = k_sel - 1;                    // ragged last tile: duplicate a valid row, never stored
+    // an index outside [0, N) reads a valid row instead
+    const int64_t qrow = q_is_compact ? r : (int64_t)clamp_row(idx_sel[r], (int32_t)N);
+    const float *qp = q + qrow * q_stride_n + (int64_t)head * q_stride_h + 8 * hf;
+    float qreg[D / 2];
+#pragma unroll
+    for (int s = 0; s < DS; ++s) {
+        const floatx4 lo = *reinterpret_cast<const floatx4 *>(qp + 16 * s), hi = *reinterpret_cast<const floatx4 *>(qp + 16 * s + 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            qreg[8 * s + j] = lo[j];
+            qreg[8 * s + 4 + j] = hi[j];
+        }
+    }
+    // a load still counted as pending at the loop header would make the compiler wait on the copies inside the loop
+#pragma unroll
+    for (int s = 0; s < D / 2; ++s) asm volatile("" : "+v"(qreg[s]));
+
+    // ---- LDS read offsets inside a stage; the stage is a constant of the unrolled loop.
+    // K fragment (s, half): row qc, logical chunk 4 s + 2 hf + half; s >= 4 adds 256 bytes
+    uint32_t ka[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) ka[u] = lds0 + qc * kRowBytes + (((4 * (u >> 1) + 2 * hf + (u & 1)) ^ (qc & 15)) << 4);
+    // V fragment (i, b): row (i/4)*8 + 4 hf + i%4, float 32 b + qc; b >= 2 adds 256 bytes
+    uint32_t va[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+        va[b] = lds0 + kTileBytes + 4 * hf * kRowBytes + (((8 * b + (qc >> 2)) ^ (hf << 3)) << 4) + 4 * (qc & 3);
+
+    floatx16 oacc[DB];
+    float m_run;               // exponent offset of the row: max of its scaled logits in log2 units, over the first tile or so far
+    float l_run;               // this lane's share of the running sum
+
+    // One tile out of stage PAR; the copies of the next tile go out behind the first MFMAs.
+    auto tile = [&](int64_t t, auto exact_tag, auto par_tag) __attribute__((always_inline)) {
+        constexpr bool EXACT = decltype(exact_tag)::value;
+        constexpr uint32_t at = decltype(par_tag)::value * kStageBytes, next = kStageBytes - at;
+        // tile t has landed, for every wave, and every wave is past its last read of tile t - 1
+        wait_dma();
+        __builtin_amdgcn_s_barrier();
+        const int64_t tn = t + 1 < t_end ? t + 1 : t;
+        if ((tn + 1) * kBk > N) offsets(N - tn * kBk);         // only the last tile can be ragged
+        const char *kt = kb + tn * tile_pitch, *vt = vb + tn * tile_pitch;
 
         // S^T[key, q] = sum_d K[key, d] Q[q, d]
+        floatx4 kf[2][2];
+        float vf[2][4 * DB];
+        auto read_k = [&](int s, int half) { kf[s & 1][half] = lds_read_f32x4(ka[2 * (s & 3) + half] + (at + (s >> 2) * 256)); };
+        auto read_v = [&](int g, int u) {          // u = 4 keys of group g by DB blocks
+            const int i = 4 * g + u / DB, b = u % DB;
+            vf[g & 1][u] = lds_read_f32(va[b & 1] + (at + (8 * (i >> 2) + (i & 3)) * kRowBytes + (b >> 1) * 256));
+        };
+        read_k(0, 0);
+        read_k(0, 1);
         floatx16 sacc;
 #pragma unroll
         for (int i = 0; i < 16; ++i) sacc[i] = 0.0f;
 #pragma unroll
-        for (int s = 0; s < D / 2; ++s) {
-            const float a = k_lds[qc * KP + 2 * s + hf];      // A: row = key (lane&31), k index = hf
-            sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, qreg[s], sacc, 0, 0, 0);
+        for (int s = 0; s < DS; ++s)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[s & 1][j >> 2][j & 3], qreg[8 * s + j], sacc, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (s + 1 < DS) {
+                    if (j < 2) read_k(s + 1, j);
+                    } else {
+#pragma unroll
+                    for (int u = 0; u < 4 * DB; ++u)
+                        if (u * 8 / (4 * DB) == j) read_v(0, u);
+                }
+                if (s < 2 && j >= 3 && j < 3 + kCopies) copy(kt, vt, next, s * kCopies + j - 3);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        // register i of sacc: key = 32 t + (i/4)*8 + hf*4 + i%4, query = qc
+        if ((t + 1) * kBk > N) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (t * kBk + (i >> 2) * 8 + hf * 4 + (i & 3) >= N) sacc[i] = -INFINITY;
         }
-        // register i of sacc: key = key0 + (i/4)*8 + hf*4 + i%4, query = qc
-        float tmax = -INFINITY;
+        if (EXACT || t == t_begin) {
+            float tmax = sacc[0];
+#pragma unroll
+            for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, sacc[i]);
+            tmax = xhalf_max(tmax) * scale_log2e;
+            const float m_new = fmaxf(m_run, tmax);
+            if (EXACT) {
+                const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);          // 0 on the first tile
+                l_run *= alpha;
+#pragma unroll
+                for (int b = 0; b < DB; ++b)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
+            }
+            m_run = m_new;
+        }
+        float ps[2] = {0.0f, 0.0f};
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            float sv = sacc[i] * scale_log2e;
-            const int64_t key = key0 + (i >> 2) * 8 + hf * 4 + (i & 3);
-            if (key >= N) sv = -INFINITY;
-            sacc[i] = sv;
-            tmax = fmaxf(tmax, sv);
+            sacc[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[i], scale_log2e, -m_run));
+            ps[i & 1] += sacc[i];
         }
-        tmax = xhalf_max(tmax);
-        const float m_new = fmaxf(m_run, tmax);
-        const float alpha = exp2f(m_run - m_new);          // 0 on the first tile
-        float psum = 0.0f;
+        l_run += ps[0] + ps[1];
+        // O^T[d, q] += sum_key V[key, d] P^T[key, q]; MFMA i contracts keys (i/4)*8 + i%4 (+4 in the upper half)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const float p = exp2f(sacc[i] - m_new);
-            sacc[i] = p;
-            psum += p;
-        }
-        l_run = l_run * alpha + psum;
-        m_run = m_new;
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+            for (int b = 0; b < DB; ++b) {
+                oacc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[(i >> 2) & 1][(i & 3) * DB + b], sacc[i], oacc[b], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (i < 12) read_v((i >> 2) + 1, (i & 3) * DB + b);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    };
+    auto sweep = [&](auto exact_tag) __attribute__((always_inline)) {
+        using P0 = std::integral_constant<int, 0>;
+        using P1 = std::integral_constant<int, 1>;
 #pragma unroll
         for (int b = 0; b < DB; ++b)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
-        // O^T[d, q] += sum_key V[key, d] P^T[key, q]; MFMA i contracts keys (i/4)*8 + i%4 (+4 in the upper half)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int key = (i >> 2) * 8 + hf * 4 + (i & 3);
-#pragma unroll
-            for (int b = 0; b < DB; ++b) {
-                const float a = v_lds[key * VP + b * 32 + qc];   // A: row = d (lane&31), k index = hf
-                oacc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, sacc[i], oacc[b], 0, 0, 0);
-            }
+            for (int i = 0; i < 16; ++i) oacc[b][i] = 0.0f;
+        m_run = -INFINITY;
+        l_run = 0.0f;
+        int64_t t = t_begin;
+        for (; t + 1 < t_end; t += 2) {
+            tile(t, exact_tag, P0{});
+            tile(t + 1, exact_tag, P1{});
         }
+        if (t < t_end) tile(t, exact_tag, P0{});
+    };
+    sweep(std::false_type{});
+    float l_tot = xhalf_sum(l_run);
+    // Did a row outgrow its offset (or overflow, or meet a NaN)?  The workgroup decides as one, since its waves share the tiles.
+    const bool outgrew = __builtin_amdgcn_ballot_w64(!(l_tot <= kBig)) != 0;
+    if (lane == 0) wave_outgrew[wave] = outgrew ? 1u : 0u;
+    wait_dma();
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(wave_outgrew[0] | wave_outgrew[1] | wave_outgrew[2] | wave_outgrew[3]) != 0) {
+        first_tile();
+        sweep(std::true_type{});
+        l_tot = xhalf_sum(l_run);
     }
-
-    const float l_tot = xhalf_sum(l_run);
     const int64_t rr = r0 + qc;
     if (rr >= k_sel) return;
     if (splits > 1) {
@@ -266,14 +385,14 @@ int launch_attn_f32(const void *q, const void *k, const void *v, int64_t N, int3
     dim3 grid((unsigned)((k_sel + kBq - 1) / kBq), (unsigned)H, (unsigned)splits), block(kWaves * kWave);
     const float c = scale * 1.44269504088896340736f;
     kernel_timer_begin(stream);
-    if (D == 64)
-        hipLaunchKernelGGL(attn_f32_kernel<64>, grid, block, 0, stream, (const float *)q, (const float *)k,
-                           (const float *)v, N, H, q_stride_n, q_stride_h, kv_stride_n, kv_stride_h, idx_sel, k_sel,
-                           q_is_compact, c, (float *)o_sel, o_stride_n, o_scatter, lse_sel, splits, tps, partial);
-    else
-        hipLaunchKernelGGL(attn_f32_kernel<128>, grid, block, 0, stream, (const float *)q, (const float *)k,
-                           (const float *)v, N, H, q_stride_n, q_stride_h, kv_stride_n, kv_stride_h, idx_sel, k_sel,
-                           q_is_compact, c, (float *)o_sel, o_stride_n, o_scatter, lse_sel, splits, tps, partial);
+    const bool far = kv_stride_n * 4 * kBk >= (int64_t)1 << 32;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, stream, (const float *)q, (const float *)k, (const float *)v, N, H,
+                           q_stride_n, q_stride_h, kv_stride_n, kv_stride_h, idx_sel, k_sel, q_is_compact, c,
+                           (float *)o_sel, o_stride_n, o_scatter, lse_sel, splits, tps, partial);
+    };
+    if (D == 64) go(far ? attn_f32_kernel<64, true> : attn_f32_kernel<64, false>);
+    else go(far ? attn_f32_kernel<128, true> : attn_f32_kernel<128, false>);
     kernel_timer_end(stream);
     if (splits > 1) {
         const int64_t threads = k_sel * H * (D / 4);

@@ -124,3 +124,50 @@ def test_attn_bf16_tiles(n, h, k, hot, scatter, splits):
         keep = torch.ones(out.shape, dtype=torch.bool, device=DEV)
         keep[idx.long(), :h * 128] = False
         assert torch.equal(out[keep], before[keep])
+
+
+# fp32 attention: 128 queries per workgroup, tiles of 32 keys in two LDS stages, key ranges shared out when the selection is
+# small; `hot` makes workgroups repeat their sweep in the exact form; `pitch`: keys 2^25 floats apart, past 32-bit offsets.
+# Bounds: a logit L is a sum of d products, off by up to d * 2^-24 * |L|.  Without the hot key |L| is a few nats and the
+# errors of its terms average out: 1e-5.  The hot key gives logits of up to 25 nats to the other rows (128 * 2^-24 * 25 =
+# 2e-4 of a probability, times values of size 3) and 362 nats to the hot rows, whose log-sum-exp is that logit.
+@pytest.mark.parametrize("n,h,k,d,hot,scatter,pitch", [
+    (1, 1, 1, 64, False, True, None), (31, 2, 31, 128, False, False, None), (32, 1, 5, 64, True, True, None),
+    (33, 3, 33, 64, True, True, None), (65, 2, 127, 128, True, False, None), (300, 2, 129, 64, False, True, None),
+    (1000, 3, 257, 128, True, True, None), (2085, 8, 300, 64, True, True, None), (700, 2, 5000, 64, True, False, None),
+    (40, 1, 33, 64, True, False, 1 << 25), (70, 1, 33, 128, False, False, 1 << 25),
+])
+def test_attn_f32_tiles(n, h, k, d, hot, scatter, pitch):
+    g = torch.Generator(device=DEV).manual_seed(n + h + k)
+    q, kc, vc = (torch.randn(m, h, d, device=DEV, generator=g) for m in (k, n, n))
+    if hot:
+        q[[0, k // 2, k - 1], :, 0] = 64.0
+        kc[n - 1, :, 0] = 64.0 * math.sqrt(d / 128)          # 362 nats above the rest for those rows
+    if pitch:
+        wide = [torch.empty(n, pitch, device=DEV)[:, :h * d].view(n, h, d) for _ in range(2)]
+        for dst, src in zip(wide, (kc, vc)):
+            dst.copy_(src)
+    idx = torch.randperm(max(n, k), device=DEV, generator=g)[:k].sort().values.to(torch.int32)
+    scale = 1.0 / math.sqrt(d)
+    lse = torch.full((k, h), math.nan, device=DEV)
+    ws = torch.full((max(256, ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d)),), 255, dtype=torch.uint8, device=DEV)
+    out = torch.randn(n if scatter else k, h * d + 8, device=DEV, generator=g)
+    before = out.clone()
+    kv = wide if pitch else (kc, vc)
+    if scatter:
+        ab.astraea_sparse_attn_update_fwd(q, *kv, idx, k, out[:, :h * d], scale, q_is_compact=True, lse_sel=lse, workspace=ws)
+        got = out[idx.long(), :h * d].view(k, h, d)
+    else:
+        got = torch.empty(k, h, d, device=DEV)
+        ab.astraea_sparse_attn_fwd(q, *kv, None, k, got, scale, q_is_compact=True, lse_sel=lse, workspace=ws)
+    torch.cuda.synchronize()
+    tol, tol_lse = (6e-4, d * 2.0 ** -24 * 362) if hot else (1e-5, 1e-5)
+    for i in range(h):
+        logits = (q[:, i].double() @ kc[:, i].double().T.contiguous()) * scale
+        ref = torch.softmax(logits, 1) @ vc[:, i].double()
+        assert (got[:, i].double() - ref).abs().max().item() <= tol
+        assert (lse[:, i].double() - torch.logsumexp(logits, 1)).abs().max().item() <= tol_lse
+    if scatter:
+        keep = torch.ones(out.shape, dtype=torch.bool, device=DEV)
+        keep[idx.long(), :h * d] = False
+        assert torch.equal(out[keep], before[keep])
