@@ -12,7 +12,7 @@
 //      an element is selected iff key > T, or key == T and fewer than `need` equal elements
 //      precede it.  Ranks come from wavefront ballots and prefix popcounts.
 // The score array (4N bytes) stays in L2 across the five small launches; the step is latency-bound.
-// Up to 32768 scores take a single-workgroup kernel instead (one launch, keys held in LDS).  (A single
+// Up to 32768 scores take a single-workgroup kernel instead (one launch, keys held in registers).  (A single
 // workgroup that streams more scores than LDS holds from L2 in every pass was measured too: one launch, but
 // one compute unit's loads are latency-bound, 129 us against 43 us at 118800 scores.)
 #include <mutex>
@@ -49,6 +49,12 @@ __device__ __forceinline__ uint32_t score_key(float s)
     if ((b & 0x7fffffffu) > 0x7f800000u) return 0u;        // NaN: below every number
     if (b == 0x80000000u) b = 0u;                           // -0 == +0
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+}
+
+// Set bits of a ballot below this lane.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
 // k > 0: empty prefix, the passes refine it.  k == 0: the passes are skipped and the threshold is
@@ -293,124 +299,166 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(const float *__rest
     }
 }
 
-// ---- small inputs: the whole selection in one workgroup and one launch.  Up to kSmallMax keys live in LDS
-// (128 KiB of the CU's 160); the three radix passes, the digit search and the ordered emit are the steps of
-// the kernels above with workgroup barriers where those have launches.  Thread t owns the contiguous
-// elements [t*items, (t+1)*items), so ranks follow index order; a thread adds a run of equal digits with one
-// LDS atomic, which keeps tightly clustered scores (all of them in one or two bins) from serialising.
+// ---- small inputs: the whole selection in one workgroup and one launch, the keys in registers.  Wave w owns the elements
+// [w*items*64, (w+1)*items*64), element (w*items + j)*64 + lane in register j, so that loads and stores are coalesced and
+// ranks in index order come from ballots.  The keys' range is found first and the passes look at its bits only: digit 1 is
+// (key - lowest) >> shift, up to 2048 bins, digit 2 the next 11 bits of the keys that share it, and so on until the shift
+// is 0 (at most three passes; scores of one magnitude need two).  That spreads scores of similar size, which the top
+// bits of the key would put into one or two bins; equal scores find four counters per bin.
+// Bound by instructions issued on one CU and by the chain of barriers.  Measured, indices alone / with every output (before:
+// keys in LDS, digits at fixed bits, a contiguous run of elements per thread): 4096 scores 10.0 / 11.4 -> 6.9 / 7.1 us, 17550
+// 20.0 / 40.2 -> 12.8 / 15.5, 32768 30.1 / 77.7 -> 21.4 / 26.3; scores in {0, 1, 2} 17550 25.2 / 45.2 -> 20.3 / 23.0.  A run-time
+// count of elements per thread took 18.1 / 20.5 at 17550, eight copies of the histogram side by side 20.5 / 23.5.
 constexpr int kSmallMax = 32768;
 constexpr int kSmallThreads = 1024;
+constexpr int kSmallWaves = kSmallThreads / kWave;
+constexpr int kCopies = 4;          // of the histogram, by lane: equal digits of a wave meet 16 to a counter instead of 64
+constexpr int kCopyPitch = kBins + 16;       // their counters in different banks
 
+template <int ITEMS>
 __global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(const float *__restrict__ score, int32_t N, uint32_t k,
                                                                    int32_t *__restrict__ idx_sel,
                                                                    int32_t *__restrict__ idx_remain,
                                                                    uint8_t *__restrict__ sel_mask,
                                                                    int32_t *__restrict__ skip_count)
 {
-    __shared__ uint32_t keys[kSmallMax];
-    __shared__ uint32_t hist[kBins];
-    __shared__ uint32_t wt_a[kSmallThreads / kWave], wt_b[kSmallThreads / kWave];
-    __shared__ uint32_t s_prefix, s_mask, s_krem;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const int items = ((N + kSmallThreads - 1) / kSmallThreads) | 1;    // odd: a thread's walk through its elements is free of bank conflicts
-    const int first = tid * items;
-    const int last = first + items < N ? first + items : N;         // this thread's elements: [first, last)
-    for (int i = tid; i < N; i += kSmallThreads) keys[i] = score_key(score[i]);
-    if (tid == 0) {
-        s_prefix = k ? 0u : 0xffffffffu;       // k == 0: a threshold no key reaches, nothing is selected
-        s_mask = 0;
-        s_krem = k;
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kCopyPitch * kCopies];
+    __shared__ uint32_t wt_a[kSmallWaves], wt_b[kSmallWaves];
+    __shared__ uint32_t s_base, s_krem;
+    constexpr uint32_t kPad = 0xffffffffu;      // stands for no element; above every key (the largest is +inf's, 0xff800000)
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int first = wave * ITEMS * kWave + lane;                      // element j of this thread: first + 64 j
+    uint32_t key[ITEMS];
+    int32_t skip[ITEMS];
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const int i = first + j * kWave < N ? first + j * kWave : N - 1;     // unconditional loads stay in flight together
+        key[j] = __float_as_uint(score[i]);
+        if (skip_count) skip[j] = skip_count[i];
+    }
+    for (int i = tid; i < kCopyPitch * kCopies / 4; i += kSmallThreads) reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0, 0, 0, 0);
+    uint32_t *mine = hist + (lane & (kCopies - 1)) * kCopyPitch;
+    uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const uint32_t kk = score_key(__uint_as_float(key[j]));
+        lo = kk < lo ? kk : lo;                                     // the last element's key again where there is none
+        hi = kk > hi ? kk : hi;
+        key[j] = first + j * kWave < N ? kk : kPad;
+    }
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) {
+        const uint32_t l = __shfl_xor(lo, d), h = __shfl_xor(hi, d);
+        lo = l < lo ? l : lo;
+        hi = h > hi ? h : hi;
+    }
+    if (lane == 0) {
+        wt_a[wave] = lo;
+        wt_b[wave] = hi;
     }
     __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) {
+        lo = wt_a[w] < lo ? wt_a[w] : lo;
+        hi = wt_b[w] > hi ? wt_b[w] : hi;
+    }
+    // k == 0: a threshold no key reaches, nothing is selected
+    uint32_t T = kPad - 1, need = 0;
     if (k > 0) {
-        for (int pass = 0; pass < kNumPass; ++pass) {
-            const int shift = kShift[pass];
-            const uint32_t nb = 1u << kBits[pass];
-            for (int i = tid; i < kBins; i += kSmallThreads) hist[i] = 0;
-            __syncthreads();
-            const uint32_t prefix = s_prefix, mask = s_mask, k_rem = s_krem;
-            uint32_t run_bin = 0, run_len = 0;
-            for (int i = first; i < last; ++i) {
-                const uint32_t key = keys[i];
-                if ((key & mask) != prefix) continue;
-                const uint32_t b = (key >> shift) & (nb - 1);
-                if (run_len && b != run_bin) {
-                    atomicAdd(&hist[run_bin], run_len);
-                    run_len = 0;
-                }
-                run_bin = b;
-                ++run_len;
+        // the candidates are the keys in [base, base + last]; k_rem of them are still to be taken
+        uint32_t base = __builtin_amdgcn_readfirstlane(lo), last = __builtin_amdgcn_readfirstlane(hi) - base, k_rem = k;
+        for (;;) {
+            const int width = last ? 32 - __builtin_clz(last) : 0;
+            const int shift = width > 11 ? width - 11 : 0;
+#pragma unroll
+            for (int j = 0; j < ITEMS; ++j) {
+                const uint32_t off = key[j] - base;
+                if (off <= last) atomicAdd(&mine[off >> shift], 1u);
             }
-            if (run_len) atomicAdd(&hist[run_bin], run_len);
             __syncthreads();
             // the digit: walking the bins from the largest down, the first whose running count reaches k_rem.
-            // Thread t owns bins nb-1 - (t*per + j), j < per (per = 2 or 1).
-            const uint32_t per = nb / kSmallThreads;
-            uint32_t cnt[2] = {0, 0}, mine = 0;
-            for (uint32_t j = 0; j < per; ++j) {
-                cnt[j] = hist[nb - 1 - (tid * per + j)];
-                mine += cnt[j];
+            // Thread t owns bins 2047 - 2t and 2046 - 2t.
+            const uint32_t top = kBins - 1 - 2 * tid;
+            uint2 *cells = reinterpret_cast<uint2 *>(hist + top - 1);
+            uint32_t c0 = 0, c1 = 0;
+#pragma unroll
+            for (int c = 0; c < kCopies; ++c) {
+                const uint2 u = cells[c * (kCopyPitch / 2)];
+                c1 += u.x;
+                c0 += u.y;
             }
-            uint32_t incl = mine;
+            uint32_t incl = c0 + c1;
 #pragma unroll
             for (int d = 1; d < kWave; d <<= 1) {
                 const uint32_t o = __shfl_up(incl, d);
                 if (lane >= d) incl += o;
             }
-            if (lane == kWave - 1) wt_a[wv] = incl;
+            if (lane == kWave - 1) wt_a[wave] = incl;
+#pragma unroll
+            for (int c = 0; c < kCopies; ++c) cells[c * (kCopyPitch / 2)] = make_uint2(0, 0);           // for the next pass
             __syncthreads();
-            uint32_t run = incl - mine;
-            for (int w = 0; w < wv; ++w) run += wt_a[w];
-            for (uint32_t j = 0; j < per; ++j) {
-                const uint32_t b = nb - 1 - (tid * per + j);
-                if (run < k_rem && run + cnt[j] >= k_rem) {          // true for exactly one bin of one thread
-                    s_prefix = prefix | (b << shift);
-                    s_mask = mask | ((nb - 1) << shift);
-                    s_krem = k_rem - run;
-                }
-                run += cnt[j];
+            uint32_t run = incl - (c0 + c1);
+#pragma unroll
+            for (int w = 0; w < kSmallWaves; ++w) run += w < wave ? wt_a[w] : 0u;
+            if (run < k_rem && run + c0 + c1 >= k_rem) {          // true for exactly one thread
+                const bool second = run + c0 < k_rem;
+                s_base = base + ((second ? top - 1 : top) << shift);
+                s_krem = k_rem - run - (second ? c0 : 0u);
             }
             __syncthreads();
+            base = __builtin_amdgcn_readfirstlane(s_base);
+            k_rem = __builtin_amdgcn_readfirstlane(s_krem);
+            if (shift == 0) break;
+            last = (1u << shift) - 1;
         }
+        T = base;
+        need = k_rem;
     }
     // ordered emit, as in topk_emit_kernel
-    const uint32_t T = s_prefix, need = s_krem;
+    auto above = [&](uint32_t kk) { return kk - (T + 1) < kPad - (T + 1); };       // kk > T and an element
     uint32_t mg = 0, me = 0;
-    for (int i = first; i < last; ++i) {
-        mg += keys[i] > T;
-        me += keys[i] == T;
-    }
-    uint32_t ig = mg, ie = me;
 #pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const uint32_t og = __shfl_up(ig, d), oe = __shfl_up(ie, d);
-        if (lane >= d) {
-            ig += og;
-            ie += oe;
-        }
+    for (int j = 0; j < ITEMS; ++j) {
+        mg += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(above(key[j])));
+        me += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(key[j] == T));
     }
-    if (lane == kWave - 1) {
-        wt_a[wv] = ig;
-        wt_b[wv] = ie;
+    if (lane == 0) {
+        wt_a[wave] = mg;                         // last read before the barriers above
+        wt_b[wave] = me;
     }
     __syncthreads();
-    uint32_t g_before = ig - mg, e_before = ie - me;
-    for (int w = 0; w < wv; ++w) {
-        g_before += wt_a[w];
-        e_before += wt_b[w];
+    uint32_t g_before = 0, e_before = 0;         // keys above / equal to T in front of the wave's present 64 elements
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) {
+        g_before += w < wave ? wt_a[w] : 0u;
+        e_before += w < wave ? wt_b[w] : 0u;
     }
-    for (int i = first; i < last; ++i) {
-        const bool g = keys[i] > T, e = keys[i] == T;
-        const uint32_t sel_before = g_before + (e_before < need ? e_before : need);
-        const bool sel = g || (e && e_before < need);
+    g_before = __builtin_amdgcn_readfirstlane(g_before);
+    e_before = __builtin_amdgcn_readfirstlane(e_before);
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const int i = first + j * kWave;
+        bool sel = above(key[j]);
+        const uint64_t gm = __builtin_amdgcn_ballot_w64(sel), em = __builtin_amdgcn_ballot_w64(key[j] == T);
+        uint32_t sel_before = g_before + lanes_below(gm);
+        if (em == 0) {
+            sel_before += e_before < need ? e_before : need;
+        } else {
+            const uint32_t eb = e_before + lanes_below(em);
+            sel_before += eb < need ? eb : need;
+            sel = sel || (key[j] == T && eb < need);
+        }
         if (sel)
             idx_sel[sel_before] = i;
-        else if (idx_remain)
-            idx_remain[i - sel_before] = i;
-        if (sel_mask) sel_mask[i] = sel ? 1 : 0;
-        if (skip_count) skip_count[i] = sel ? 0 : skip_count[i] + 1;
-        g_before += g;
-        e_before += e;
+        else if (idx_remain && key[j] != kPad)
+            idx_remain[(uint32_t)i - sel_before] = i;
+        if (key[j] != kPad) {
+            if (sel_mask) sel_mask[i] = sel ? 1 : 0;
+            if (skip_count) skip_count[i] = sel ? 0 : skip[j] + 1;
+        }
+        g_before += (uint32_t)__popcll(gm);
+        e_before += (uint32_t)__popcll(em);
     }
 }
 
@@ -465,8 +513,30 @@ int launch_select_topk(const float *score, int64_t N, int64_t k, int32_t *idx_se
 {
     if (N == 0) return ASTRAEA_OK;
     if (N <= kSmallMax) {
-        hipLaunchKernelGGL(topk_small_kernel, dim3(1), dim3(kSmallThreads), 0, stream, score, (int32_t)N, (uint32_t)k,
-                           idx_sel, idx_remain, sel_mask, skip_count);
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(1), dim3(kSmallThreads), 0, stream, score, (int32_t)N, (uint32_t)k, idx_sel,
+                               idx_remain, sel_mask, skip_count);
+        };
+        // elements per thread, rounded up to an even number: a constant, so that nothing is tested per element and
+        // all loads go out together
+        switch ((N + 2 * kSmallThreads - 1) / (2 * kSmallThreads)) {
+        case 1: go(topk_small_kernel<2>); break;
+        case 2: go(topk_small_kernel<4>); break;
+        case 3: go(topk_small_kernel<6>); break;
+        case 4: go(topk_small_kernel<8>); break;
+        case 5: go(topk_small_kernel<10>); break;
+        case 6: go(topk_small_kernel<12>); break;
+        case 7: go(topk_small_kernel<14>); break;
+        case 8: go(topk_small_kernel<16>); break;
+        case 9: go(topk_small_kernel<18>); break;
+        case 10: go(topk_small_kernel<20>); break;
+        case 11: go(topk_small_kernel<22>); break;
+        case 12: go(topk_small_kernel<24>); break;
+        case 13: go(topk_small_kernel<26>); break;
+        case 14: go(topk_small_kernel<28>); break;
+        case 15: go(topk_small_kernel<30>); break;
+        default: go(topk_small_kernel<32>); break;
+        }
         return check_launch("astraea_select_topk");
     }
     const unsigned nblk = (unsigned)((N + kChunk - 1) / kChunk);

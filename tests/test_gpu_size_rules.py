@@ -171,3 +171,35 @@ def test_attn_f32_tiles(n, h, k, d, hot, scatter, pitch):
         keep = torch.ones(out.shape, dtype=torch.bool, device=DEV)
         keep[idx.long(), :h * d] = False
         assert torch.equal(out[keep], before[keep])
+
+
+# top-k in one workgroup: an even number of elements per thread up to 32768 scores, wave w owning a contiguous range; passes
+# over the bits in which the keys differ.  Whole numbers, exact.
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1025, 2047, 2048, 2049, 4096, 4097, 18431, 18432, 18433, 30720, 30721, 32768, 32769])
+@pytest.mark.parametrize("kind", ["narrow", "ties", "equal", "extremes"])
+def test_topk_sizes(n, kind):
+    g = torch.Generator().manual_seed(n)
+    s = 5.54 + 0.1 * torch.randn(n, generator=g)
+    if kind == "ties":
+        s = torch.randint(0, 3, (n,), generator=g).float()
+    elif kind == "equal":
+        s = torch.full((n,), -0.0)
+        s[n // 2:] = 0.0                                      # -0 and +0 are the same score
+    elif kind == "extremes":
+        special = torch.tensor([math.inf, -math.inf, math.nan, 3.4e38, -3.4e38, 1e-45, -1e-45, 0.0, -0.0])
+        pick = torch.rand(n, generator=g) < 0.4
+        s[pick] = special[torch.randint(0, 9, (int(pick.sum()),), generator=g)]
+    skip0 = torch.randint(0, 9, (n,), generator=g).to(torch.int32)
+    for k in sorted({0, 1, n // 3, n - 1, n}):
+        e_idx, e_rest, e_mask = oracle.topk(s.numpy(), k)
+        idx, rest, skip = (torch.full((n + 1,), -7, dtype=torch.int32, device=DEV) for _ in range(3))
+        mask = torch.full((n + 1,), 9, dtype=torch.uint8, device=DEV)
+        skip[:n] = skip0.to(DEV)
+        ws = torch.full((ab.workspace_bytes(ab.OP_SELECT_TOPK, n),), 255, dtype=torch.uint8, device=DEV)
+        ab.astraea_select_topk(s.to(DEV), k, idx, ws, idx_remain=rest, sel_mask=mask, skip_count=skip)
+        torch.cuda.synchronize()
+        assert np.array_equal(idx[:k].cpu().numpy(), e_idx) and (idx[k:] == -7).all()
+        assert np.array_equal(rest[:n - k].cpu().numpy(), e_rest) and (rest[n - k:] == -7).all()
+        assert np.array_equal(mask[:n].cpu().numpy(), e_mask) and mask[n].item() == 9
+        e_skip = np.where(e_mask != 0, 0, skip0.numpy() + 1)
+        assert np.array_equal(skip[:n].cpu().numpy(), e_skip) and skip[n].item() == -7
