@@ -12,7 +12,8 @@
 //    operand and x the B operand, so that an accumulator lane owns one token and 4 consecutive output
 //    features per register group: the epilogue packs them to 8-byte stores along the output row.
 //  * workgroup = 8 waves, two per SIMD, output tile 256 features x 256 tokens, each wave 128 features
-//    x 64 tokens (4 x 2 MFMA blocks, 128 accumulator registers, 3 LDS fragment reads per 4 MFMAs).
+//    x 64 tokens (4 x 2 MFMA blocks, 128 accumulator registers, 3 LDS fragment reads per 4 MFMAs); or, where
+//    that leaves fewer idle CUs in the last round of tiles, 192 or 128 tokens (waves of 64 x 96 or 64 x 64).
 //    One wave per SIMD with 128 x 128 (kWaves = 4, every wave copying, the step's barrier moved in
 //    front of the last quarter so that no fragment read follows it) runs fewer clocks per step at a
 //    lower clock rate, or the other way round: the chip holds its power limit and the two designs
@@ -27,24 +28,25 @@
 //    neighbour's MFMAs fill exactly that time.  A 4-byte load per row touches the lines of two
 //    steps ahead so that the copies hit in L2.
 //  * workgroup ids are mapped so that the 32 workgroups resident on one XCD form an 8 x 4 block of
-//    tiles: they stream 8 row tiles and 4 weight tiles through that XCD's L2 instead of 32 + 32.
+//    tiles: they stream 8 row tiles and 4 weight tiles through that XCD's L2 instead of 32 + 32.  The tiles
+//    left after whole rounds go to all XCDs evenly.
+// Measured with both (us; before: 256-token tiles only, blocks of 8 x 4 dealt whole to the XCDs, so that some had a
+// round more than others): 5000 rows 3072 -> 3072 132 -> 84, 12288 -> 3072 489 -> 300; 7020 rows 3072 -> 9216 380 -> 328, 3072 ->
+// 3072 150 -> 125, 12288 -> 3072 550 -> 457; 1755 rows 3072 -> 9216 143 -> 88; 608 rows 54 -> 45.
 #include "gfx950.h"
 
 namespace astraea {
 namespace {
 
 
-constexpr int kBm = 256;                 // tokens per tile
 constexpr int kBn = 256;                 // output features per tile
 constexpr int kBk = 64;                  // contraction step
 constexpr int kRowBytes = kBk * 2;       // 128 B of a row per step
 constexpr int kTileBytes = 256 * kRowBytes;          // 32 KiB
-constexpr int kStageBytes = 2 * kTileBytes;          // w tile, then x tile
-constexpr int kWaves = 8;                // two per SIMD, 128 features x 64 tokens each
-constexpr int kTb = 16 / kWaves;         // 32-token MFMA blocks per wave
+constexpr int kStageBytes = 2 * kTileBytes;          // w tile, then x tile (32 KiB or less)
+constexpr int kWaves = 8;                // two per SIMD
 constexpr int kCopyWaves = kWaves / 2;   // the waves that issue the tile copies (the second wave of each SIMD)
-constexpr int kCopies = 32 / kCopyWaves; // 1 KiB copy instructions per copying wave and tile
-constexpr int kNumXcd = 8;
+constexpr int kNumXcd = 8, kCuPerXcd = 32, kCus = kNumXcd * kCuPerXcd;
 constexpr int kSbM = 8, kSbN = 4;        // tiles of one XCD round: 8 token tiles x 4 feature tiles
 
 // Waits until only the two most recent vector-memory instructions (the L2 warm-up loads) are pending:
@@ -78,14 +80,21 @@ struct LinearArgs {
     int32_t k_sel, c_in, c_out;
     int32_t n_rows;            // rows of the indexed buffer(s): indices outside [0, n_rows) read a valid row, write none
     int32_t x_indexed, y_indexed, act;
-    int32_t m_tiles, n_tiles, sb_n;   // tile counts and 4-wide super-block count along the features
+    int32_t m_tiles, n_tiles;  // token and feature tiles
 };
 
+// A wave has NB x TB MFMA blocks of 32 features x 32 tokens: <4, 2> makes tiles of 256 tokens, <2, 3> of 192.
+template <int NB, int TB>
 __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArgs a)
 {
+    constexpr int kWn = kBn / (32 * NB), kWm = kWaves / kWn;      // waves along the features and along the tokens
+    constexpr int kBm = 32 * TB * kWm;                            // tokens per tile
+    constexpr int kCopiesW = kBn / 8 / kCopyWaves, kCopiesX = kBm / 8 / kCopyWaves;   // 1 KiB copies per copying wave and step
+    constexpr int kCopies = kCopiesW + kCopiesX;
     // [stage][w tile | x tile].  Stage flips XOR offsets relative to this array, never absolute addresses.
-    constexpr int kPitch = 272;          // epilogue staging: 128 features of a token, padded
-    constexpr int kEpiBytes = kWaves * 64 * kPitch;   // every wave stages 64 tokens at a time
+    constexpr int kPitch = 64 * NB + 16; // epilogue staging: the wave's features of a token, padded
+    constexpr int kEpiTokens = TB == 2 ? 64 : 32 * TB;            // tokens a wave stages at a time
+    constexpr int kEpiBytes = kWaves * kEpiTokens * kPitch;
     __shared__ __attribute__((aligned(1024))) char lds[2 * kStageBytes > kEpiBytes ? 2 * kStageBytes : kEpiBytes];
     __shared__ __attribute__((aligned(256))) uint32_t scrap[kWave];      // where the L2 warm-up loads land
     // destination rows and bias of this tile, fetched while the first step's tiles are on their way: the
@@ -93,26 +102,34 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
     __shared__ int32_t tile_rows[kBm];
     __shared__ __attribute__((aligned(16))) uint16_t tile_bias[kBn];
 
-    // ---- which tile: workgroup ids reach the XCDs round-robin; each XCD takes every 8th super-block
-    // of 8 x 4 tiles and runs its 32 tiles at the same time.
+    // ---- which tile: workgroup ids reach the XCDs round-robin.  The tiles are listed super-block by super-block (8 token
+    // tiles x 4 feature tiles, fewer at the edges); while whole rounds of 256 are left, each XCD takes 32 of the list at
+    // a time, and what is left after them is dealt evenly.
     const int xcd = blockIdx.x % kNumXcd, seq = blockIdx.x / kNumXcd;
-    const int sb = (seq / (kSbM * kSbN)) * kNumXcd + xcd, inner = seq % (kSbM * kSbN);
-    const int mt = (sb / a.sb_n) * kSbM + inner % kSbM;
-    const int nt = (sb % a.sb_n) * kSbN + inner / kSbM;
-    if (mt >= a.m_tiles || nt >= a.n_tiles) return;
+    const int tiles = a.m_tiles * a.n_tiles, whole = tiles / kCus * kCuPerXcd;
+    int tile = (seq / kCuPerXcd * kNumXcd + xcd) * kCuPerXcd + seq % kCuPerXcd;
+    if (seq >= whole) {
+        const int left = tiles - whole * kNumXcd, per_xcd = (left + kNumXcd - 1) / kNumXcd, at = xcd * per_xcd + seq - whole;
+        if (at >= left) return;
+        tile = whole * kNumXcd + at;
+    }
+    const int sb_row = tile / (kSbM * a.n_tiles), in_row = tile % (kSbM * a.n_tiles);
+    const int sb_h = a.m_tiles - sb_row * kSbM < kSbM ? a.m_tiles - sb_row * kSbM : kSbM;
+    const int sb_col = in_row / (kSbN * sb_h), inner = in_row % (kSbN * sb_h);
+    const int mt = sb_row * kSbM + inner % sb_h, nt = sb_col * kSbN + inner / sb_h;
     const int m0 = mt * kBm, n0 = nt * kBn;
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int qc = lane & 31, hf = lane >> 5;
-    const int wn = wave & 1, wm = wave >> 1;          // this wave's 128 features and 32*kTb tokens of the tile
+    const int wn = wave % kWn, wm = wave / kWn;       // this wave's 32*NB features and 32*TB tokens of the tile
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
-    // thread t < 256: destination row of the tile's token t (-1: not stored) and bias of its feature t
+    // thread t: destination row of the tile's token t (-1: not stored) and bias of its feature t
     int32_t my_row = -1;
     uint16_t my_bias = 0;
-    if (tid < kBm) {
+    if (tid < kBn) {
         const int m = m0 + tid;
-        if (m < a.k_sel) {
+        if (tid < kBm && m < a.k_sel) {
             my_row = m;
             if (a.y_indexed) {
                 const int32_t ix = a.idx_sel[m];
@@ -137,40 +154,35 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
     if (copier) __builtin_amdgcn_s_setprio(1);
     const int d_row = lane >> 3;
     const int lchunk = (lane & 7) ^ ((4 * (cw & 1) + (lane >> 4)) & 7);
-    uint32_t woff[kCopies], xoff[kCopies];   // byte offsets of this lane's rows from w and x
-#pragma unroll
-    for (int t = 0; t < kCopies; ++t) {
-        const int r = 8 * (cw + kCopyWaves * t) + d_row;
-        int n = n0 + r;                  // rows past the end re-read the last one; they are never stored
-        if (n > a.c_out - 1) n = a.c_out - 1;
-        woff[t] = (uint32_t)n * (uint32_t)a.c_in * 2u + (uint32_t)lchunk * 16u;
-        int m = m0 + r;
-        if (m > a.k_sel - 1) m = a.k_sel - 1;
+    uint32_t woff[kCopiesW], xoff[kCopiesX];   // byte offsets of this lane's rows from w and x
+    auto w_row = [&](int r) __attribute__((always_inline)) {
+        const int n = n0 + r;            // rows past the end re-read the last one; they are never stored
+        return (uint32_t)(n < a.c_out ? n : a.c_out - 1) * (uint32_t)a.c_in * 2u;
+    };
+    auto x_row = [&](int r) __attribute__((always_inline)) {
+        const int m = m0 + r < a.k_sel ? m0 + r : a.k_sel - 1;
         const int64_t row = a.x_indexed ? (int64_t)clamp_row(a.idx_sel[m], a.n_rows) : (int64_t)m;
-        xoff[t] = (uint32_t)(row * a.ldx * 2) + (uint32_t)lchunk * 16u;
-    }
+        return (uint32_t)(row * a.ldx * 2);
+    };
+#pragma unroll
+    for (int t = 0; t < kCopiesW; ++t) woff[t] = w_row(8 * (cw + kCopyWaves * t) + d_row) + (uint32_t)lchunk * 16u;
+#pragma unroll
+    for (int t = 0; t < kCopiesX; ++t) xoff[t] = x_row(8 * (cw + kCopyWaves * t) + d_row) + (uint32_t)lchunk * 16u;
     // all index loads must have landed before the loop: a load still pending at the loop header would
     // make the compiler wait on the vector-memory counter inside it
 #pragma unroll
-    for (int t = 0; t < kCopies; ++t) asm volatile("" ::"v"(xoff[t]), "v"(woff[t]));
+    for (int t = 0; t < kCopiesW; ++t) asm volatile("" ::"v"(woff[t]));
+#pragma unroll
+    for (int t = 0; t < kCopiesX; ++t) asm volatile("" ::"v"(xoff[t]));
 
     const char *wg = reinterpret_cast<const char *>(a.w);
     const char *xg = reinterpret_cast<const char *>(a.x);
-    // L2 warm-up: a step's 128 bytes of one row are one cache line, and this wave copies 64 rows of
+    // L2 warm-up: a step's 128 bytes of one row are one cache line, and this wave copies up to 64 rows of
     // each tile, so one lane per row touches all of them (lane l: the l/8-th copy's row l%8).
     // Rows come from HBM (gathered x rows) or the memory-side cache (w), whose latency exceeds one step;
     // touching them kPrefetch steps ahead lets the tile copies hit in L2.
-    uint32_t pf_w, pf_x;
-    {
-        const int r = 8 * (cw + kCopyWaves * ((lane >> 3) % kCopies)) + (lane & 7);
-        int n = n0 + r;
-        if (n > a.c_out - 1) n = a.c_out - 1;
-        pf_w = (uint32_t)n * (uint32_t)a.c_in * 2u;
-        int m = m0 + r;
-        if (m > a.k_sel - 1) m = a.k_sel - 1;
-        const int64_t row = a.x_indexed ? (int64_t)clamp_row(a.idx_sel[m], a.n_rows) : (int64_t)m;
-        pf_x = (uint32_t)(row * a.ldx * 2);
-    }
+    const uint32_t pf_w = w_row(8 * (cw + kCopyWaves * ((lane >> 3) % kCopiesW)) + (lane & 7));
+    const uint32_t pf_x = x_row(8 * (cw + kCopyWaves * ((lane >> 3) % kCopiesX)) + (lane & 7));
     asm volatile("" ::"v"(pf_x), "v"(pf_w));
     const uint32_t scrap0 = (uint32_t)(uintptr_t)scrap;
     constexpr int kPrefetch = 2;      // 3: 2-3 % slower, 1: the copy is already on its way
@@ -186,15 +198,15 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
         const uint32_t sw = (uint32_t)(((2 * s + hf) ^ ((qc >> 1) & 7)) << 4);
-        wa[s] = (wn * 128 + qc) * kRowBytes + sw;
-        xa[s] = kTileBytes + (wm * 32 * kTb + qc) * kRowBytes + sw;
+        wa[s] = (wn * 32 * NB + qc) * kRowBytes + sw;
+        xa[s] = kTileBytes + (wm * 32 * TB + qc) * kRowBytes + sw;
     }
 
-    floatx16 acc[4][kTb];                // [feature block][token block]
+    floatx16 acc[NB][TB];                // [feature block][token block]
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int j = 0; j < kTb; ++j)
+        for (int j = 0; j < TB; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
@@ -202,9 +214,9 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
     // prologue: first stage
     if (copier) {
 #pragma unroll
-        for (int t = 0; t < kCopies; ++t) {
+        for (int t = 0; t < kCopiesW; ++t) {
             dma_w(t, 0, 0);
-            dma_x(t, 0, 0);
+            if (t < kCopiesX) dma_x(t, 0, 0);
         }
         for (int p = 1; p < kPrefetch; ++p) {
             const int kp = p < nk ? p : nk - 1;
@@ -213,47 +225,48 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
         }
     }
     wait_dma();
-    if (tid < kBm) {
-        tile_rows[tid] = my_row;
+    if (tid < kBn) {
+        if (tid < kBm) tile_rows[tid] = my_row;
         tile_bias[tid] = my_bias;
     }
     __builtin_amdgcn_s_barrier();
 
-    bf16x8 wf[2][4], xf[2][kTb];
+    bf16x8 wf[2][NB], xf[2][TB];
     // the fragments of a step's first quarter
     auto read_first = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < kTb; ++j) xf[0][j] = lds_read_b128(lds0 + xa[0] + j * 32 * kRowBytes);
+        for (int j = 0; j < TB; ++j) xf[0][j] = lds_read_b128(lds0 + xa[0] + j * 32 * kRowBytes);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) wf[0][i] = lds_read_b128(lds0 + wa[0] + i * 32 * kRowBytes);
+        for (int i = 0; i < NB; ++i) wf[0][i] = lds_read_b128(lds0 + wa[0] + i * 32 * kRowBytes);
     };
     uint32_t next_stage = kStageBytes;   // where the copies of step kk+1 go
     int kn = 0, kp = 0;
     // Quarter s of a step, in the order written: behind each of its first MFMAs one fragment read of quarter
-    // s + 1; a copying wave also puts one tile copy behind each MFMA of quarters 0 and 1 and the two warm-up
-    // loads into quarter 2.  The memory pipe takes a copy every ~16 clocks per CU, ~57 per wave with four
+    // s + 1; a copying wave also puts one tile copy behind each of the step's first MFMAs, and the two warm-up
+    // loads behind the next.  The memory pipe takes a copy every ~16 clocks per CU, ~57 per wave with four
     // waves at it, so a copying wave spends half a step held up at its copies; its SIMD neighbour's MFMAs
     // run in exactly that time.
     auto quarter = [&](auto s_tag) __attribute__((always_inline)) {
         constexpr int s = decltype(s_tag)::value;
         constexpr int cur = s & 1, nxt = cur ^ 1;
 #pragma unroll
-        for (int n = 0; n < 4 * kTb; ++n) {
-            const int i = n / kTb, j = n % kTb;
+        for (int n = 0; n < NB * TB; ++n) {
+            const int i = n / TB, j = n % TB;
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[cur][i], xf[cur][j], acc[i][j], 0, 0, 0);
             if (s < 3) {
-                if (n < kTb) xf[nxt][n] = lds_read_b128(lds0 + xa[(s + 1) & 3] + n * 32 * kRowBytes);
-                else if (n < kTb + 4) wf[nxt][n - kTb] = lds_read_b128(lds0 + wa[(s + 1) & 3] + (n - kTb) * 32 * kRowBytes);
+                if (n < TB) xf[nxt][n] = lds_read_b128(lds0 + xa[(s + 1) & 3] + n * 32 * kRowBytes);
+                else if (n < TB + NB) wf[nxt][n - TB] = lds_read_b128(lds0 + wa[(s + 1) & 3] + (n - TB) * 32 * kRowBytes);
             }
-            if (s < 2) {
-                const int c = s * 4 * kTb + n;          // 0 .. 15
+            const int c = s * NB * TB + n;              // MFMA of the step
+            if (c < kCopies) {
                 if (copier) {
-                    if (c & 1) dma_x(c >> 1, kn, next_stage);
+                    if (c >= 2 * kCopiesX) dma_w(c - kCopiesX, kn, next_stage);
+                    else if (c & 1) dma_x(c >> 1, kn, next_stage);
                     else dma_w(c >> 1, kn, next_stage);
                 }
-            } else if (s == 2 && n < 2) {
+            } else if (c < kCopies + 2) {
                 if (copier) {
-                    if (n == 0) touch_line(wg + (int64_t)kp * kRowBytes, pf_w, scrap0);
+                    if (c == kCopies) touch_line(wg + (int64_t)kp * kRowBytes, pf_w, scrap0);
                     else touch_line(xg + (int64_t)kp * kRowBytes, pf_x, scrap0);
                 }
             }
@@ -289,33 +302,35 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
 
     wait_dma();
     // ---- epilogue: bias, activation, bf16; then through LDS so that global stores cover whole rows.
-    // Register group g of block (i, j): features 128*wn + 32*i + 8*g + 4*hf + 0..3, token
-    // 32*kTb*wm + 32*j + qc of the tile.  An accumulator lane owns one token, so stores straight from the
+    // Register group g of block (i, j): features 32*NB*wn + 32*i + 8*g + 4*hf + 0..3, token
+    // 32*TB*wm + 32*j + qc of the tile.  An accumulator lane owns one token, so stores straight from the
     // registers would put 16 bytes on each of 32 rows per instruction; partial-line writes of that kind
     // cost several times the main loop's share of HBM time.  Instead each wave transposes its block,
-    // 64 tokens at a time, through its own 17 KiB of LDS (rows of 128 features, pitch 272
-    // bytes) and writes 4 rows x 256 contiguous bytes per instruction.  The tile buffers are free: every
+    // kEpiTokens at a time, through its own part of LDS (rows of its features, padded by 16 bytes) and
+    // writes whole 128-byte lines (4 rows x 256 bytes per instruction, or 8 x 128).  The tile buffers are free: every
     // wave has passed the barrier that ends the last step.  The region is private to the wave, so no
     // workgroup barrier is needed, only the wave's own LDS counter.
-    // this lane's 64 bias values (16 groups of 4 features), from the copy in LDS
-    uint2v bias2[4][4];
+    // this lane's bias values (4 NB groups of 4 features), from the copy in LDS
+    uint2v bias2[NB][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
         for (int g = 0; g < 4; ++g)
-            bias2[i][g] = *reinterpret_cast<const uint2v *>(&tile_bias[wn * 128 + 32 * i + 8 * g + 4 * hf]);
-    const uint32_t ebase = lds0 + wave * (64 * kPitch);
-    const int o_row = lane >> 4, o_chunk = lane & 15;      // read-back: 4 rows per instruction, 16 lanes x 16 B each
+            bias2[i][g] = *reinterpret_cast<const uint2v *>(&tile_bias[wn * 32 * NB + 32 * i + 8 * g + 4 * hf]);
+    const uint32_t ebase = lds0 + wave * (kEpiTokens * kPitch);
+    constexpr int kRowLanes = 4 * NB, kRowsPerStore = kWave / kRowLanes;      // read-back: 16 bytes per lane
+    const int o_row = lane / kRowLanes, o_chunk = lane % kRowLanes;
+    constexpr int kJ = kEpiTokens / 32;
 #pragma unroll
-    for (int jh = 0; jh < kTb / 2; ++jh) {
+    for (int jh = 0; jh < TB / kJ; ++jh) {
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-            const int j = 2 * jh + jj;
+        for (int jj = 0; jj < kJ; ++jj) {
+            const int j = kJ * jh + jj;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < NB; ++i)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const int nl = 32 * i + 8 * g + 4 * hf;      // feature inside the wave's 128
+                    const int nl = 32 * i + 8 * g + 4 * hf;      // feature inside the wave's part
                     float v[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * g + e];
@@ -336,23 +351,34 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
                 }
         }
         __builtin_amdgcn_s_waitcnt(0xc07f);                      // lgkmcnt(0): this wave's LDS writes are done
-        // destination rows of this half first (16 per lane), then the stores: an index load between
+        // destination rows of this part first, then the stores: an index load between
         // two stores would be waited for each time
 #pragma unroll
-        for (int it = 0; it < 16; ++it) {
-            const int tl = 4 * it + o_row;                       // token inside this half
-            const int64_t orow = tile_rows[wm * 32 * kTb + 64 * jh + tl];    // -1: past the end or a bad index
-            const int n = n0 + wn * 128 + 8 * o_chunk;           // c_out is a multiple of 8: a chunk is all in or all out
+        for (int it = 0; it < kEpiTokens / kRowsPerStore; ++it) {
+            const int tl = kRowsPerStore * it + o_row;           // token inside this part
+            const int64_t orow = tile_rows[wm * 32 * TB + kEpiTokens * jh + tl];    // -1: past the end or a bad index
+            const int n = n0 + wn * 32 * NB + 8 * o_chunk;       // c_out is a multiple of 8: a chunk is all in or all out
             const uint4v val = *reinterpret_cast<const uint4v __attribute__((address_space(3))) *>(
                 (uintptr_t)(ebase + tl * kPitch + o_chunk * 16));
             // written once: streaming stores leave the tiles other workgroups still read in L2 (+1-3 %)
             if (n < a.c_out && orow >= 0)
                 __builtin_nontemporal_store(val, reinterpret_cast<uint4v *>(a.y + orow * a.ldy + n));
         }
-        __builtin_amdgcn_s_waitcnt(0xc07f);                      // reads done before the second half overwrites
+        __builtin_amdgcn_s_waitcnt(0xc07f);                      // reads done before the next part overwrites
     }
 }
 
+
+// Estimated microseconds of a layer of `tiles` tiles and nk contraction steps: rounds of 256 workgroups, each 9 us besides its
+// steps, a step taking `base` us while few of the CUs are at work (the latency of its copies) and, past a share `from` of
+// them, `slope` more per unit (the chip at its power limit).  Measured per step, 256 / 192 / 128 tokens per tile: 0.97 / 0.81 /
+// 0.83 with a tenth of the CUs at work, 1.19 / 1.17 (0.9) / 0.82 with two thirds, 1.55 / 1.28 / 1.08 with all.
+static double layer_us(int64_t tiles, int nk, double base, double from, double slope)
+{
+    auto round = [&](double share) { return 9.0 + nk * (base + (share > from ? (share - from) * slope : 0.0)); };
+    const int64_t last = tiles % kCus;
+    return (double)(tiles / kCus) * round(1.0) + (last ? round((double)last / kCus) : 0.0);
+}
 
 }  // namespace
 
@@ -376,15 +402,21 @@ int launch_linear_bf16(const void *x, const void *w, const void *bias, void *y, 
     a.x_indexed = x_indexed;
     a.y_indexed = y_indexed;
     a.act = act;
-    a.m_tiles = (int32_t)((k_sel + kBm - 1) / kBm);
     a.n_tiles = (c_out + kBn - 1) / kBn;
-    a.sb_n = (a.n_tiles + kSbN - 1) / kSbN;
-    const int64_t sb_m = (a.m_tiles + kSbM - 1) / kSbM;
-    const int64_t sbs = sb_m * a.sb_n;                                  // super-blocks, dealt round-robin to the XCDs
-    const int64_t rounds = (sbs + kNumXcd - 1) / kNumXcd;
-    const int64_t grid = rounds * kNumXcd * (kSbM * kSbN);
-    if (grid > 2147483647LL) return fail(ASTRAEA_ERR_INVALID, "astraea_sparse_linear: grid too large");
-    hipLaunchKernelGGL(linear_bf16_kernel, dim3((unsigned)grid), dim3(kWaves * kWave), 0, stream, a);
+    auto tiles = [&](int64_t bm) { return (k_sel + bm - 1) / bm * a.n_tiles; };
+    if (tiles(128) > 2147483647LL / 16) return fail(ASTRAEA_ERR_INVALID, "astraea_sparse_linear: grid too large");
+    auto go = [&](auto kernel, int bm) {
+        a.m_tiles = (int32_t)((k_sel + bm - 1) / bm);
+        const int64_t t = tiles(bm);
+        const int64_t grid = t / kCus * kCus + (t % kCus + kNumXcd - 1) / kNumXcd * kNumXcd;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kWaves * kWave), 0, stream, a);
+    };
+    const int nk = c_in / kBk;
+    const double us256 = layer_us(tiles(256), nk, 0.95, 0.3, 0.85), us192 = layer_us(tiles(192), nk, 0.81, 0.3, 0.66),
+                 us128 = layer_us(tiles(128), nk, 0.81, 0.6, 0.65);
+    if (us256 <= us192 && us256 <= us128) go(linear_bf16_kernel<4, 2>, 256);
+    else if (us192 < us128) go(linear_bf16_kernel<2, 3>, 192);
+    else go(linear_bf16_kernel<2, 2>, 128);
     return check_launch("astraea_sparse_linear(bf16)");
 }
 

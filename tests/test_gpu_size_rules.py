@@ -203,3 +203,34 @@ def test_topk_sizes(n, kind):
         assert np.array_equal(mask[:n].cpu().numpy(), e_mask) and mask[n].item() == 9
         e_skip = np.where(e_mask != 0, 0, skip0.numpy() + 1)
         assert np.array_equal(skip[:n].cpu().numpy(), e_skip) and skip[n].item() == -7
+
+
+# bf16 linear: tiles of 256 features x 256, 192 or 128 tokens by the launch's estimate (the sizes below take each of them), edges
+# of the token tiles, ragged features, more and fewer tiles than CUs, one to many contraction steps.  Reference: fp64; bar:
+# relative L2 1e-2 per row (bf16 inputs and result).
+@pytest.mark.parametrize("n,k,c_in,c_out,gather,scatter,bias,act", [
+    (5, 1, 64, 8, True, True, True, ab.ACT_NONE), (300, 127, 64, 264, True, False, False, ab.ACT_GELU_TANH),
+    (300, 129, 128, 512, False, True, True, ab.ACT_NONE), (700, 608, 192, 3072, True, True, True, ab.ACT_GELU_TANH),      # 128
+    (2000, 1755, 512, 12288, True, False, True, ab.ACT_NONE), (3600, 3457, 320, 3072, False, True, True, ab.ACT_NONE),    # 192
+    (3600, 3456, 256, 3080, True, True, False, ab.ACT_GELU_TANH), (7100, 7020, 320, 3072, True, True, True, ab.ACT_NONE), # 192
+    (5100, 5000, 128, 3072, True, True, True, ab.ACT_NONE), (5200, 5121, 192, 3064, False, True, True, ab.ACT_GELU_TANH), # 256
+    (9000, 8192, 64, 2048, True, False, True, ab.ACT_NONE), (9000, 8193, 128, 2048, True, True, True, ab.ACT_NONE),       # one round, one more
+])
+def test_linear_bf16_tiles(n, k, c_in, c_out, gather, scatter, bias, act):
+    g = torch.Generator(device=DEV).manual_seed(n + k + c_in)
+    idx = torch.randperm(n, device=DEV, generator=g)[:k].sort().values.to(torch.int32)
+    x = torch.randn(n if gather else k, c_in, device=DEV, generator=g).bfloat16()
+    w = (torch.randn(c_out, c_in, device=DEV, generator=g) * c_in ** -0.5).bfloat16()
+    b = torch.randn(c_out, device=DEV, generator=g).bfloat16() if bias else None
+    y = torch.randn(n if scatter else k, c_out + 8, device=DEV, generator=g).bfloat16()
+    before = y.clone()
+    ref = (x[idx.long()] if gather else x).double() @ w.double().T.contiguous() + (b.double() if bias else 0.0)
+    if act == ab.ACT_GELU_TANH:
+        ref = torch.nn.functional.gelu(ref, approximate="tanh")
+    ab.astraea_sparse_linear(x, w, b, idx, k, y[:, :c_out], act=act, x_is_compact=not gather, y_is_compact=not scatter, N=n)
+    torch.cuda.synchronize()
+    got = y[idx.long() if scatter else slice(None), :c_out]
+    assert_rel_l2(got.double().cpu().numpy(), ref.cpu().numpy())
+    keep = torch.ones(y.shape, dtype=torch.bool, device=DEV)
+    keep[idx.long() if scatter else slice(None), :c_out] = False
+    assert torch.equal(y[keep], before[keep])
