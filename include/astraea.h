@@ -135,8 +135,8 @@ int astraea_select_topk_static(const float *score, int64_t N, int64_t k, int32_t
  *   lse_sel     [k_sel, H] fp32 natural-log sum of exponentials of the scaled logits, or NULL.
  *   workspace   at least astraea_workspace_bytes(ASTRAEA_OP_SPARSE_ATTN, N, k_sel, H, D) bytes,
  *               256-byte aligned (may be NULL when that is 0).  The bf16 path stages a re-tiled
- *               copy of V there (N rounded up to 64, times H*D*2 bytes) plus 68 MB of partial
- *               results on every call; contents need not be initialised and are clobbered.
+ *               copy of V there (N rounded up to 64, times H*D*2 bytes; large selections) and up to
+ *               68 MB of partial results; contents need not be initialised and are clobbered.
  *               The fp32 path uses it only for a selection too small to fill the chip, which
  *               it then cuts into key ranges (up to 8 x k_sel x H x (D + 4) floats of partial
  *               results); there the workspace is optional: with NULL, or fewer bytes than

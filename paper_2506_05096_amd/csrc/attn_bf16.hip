@@ -16,12 +16,13 @@
 //    each 256-byte row, applied through the per-lane global address.
 //  * the LDS pipe issues one wave instruction every ~4.5 clocks whatever its width, so fragments
 //    must come in 16-byte reads.  K rows are head-dim contiguous, which is what S^T = K Q^T wants.
-//    V is contracted over keys, so a pre-pass rewrites V once per call into 16 KiB tiles of V^T
+//    V is contracted over keys.  For large selections a pre-pass rewrites V once per call into 16 KiB tiles of V^T
 //    ([128 head-dim rows][64 keys], keys permuted inside each group of 16 to match the register
 //    order of P^T, 16-byte chunks already XOR-swizzled); the main kernel then copies a tile
 //    linearly into LDS and reads every V^T fragment with one ds_read_b128.  The pre-pass moves
-//    2*N*H*D*2 bytes, under 1% of the attention time, and needs N_pad*H*D*2 bytes of workspace.
-//  * queries are gathered by index while loading the Q fragment, which then lives in registers
+//    2*N*H*D*2 bytes and needs N_pad*H*D*2 bytes of workspace.  For smaller ones, where that pass is 2 to 20 % of the
+//    call, V rows are copied as they lie and a fragment is two transposing reads (ds_read_b64_tr_b16).
+//  * queries are gathered by index on their way through LDS into the Q fragment, which then lives in registers
 //    for the whole sweep (the "gather" step of the path is fused here).
 //  * the exponent offset of a row need not be its exact max: a stale one costs range, not accuracy
 //    (P, the row sums and the O accumulators are floating point with 8-bit exponents).  The main
@@ -54,6 +55,11 @@ constexpr int kRowsBytes = 32 * kRowBytes;           // a wave's 32 query or out
 constexpr float kTau = 8.0f;            // exact form: lazy-rescale threshold, log2 units
 constexpr float kBig = 0x1p80f;         // fast form: after a final row sum above this the workgroup repeats its sweep in the exact form
 constexpr int kNumXcd = 8;
+// The pre-pass costs a read and a write of V whatever the selection, direct V tiles half as many LDS reads again per key and
+// query.  Retiled against direct, same results, us: 608 queries x 2025 keys 38.5 / 32.2; 7020 x 512 64.5 / 60.0; 1755 x 17550
+// 376 / 344; 7020 x 17550 1323 / 1301; 17550 x 17550 3159 / 3151; 11880 x 118800 14315 / 14225; 35640 x 118800 41688 / 41906.
+// Both costs grow with the number of keys, so the line is a number of queries.
+constexpr int64_t kRetileRows = 16384;
 
 __device__ __forceinline__ float xhalf_max(float x)
 {
@@ -126,6 +132,16 @@ __device__ __forceinline__ uint4v rows_get(uint32_t rows_lds, int row, int chunk
     return __builtin_bit_cast(uint4v, lds_read_b128(rows_lds + row * kRowBytes + ((chunk ^ (row & 15)) << 4)));
 }
 
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+// The transposing LDS read: of each 16 lanes, lane 4 r + c supplies elements 4 c .. 4 c + 3 of row r, and lane i gets element i of
+// the four rows.
+__device__ __forceinline__ bf16x4 lds_read_tr(uint32_t addr)
+{
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                          reinterpret_cast<s16x4 __attribute__((address_space(3))) *>((uintptr_t)addr)));
+}
+
 // Budget-aware work split.  Work item = (head, tile of 256 selected queries), head-major; XCD x owns the
 // contiguous item range [x * items_per_xcd, (x+1) * items_per_xcd) and workgroups reach XCDs round-robin
 // by id.  With 32 CUs per XCD the items of an XCD run in rounds of 32.  The first `full_items` of each
@@ -155,8 +171,11 @@ constexpr int MFMA = 0x008, DSR = 0x100;
         __builtin_amdgcn_sched_barrier(0); \
     } while (0)
 
+// RETILED: V comes from the pre-pass's V^T tiles.  Otherwise its rows are copied as they lie, in the K tile's shape, and the
+// fragments are read through the transposing LDS read.
+template <bool RETILED>
 __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
-    const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const char *__restrict__ vt, int64_t N, int32_t H,
+    const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const void *__restrict__ v, int64_t N, int32_t H,
     int64_t q_stride_n, int64_t q_stride_h, int64_t kv_stride_n, int64_t kv_stride_h,
     const int32_t *__restrict__ idx_sel, int64_t k_sel, int q_is_compact, float scale_log2e,
     __bf16 *__restrict__ o_sel, int64_t o_stride_n, int o_scatter, float *__restrict__ lse_sel, AttnSchedule sch,
@@ -198,39 +217,52 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
     // K: block = 4 key rows; physical chunk p of row r holds logical chunk p ^ (r & 15).
     // V^T: the pre-pass already wrote the tile as its LDS image, so the copy is linear.
     const char *kbase = reinterpret_cast<const char *>(k + (int64_t)head * kv_stride_h);
-    const char *vtbase = vt + (int64_t)head * ntiles * kTileBytes;
+    const char *vbase = RETILED ? reinterpret_cast<const char *>(v) + (int64_t)head * ntiles * kTileBytes
+                                : reinterpret_cast<const char *>(reinterpret_cast<const __bf16 *>(v) + (int64_t)head * kv_stride_h);
     const int64_t row_pitch = kv_stride_n * 2;       // bytes between consecutive keys
     const int d_row = lane >> 4, d_p = lane & 15;
     const uint32_t lin_off = lane * 16;
-    // Copies one tile with NW waves taking part (this wave is number w of them): block b of the
-    // tile is copied by wave b % NW.
-    auto dma_v_tile = [&](int64_t tile, int par, int w, auto nw_tag) __attribute__((always_inline)) {
-        constexpr int NW = decltype(nw_tag)::value;
-        const char *src = vtbase + tile * kTileBytes + w * 1024;
-        const uint32_t dst = lds0 + par * kBufBytes + kTileBytes + w * 1024;
-#pragma unroll
-        for (int i = 0; i < 16 / NW; ++i) dma16(src + i * NW * 1024, lin_off, dst + i * NW * 1024);
-    };
-    auto dma_k_tile = [&](int64_t tile, int par, int w, auto nw_tag) __attribute__((always_inline)) {
+    // Rows [key0, key0 + 64) of K or V; physical chunk p of row r holds logical chunk p ^ sw(r).
+    auto dma_rows = [&](const char *base, int64_t tile, uint32_t buf, int w, auto nw_tag, int swz, bool zero_fill) __attribute__((always_inline)) {
         constexpr int NW = decltype(nw_tag)::value;  // 4 or 8: a wave's rows advance by 16 or 32 per step,
-        const int64_t key0 = tile * kBk;             // so row & 15 (the swizzle) is the same for all of them
-        const char *src = kbase + key0 * row_pitch;
-        const uint32_t dst = lds0 + par * kBufBytes + w * 1024;
+        const int64_t key0 = tile * kBk;             // so the swizzle is the same for all of them
+        const char *src = base + key0 * row_pitch;
+        const uint32_t dst = buf + w * 1024;
         const int row0 = 4 * w + d_row;
-        const uint32_t sw = (uint32_t)((d_p ^ (row0 & 15)) << 4);
+        const uint32_t sw = (uint32_t)((d_p ^ swz) << 4);
         if (key0 + kBk <= N) {
             const uint32_t off = (uint32_t)row0 * (uint32_t)row_pitch + sw;
 #pragma unroll
             for (int i = 0; i < 16 / NW; ++i) dma16(src + i * 4 * NW * row_pitch, off, dst + i * NW * 1024);
         } else {
-            const int64_t last = N - 1 - key0;       // rows past the last key re-read it (masked later)
+            const int64_t last = N - 1 - key0;       // K rows past the last key re-read it (masked later); V rows are zero
 #pragma unroll
             for (int i = 0; i < 16 / NW; ++i) {
                 const int rr = row0 + 4 * NW * i;
                 const int64_t rc = rr < last ? rr : last;
-                dma16(src, (uint32_t)(rc * row_pitch) + sw, dst + i * NW * 1024);
+                if (!zero_fill || rr <= last)
+                    dma16(src, (uint32_t)(rc * row_pitch) + sw, dst + i * NW * 1024);
+                else
+                    *reinterpret_cast<uint4v __attribute__((address_space(3))) *>((uintptr_t)(dst + i * NW * 1024 + lane * 16)) = uint4v{0u, 0u, 0u, 0u};
             }
+            if (zero_fill) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
+    };
+    // Copies one tile with NW waves taking part (this wave is number w of them): block b of the
+    // tile is copied by wave b % NW.
+    auto dma_v_tile = [&](int64_t tile, int par, int w, auto nw_tag) __attribute__((always_inline)) {
+        constexpr int NW = decltype(nw_tag)::value;
+        const uint32_t buf = lds0 + par * kBufBytes + kTileBytes;
+        if (RETILED) {
+            const char *src = vbase + tile * kTileBytes + w * 1024;
+#pragma unroll
+            for (int i = 0; i < 16 / NW; ++i) dma16(src + i * NW * 1024, lin_off, buf + w * 1024 + i * NW * 1024);
+        } else {
+            dma_rows(vbase, tile, buf, w, nw_tag, d_row << 2, true);
+        }
+    };
+    auto dma_k_tile = [&](int64_t tile, int par, int w, auto nw_tag) __attribute__((always_inline)) {
+        dma_rows(kbase, tile, lds0 + par * kBufBytes, w, nw_tag, (4 * w + d_row) & 15, false);
     };
 
     const int grp = wave >> 2, wig = wave & 3;
@@ -270,10 +302,22 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
 #pragma unroll
     for (int s = 0; s < D / 16; ++s) ka[s] = qc * kRowBytes + (((2 * s + hf) ^ (qc & 15)) << 4);
     // V^T fragment (tt, b): row d = 32*b + qc (128-byte rows), logical chunk 2*tt + hf; b is an immediate
+    // Not retiled: lane 16 g + i of a transposing read supplies 4 head-dims of key 4 (g / 2) + i / 4 and gets head-dim
+    // 16 (g % 2) + i of four keys; V fragment (tt, b) is two of them, keys 16 tt + 4 hf + 0..3 and 8 further.  va[b] is
+    // their place: chunk 4 b + 2 (g % 2) + (i % 4) / 2 of that row, swizzled by 4 (row % 4).
     uint32_t va[4];
+    const int tr_row = qc & 15;
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
-        va[tt] = kTileBytes + qc * 128 + (((2 * tt + hf) ^ ((qc >> 1) & 7)) << 4);
+    for (int u = 0; u < 4; ++u)
+        va[u] = RETILED ? kTileBytes + qc * 128 + (((2 * u + hf) ^ ((qc >> 1) & 7)) << 4)
+                        : kTileBytes + (4 * hf + (tr_row >> 2)) * kRowBytes +
+                              ((((u ^ (tr_row >> 2)) << 2) + 2 * (qc >> 4) + ((tr_row >> 1) & 1)) << 4) + 8 * (tr_row & 1);
+    auto read_v = [&](int u, uint32_t at) __attribute__((always_inline)) -> bf16x8 {     // fragment tt = u / 4, b = u % 4 of the buffer pair at `at`
+        if (RETILED) return lds_read_b128(lds0 + va[u >> 2] + (at + (u & 3) * 32 * 128));
+        const uint32_t p = lds0 + va[u & 3] + (at + (u >> 2) * 16 * kRowBytes);
+        const bf16x4 lo = lds_read_tr(p), hi = lds_read_tr(p + 8 * kRowBytes);
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
 
     floatx16 sacc[2];          // S^T of the current tile (two blocks of 32 keys)
     uint32_t pw[16];           // P^T as bf16 pairs: pw[8*kb + i] = registers 2i, 2i+1 of block kb
@@ -348,7 +392,7 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
         constexpr uint32_t KP = (decltype(par_tag)::value ^ 1) * kBufBytes;
         bf16x8 vf[16], kf[16];
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) vf[u] = lds_read_b128(lds0 + va[u >> 2] + (VP + (u & 3) * 32 * 128));
+        for (int u = 0; u < kAhead; ++u) vf[u] = read_v(u, VP);
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
             const int tt = u >> 2, b = u & 3;
@@ -356,7 +400,7 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
             oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[u], __builtin_bit_cast(bf16x8, p4), oacc[b], 0, 0, 0);
             const int n = u + kAhead;
             if (n < 16)
-                vf[n] = lds_read_b128(lds0 + va[n >> 2] + (VP + (n & 3) * 32 * 128));
+                vf[n] = read_v(n, VP);
             else if (WITH_QK)
                 kf[n - 16] = lds_read_b128(lds0 + ka[(n - 16) >> 1] + (KP + ((n - 16) & 1) * 32 * kRowBytes));
         }
@@ -373,11 +417,19 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
                 if (n < 16) kf[n] = lds_read_b128(lds0 + ka[n >> 1] + (KP + (n & 1) * 32 * kRowBytes));
             }
         }
-        SGB(DSR, kAhead);
+        constexpr int kVReads = RETILED ? 1 : 2;         // LDS instructions per V fragment
+        SGB(DSR, kAhead * kVReads);
 #pragma unroll
-        for (int u = 0; u < (WITH_QK ? 32 : 16) - kAhead; ++u) {
+        for (int u = 0; u < 16 - kAhead; ++u) {
             SGB(MFMA, 1);
-            SGB(DSR, 1);
+            SGB(DSR, kVReads);
+        }
+        if (WITH_QK) {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                SGB(MFMA, 1);
+                SGB(DSR, 1);
+            }
         }
         SGB(MFMA, kAhead);
     };
@@ -687,14 +739,20 @@ int launch_attn_bf16_d128(const void *q, const void *k, const void *v, int64_t N
     const int64_t left = sch.items_per_xcd - sch.full_items;
     char *vt = (char *)workspace;
     float *partial = (float *)(vt + vt_bytes(N, H));
-    hipLaunchKernelGGL(transpose_v_kernel, dim3((unsigned)ntiles, (unsigned)H), dim3(256), 0, stream,
-                       (const __bf16 *)v, N, kv_stride_n, kv_stride_h, ntiles, vt);
+    const bool retile = k_sel > kRetileRows;
     dim3 grid((unsigned)(slots * kNumXcd)), block(kWaves * kWave);
     const float c = scale * 1.44269504088896340736f;
+    if (retile)
+        hipLaunchKernelGGL(transpose_v_kernel, dim3((unsigned)ntiles, (unsigned)H), dim3(256), 0, stream, (const __bf16 *)v, N,
+                           kv_stride_n, kv_stride_h, ntiles, vt);
+    auto go = [&](auto kernel, const void *vsrc) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, stream, (const __bf16 *)q, (const __bf16 *)k, vsrc, N, H, q_stride_n,
+                           q_stride_h, kv_stride_n, kv_stride_h, idx_sel, k_sel, q_is_compact, c, (__bf16 *)o_sel,
+                           o_stride_n, o_scatter, lse_sel, sch, partial);
+    };
     kernel_timer_begin(stream);
-    hipLaunchKernelGGL(attn_bf16_kernel, grid, block, 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const char *)vt,
-                       N, H, q_stride_n, q_stride_h, kv_stride_n, kv_stride_h, idx_sel, k_sel, q_is_compact, c,
-                       (__bf16 *)o_sel, o_stride_n, o_scatter, lse_sel, sch, partial);
+    if (retile) go(attn_bf16_kernel<true>, vt);
+    else go(attn_bf16_kernel<false>, v);
     kernel_timer_end(stream);
     if (left > 0)
         hipLaunchKernelGGL(merge_partials_kernel, dim3((unsigned)(left * kNumXcd), kBq / 32), dim3(256), 0, stream, partial, sch,

@@ -88,6 +88,7 @@ def test_linear_f32_operand_past_4_gib():
 @pytest.mark.parametrize("n,h,k,hot,scatter,splits", [
     (1, 1, 1, False, True, 1), (63, 2, 31, False, True, 1), (64, 1, 33, True, False, 1), (65, 3, 65, True, True, 1),
     (129, 2, 5000, True, False, 1), (300, 1, 255, False, True, 1), (512, 9, 257, True, True, 1),
+    (100, 2, 16384, True, False, 1), (100, 2, 16385, True, False, 1), (128, 1, 16385, False, False, 1),      # V direct, retiled
     (4000, 1, 30, True, True, 8), (2025, 24, 608, True, True, 3), (4100, 24, 1100, False, False, 2), (900, 24, 450, True, True, 1),
 ])
 def test_attn_bf16_tiles(n, h, k, hot, scatter, splits):
@@ -234,3 +235,20 @@ def test_linear_bf16_tiles(n, k, c_in, c_out, gather, scatter, bias, act):
     keep = torch.ones(y.shape, dtype=torch.bool, device=DEV)
     keep[idx.long() if scatter else slice(None), :c_out] = False
     assert torch.equal(y[keep], before[keep])
+
+
+@pytest.mark.parametrize("k", [300, 16385])      # V tiles direct and retiled
+def test_attn_bf16_non_finite_values_stay_in_their_head_dims(k):
+    """An infinity in the last row of V, which the last, partly filled tile ends on, reaches every result of its head-dim
+    and nothing else: rows past the last key count as zero."""
+    n, h = 100, 2
+    g = torch.Generator(device=DEV).manual_seed(k)
+    q, kc, vc = (torch.randn(m, h, 128, device=DEV, generator=g).bfloat16() for m in (k, n, n))
+    vc[n - 1, 1, 7], vc[n - 1, 0, 70] = math.inf, math.nan
+    o = torch.empty(k, h, 128, dtype=torch.bfloat16, device=DEV)
+    ws = torch.full((ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, 128),), 255, dtype=torch.uint8, device=DEV)
+    ab.astraea_sparse_attn_fwd(q, kc, vc, None, k, o, 1.0 / math.sqrt(128), q_is_compact=True, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.isposinf(o[:, 1, 7]).all() and torch.isnan(o[:, 0, 70]).all()
+    o[:, 1, 7], o[:, 0, 70] = 0.0, 0.0
+    assert torch.isfinite(o).all()
