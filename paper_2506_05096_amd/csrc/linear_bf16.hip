@@ -25,14 +25,17 @@
 //    L1 fetches every line from L2 twice and the kernel is 30 % slower.
 //    The second wave of each SIMD issues the copy instructions of the next step, one behind each of
 //    its first 16 MFMAs, and has the higher priority: the memory pipe holds it at every copy, and its
-//    neighbour's MFMAs fill exactly that time.  A 4-byte load per row touches the lines of two
-//    steps ahead so that the copies hit in L2.
+//    neighbour's MFMAs fill exactly that time.  A 4-byte load per row, shared out among the
+//    workgroups that use the row, touches the lines of two steps ahead so that the copies hit in L2.  The 128-token tile has
+//    three stages, copied two ahead, and no touches: its steps are shorter than a copy takes (all linear layers of a
+//    block, 608 rows: 387 us with two stages' touches, 316 shared, 308 without).
 //  * workgroup ids are mapped so that the 32 workgroups resident on one XCD form an 8 x 4 block of
 //    tiles: they stream 8 row tiles and 4 weight tiles through that XCD's L2 instead of 32 + 32.  The tiles
 //    left after whole rounds go to all XCDs evenly.
-// Measured with both (us; before: 256-token tiles only, blocks of 8 x 4 dealt whole to the XCDs, so that some had a
-// round more than others): 5000 rows 3072 -> 3072 132 -> 84, 12288 -> 3072 489 -> 300; 7020 rows 3072 -> 9216 380 -> 328, 3072 ->
-// 3072 150 -> 125, 12288 -> 3072 550 -> 457; 1755 rows 3072 -> 9216 143 -> 88; 608 rows 54 -> 45.
+// Measured with all of this (us; before: 256-token tiles only, blocks of 8 x 4 dealt whole to the XCDs, so that some had a
+// round more than others, every workgroup touching all its rows): 35640 rows 12288 -> 3072 2146 -> 2074 (1.30 PFLOP/s); 5000
+// rows 3072 -> 3072 132 -> 80, 12288 -> 3072 489 -> 292; 7020 rows 3072 -> 9216 380 -> 322, 3072 -> 3072 150 -> 119, 12288 -> 3072
+// 550 -> 439; 1755 rows 3072 -> 9216 143 -> 83; 608 rows 3072 -> 3072 54 -> 33, 12288 -> 3072 190 -> 115.
 #include "gfx950.h"
 
 namespace astraea {
@@ -43,15 +46,11 @@ constexpr int kBn = 256;                 // output features per tile
 constexpr int kBk = 64;                  // contraction step
 constexpr int kRowBytes = kBk * 2;       // 128 B of a row per step
 constexpr int kTileBytes = 256 * kRowBytes;          // 32 KiB
-constexpr int kStageBytes = 2 * kTileBytes;          // w tile, then x tile (32 KiB or less)
 constexpr int kWaves = 8;                // two per SIMD
 constexpr int kCopyWaves = kWaves / 2;   // the waves that issue the tile copies (the second wave of each SIMD)
 constexpr int kNumXcd = 8, kCuPerXcd = 32, kCus = kNumXcd * kCuPerXcd;
 constexpr int kSbM = 8, kSbN = 4;        // tiles of one XCD round: 8 token tiles x 4 feature tiles
 
-// Waits until only the two most recent vector-memory instructions (the L2 warm-up loads) are pending:
-// the counter retires loads in order, so everything issued before them has then landed.
-__device__ __forceinline__ void wait_dma_keep2() { asm volatile("s_waitcnt vmcnt(2)" ::: "memory"); }
 // A 4-byte load per lane whose only purpose is to pull its 128-byte line into L2.  It is the copy form
 // of the load (global -> LDS), aimed at a 256-byte scrap area every wave may scribble on: the data lands
 // whenever it arrives, and with no register as its destination nothing the compiler does with registers
@@ -83,7 +82,7 @@ struct LinearArgs {
     int32_t m_tiles, n_tiles;  // token and feature tiles
 };
 
-// A wave has NB x TB MFMA blocks of 32 features x 32 tokens: <4, 2> makes tiles of 256 tokens, <2, 3> of 192.
+// A wave has NB x TB MFMA blocks of 32 features x 32 tokens: <4, 2> makes tiles of 256 tokens, <2, 3> of 192, <2, 2> of 128.
 template <int NB, int TB>
 __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArgs a)
 {
@@ -91,11 +90,16 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
     constexpr int kBm = 32 * TB * kWm;                            // tokens per tile
     constexpr int kCopiesW = kBn / 8 / kCopyWaves, kCopiesX = kBm / 8 / kCopyWaves;   // 1 KiB copies per copying wave and step
     constexpr int kCopies = kCopiesW + kCopiesX;
-    // [stage][w tile | x tile].  Stage flips XOR offsets relative to this array, never absolute addresses.
+    // Stages of [w tile | x tile] in a ring: two, or three where they fit, with the copies one step more ahead.  A step of a
+    // small tile is shorter than a copy takes, and small tiles serve layers with few of them, which nothing else hides.
+    constexpr int kStageBytes = kTileBytes + kBm * kRowBytes;
+    constexpr int kStages = 3 * kStageBytes <= 144 * 1024 ? 3 : 2;
+    constexpr int kAhead = kStages - 1;
+    constexpr int kTouches = kStages == 2 ? 2 : 0;     // L2 warm-up loads per copying wave and step
     constexpr int kPitch = 64 * NB + 16; // epilogue staging: the wave's features of a token, padded
     constexpr int kEpiTokens = TB == 2 ? 64 : 32 * TB;            // tokens a wave stages at a time
     constexpr int kEpiBytes = kWaves * kEpiTokens * kPitch;
-    __shared__ __attribute__((aligned(1024))) char lds[2 * kStageBytes > kEpiBytes ? 2 * kStageBytes : kEpiBytes];
+    __shared__ __attribute__((aligned(1024))) char lds[kStages * kStageBytes > kEpiBytes ? kStages * kStageBytes : kEpiBytes];
     __shared__ __attribute__((aligned(256))) uint32_t scrap[kWave];      // where the L2 warm-up loads land
     // destination rows and bias of this tile, fetched while the first step's tiles are on their way: the
     // epilogue then reads them from LDS instead of waiting for global loads three times over
@@ -184,8 +188,14 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
     const uint32_t pf_w = w_row(8 * (cw + kCopyWaves * ((lane >> 3) % kCopiesW)) + (lane & 7));
     const uint32_t pf_x = x_row(8 * (cw + kCopyWaves * ((lane >> 3) % kCopiesX)) + (lane & 7));
     asm volatile("" ::"v"(pf_x), "v"(pf_w));
+    // The 8 token tiles of a block share its weight rows and the 4 feature tiles its token rows, so each workgroup touches an
+    // eighth of the one and a quarter of the other: a load of one word of each of 64 rows holds the memory pipe like
+    // four tile copies.  All linear layers of a block, 17550 tokens at 40 % / 118800 at 30 %: every workgroup touching all
+    // its rows 1484 / 6689 us, no touches 1540 / 6757, shared 1340 / 6346.  (Of a layer by itself, repeated with its weights still
+    // cached, no touches would be as fast.)  Whether the neighbours run at the same time matters for speed only.
+    const bool touch_w = (lane & (kSbM - 1)) == mt % kSbM, touch_x = (lane & (kSbN - 1)) == nt % kSbN;
     const uint32_t scrap0 = (uint32_t)(uintptr_t)scrap;
-    constexpr int kPrefetch = 2;      // 3: 2-3 % slower, 1: the copy is already on its way
+    constexpr int kPrefetch = kAhead + 1;      // one step before the copy; 3 with copies one ahead: 2-3 % slower
     auto dma_w = [&](int t, int kstep, uint32_t stage) __attribute__((always_inline)) {
         dma16(wg + (int64_t)kstep * kRowBytes, woff[t], lds0 + stage + (cw + kCopyWaves * t) * 1024);
     };
@@ -211,20 +221,20 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
     const int nk = a.c_in / kBk;
-    // prologue: first stage
+    // prologue: the first stages
     if (copier) {
 #pragma unroll
-        for (int t = 0; t < kCopiesW; ++t) {
-            dma_w(t, 0, 0);
-            if (t < kCopiesX) dma_x(t, 0, 0);
-        }
-        for (int p = 1; p < kPrefetch; ++p) {
-            const int kp = p < nk ? p : nk - 1;
-            touch_line(wg + (int64_t)kp * kRowBytes, pf_w, scrap0);
-            touch_line(xg + (int64_t)kp * kRowBytes, pf_x, scrap0);
-        }
+        for (int p = 0; p < kAhead; ++p)
+#pragma unroll
+            for (int t = 0; t < kCopiesW; ++t) {
+                dma_w(t, p < nk ? p : nk - 1, p * kStageBytes);
+                if (t < kCopiesX) dma_x(t, p < nk ? p : nk - 1, p * kStageBytes);
+            }
+        const int kp = kAhead < nk ? kAhead : nk - 1;
+        if (kTouches && touch_w) touch_line(wg + (int64_t)kp * kRowBytes, pf_w, scrap0);
+        if (kTouches && touch_x) touch_line(xg + (int64_t)kp * kRowBytes, pf_x, scrap0);
     }
-    wait_dma();
+    wait_dma_but<(kAhead - 1) * kCopies + kTouches>();
     if (tid < kBn) {
         if (tid < kBm) tile_rows[tid] = my_row;
         tile_bias[tid] = my_bias;
@@ -239,8 +249,8 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
 #pragma unroll
         for (int i = 0; i < NB; ++i) wf[0][i] = lds_read_b128(lds0 + wa[0] + i * 32 * kRowBytes);
     };
-    uint32_t next_stage = kStageBytes;   // where the copies of step kk+1 go
-    int kn = 0, kp = 0;
+    uint32_t next_stage = kAhead * kStageBytes;   // where the copies of step kk + kAhead go
+    int kn = 0, kp = 0, stage = 0;       // stage: the ring position of the present step
     // Quarter s of a step, in the order written: behind each of its first MFMAs one fragment read of quarter
     // s + 1; a copying wave also puts one tile copy behind each of the step's first MFMAs, and the two warm-up
     // loads behind the next.  The memory pipe takes a copy every ~16 clocks per CU, ~57 per wave with four
@@ -264,10 +274,13 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
                     else if (c & 1) dma_x(c >> 1, kn, next_stage);
                     else dma_w(c >> 1, kn, next_stage);
                 }
-            } else if (c < kCopies + 2) {
+            } else if (c < kCopies + kTouches) {
                 if (copier) {
-                    if (c == kCopies) touch_line(wg + (int64_t)kp * kRowBytes, pf_w, scrap0);
-                    else touch_line(xg + (int64_t)kp * kRowBytes, pf_x, scrap0);
+                    if (c == kCopies) {
+                        if (touch_w) touch_line(wg + (int64_t)kp * kRowBytes, pf_w, scrap0);
+                    } else if (touch_x) {
+                        touch_line(xg + (int64_t)kp * kRowBytes, pf_x, scrap0);
+                    }
                 }
             }
             SB();
@@ -278,9 +291,9 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
     using Q2 = std::integral_constant<int, 2>;
     using Q3 = std::integral_constant<int, 3>;
     for (int kk = 0; kk < nk; ++kk) {
-        // the last step has nothing to prefetch: it copies its own tiles again into the idle stage
+        // the last steps have nothing to prefetch: they copy the last tiles again into the idle stage
         // rather than branch around every copy
-        kn = kk + 1 < nk ? kk + 1 : kk;
+        kn = kk + kAhead < nk ? kk + kAhead : nk - 1;
         kp = kk + kPrefetch < nk ? kk + kPrefetch : nk - 1;
         read_first();
         SB();
@@ -288,19 +301,24 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
         quarter(Q1{});
         quarter(Q2{});
         quarter(Q3{});
-        // the next step's tiles are complete and this step's are no longer read: swap stages
-        wait_dma_keep2();
+        // the next step's tiles are complete (what may still be pending is what this step issued: its copies where they go
+        // more than one step ahead, and its two warm-up loads) and this step's are no longer read: on to the next stage
+        wait_dma_but<(kAhead - 1) * (kCopies + kTouches) + kTouches>();
         __builtin_amdgcn_s_barrier();
         SB();
+        const uint32_t step = stage == kStages - 1 ? 0u - (kStages - 1) * kStageBytes : kStageBytes;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            wa[s] ^= kStageBytes;
-            xa[s] ^= kStageBytes;
+            wa[s] += step;
+            xa[s] += step;
         }
-        next_stage ^= kStageBytes;
+        next_stage = stage * kStageBytes;
+        stage = stage == kStages - 1 ? 0 : stage + 1;
     }
 
     wait_dma();
+    // copies that ran on past the last step must not land in what another wave stages there
+    if (kAhead > 1) __builtin_amdgcn_s_barrier();
     // ---- epilogue: bias, activation, bf16; then through LDS so that global stores cover whole rows.
     // Register group g of block (i, j): features 32*NB*wn + 32*i + 8*g + 4*hf + 0..3, token
     // 32*TB*wm + 32*j + qc of the tile.  An accumulator lane owns one token, so stores straight from the
@@ -369,13 +387,13 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
 }
 
 
-// Estimated microseconds of a layer of `tiles` tiles and nk contraction steps: rounds of 256 workgroups, each 9 us besides its
-// steps, a step taking `base` us while few of the CUs are at work (the latency of its copies) and, past a share `from` of
-// them, `slope` more per unit (the chip at its power limit).  Measured per step, 256 / 192 / 128 tokens per tile: 0.97 / 0.81 /
-// 0.83 with a tenth of the CUs at work, 1.19 / 1.17 (0.9) / 0.82 with two thirds, 1.55 / 1.28 / 1.08 with all.
-static double layer_us(int64_t tiles, int nk, double base, double from, double slope)
+// Estimated microseconds of a layer of `tiles` tiles and nk contraction steps: rounds of 256 workgroups, each `fixed` us besides
+// its steps, a step taking `base` us while few of the CUs are at work and, past a share `from` of them, `slope` more per unit
+// (the chip at its power limit).  Measured per step, 256 / 192 / 128 tokens per tile: 1.03 / 0.93 / 0.56 with a fifth of the CUs
+// at work, 1.25 / 1.0 / 0.61 with two thirds, 1.52 / 1.2 / 0.83 with all.
+static double layer_us(int64_t tiles, int nk, double fixed, double base, double from, double slope)
 {
-    auto round = [&](double share) { return 9.0 + nk * (base + (share > from ? (share - from) * slope : 0.0)); };
+    auto round = [&](double share) { return fixed + nk * (base + (share > from ? (share - from) * slope : 0.0)); };
     const int64_t last = tiles % kCus;
     return (double)(tiles / kCus) * round(1.0) + (last ? round((double)last / kCus) : 0.0);
 }
@@ -412,8 +430,8 @@ int launch_linear_bf16(const void *x, const void *w, const void *bias, void *y, 
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kWaves * kWave), 0, stream, a);
     };
     const int nk = c_in / kBk;
-    const double us256 = layer_us(tiles(256), nk, 0.95, 0.3, 0.85), us192 = layer_us(tiles(192), nk, 0.81, 0.3, 0.66),
-                 us128 = layer_us(tiles(128), nk, 0.81, 0.6, 0.65);
+    const double us256 = layer_us(tiles(256), nk, 9.0, 1.05, 0.4, 0.78), us192 = layer_us(tiles(192), nk, 7.5, 0.93, 0.6, 0.65),
+                 us128 = layer_us(tiles(128), nk, 6.0, 0.56, 0.6, 0.7);
     if (us256 <= us192 && us256 <= us128) go(linear_bf16_kernel<4, 2>, 256);
     else if (us192 < us128) go(linear_bf16_kernel<2, 3>, 192);
     else go(linear_bf16_kernel<2, 2>, 128);

@@ -215,7 +215,8 @@ def test_topk_sizes(n, kind):
     (2000, 1755, 512, 12288, True, False, True, ab.ACT_NONE), (3600, 3457, 320, 3072, False, True, True, ab.ACT_NONE),    # 192
     (3600, 3456, 256, 3080, True, True, False, ab.ACT_GELU_TANH), (7100, 7020, 320, 3072, True, True, True, ab.ACT_NONE), # 192
     (5100, 5000, 128, 3072, True, True, True, ab.ACT_NONE), (5200, 5121, 192, 3064, False, True, True, ab.ACT_GELU_TANH), # 256
-    (9000, 8192, 64, 2048, True, False, True, ab.ACT_NONE), (9000, 8193, 128, 2048, True, True, True, ab.ACT_NONE),       # one round, one more
+    (9000, 8192, 64, 2048, True, False, True, ab.ACT_NONE), (9000, 8193, 128, 2048, True, True, True, ab.ACT_NONE),       # 256: one round; 192
+    (33100, 33000, 3136, 3072, True, True, True, ab.ACT_NONE), (12100, 12000, 9216, 2048, False, True, True, ab.ACT_NONE),  # 256, 192
 ])
 def test_linear_bf16_tiles(n, k, c_in, c_out, gather, scatter, bias, act):
     g = torch.Generator(device=DEV).manual_seed(n + k + c_in)
