@@ -145,7 +145,8 @@ int astraea_select_topk_static(const float *score, int64_t N, int64_t k, int32_t
  * The bf16 path runs its main kernel with each row's exponent offset fixed at the row max over the
  * first key tile, which is exact as long as no later logit exceeds that max by more than 80 powers of
  * two; a workgroup with a row that does repeats its sweep with a max per key tile.
- * The result does not depend on which of the two served a row beyond rounding.
+ * The result does not depend on which of the two served a row beyond rounding.  The fp32 path raises
+ * a row's offset whenever a logit passes it.
  * Supported: (BF16, D = 128) on bf16 MFMA with fp32 softmax and accumulation;
  * (F32, D = 64 or 128) on fp32 MFMA.  k_sel == 0 enqueues nothing.
  * Pointers must be 16-byte aligned and strides multiples of 8 elements.

@@ -15,13 +15,17 @@
 //  * the first product's contraction is permuted: a lane reads 8 consecutive floats of its key row (two 16-byte reads) and
 //    MFMA j of the step takes index pair {j, 8 + j}; the second product reads V by the float, 32 consecutive ones of a row.
 //  * bound by the matrix pipe (4096 flops per MFMA in 64 clocks, 157 TFLOP/s) plus the vector instructions, which do not
-//    overlap fp32 MFMAs.  So each row's exponent offset is fixed at its max over the first tile, and the sweep takes
-//    no max and rescales nothing: fma, exponential and add per logit.  A row that outgrows the offset by more than 2^80
-//    shows in its row sum; the workgroup then repeats its sweep in the exact form (running max).
+//    overlap fp32 MFMAs.  So a row's exponent offset is not its exact running max: it is raised, to kSlack above the max so
+//    far, only when a logit passes it, which after the first tiles is rare, and the other tiles rescale nothing and exchange
+//    nothing between lanes: per logit half a max, an fma, an exponential and an add.  Probabilities stay at most 1 and the
+//    arguments that matter close to 0, as under a running max, so accumulators overflow no earlier than theirs and the error is
+//    no larger.  (An offset left at the first tile's max takes no max at all and is 2 - 5 % faster, but overflows on rows
+//    that rise by r powers of two over values of 2^(128 - r), and its error grows with the rise, 6.5e-7 -> 11e-7 at 45 nats.)
 // Measured (call with merge; before: tiles staged through registers between two barriers, running max, 4-byte K reads):
-// 2048 queries x 4096 keys x 8 heads x 64 196 -> 146 us (118 TFLOP/s), 6000 x 6000 x 24 x 64 2303 -> 1786, 3000 x 6000 x 24 x
-// 128 3439 -> 2092, 250 x 2500 x 8 x 128 79 -> 51.  Error against 64 bits unchanged (6.7e-7 at the first).  Not the number
-// of workgroups per CU (forced to two: no change); with flat softmax rows, whose operands switch less, 136 us.
+// 2048 queries x 4096 keys x 8 heads x 64 190 -> 153 us (112 TFLOP/s), 6000 x 6000 x 24 x 64 2292 -> 1816, 3000 x 6000 x 24 x
+// 128 3431 -> 2129, 250 x 2500 x 8 x 128 79 -> 53.  Error against 64 bits, both: 6.7e-7 at the first, 6.5e-7 for rows that rise
+// by 10, 30 or 45 nats; kSlack 1 / 2 / 3 / 4 at the first: 6.72 / 6.73 / 6.73 / 6.75e-7, 153.5 / 152.9 / 151.4 / 151.2 us.  Not
+// bound by the number of workgroups per CU (forced to two: no change).
 #include <type_traits>
 
 #include "gfx950.h"
@@ -33,7 +37,7 @@ namespace {
 constexpr int kWaves = 4;
 constexpr int kBq = 32 * kWaves;   // queries per workgroup
 constexpr int kBk = 32;            // keys per tile
-constexpr float kBig = 0x1p80f;    // a final row sum above this: the workgroup repeats its sweep in the exact form
+constexpr float kSlack = 1.0f;     // log2 units by which a raised exponent offset lies above the row's max so far
 
 __device__ __forceinline__ float xhalf_max(float x)
 {
@@ -63,7 +67,6 @@ __global__ __launch_bounds__(kWaves *kWave, 2) void attn_f32_kernel(
     constexpr int kRowsPerCopy = 1024 / kRowBytes;                   // a copy instruction fills 1 KiB of a tile
     constexpr int kCopies = kTileBytes / 1024 / kWaves;              // per wave and tile, K and V each
     __shared__ __attribute__((aligned(1024))) char lds[2 * kStageBytes];
-    __shared__ uint32_t wave_outgrew[kWaves];
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -106,12 +109,9 @@ __global__ __launch_bounds__(kWaves *kWave, 2) void attn_f32_kernel(
         else dma16(src, (uint32_t)off, dst);
     };
     auto rows_of = [&](int64_t t) { return N - t * kBk < kBk ? N - t * kBk : (int64_t)kBk; };
-    auto first_tile = [&]() __attribute__((always_inline)) {
-        offsets(rows_of(t_begin));
+    offsets(rows_of(t_begin));
 #pragma unroll
-        for (int n = 0; n < 2 * kCopies; ++n) copy(kb + t_begin * tile_pitch, vb + t_begin * tile_pitch, 0, n);
-    };
-    first_tile();
+    for (int n = 0; n < 2 * kCopies; ++n) copy(kb + t_begin * tile_pitch, vb + t_begin * tile_pitch, 0, n);
 
     // Q operand: lane holds query column qc, head-dim elements 16 s + 8 hf + j in qreg[8 s + j]
     int64_t r = r0 + qc;
@@ -145,12 +145,15 @@ __global__ __launch_bounds__(kWaves *kWave, 2) void attn_f32_kernel(
         va[b] = lds0 + kTileBytes + 4 * hf * kRowBytes + (((8 * b + (qc >> 2)) ^ (hf << 3)) << 4) + 4 * (qc & 3);
 
     floatx16 oacc[DB];
-    float m_run;               // exponent offset of the row: max of its scaled logits in log2 units, over the first tile or so far
-    float l_run;               // this lane's share of the running sum
+    float m_run = -INFINITY;   // exponent offset of the row, in log2 units: at least the max of its scaled logits so far
+    float l_run = 0.0f;        // this lane's share of the running sum
+#pragma unroll
+    for (int b = 0; b < DB; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[b][i] = 0.0f;
 
     // One tile out of stage PAR; the copies of the next tile go out behind the first MFMAs.
-    auto tile = [&](int64_t t, auto exact_tag, auto par_tag) __attribute__((always_inline)) {
-        constexpr bool EXACT = decltype(exact_tag)::value;
+    auto tile = [&](int64_t t, auto par_tag) __attribute__((always_inline)) {
         constexpr uint32_t at = decltype(par_tag)::value * kStageBytes, next = kStageBytes - at;
         // tile t has landed, for every wave, and every wave is past its last read of tile t - 1
         wait_dma();
@@ -194,20 +197,20 @@ __global__ __launch_bounds__(kWaves *kWave, 2) void attn_f32_kernel(
             for (int i = 0; i < 16; ++i)
                 if (t * kBk + (i >> 2) * 8 + hf * 4 + (i & 3) >= N) sacc[i] = -INFINITY;
         }
-        if (EXACT || t == t_begin) {
-            float tmax = sacc[0];
+        // A logit above its row's offset raises it, to kSlack above the row's max.  Lanes look at their own half of the keys;
+        // only when one of them finds something do the halves meet and the accumulators get rescaled.
+        float tmax = sacc[0];
 #pragma unroll
-            for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, sacc[i]);
+        for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, sacc[i]);
+        if (__builtin_amdgcn_ballot_w64(tmax * scale_log2e > m_run) != 0) {
             tmax = xhalf_max(tmax) * scale_log2e;
-            const float m_new = fmaxf(m_run, tmax);
-            if (EXACT) {
-                const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);          // 0 on the first tile
-                l_run *= alpha;
+            const float m_new = tmax > m_run ? tmax + kSlack : m_run;
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);          // 0 on the first tile
+            l_run *= alpha;
 #pragma unroll
-                for (int b = 0; b < DB; ++b)
+            for (int b = 0; b < DB; ++b)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
-            }
+                for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
             m_run = m_new;
         }
         float ps[2] = {0.0f, 0.0f};
@@ -228,34 +231,16 @@ __global__ __launch_bounds__(kWaves *kWave, 2) void attn_f32_kernel(
                 __builtin_amdgcn_sched_barrier(0);
             }
     };
-    auto sweep = [&](auto exact_tag) __attribute__((always_inline)) {
-        using P0 = std::integral_constant<int, 0>;
-        using P1 = std::integral_constant<int, 1>;
-#pragma unroll
-        for (int b = 0; b < DB; ++b)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) oacc[b][i] = 0.0f;
-        m_run = -INFINITY;
-        l_run = 0.0f;
-        int64_t t = t_begin;
-        for (; t + 1 < t_end; t += 2) {
-            tile(t, exact_tag, P0{});
-            tile(t + 1, exact_tag, P1{});
-        }
-        if (t < t_end) tile(t, exact_tag, P0{});
-    };
-    sweep(std::false_type{});
-    float l_tot = xhalf_sum(l_run);
-    // Did a row outgrow its offset (or overflow, or meet a NaN)?  The workgroup decides as one, since its waves share the tiles.
-    const bool outgrew = __builtin_amdgcn_ballot_w64(!(l_tot <= kBig)) != 0;
-    if (lane == 0) wave_outgrew[wave] = outgrew ? 1u : 0u;
-    wait_dma();
-    __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(wave_outgrew[0] | wave_outgrew[1] | wave_outgrew[2] | wave_outgrew[3]) != 0) {
-        first_tile();
-        sweep(std::true_type{});
-        l_tot = xhalf_sum(l_run);
+    using P0 = std::integral_constant<int, 0>;
+    using P1 = std::integral_constant<int, 1>;
+    int64_t t = t_begin;
+    for (; t + 1 < t_end; t += 2) {
+        tile(t, P0{});
+        tile(t + 1, P1{});
     }
+    if (t < t_end) tile(t, P0{});
+    const float l_tot = xhalf_sum(l_run);
+    wait_dma();                // the copies past the last tile
     const int64_t rr = r0 + qc;
     if (rr >= k_sel) return;
     if (splits > 1) {

@@ -128,7 +128,7 @@ def test_attn_bf16_tiles(n, h, k, hot, scatter, splits):
 
 
 # fp32 attention: 128 queries per workgroup, tiles of 32 keys in two LDS stages, key ranges shared out when the selection is
-# small; `hot` makes workgroups repeat their sweep in the exact form; `pitch`: keys 2^25 floats apart, past 32-bit offsets.
+# small; `hot` raises a row's exponent offset in the last tile; `pitch`: keys 2^25 floats apart, past 32-bit offsets.
 # Bounds: a logit L is a sum of d products, off by up to d * 2^-24 * |L|.  Without the hot key |L| is a few nats and the
 # errors of its terms average out: 1e-5.  The hot key gives logits of up to 25 nats to the other rows (128 * 2^-24 * 25 =
 # 2e-4 of a probability, times values of size 3) and 362 nats to the hot rows, whose log-sum-exp is that logit.
@@ -172,6 +172,55 @@ def test_attn_f32_tiles(n, h, k, d, hot, scatter, pitch):
         keep = torch.ones(out.shape, dtype=torch.bool, device=DEV)
         keep[idx.long(), :h * d] = False
         assert torch.equal(out[keep], before[keep])
+
+
+def _attn_rise_case(n, h, k, d, rise_nats, dtype, first_tile):
+    """Logits near zero, except that those of the first key tile lie `rise_nats` lower."""
+    g = torch.Generator(device=DEV).manual_seed(n + k + d)
+    q, kc = (0.05 * torch.randn(m, h, d, device=DEV, generator=g) for m in (k, n))
+    q[:, :, 0], kc[:, :, 0] = 8.0, 0.0
+    kc[:first_tile, :, 0] = -rise_nats * math.sqrt(d) / 8.0
+    return q.to(dtype), kc.to(dtype), torch.randn(n, h, d, device=DEV, generator=g).to(dtype)
+
+
+# Rows whose first key tile lies 45 nats below the rest: a fixed exponent offset would leave arguments of 65 to the
+# exponential (rounded by 2^-18: 1.5e-6 of a probability in the mean square) and 2^65 in the accumulators, which
+# values of 2^64 then overflow.  Values of 2^110 leave the accumulators seven bits above the largest sum of 1300.  Expected
+# error: arguments of 4 are rounded by 2^-22, 1e-7 in the mean square; an accumulator walks 1300 steps at random, each
+# rounded by 0.4 * 2^-24 of its size in the mean square: sqrt(1300 / 2) * 0.4 * 2^-24 = 6.1e-7.  Bound: 1.5 times that,
+# since the head-dims of one head are few.  16 queries and more: with and without key shares.
+@pytest.mark.parametrize("rise_nats,size", [(45.0, 0), (45.0, 64), (0.0, 110)])
+@pytest.mark.parametrize("h,k,d", [(2, 16, 64), (12, 3000, 64), (2, 16, 128), (6, 6000, 128)])
+def test_attn_f32_rows_that_rise_from_a_low_first_tile(h, k, d, rise_nats, size):
+    n = 1300
+    q, kc, vc = _attn_rise_case(n, h, k, d, rise_nats, torch.float32, 32)
+    vc *= 2.0 ** size
+    out = torch.empty(k, h, d, device=DEV)
+    ws = torch.empty(max(256, ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d)), dtype=torch.uint8, device=DEV)
+    ab.astraea_sparse_attn_fwd(q, kc, vc, None, k, out, 1.0 / math.sqrt(d), q_is_compact=True, workspace=ws)
+    torch.cuda.synchronize()
+    for i in range(h):
+        ref = torch.softmax((q[:, i].double() @ kc[:, i].double().T.contiguous()) / math.sqrt(d), 1) @ vc[:, i].double()
+        assert ((out[:, i].double() - ref).norm() / ref.norm()).item() <= 9e-7
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_attn_f32_non_finite_inputs_stay_in_their_rows_and_head_dims(d):
+    """A NaN or an infinity in a row of Q spoils that row alone, one in V its head-dim alone."""
+    n, h, k = 300, 2, 140
+    g = torch.Generator(device=DEV).manual_seed(d)
+    q, kc, vc = (torch.randn(m, h, d, device=DEV, generator=g) for m in (k, n, n))
+    ref = torch.softmax((q[:, 1].double() @ kc[:, 1].double().T.contiguous()) / math.sqrt(d), 1) @ vc[:, 1].double()
+    q[3, 1, 5], q[133, 1, 0], vc[50, 1, 7], vc[2, 1, 40] = math.nan, math.inf, math.inf, math.nan
+    o = torch.empty(k, h, d, device=DEV)
+    ws = torch.empty(max(256, ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d)), dtype=torch.uint8, device=DEV)
+    ab.astraea_sparse_attn_fwd(q, kc, vc, None, k, o, 1.0 / math.sqrt(d), q_is_compact=True, workspace=ws)
+    torch.cuda.synchronize()
+    rows, dims = torch.ones(k, dtype=torch.bool, device=DEV), torch.ones(d, dtype=torch.bool, device=DEV)
+    rows[[3, 133]], dims[[7, 40]] = False, False
+    assert torch.isfinite(o[:, 0]).all() and torch.isnan(o[~rows, 1]).all()
+    assert torch.isposinf(o[rows, 1][:, 7]).all() and torch.isnan(o[rows, 1][:, 40]).all()
+    assert (o[rows, 1][:, dims].double() - ref[rows][:, dims]).abs().max().item() <= 1e-5
 
 
 # top-k in one workgroup: an even number of elements per thread up to 32768 scores, wave w owning a contiguous range; passes
