@@ -144,7 +144,8 @@ int astraea_select_topk_static(const float *score, int64_t N, int64_t k, int32_t
  *               to summation order.
  * The bf16 path runs its main kernel with each row's exponent offset fixed at the row max over the
  * first key tile, which is exact as long as no later logit exceeds that max by more than 80 powers of
- * two; a workgroup with a row that does repeats its sweep with a max per key tile.
+ * two and the unnormalised sums stay finite; a workgroup with a row where that fails, or with a NaN or an
+ * infinity among its operands, repeats its sweep with a max per key tile.
  * The result does not depend on which of the two served a row beyond rounding.  The fp32 path raises
  * a row's offset whenever a logit passes it.
  * Supported: (BF16, D = 128) on bf16 MFMA with fp32 softmax and accumulation;

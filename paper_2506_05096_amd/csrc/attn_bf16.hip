@@ -28,9 +28,11 @@
 //    (P, the row sums and the O accumulators are floating point with 8-bit exponents).  The main
 //    kernel therefore fixes each row's offset at the max over the first key tile and takes no max in
 //    the sweep at all, which removes a fifth of the softmax arithmetic.  A row whose later logits
-//    outgrow that offset by more than 2^80 (or overflow) shows in its final row sum; its workgroup
+//    outgrow that offset by more than 2^80 (or overflow) shows in its final row sum, one whose rise
+//    is smaller but meets values large enough to overflow the output shows in its accumulators; the workgroup
 //    then sweeps its keys once more in the exact form (a max per tile, lazy rescale when it grew by
-//    more than 2^kTau).  Both forms are in the one kernel: as a launch of its own over the same grid the
+//    more than 2^kTau).  So a workgroup with such a row, or with a NaN or an infinity among its operands, takes up
+//    to twice the time.  Both forms are in the one kernel: as a launch of its own over the same grid the
 //    exact form cost 4 - 7 us a call with nothing to redo, and needed a flag per workgroup.
 //  * workgroup ids are mapped so that the workgroups resident on one XCD work on the same head and
 //    sweep the keys together; K/V tiles are then served from that XCD's L2.
@@ -53,6 +55,7 @@ constexpr int kTileBytes = kBk * kRowBytes;          // 16 KiB
 constexpr int kBufBytes = 2 * kTileBytes;            // K tile then V tile
 constexpr int kRowsBytes = 32 * kRowBytes;           // a wave's 32 query or output rows
 constexpr float kTau = 8.0f;            // exact form: lazy-rescale threshold, log2 units
+constexpr float kRose = 0x1p8f;         // 2^kTau
 constexpr float kBig = 0x1p80f;         // fast form: after a final row sum above this the workgroup repeats its sweep in the exact form
 constexpr int kNumXcd = 8;
 // The pre-pass costs a read and a write of V whatever the selection, direct V tiles half as many LDS reads again per key and
@@ -513,9 +516,20 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
     };
     sweep(std::false_type{});
     float l_tot = xhalf_sum(l_run);
-    // Did a row outgrow its offset?  Its row sum then passed 2^80, or is infinite or NaN (the comparison is
-    // written so that those fail it too).  The workgroup decides as one, since its waves share the tiles.
-    const bool outgrew = __builtin_amdgcn_ballot_w64(!(l_tot <= kBig)) != 0;
+    // Did a row outgrow its offset?  Its row sum then passed 2^80, or is infinite or NaN (the comparisons are
+    // written so that those fail them too), or one of its accumulators overflowed, which shows in their sum.  With a row sum of
+    // at most 2^kTau no logit passed the offset by more than kTau, and the exact form would do the very same: short flat
+    // sweeps skip the 64 additions (0.7 us of a 57 us call of 7020 queries x 512 keys).  The workgroup decides as one,
+    // since its waves share the tiles.
+    bool lost = !(l_tot <= kBig);
+    const bool rose = l_tot > kRose;
+    if (__builtin_amdgcn_ballot_w64(rose) != 0) {
+        float o_sum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o_sum += (oacc[0][i] + oacc[1][i]) + (oacc[2][i] + oacc[3][i]);
+        lost = lost || (rose && !(__builtin_fabsf(o_sum) < INFINITY));
+    }
+    const bool outgrew = __builtin_amdgcn_ballot_w64(lost) != 0;
     if (lane == 0) wave_outgrew[wave] = outgrew ? 1u : 0u;
     __syncthreads();
     uint32_t any = 0;

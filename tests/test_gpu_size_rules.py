@@ -127,6 +127,31 @@ def test_attn_bf16_tiles(n, h, k, hot, scatter, splits):
         assert torch.equal(out[keep], before[keep])
 
 
+def _attn_rise_case(n, h, k, d, rise_nats, dtype, first_tile):
+    """Logits near zero, except that those of the first key tile lie `rise_nats` lower."""
+    g = torch.Generator(device=DEV).manual_seed(n + k + d)
+    q, kc = (0.05 * torch.randn(m, h, d, device=DEV, generator=g) for m in (k, n))
+    q[:, :, 0], kc[:, :, 0] = 8.0, 0.0
+    kc[:first_tile, :, 0] = -rise_nats * math.sqrt(d) / 8.0
+    return q.to(dtype), kc.to(dtype), torch.randn(n, h, d, device=DEV, generator=g).to(dtype)
+
+
+# Logits 45 nats above those of the first key tile, inside the margin of the row sums, over values of 2^66: the accumulators
+# of the first sweep overflow.  Compact queries fewer and more than the keys, with and without key shares, V direct and
+# retiled.  Bar: relative L2 1e-2 per row (bf16 probabilities and results).
+@pytest.mark.parametrize("n,h,k", [(1300, 2, 100), (4100, 24, 1100), (1300, 2, 5000), (300, 1, 16385)])
+def test_attn_bf16_large_values_in_rows_that_rise(n, h, k):
+    q, kc, vc = _attn_rise_case(n, h, k, 128, 45.0, torch.bfloat16, 64)
+    vc *= 2.0 ** 66
+    out = torch.empty(k, h, 128, dtype=torch.bfloat16, device=DEV)
+    ws = torch.empty(ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, 128), dtype=torch.uint8, device=DEV)
+    ab.astraea_sparse_attn_fwd(q, kc, vc, None, k, out, 1.0 / math.sqrt(128), q_is_compact=True, workspace=ws)
+    torch.cuda.synchronize()
+    for i in range(h):
+        ref = torch.softmax((q[:, i].double() @ kc[:, i].double().T.contiguous()) / math.sqrt(128), 1) @ vc[:, i].double()
+        assert_rel_l2(out[:, i].double().cpu().numpy(), ref.cpu().numpy(), tag=f"head {i}")
+
+
 # fp32 attention: 128 queries per workgroup, tiles of 32 keys in two LDS stages, key ranges shared out when the selection is
 # small; `hot` raises a row's exponent offset in the last tile; `pitch`: keys 2^25 floats apart, past 32-bit offsets.
 # Bounds: a logit L is a sum of d products, off by up to d * 2^-24 * |L|.  Without the hot key |L| is a few nats and the
@@ -172,15 +197,6 @@ def test_attn_f32_tiles(n, h, k, d, hot, scatter, pitch):
         keep = torch.ones(out.shape, dtype=torch.bool, device=DEV)
         keep[idx.long(), :h * d] = False
         assert torch.equal(out[keep], before[keep])
-
-
-def _attn_rise_case(n, h, k, d, rise_nats, dtype, first_tile):
-    """Logits near zero, except that those of the first key tile lie `rise_nats` lower."""
-    g = torch.Generator(device=DEV).manual_seed(n + k + d)
-    q, kc = (0.05 * torch.randn(m, h, d, device=DEV, generator=g) for m in (k, n))
-    q[:, :, 0], kc[:, :, 0] = 8.0, 0.0
-    kc[:first_tile, :, 0] = -rise_nats * math.sqrt(d) / 8.0
-    return q.to(dtype), kc.to(dtype), torch.randn(n, h, d, device=DEV, generator=g).to(dtype)
 
 
 # Rows whose first key tile lies 45 nats below the rest: a fixed exponent offset would leave arguments of 65 to the
