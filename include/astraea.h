@@ -333,6 +333,13 @@ int astraea_check_indices(const int32_t *idx_sel, int64_t k_sel, int64_t N, int3
 int astraea_attn_plan(int64_t N, int32_t H, int64_t k_sel, int64_t plan_out[8]);
 
 /*
+ * The tile astraea_sparse_linear would give a workgroup for k_sel rows, c_in -> c_out.  Host only, nothing is
+ * enqueued; for inspection and tests.  plan_out (host, 3 entries): output features per tile, tokens per
+ * tile, tiles.
+ */
+int astraea_linear_plan(astraea_dtype dt, int64_t k_sel, int64_t c_in, int64_t c_out, int64_t plan_out[3]);
+
+/*
  * Measurement aids for the benchmark; neither is a step of the method.
  *
  * astraea_probe_mfma_bf16 runs a register-resident loop of v_mfma_f32_32x32x16_bf16

@@ -398,7 +398,19 @@ static double layer_us(int64_t tiles, int nk, double fixed, double base, double 
     return (double)(tiles / kCus) * round(1.0) + (last ? round((double)last / kCus) : 0.0);
 }
 
+int64_t tiles_of(int64_t k_sel, int64_t c_out, int64_t bm) { return (k_sel + bm - 1) / bm * ((c_out + kBn - 1) / kBn); }
+
 }  // namespace
+
+// Tokens per tile, by the estimate above.
+int linear_bf16_tile(int64_t k_sel, int32_t c_in, int64_t c_out)
+{
+    const int nk = c_in / kBk;
+    const double us256 = layer_us(tiles_of(k_sel, c_out, 256), nk, 9.0, 1.05, 0.4, 0.78),
+                 us192 = layer_us(tiles_of(k_sel, c_out, 192), nk, 7.5, 0.93, 0.6, 0.65),
+                 us128 = layer_us(tiles_of(k_sel, c_out, 128), nk, 6.0, 0.56, 0.6, 0.7);
+    return us256 <= us192 && us256 <= us128 ? 256 : us192 < us128 ? 192 : 128;
+}
 
 int launch_linear_bf16(const void *x, const void *w, const void *bias, void *y, const int32_t *idx_sel, int64_t k_sel,
                        int64_t n_rows, int32_t c_in, int32_t c_out, int64_t ldx, int64_t ldy, int x_indexed, int y_indexed, int act,
@@ -421,20 +433,17 @@ int launch_linear_bf16(const void *x, const void *w, const void *bias, void *y, 
     a.y_indexed = y_indexed;
     a.act = act;
     a.n_tiles = (c_out + kBn - 1) / kBn;
-    auto tiles = [&](int64_t bm) { return (k_sel + bm - 1) / bm * a.n_tiles; };
-    if (tiles(128) > 2147483647LL / 16) return fail(ASTRAEA_ERR_INVALID, "astraea_sparse_linear: grid too large");
-    auto go = [&](auto kernel, int bm) {
+    if (tiles_of(k_sel, c_out, 128) > 2147483647LL / 16) return fail(ASTRAEA_ERR_INVALID, "astraea_sparse_linear: grid too large");
+    const int bm = linear_bf16_tile(k_sel, c_in, c_out);
+    auto go = [&](auto kernel) {
         a.m_tiles = (int32_t)((k_sel + bm - 1) / bm);
-        const int64_t t = tiles(bm);
+        const int64_t t = tiles_of(k_sel, c_out, bm);
         const int64_t grid = t / kCus * kCus + (t % kCus + kNumXcd - 1) / kNumXcd * kNumXcd;
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kWaves * kWave), 0, stream, a);
     };
-    const int nk = c_in / kBk;
-    const double us256 = layer_us(tiles(256), nk, 9.0, 1.05, 0.4, 0.78), us192 = layer_us(tiles(192), nk, 7.5, 0.93, 0.6, 0.65),
-                 us128 = layer_us(tiles(128), nk, 6.0, 0.56, 0.6, 0.7);
-    if (us256 <= us192 && us256 <= us128) go(linear_bf16_kernel<4, 2>, 256);
-    else if (us192 < us128) go(linear_bf16_kernel<2, 3>, 192);
-    else go(linear_bf16_kernel<2, 2>, 128);
+    if (bm == 256) go(linear_bf16_kernel<4, 2>);
+    else if (bm == 192) go(linear_bf16_kernel<2, 3>);
+    else go(linear_bf16_kernel<2, 2>);
     return check_launch("astraea_sparse_linear(bf16)");
 }
 

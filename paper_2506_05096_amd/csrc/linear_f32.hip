@@ -285,7 +285,20 @@ __global__ __launch_bounds__(kWaves *kWave) void linear_f32_kernel(LinearF32Args
     store(orow[0], feature(0, 0), sum, bias4[0][0]);
 }
 
+int64_t tiles_of(int64_t k_sel, int64_t c_out, int64_t t) { return ((c_out + t - 1) / t) * ((k_sel + t - 1) / t); }
+
 }  // namespace
+
+// Features and tokens per tile: the rounds of tiles over the 256 CUs, in units of a 32 x 32 tile's work.  At equal rounds the
+// larger tile is the better one (4096 rows, 3072 -> 3072: 533 us with 128, 559 with 64, 666 with 32, hence the factor 5/4
+// against the last); fewer rounds outweigh it (6000 rows: 879 with 128, 830 with 64; 200 rows, 512 -> 512: 12 with 64, 8.5
+// with 32).
+int linear_f32_tile(int64_t k_sel, int64_t c_out)
+{
+    auto rounds = [&](int64_t t) { return (tiles_of(k_sel, c_out, t) + 255) / 256 * (t * t / 1024); };
+    const int64_t c128 = rounds(128), c64 = rounds(64), c32 = rounds(32);
+    return c128 <= c64 && 4 * c128 <= 5 * c32 ? 128 : 4 * c64 <= 5 * c32 ? 64 : 32;
+}
 
 int launch_linear_f32(const void *x, const void *w, const void *bias, void *y, const int32_t *idx_sel, int64_t k_sel,
                       int64_t n_rows, int32_t c_in, int32_t c_out, int64_t ldx, int64_t ldy, int x_indexed,
@@ -307,27 +320,23 @@ int launch_linear_f32(const void *x, const void *w, const void *bias, void *y, c
     a.x_indexed = x_indexed;
     a.y_indexed = y_indexed;
     a.act = act;
-    auto tiles = [&](int64_t t) { return ((c_out + t - 1) / t) * ((k_sel + t - 1) / t); };
-    if (tiles(128) > 2147483647LL / 16) return fail(ASTRAEA_ERR_INVALID, "astraea_sparse_linear(fp32): grid too large");
-    // Rounds of tiles over the 256 CUs, in units of a 32 x 32 tile's work.  At equal rounds the larger tile is the better one
-    // (4096 rows, 3072 -> 3072: 533 us with 128, 559 with 64, 666 with 32, hence the factor 5/4 against the last);
-    // fewer rounds outweigh it (6000 rows: 879 with 128, 830 with 64; 200 rows, 512 -> 512: 12 with 64, 8.5 with 32).
-    const int64_t c128 = (tiles(128) + 255) / 256 * 16, c64 = (tiles(64) + 255) / 256 * 4, c32 = (tiles(32) + 255) / 256;
-    auto go = [&](auto kernel, int t) {
+    if (tiles_of(k_sel, c_out, 128) > 2147483647LL / 16) return fail(ASTRAEA_ERR_INVALID, "astraea_sparse_linear(fp32): grid too large");
+    const int t = linear_f32_tile(k_sel, c_out);
+    auto go = [&](auto kernel) {
         a.n_tiles = (c_out + t - 1) / t;
         a.m_tiles = (int32_t)((k_sel + t - 1) / t);
-        hipLaunchKernelGGL(kernel, dim3((unsigned)((tiles(t) + 7) / 8 * 8)), dim3(kWaves * kWave), 0, stream, a);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((tiles_of(k_sel, c_out, t) + 7) / 8 * 8)), dim3(kWaves * kWave), 0, stream, a);
     };
     // 32-bit byte offsets serve unless an operand is larger (the far form costs one more VALU instruction per copy)
     const bool far = ((x_indexed ? n_rows : k_sel) * ldx) * 4 >= (int64_t)1 << 32 || (int64_t)c_out * c_in * 4 >= (int64_t)1 << 32;
     auto pick = [&](auto far_tag) {
         constexpr bool FAR = decltype(far_tag)::value;
-        if (c128 <= c64 && 4 * c128 <= 5 * c32)
-            go(linear_f32_kernel<2, 2, 2, 2, 1, FAR>, 128);
-        else if (4 * c64 <= 5 * c32)
-            go(linear_f32_kernel<1, 1, 2, 2, 1, FAR>, 64);
+        if (t == 128)
+            go(linear_f32_kernel<2, 2, 2, 2, 1, FAR>);
+        else if (t == 64)
+            go(linear_f32_kernel<1, 1, 2, 2, 1, FAR>);
         else
-            go(linear_f32_kernel<1, 1, 1, 1, 4, FAR>, 32);
+            go(linear_f32_kernel<1, 1, 1, 1, 4, FAR>);
     };
     if (far)
         pick(std::true_type{});

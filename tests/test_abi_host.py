@@ -317,6 +317,15 @@ def test_attention_plan_rejects_bad_arguments(L):
     assert L.astraea_attn_plan(10, 1, 1, out) == ab.OK
 
 
+def test_linear_plan_rejects_bad_arguments(L):
+    out = (C.c_int64 * 3)()
+    assert L.astraea_linear_plan(7, 1, 64, 8, out) == ab.ERR_UNSUPPORTED
+    for k, c_in, c_out in ((0, 64, 8), (1, 0, 8), (1, 64, 0), (1 << 31, 64, 8), (1, (1 << 24) + 1, 8)):
+        assert L.astraea_linear_plan(ab.F32, k, c_in, c_out, out) == ab.ERR_INVALID
+    assert L.astraea_linear_plan(ab.F32, 1, 64, 8, None) == ab.ERR_INVALID
+    assert L.astraea_linear_plan(ab.F32, 1, 64, 8, out) == ab.OK and list(out) == [32, 32, 1]
+
+
 def test_block_flop_accounting_is_the_papers_formulas_at_k():
     """TokenSparseBlock.flops: the FLOPs appendix (self-attention 8BNH^2 + 4BN^2H in total, MLP 16BNH^2, with the
     paper's H = hidden width = E here) at k = N, and exactly the budget fraction of that at k < N."""

@@ -375,7 +375,7 @@ def test_attn_bf16_rows_that_outgrow_their_first_tile_by_a_tolerated_margin(rise
 def test_attn_bf16_only_the_workgroups_that_need_it_are_redone():
     """A handful of selected rows meet one key whose logit lies hundreds of nats above everything in their first
     tile (their exponentials overflow under the first tile's offset), all other rows are ordinary.  The
-    workgroups holding those rows are redone by the exact launch, the others are not; every row, redone or not,
+    workgroups holding those rows repeat their sweep in the exact form, the others do not; every row, redone or not,
     cut into key ranges or not, must match the oracle, and twice the same call the same bits."""
     n, h, d, k_sel = 4100, 24, 128, 1100
     q, k, v, idx = _attn_case(n, h, d, k_sel, torch.bfloat16, seed=404)

@@ -35,19 +35,26 @@ def test_score_sizes(n, c, stride, dtype, mode):
 
 
 # fp32 linear: 128-, 64- or 32-wide tiles by the rounds of tiles they leave (32: the four waves split the contraction, and
-# a 64-wide contraction leaves two of them without a stage); stages of 32 indices in a ring of four.  Bound: sums of c_in
+# a 64-wide contraction leaves two of them without a stage); stages of 32 indices in a ring of four.  `tile` is what the
+# launch says it takes; each tile meets ragged rows and features and contractions that end inside the ring.  Bound: sums of c_in
 # products of size ~1/sqrt(c_in) in fp32, error below c_in * 2^-24 / sqrt(c_in) * 4 <= 1e-4 absolute at c_in <= 4096.
-@pytest.mark.parametrize("n,k,c_in,c_out,gather,scatter,bias,act", [
-    (40, 33, 64, 40, True, True, True, ab.ACT_NONE),             # 32: two stages for four waves
-    (300, 31, 192, 104, True, False, False, ab.ACT_GELU_TANH),   # 32: six stages
-    (300, 257, 448, 264, False, True, True, ab.ACT_NONE),        # 32: fourteen stages, ragged both ways
-    (2100, 2049, 128, 512, True, True, True, ab.ACT_NONE),       # 64: one stage past a tile edge
-    (2100, 2016, 320, 520, True, False, True, ab.ACT_GELU_TANH), # 64: ten stages
-    (2100, 2047, 192, 2056, False, True, True, ab.ACT_NONE),     # 64 or 128 at the edge of a round
-    (2100, 2048, 128, 2048, True, True, False, ab.ACT_NONE),     # 128
-    (4100, 4095, 64, 1032, True, True, True, ab.ACT_NONE),       # 128: two stages, ragged
+@pytest.mark.parametrize("n,k,c_in,c_out,gather,scatter,bias,act,tile", [
+    (40, 33, 64, 40, True, True, True, ab.ACT_NONE, 32),             # two stages for four waves
+    (300, 31, 192, 104, True, False, False, ab.ACT_GELU_TANH, 32),   # six stages
+    (300, 257, 448, 264, False, True, True, ab.ACT_NONE, 32),        # fourteen stages
+    (2100, 2049, 128, 512, True, True, True, ab.ACT_NONE, 32),       # one row past what the 64 tile takes
+    (2100, 2016, 320, 520, True, False, True, ab.ACT_GELU_TANH, 32), # a few features past it
+    (2100, 2047, 192, 2056, False, True, True, ab.ACT_NONE, 64),     # at the edge of a round of the 128 tile
+    (4100, 4095, 64, 1032, True, True, True, ab.ACT_NONE, 64),       # two stages
+    (2100, 2000, 320, 504, True, False, True, ab.ACT_GELU_TANH, 64), # ten stages
+    (2100, 1985, 256, 456, False, True, False, ab.ACT_NONE, 64),     # eight stages, one row in the last tile
+    (2100, 2048, 128, 2048, True, True, False, ab.ACT_NONE, 128),    # whole tiles, the ring once round
+    (4100, 4000, 64, 1000, True, True, True, ab.ACT_GELU_TANH, 128), # two stages
+    (4100, 4000, 192, 1000, False, True, True, ab.ACT_NONE, 128),    # six stages
+    (4100, 3969, 448, 904, True, False, False, ab.ACT_NONE, 128),    # fourteen stages, one row and eight features in the last tile
 ])
-def test_linear_f32_tiles(n, k, c_in, c_out, gather, scatter, bias, act):
+def test_linear_f32_tiles(n, k, c_in, c_out, gather, scatter, bias, act, tile):
+    assert ab.astraea_linear_plan(ab.F32, k, c_in, c_out)["tile_tokens"] == tile
     g = torch.Generator(device=DEV).manual_seed(n + k + c_in)
     idx = torch.randperm(n, device=DEV, generator=g)[:k].sort().values.to(torch.int32)
     x = torch.randn(n if gather else k, c_in, device=DEV, generator=g)
@@ -67,11 +74,13 @@ def test_linear_f32_tiles(n, k, c_in, c_out, gather, scatter, bias, act):
     assert torch.equal(y[keep].double(), exp[keep])
 
 
-def test_linear_f32_operand_past_4_gib():
-    """Rows beyond the reach of a 32-bit byte offset: 1040 rows of 4 MiB pitch."""
-    n, k, c_in, c_out = 1040, 100, 64, 72
+@pytest.mark.parametrize("k,c_out,tile", [(100, 72, 32), (2000, 504, 64), (4000, 1000, 128)])
+def test_linear_f32_operand_past_4_gib(k, c_out, tile):
+    """Rows beyond the reach of a 32-bit byte offset: 4110 rows of 2 MiB pitch."""
+    n, c_in = 4110, 64
+    assert ab.astraea_linear_plan(ab.F32, k, c_in, c_out)["tile_tokens"] == tile
     g = torch.Generator(device=DEV).manual_seed(3)
-    x = torch.empty(n, 1 << 20, device=DEV)[:, :c_in]
+    x = torch.empty(n, 1 << 19, device=DEV)[:, :c_in]
     x.copy_(torch.randn(n, c_in, device=DEV, generator=g))
     w = torch.randn(c_out, c_in, device=DEV, generator=g) * c_in ** -0.5
     idx = torch.arange(n - k, n, dtype=torch.int32, device=DEV)
@@ -134,6 +143,32 @@ def _attn_rise_case(n, h, k, d, rise_nats, dtype, first_tile):
     q[:, :, 0], kc[:, :, 0] = 8.0, 0.0
     kc[:first_tile, :, 0] = -rise_nats * math.sqrt(d) / 8.0
     return q.to(dtype), kc.to(dtype), torch.randn(n, h, d, device=DEV, generator=g).to(dtype)
+
+
+# V retiled (more than 16384 queries): packed cache and head-major strides, queries gathered by index, flat logits and logits
+# that rise above the first key tile's inside and past the margin of the row sums.  Bars as above.
+@pytest.mark.parametrize("layout,rise_nats", [("packed", 0.0), ("head", 0.0), ("packed", 20.0), ("head", 45.0), ("packed", 90.0)])
+def test_attn_bf16_retiled_layouts_and_rises(layout, rise_nats):
+    n, h, k = 16500, 2, 16400
+    q, kc, vc = _attn_rise_case(n, h, n, 128, rise_nats, torch.bfloat16, 64)
+    if layout == "packed":
+        q, kc, vc = torch.stack((q, kc, vc), 1).unbind(1)
+    else:
+        q, kc, vc = (t.transpose(0, 1).contiguous().transpose(0, 1) for t in (q, kc, vc))
+    assert kc.stride(0 if layout == "packed" else 1) == (3 * h * 128 if layout == "packed" else n * 128)
+    g = torch.Generator(device=DEV).manual_seed(k)
+    idx = torch.randperm(n, device=DEV, generator=g)[:k].sort().values.to(torch.int32)
+    lse = torch.full((k, h), math.nan, device=DEV)
+    ws = torch.full((ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, 128),), 255, dtype=torch.uint8, device=DEV)
+    out = torch.empty(k, h, 128, dtype=torch.bfloat16, device=DEV)
+    ab.astraea_sparse_attn_fwd(q, kc, vc, idx, k, out, 1.0 / math.sqrt(128), lse_sel=lse, workspace=ws)
+    torch.cuda.synchronize()
+    for i in range(h):
+        logits = q[idx.long(), i].double() @ kc[:, i].double().T.contiguous() / math.sqrt(128)
+        ref = torch.softmax(logits, 1) @ vc[:, i].double()
+        assert_rel_l2(out[:, i].double().cpu().numpy(), ref.cpu().numpy(), tag=f"head {i}")
+        want = torch.logsumexp(logits, 1)
+        assert ((lse[:, i].double() - want).abs() / want.abs().clamp(min=1.0)).max().item() <= 2.0 ** -9
 
 
 # Logits 45 nats above those of the first key tile, inside the margin of the row sums, over values of 2^66: the accumulators
@@ -274,16 +309,19 @@ def test_topk_sizes(n, kind):
 # bf16 linear: tiles of 256 features x 256, 192 or 128 tokens by the launch's estimate (the sizes below take each of them), edges
 # of the token tiles, ragged features, more and fewer tiles than CUs, one to many contraction steps.  Reference: fp64; bar:
 # relative L2 1e-2 per row (bf16 inputs and result).
-@pytest.mark.parametrize("n,k,c_in,c_out,gather,scatter,bias,act", [
-    (5, 1, 64, 8, True, True, True, ab.ACT_NONE), (300, 127, 64, 264, True, False, False, ab.ACT_GELU_TANH),
-    (300, 129, 128, 512, False, True, True, ab.ACT_NONE), (700, 608, 192, 3072, True, True, True, ab.ACT_GELU_TANH),      # 128
-    (2000, 1755, 512, 12288, True, False, True, ab.ACT_NONE), (3600, 3457, 320, 3072, False, True, True, ab.ACT_NONE),    # 192
-    (3600, 3456, 256, 3080, True, True, False, ab.ACT_GELU_TANH), (7100, 7020, 320, 3072, True, True, True, ab.ACT_NONE), # 192
-    (5100, 5000, 128, 3072, True, True, True, ab.ACT_NONE), (5200, 5121, 192, 3064, False, True, True, ab.ACT_GELU_TANH), # 256
-    (9000, 8192, 64, 2048, True, False, True, ab.ACT_NONE), (9000, 8193, 128, 2048, True, True, True, ab.ACT_NONE),       # 256: one round; 192
-    (33100, 33000, 3136, 3072, True, True, True, ab.ACT_NONE), (12100, 12000, 9216, 2048, False, True, True, ab.ACT_NONE),  # 256, 192
+@pytest.mark.parametrize("n,k,c_in,c_out,gather,scatter,bias,act,tile", [
+    (5, 1, 64, 8, True, True, True, ab.ACT_NONE, 128), (300, 127, 64, 264, True, False, False, ab.ACT_GELU_TANH, 128),
+    (300, 129, 128, 512, False, True, True, ab.ACT_NONE, 128), (700, 608, 192, 3072, True, True, True, ab.ACT_GELU_TANH, 128),
+    (2000, 1755, 512, 12288, True, False, True, ab.ACT_NONE, 192), (3600, 3457, 320, 3072, False, True, True, ab.ACT_NONE, 192),
+    (3600, 3456, 256, 3080, True, True, False, ab.ACT_GELU_TANH, 192), (7100, 7020, 320, 3072, True, True, True, ab.ACT_NONE, 192),
+    (5100, 5000, 128, 3072, True, True, True, ab.ACT_NONE, 256), (5200, 5121, 192, 3064, False, True, True, ab.ACT_GELU_TANH, 256),
+    (9000, 8192, 64, 2048, True, False, True, ab.ACT_NONE, 256),                                   # one whole round
+    (9000, 8193, 128, 2048, True, True, True, ab.ACT_NONE, 192), (12100, 12000, 9216, 2048, False, True, True, ab.ACT_NONE, 192),
+    (33100, 33000, 3136, 3072, True, True, True, ab.ACT_NONE, 256),
 ])
-def test_linear_bf16_tiles(n, k, c_in, c_out, gather, scatter, bias, act):
+def test_linear_bf16_tiles(n, k, c_in, c_out, gather, scatter, bias, act, tile):
+    assert ab.astraea_linear_plan(ab.BF16, k, c_in, c_out) == {
+        "tile_features": 256, "tile_tokens": tile, "tiles": -(-k // tile) * -(-c_out // 256)}
     g = torch.Generator(device=DEV).manual_seed(n + k + c_in)
     idx = torch.randperm(n, device=DEV, generator=g)[:k].sort().values.to(torch.int32)
     x = torch.randn(n if gather else k, c_in, device=DEV, generator=g).bfloat16()
