@@ -18,13 +18,13 @@
 //    front of the last quarter so that no fragment read follows it) runs fewer clocks per step at a
 //    lower clock rate, or the other way round: the chip holds its power limit and the two designs
 //    end up within 1 % of each other.
-//  * the contraction advances in steps of 64; the two 32 KiB tiles of a step go from global memory
+//  * the contraction advances in steps of 64; the w tile (32 KiB) and the x tile (16 to 32) of a step go from global memory
 //    straight into LDS (global_load_lds_dwordx4, per-lane addresses, so the row gather costs nothing),
-//    double buffered, 16-byte chunks XOR-swizzled inside each 128-byte row against bank conflicts.
+//    into a ring of stages, 16-byte chunks XOR-swizzled inside each 128-byte row against bank conflicts.
 //    A copy must cover whole 128-byte lines: with 64-byte pieces (a ring of four 32-deep units) the
 //    L1 fetches every line from L2 twice and the kernel is 30 % slower.
-//    The second wave of each SIMD issues the copy instructions of the next step, one behind each of
-//    its first 16 MFMAs, and has the higher priority: the memory pipe holds it at every copy, and its
+//    The second wave of each SIMD issues the copy instructions of a coming step, one behind each of
+//    its first 12 to 16 MFMAs, and has the higher priority: the memory pipe holds it at every copy, and its
 //    neighbour's MFMAs fill exactly that time.  A 4-byte load per row, shared out among the
 //    workgroups that use the row, touches the lines of two steps ahead so that the copies hit in L2.  The 128-token tile has
 //    three stages, copied two ahead, and no touches: its steps are shorter than a copy takes (all linear layers of a
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
     constexpr int kAhead = kStages - 1;
     constexpr int kTouches = kStages == 2 ? 2 : 0;     // L2 warm-up loads per copying wave and step
     constexpr int kPitch = 64 * NB + 16; // epilogue staging: the wave's features of a token, padded
-    constexpr int kEpiTokens = TB == 2 ? 64 : 32 * TB;            // tokens a wave stages at a time
+    constexpr int kEpiTokens = 32 * TB;  // the wave's tokens
     constexpr int kEpiBytes = kWaves * kEpiTokens * kPitch;
     __shared__ __attribute__((aligned(1024))) char lds[kStages * kStageBytes > kEpiBytes ? kStages * kStageBytes : kEpiBytes];
     __shared__ __attribute__((aligned(256))) uint32_t scrap[kWave];      // where the L2 warm-up loads land
@@ -145,13 +145,13 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
     }
 
     // ---- tile copies.  The memory pipe accepts a 1 KiB copy instruction only every ~16 clocks per CU
-    // (~57 per wave with four waves at it), so the 64 of a step hold whoever issues them for half a step.
-    // The second wave of each SIMD does all of it, one copy behind each of its first 16 MFMAs, and runs at
+    // (~57 per wave with four waves at it), so the 48 to 64 of a step hold whoever issues them for half a step.
+    // The second wave of each SIMD does all of it, one copy behind each of its first MFMAs, and runs at
     // the higher priority: while it is held at a copy the first wave's MFMAs have the matrix pipe, and
     // when it is not, its own go first.  Both waves end their step at about the same time.
-    // One instruction fills 8 rows of a tile; copying wave c = wave - 4 issues instructions c, c+4, ...,
-    // c+28 of each tile.  Lane l serves row 8*i + l/8 and the physical chunk l%8, which holds logical
-    // chunk (l%8) ^ ((row/2)%8); for the rows of one wave that is the same in all 8 instructions, so a
+    // One instruction fills 8 rows of a tile; copying wave c = wave - 4 issues instructions c, c+4, ...
+    // of each tile.  Lane l serves row 8*i + l/8 and the physical chunk l%8, which holds logical
+    // chunk (l%8) ^ ((row/2)%8); for the rows of one wave that is the same in all its instructions, so a
     // lane's byte offset inside its rows is fixed.
     const bool copier = wave >= kCopyWaves;
     const int cw = wave & (kCopyWaves - 1);
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
     // touching them kPrefetch steps ahead lets the tile copies hit in L2.
     const uint32_t pf_w = w_row(8 * (cw + kCopyWaves * ((lane >> 3) % kCopiesW)) + (lane & 7));
     const uint32_t pf_x = x_row(8 * (cw + kCopyWaves * ((lane >> 3) % kCopiesX)) + (lane & 7));
-    asm volatile("" ::"v"(pf_x), "v"(pf_w));
+    if (kTouches) asm volatile("" ::"v"(pf_x), "v"(pf_w));
     // The 8 token tiles of a block share its weight rows and the 4 feature tiles its token rows, so each workgroup touches an
     // eighth of the one and a quarter of the other: a load of one word of each of 64 rows holds the memory pipe like
     // four tile copies.  All linear layers of a block, 17550 tokens at 40 % / 118800 at 30 %: every workgroup touching all
@@ -323,10 +323,10 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
     // Register group g of block (i, j): features 32*NB*wn + 32*i + 8*g + 4*hf + 0..3, token
     // 32*TB*wm + 32*j + qc of the tile.  An accumulator lane owns one token, so stores straight from the
     // registers would put 16 bytes on each of 32 rows per instruction; partial-line writes of that kind
-    // cost several times the main loop's share of HBM time.  Instead each wave transposes its block,
-    // kEpiTokens at a time, through its own part of LDS (rows of its features, padded by 16 bytes) and
-    // writes whole 128-byte lines (4 rows x 256 bytes per instruction, or 8 x 128).  The tile buffers are free: every
-    // wave has passed the barrier that ends the last step.  The region is private to the wave, so no
+    // cost several times the main loop's share of HBM time.  Instead each wave transposes its block
+    // through its own part of LDS (rows of its features, padded by 16 bytes) and
+    // writes whole 128-byte lines (4 rows x 256 bytes per instruction, or 8 x 128).  The stages are free: every
+    // wave has passed the barrier behind the last step and its copies.  The region is private to the wave, so no
     // workgroup barrier is needed, only the wave's own LDS counter.
     // this lane's bias values (4 NB groups of 4 features), from the copy in LDS
     uint2v bias2[NB][4];
@@ -338,51 +338,42 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
     const uint32_t ebase = lds0 + wave * (kEpiTokens * kPitch);
     constexpr int kRowLanes = 4 * NB, kRowsPerStore = kWave / kRowLanes;      // read-back: 16 bytes per lane
     const int o_row = lane / kRowLanes, o_chunk = lane % kRowLanes;
-    constexpr int kJ = kEpiTokens / 32;
 #pragma unroll
-    for (int jh = 0; jh < TB / kJ; ++jh) {
+    for (int j = 0; j < TB; ++j)
 #pragma unroll
-        for (int jj = 0; jj < kJ; ++jj) {
-            const int j = kJ * jh + jj;
+        for (int i = 0; i < NB; ++i)
 #pragma unroll
-            for (int i = 0; i < NB; ++i)
+            for (int g = 0; g < 4; ++g) {
+                const int nl = 32 * i + 8 * g + 4 * hf;      // feature inside the wave's part
+                float v[4];
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int nl = 32 * i + 8 * g + 4 * hf;      // feature inside the wave's part
-                    float v[4];
+                for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * g + e];
+                const uint2v b2 = bias2[i][g];
+                v[0] += __uint_as_float(b2[0] << 16);
+                v[1] += __uint_as_float(b2[0] & 0xffff0000u);
+                v[2] += __uint_as_float(b2[1] << 16);
+                v[3] += __uint_as_float(b2[1] & 0xffff0000u);
+                if (a.act == ASTRAEA_ACT_GELU_TANH) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * g + e];
-                    const uint2v b2 = bias2[i][g];
-                    v[0] += __uint_as_float(b2[0] << 16);
-                    v[1] += __uint_as_float(b2[0] & 0xffff0000u);
-                    v[2] += __uint_as_float(b2[1] << 16);
-                    v[3] += __uint_as_float(b2[1] & 0xffff0000u);
-                    if (a.act == ASTRAEA_ACT_GELU_TANH) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] = gelu_tanh(v[e]);
-                    }
-                    uint2v o2;
-                    o2[0] = pack_bf16(v[0], v[1]);
-                    o2[1] = pack_bf16(v[2], v[3]);
-                    *reinterpret_cast<uint2v __attribute__((address_space(3))) *>(
-                        (uintptr_t)(ebase + (32 * jj + qc) * kPitch + nl * 2)) = o2;
+                    for (int e = 0; e < 4; ++e) v[e] = gelu_tanh(v[e]);
                 }
-        }
-        __builtin_amdgcn_s_waitcnt(0xc07f);                      // lgkmcnt(0): this wave's LDS writes are done
-        // destination rows of this part first, then the stores: an index load between
-        // two stores would be waited for each time
+                uint2v o2;
+                o2[0] = pack_bf16(v[0], v[1]);
+                o2[1] = pack_bf16(v[2], v[3]);
+                *reinterpret_cast<uint2v __attribute__((address_space(3))) *>(
+                    (uintptr_t)(ebase + (32 * j + qc) * kPitch + nl * 2)) = o2;
+            }
+    __builtin_amdgcn_s_waitcnt(0xc07f);                      // lgkmcnt(0): this wave's LDS writes are done
 #pragma unroll
-        for (int it = 0; it < kEpiTokens / kRowsPerStore; ++it) {
-            const int tl = kRowsPerStore * it + o_row;           // token inside this part
-            const int64_t orow = tile_rows[wm * 32 * TB + kEpiTokens * jh + tl];    // -1: past the end or a bad index
-            const int n = n0 + wn * 32 * NB + 8 * o_chunk;       // c_out is a multiple of 8: a chunk is all in or all out
-            const uint4v val = *reinterpret_cast<const uint4v __attribute__((address_space(3))) *>(
-                (uintptr_t)(ebase + tl * kPitch + o_chunk * 16));
-            // written once: streaming stores leave the tiles other workgroups still read in L2 (+1-3 %)
-            if (n < a.c_out && orow >= 0)
-                __builtin_nontemporal_store(val, reinterpret_cast<uint4v *>(a.y + orow * a.ldy + n));
-        }
-        __builtin_amdgcn_s_waitcnt(0xc07f);                      // reads done before the next part overwrites
+    for (int it = 0; it < kEpiTokens / kRowsPerStore; ++it) {
+        const int tl = kRowsPerStore * it + o_row;           // token inside the wave's part
+        const int64_t orow = tile_rows[wm * 32 * TB + tl];   // -1: past the end or a bad index
+        const int n = n0 + wn * 32 * NB + 8 * o_chunk;       // c_out is a multiple of 8: a chunk is all in or all out
+        const uint4v val = *reinterpret_cast<const uint4v __attribute__((address_space(3))) *>(
+            (uintptr_t)(ebase + tl * kPitch + o_chunk * 16));
+        // written once: streaming stores leave the tiles other workgroups still read in L2 (+1-3 %)
+        if (n < a.c_out && orow >= 0)
+            __builtin_nontemporal_store(val, reinterpret_cast<uint4v *>(a.y + orow * a.ldy + n));
     }
 }
 

@@ -424,7 +424,7 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(const float *
         me += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(key[j] == T));
     }
     if (lane == 0) {
-        wt_a[wave] = mg;                         // last read before the barriers above
+        wt_a[wave] = mg;                         // last read before the barriers above (k == 0: for the key range, unused then)
         wt_b[wave] = me;
     }
     __syncthreads();
