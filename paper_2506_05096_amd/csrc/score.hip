@@ -13,11 +13,12 @@
 //    short sequence needs: at 17550 tokens 64 per wave make 275 waves, one per CU, and each slab's
 //    load latency, its conversion and its chain came one after the other.  Cold arrays, 64 per wave -> this
 //    kernel: 2025 x 3072 bf16 63 -> 14.5 us; 17550 x 3072 80 -> 41 us (5.3 TB/s); 16384 x 512 13.1 -> 8.8;
-//    4096 x 512 fp32 14.3 -> 8.5; 40000 x 1536 49 -> 42.  Tried: one wave for both jobs 22 and 49 us at
+//    4096 x 512 fp32 14.3 -> 8.5; 36000 x 3072 89.8 -> 74.5.  Tried: one wave for both jobs 22 and 49 us at
 //    2025 and 17550 tokens; slabs of 8 x 512 B the same, 32 x 128 B 20 us at 2025.
 //  * score_wide_kernel: a wave owns 64 tokens and does both jobs (a [64 x 128 byte] slab, the next one in flight).
 //    With three such waves per CU or more the latencies are covered and all 64 lanes run chains: 111 us
-//    (6.7 TB/s) at 60000 x 3072 and 217 us at 118800 x 3072, against 116 and 220 for the other kernel.
+//    (6.7 TB/s) at 60000 x 3072 and 217 us at 118800 x 3072, against 116 and 220 for the other kernel.  Arrays that
+//    the memory-side cache may still hold need fewer: there the latencies are shorter, see launch_score.
 //
 // HBM-bound: 2*C*sizeof(T) bytes read and 4 written per token.
 #include <type_traits>
@@ -35,8 +36,11 @@ constexpr int kWideWavesPerBlock = 4;
 constexpr int kWideTok = 64;            // tokens per wave (lane == token in the reduce phase)
 constexpr int kWideSegBytes = 128;      // bytes of each row handled per slab
 constexpr int kWideVecPerLane = 8;      // 64 rows * 8 vec16 per row / 64 lanes
-// The wide kernel is for at least this many tokens: three waves per CU.
+// The wide kernel is for at least this many tokens, three waves per CU; where both arrays fit in the memory-side cache, for
+// fewer (launch_score has the figures).
 constexpr int64_t kWideMinTokens = 3 * 256 * kWideTok;
+constexpr int64_t kWideMinCachedBf16 = 28672, kWideMinCachedF32 = 20480;
+constexpr int64_t kCacheBytes = (int64_t)256 << 20;
 
 constexpr int kTok = 16;            // tokens per workgroup; lane t < kTok of the second wave reduces token t
 constexpr int kSegBytes = 256;      // bytes of each row handled per slab
@@ -401,13 +405,23 @@ int launch_score(const void *x_cur, const void *x_prev, astraea_dtype dt, int64_
 {
     if (N == 0) return ASTRAEA_OK;
     const int64_t es = dt == ASTRAEA_F32 ? 4 : 2;
-    // a 16-token workgroup addresses its rows with 32-bit byte offsets
-    const bool wide = N >= kWideMinTokens || kTok * row_stride * es > 2147483647LL;
+    // Which kernel.  Past the 256 MB of the memory-side cache the line is three wide waves per CU (36000 x 3072 bf16: wide 84.7 us,
+    // 16 tokens 73.7).  Arrays below that are either hot, still in the cache from their producer, or cold.  Cold, 16 tokens
+    // win up to about the same line; hot, they lose it earlier, since the wide kernel then has less latency to cover: bf16 hot /
+    // cold, wide and 16 tokens: 28000 x 512 13.7 / 16.5 and 12.6 / 14.4, 36000 x 512 14.1 / 17.3 and 14.8 / 16.4, 49000 x 256 9.1 /
+    // 11.4 and 10.8 / 11.7; 28000 x 2048 44.6 / 60.5 and 42.2 / 50.4, 32000 x 2048 44.7 / 65.1 and 51.0 / 58.6; fp32: 20000 x 512
+    // 15.3 / 22.6 and 14.1 / 16.0, 28000 x 512 17.9 / 25.3 and 18.7 / 22.2, 24000 x 1024 29.5 / 52.3 and 33.7 / 41.0.  The lines
+    // lie where neither loses hot.  (A 16-token workgroup also addresses its rows with 32-bit byte offsets.)
+    const int64_t bytes = 2 * N * row_stride * es;
+    const int64_t line = bytes > kCacheBytes ? kWideMinTokens : dt == ASTRAEA_F32 ? kWideMinCachedF32 : kWideMinCachedBf16;
+    const bool wide = N >= line || kTok * row_stride * es > 2147483647LL;
     const bool vec = C * es >= 16 && ((uintptr_t)x_cur % 16 == 0) && ((uintptr_t)x_prev % 16 == 0) && ((row_stride * es) % 16 == 0);
-    // The streaming hint (the line is not kept in L2) is for arrays that are not still cached from their producer.
-    // Wide kernel: above the 256 MB of the memory-side cache, 5.96 -> 6.77 TB/s at 118800 x 3072.  The other, both
-    // arrays together above 128 MB: cold 45.3 -> 40.9 us and hot 38.5 -> 39.2 us at 17550 x 3072.
-    const bool stream_loads = vec && 2 * N * row_stride * es > ((int64_t)(wide ? 256 : 128) << 20);
+    // The streaming hint (the line is not kept in L2) is for arrays that are not still cached from their producer:
+    // above the 256 MB of the memory-side cache, 5.96 -> 6.77 TB/s at 118800 x 3072 (wide).  Up to 24576 tokens the
+    // 16-token kernel takes it from 200 MB on, where it costs little even hot: cold 45.5 -> 41.6 us and hot 39.7 -> 40.8 at
+    // 17550 x 3072 (206 MB); not so below, hot 24.9 -> 32.2 and cold 34.5 -> 32.3 at 17550 x 1024 fp32 (137 MB), nor past
+    // that many tokens, hot 42.2 -> 48.0 and cold 50.4 -> 47.5 at 28000 x 2048 bf16 (219 MB).
+    const bool stream_loads = vec && bytes > (!wide && N <= 24576 ? (int64_t)200 << 20 : kCacheBytes);
 #define ASTRAEA_SCORE_LAUNCH(T, VEC, NT)                                                                                  \
     launch_mode<T, VEC, NT>(mode, wide, stream, (const T *)x_cur, (const T *)x_prev, N, C, row_stride, lse_weight,        \
                             skip_count, penalty_table, table_len, w_alpha, w_beta, score_out)

@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 
-# score: 16 tokens per workgroup below 49152 tokens, 64 per wave from there on; slabs of 256 bytes, four in flight;
+# score: 16 tokens per workgroup below 28672 tokens (fp32 20480; 49152 where the arrays hold more than 256 MB), 64 per wave from
+# there on; streaming loads above 256 MB, up to 24576 tokens above 200; slabs of 256 bytes, four in flight;
 # a width that is no multiple of the 16-byte vector ends on single channels.  Bit-exact.
 @pytest.mark.parametrize("n,c,stride,dtype", [
     (15, 128, 128, torch.bfloat16), (16, 256, 256, torch.bfloat16), (17, 384, 384, torch.bfloat16),      # 1 - 3 slabs
@@ -22,6 +23,8 @@ DEV = "cuda"
     (50, 515, 520, torch.bfloat16), (50, 1, 8, torch.bfloat16), (50, 130, 131, torch.bfloat16),          # ragged widths, element path
     (47, 63, 64, torch.float32), (48, 64, 64, torch.float32), (49, 321, 324, torch.float32), (20, 3, 4, torch.float32),
     (49151, 24, 24, torch.bfloat16), (49152, 24, 24, torch.bfloat16), (49153, 40, 40, torch.float32),
+    (28671, 24, 24, torch.bfloat16), (28672, 24, 24, torch.bfloat16), (20479, 20, 20, torch.float32), (20480, 40, 40, torch.float32),
+    (49151, 1371, 1376, torch.bfloat16), (49152, 1371, 1376, torch.bfloat16), (24576, 2136, 2136, torch.bfloat16),   # streaming
 ])
 @pytest.mark.parametrize("mode", [ab.DELTA_L2, ab.DELTA_MEAN_ABS])
 def test_score_sizes(n, c, stride, dtype, mode):
