@@ -52,7 +52,7 @@ int launch_linear_f32(const void *x, const void *w, const void *bias, void *y, c
 
 // Tokens per tile a linear launch takes (fp32: as many features; bf16: 256 features).
 int linear_bf16_tile(int64_t k_sel, int32_t c_in, int64_t c_out);
-int linear_f32_tile(int64_t k_sel, int64_t c_out);
+int linear_f32_tile(int64_t k_sel, int64_t c_in, int64_t c_out);
 
 size_t attn_bf16_workspace_bytes(int64_t N, int32_t H);
 int attn_bf16_plan(int64_t N, int32_t H, int64_t k_sel, int64_t plan[8]);

@@ -16,7 +16,7 @@
 //    vector instructions do not overlap its fp32 MFMAs: each one in the loop is matrix time lost (measured: address
 //    arithmetic for reads and copies took a fifth of the rate, with one or two waves per SIMD).  Hence the loop is unrolled over the ring, all LDS addresses
 //    are constants in the instructions, and copies advance a scalar base with 32-bit lane offsets.
-//  * three tile shapes, by the rounds of tiles over 256 CUs that they leave: 128 x 128 (waves of 64 x 64), 64 x 64 (waves of
+//  * three tile shapes, by what the rounds of tiles over 256 CUs that they leave take: 128 x 128 (waves of 64 x 64), 64 x 64 (waves of
 //    32 x 32; two workgroups share a CU), and, where those leave CUs without a tile, 32 x 32 with the four waves
 //    splitting the contraction, each from a ring of its own, and the sums meeting in LDS.
 // Measured (us; before = 128 x 128 tiles, operands read from global memory into registers): 2048 rows 512 -> 512
@@ -289,15 +289,19 @@ int64_t tiles_of(int64_t k_sel, int64_t c_out, int64_t t) { return ((c_out + t -
 
 }  // namespace
 
-// Features and tokens per tile: the rounds of tiles over the 256 CUs, in units of a 32 x 32 tile's work.  At equal rounds the
-// larger tile is the better one (4096 rows, 3072 -> 3072: 533 us with 128, 559 with 64, 666 with 32, hence the factor 5/4
-// against the last); fewer rounds outweigh it (6000 rows: 879 with 128, 830 with 64; 200 rows, 512 -> 512: 12 with 64, 8.5
-// with 32).
-int linear_f32_tile(int64_t k_sel, int64_t c_out)
+// Features and tokens per tile: the least of an estimate in microseconds, rounds of tiles over the 256 CUs times what a round
+// takes, a fixed part and one that grows with the contraction (fitted to 1200 shapes of 16 to 6000 rows, 64 to 2048 -> 64 to
+// 6144, of which this picks the best within 9 %, 0.5 % on average).  Larger tiles work faster, smaller ones fill the last
+// round better and start sooner: us with 128 / 64 / 32: 4096 rows 3072 -> 3072 533 / 559 / 666, 6000 rows 879 / 830 / -, 200 rows
+// 512 -> 512 33 / 10.9 / 10.4.  The fixed part decides shallow contractions, where many rounds of small tiles are mostly start
+// and end: 765 rows 64 -> 3072 10.9 / 10.2 / 22.1, 1500 rows 192 -> 1408 17.8 / 14.9 / 25.4, which work alone would give to 32.
+int linear_f32_tile(int64_t k_sel, int64_t c_in, int64_t c_out)
 {
-    auto rounds = [&](int64_t t) { return (tiles_of(k_sel, c_out, t) + 255) / 256 * (t * t / 1024); };
-    const int64_t c128 = rounds(128), c64 = rounds(64), c32 = rounds(32);
-    return c128 <= c64 && 4 * c128 <= 5 * c32 ? 128 : 4 * c64 <= 5 * c32 ? 64 : 32;
+    auto us = [&](int64_t t, double fixed, double per_index) {
+        return (double)((tiles_of(k_sel, c_out, t) + 255) / 256) * (fixed + per_index * (double)c_in);
+    };
+    const double us128 = us(128, 6.5, 0.054), us64 = us(64, 1.9, 0.0139), us32 = us(32, 2.0, 0.0034);
+    return us128 <= us64 && us128 <= us32 ? 128 : us64 <= us32 ? 64 : 32;
 }
 
 int launch_linear_f32(const void *x, const void *w, const void *bias, void *y, const int32_t *idx_sel, int64_t k_sel,
@@ -321,7 +325,7 @@ int launch_linear_f32(const void *x, const void *w, const void *bias, void *y, c
     a.y_indexed = y_indexed;
     a.act = act;
     if (tiles_of(k_sel, c_out, 128) > 2147483647LL / 16) return fail(ASTRAEA_ERR_INVALID, "astraea_sparse_linear(fp32): grid too large");
-    const int t = linear_f32_tile(k_sel, c_out);
+    const int t = linear_f32_tile(k_sel, c_in, c_out);
     auto go = [&](auto kernel) {
         a.n_tiles = (c_out + t - 1) / t;
         a.m_tiles = (int32_t)((k_sel + t - 1) / t);

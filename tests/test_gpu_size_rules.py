@@ -37,7 +37,7 @@ def test_score_sizes(n, c, stride, dtype, mode):
     assert np.array_equal(out.cpu().numpy().view(np.uint32), exp.view(np.uint32))
 
 
-# fp32 linear: 128-, 64- or 32-wide tiles by the rounds of tiles they leave (32: the four waves split the contraction, and
+# fp32 linear: 128-, 64- or 32-wide tiles by an estimate of the rounds they leave (32: the four waves split the contraction, and
 # a 64-wide contraction leaves two of them without a stage); stages of 32 indices in a ring of four.  `tile` is what the
 # launch says it takes; each tile meets ragged rows and features and contractions that end inside the ring.  Bound: sums of c_in
 # products of size ~1/sqrt(c_in) in fp32, error below c_in * 2^-24 / sqrt(c_in) * 4 <= 1e-4 absolute at c_in <= 4096.
@@ -45,8 +45,9 @@ def test_score_sizes(n, c, stride, dtype, mode):
     (40, 33, 64, 40, True, True, True, ab.ACT_NONE, 32),             # two stages for four waves
     (300, 31, 192, 104, True, False, False, ab.ACT_GELU_TANH, 32),   # six stages
     (300, 257, 448, 264, False, True, True, ab.ACT_NONE, 32),        # fourteen stages
-    (2100, 2049, 128, 512, True, True, True, ab.ACT_NONE, 32),       # one row past what the 64 tile takes
-    (2100, 2016, 320, 520, True, False, True, ab.ACT_GELU_TANH, 32), # a few features past it
+    (1100, 1001, 512, 264, True, True, True, ab.ACT_NONE, 32),       # sixteen stages
+    (2100, 2049, 128, 512, True, True, True, ab.ACT_NONE, 64),       # four stages, one row in the last tile
+    (2100, 2016, 320, 520, True, False, True, ab.ACT_GELU_TANH, 64), # ten stages, eight features in the last tile
     (2100, 2047, 192, 2056, False, True, True, ab.ACT_NONE, 64),     # at the edge of a round of the 128 tile
     (4100, 4095, 64, 1032, True, True, True, ab.ACT_NONE, 64),       # two stages
     (2100, 2000, 320, 504, True, False, True, ab.ACT_GELU_TANH, 64), # ten stages
