@@ -304,16 +304,17 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(const float *__rest
 // ranks in index order come from ballots.  The keys' range is found first and the passes look at its bits only: digit 1 is
 // (key - lowest) >> shift, up to 2048 bins, digit 2 the next 11 bits of the keys that share it, and so on until the shift
 // is 0 (at most three passes; scores of one magnitude need two).  That spreads scores of similar size, which the top
-// bits of the key would put into one or two bins; equal scores find four counters per bin.
+// bits of the key would put into one or two bins; equal scores find four counters per bin, and the lowest are not counted at all.
 // Bound by instructions issued on one CU and by the chain of barriers.  Measured, indices alone / with every output (before:
 // keys in LDS, digits at fixed bits, a contiguous run of elements per thread): 4096 scores 10.0 / 11.4 -> 6.9 / 7.1 us, 17550
-// 20.0 / 40.2 -> 12.8 / 15.5, 32768 30.1 / 77.7 -> 21.4 / 26.3; scores in {0, 1, 2} 17550 25.2 / 45.2 -> 20.3 / 23.0.  A run-time
-// count of elements per thread took 18.1 / 20.5 at 17550, eight copies of the histogram side by side 20.5 / 23.5.
+// 20.0 / 40.2 -> 12.8 / 15.5, 32768 30.1 / 77.7 -> 21.4 / 26.3; 17550 scores, 70 % of them 0, 22.7 / 42.3 -> 15.0 / 17.4 (with the
+// lowest counted 20.8 / 23.2), 25000, nearly all 0, 28.3 / 58.2 -> 19.7 / 23.4 (32.5 / 36.1), 17550 half 1 and half -1 24.4 / 44.6 ->
+// 19.5 / 22.0.  A run-time count of elements per thread took 18.1 / 20.5 at 17550, eight copies of the histogram side by side
+// 20.5 / 23.5; a digit that many lanes share counted by ballot cost all other distributions 0.5 us.
 constexpr int kSmallMax = 32768;
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / kWave;
-constexpr int kCopies = 4;          // of the histogram, by lane: equal digits of a wave meet 16 to a counter instead of 64
-constexpr int kCopyPitch = kBins + 16;       // their counters in different banks
+constexpr int kCopyPitch = kBins + 16;       // of the histogram's copies: their counters lie in different banks
 
 template <int ITEMS>
 __global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(const float *__restrict__ score, int32_t N, uint32_t k,
@@ -322,6 +323,9 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(const float *
                                                                    uint8_t *__restrict__ sel_mask,
                                                                    int32_t *__restrict__ skip_count)
 {
+    // copies of the histogram, by lane: equal digits of a wave meet 16 (32) to a counter instead of 64; few scores pay more for
+    // clearing and reading four than they gain (50 scores 6.85 us with four, 6.45 with two)
+    constexpr int kCopies = ITEMS == 2 ? 2 : 4;
     __shared__ __attribute__((aligned(16))) uint32_t hist[kCopyPitch * kCopies];
     __shared__ uint32_t wt_a[kSmallWaves], wt_b[kSmallWaves];
     __shared__ uint32_t s_base, s_krem;
@@ -371,10 +375,12 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(const float *
         for (;;) {
             const int width = last ? 32 - __builtin_clz(last) : 0;
             const int shift = width > 11 ? width - 11 : 0;
+            // Keys equal to the lowest of the range are not counted (the walk below ends at them anyway): often many tokens share
+            // the lowest score, and all their atomics would meet on the counters of one bin.
 #pragma unroll
             for (int j = 0; j < ITEMS; ++j) {
                 const uint32_t off = key[j] - base;
-                if (off <= last) atomicAdd(&mine[off >> shift], 1u);
+                if (off - 1 < last) atomicAdd(&mine[off >> shift], 1u);
             }
             __syncthreads();
             // the digit: walking the bins from the largest down, the first whose running count reaches k_rem.
@@ -388,6 +394,7 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(const float *
                 c1 += u.x;
                 c0 += u.y;
             }
+            if (tid == kSmallThreads - 1) c1 += k_rem;          // bin 0, with the uncounted keys: the last resort
             uint32_t incl = c0 + c1;
 #pragma unroll
             for (int d = 1; d < kWave; d <<= 1) {

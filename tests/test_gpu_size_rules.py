@@ -281,7 +281,7 @@ def test_attn_f32_non_finite_inputs_stay_in_their_rows_and_head_dims(d):
 # top-k in one workgroup: an even number of elements per thread up to 32768 scores, wave w owning a contiguous range; passes
 # over the bits in which the keys differ.  Whole numbers, exact.
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 1025, 2047, 2048, 2049, 4096, 4097, 18431, 18432, 18433, 30720, 30721, 32768, 32769])
-@pytest.mark.parametrize("kind", ["narrow", "ties", "equal", "extremes"])
+@pytest.mark.parametrize("kind", ["narrow", "ties", "equal", "extremes", "zeros"])
 def test_topk_sizes(n, kind):
     g = torch.Generator().manual_seed(n)
     s = 5.54 + 0.1 * torch.randn(n, generator=g)
@@ -290,12 +290,14 @@ def test_topk_sizes(n, kind):
     elif kind == "equal":
         s = torch.full((n,), -0.0)
         s[n // 2:] = 0.0                                      # -0 and +0 are the same score
+    elif kind == "zeros":                                     # the lowest score shared by most: thresholds above it and at it
+        s[torch.rand(n, generator=g) < 0.8] = 0.0
     elif kind == "extremes":
         special = torch.tensor([math.inf, -math.inf, math.nan, 3.4e38, -3.4e38, 1e-45, -1e-45, 0.0, -0.0])
         pick = torch.rand(n, generator=g) < 0.4
         s[pick] = special[torch.randint(0, 9, (int(pick.sum()),), generator=g)]
     skip0 = torch.randint(0, 9, (n,), generator=g).to(torch.int32)
-    for k in sorted({0, 1, n // 3, n - 1, n}):
+    for k in sorted({0, 1, n // 10, n // 3, n - 1, n}):
         e_idx, e_rest, e_mask = oracle.topk(s.numpy(), k)
         idx, rest, skip = (torch.full((n + 1,), -7, dtype=torch.int32, device=DEV) for _ in range(3))
         mask = torch.full((n + 1,), 9, dtype=torch.uint8, device=DEV)
