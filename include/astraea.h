@@ -221,7 +221,9 @@ int astraea_kv_refresh(void *k_cache, void *v_cache, const void *k_new, const vo
  *   act      ASTRAEA_ACT_NONE, or ASTRAEA_ACT_GELU_TANH: 0.5 t (1 + tanh(sqrt(2/pi) (t + 0.044715 t^3))).
  * BF16: bf16 MFMA, fp32 accumulation, bias and activation in fp32, one rounding to bf16; x and w must
  * each span less than 4 GiB.  F32: fp32 in, out and accumulated; products on fp32 MFMA or, in
- * larger tiles, of fp16 halves as in the attention.  Both: c_in a multiple of 64, c_out a
+ * larger tiles, of the operands' three bf16 parts, which hold every fp32 number below 2^112 whole: six products of parts for
+ * one of numbers, off by less than 2^-23 of it.  A tile with a sum that is not finite there (infinities, NaN, results from 2^96)
+ * is done again on fp32 MFMA.  Either way a row depends on no other row.  Both: c_in a multiple of 64, c_out a
  * multiple of 8, strides multiples of 8 elements, pointers 16-byte aligned.
  * idx_sel (distinct, in [0, N)) is required unless both sides are compact.  No workspace.
  * k_sel == 0 enqueues nothing.

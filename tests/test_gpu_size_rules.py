@@ -94,10 +94,9 @@ def test_linear_f32_operand_past_4_gib(k, c_out, tile):
     assert (y.double() - x[n - k:].double() @ w.double().T).abs().max().item() <= 1e-4
 
 
-# fp32 linear on fp16 halves (tiles of 128, of 64 in more than one round or past 1024 deep): an operand is scaled by its first two
-# stages; zeros at its start, growth past what that leaves room for, magnitudes at the ends of the range and infinities go to
-# the fp32 products.  Bound, of the sum of magnitudes: 2^-21 for the products (either operand is off by 2^-23, the product of second
-# halves, each at most 2^-11 of its operand, is left out) and 2^-24 for each rounding of the sum, three per 16 indices.
+# fp32 linear, magnitudes of a whole operand or of part of the contraction: zeros at its start, growth and fall along it, the ends of the
+# range, infinities, in tiles that form products of bf16 parts (128) and of fp32 numbers (64).  Bound, of the sum of magnitudes: 2^-21 for
+# the products and 2^-24 for each rounding of the sum, of which three per 16 indices are allowed here; either form stays below.
 @pytest.mark.parametrize("k,c_in,c_out,tile", [(705, 1088, 1096, 64), (2049, 128, 512, 64), (1000, 64, 4096, 128), (1001, 320, 3976, 128)])
 @pytest.mark.parametrize("values", ["plain", "w tiny", "x huge", "x grows", "x falls", "w starts at 0", "x is 0", "x inf"])
 def test_linear_f32_split_range(k, c_in, c_out, tile, values):
@@ -127,6 +126,47 @@ def test_linear_f32_split_range(k, c_in, c_out, tile, values):
     ref, size = x.double() @ w.double().T, x.double().abs() @ w.double().abs().T
     bound = (2.0 ** -21 + c_in * 3 / 16 * 2.0 ** -24) * size + 2.0 ** -140
     assert bool(((y.double() - ref).abs() <= bound).all()), ((y.double() - ref).abs() / bound).max().item()
+
+
+# fp32 linear, magnitudes that differ between rows, between channels and inside a row: each result stands on its own row and feature
+# alone.  Bound, elementwise, of the sum of magnitudes: 2^-22 for the products and 2^-24 for each rounding of the sum, eight per 16 indices.
+@pytest.mark.parametrize("k,c_in,c_out,tile", [(300, 128, 264, 32), (705, 1088, 1096, 64), (2049, 128, 512, 64), (1000, 64, 4096, 128), (1001, 320, 3976, 128)])
+@pytest.mark.parametrize("values", ["x rows", "w rows", "opposed", "outlier", "tiny x huge", "nan"])
+def test_linear_f32_spread_magnitudes(k, c_in, c_out, tile, values):
+    assert ab.astraea_linear_plan(ab.F32, k, c_in, c_out)["tile_tokens"] == tile
+    g = torch.Generator(device=DEV).manual_seed(k + c_in)
+    x, w = torch.randn(k, c_in, device=DEV, generator=g), torch.randn(c_out, c_in, device=DEV, generator=g)
+    fall = {m: 2.0 ** -(torch.arange(m, device=DEV) % 24).float() for m in (k, c_in, c_out)}
+    if values == "x rows":
+        x *= fall[k][:, None]
+    elif values == "w rows":
+        w *= fall[c_out][:, None]
+    elif values == "opposed":
+        x, w = x * fall[c_in], w / fall[c_in]
+    elif values == "outlier":
+        x[5] *= 2.0 ** 40
+        x[9, c_in - 1] = 2.0 ** 20
+        w[7, 3] = -2.0 ** 30
+    elif values == "tiny x huge":              # magnitudes near fp32's lowest, which lose bits in narrower parts
+        x, w = x * 2.0 ** -(100 + torch.arange(k, device=DEV) % 24).float()[:, None], w * 2.0 ** 100
+    elif values == "nan":
+        x[k // 2, c_in - 1] = math.nan
+    y = torch.full((k, c_out), math.inf, device=DEV)
+    ab.astraea_sparse_linear(x, w, None, None, k, y, x_is_compact=True, y_is_compact=True, N=k)
+    torch.cuda.synchronize()
+    if values == "nan":
+        assert bool(y[k // 2].isnan().all())
+        x[k // 2], y[k // 2] = 0.0, 0.0
+    ref, size = x.double() @ w.double().T, x.double().abs() @ w.double().abs().T
+    bound = (2.0 ** -22 + c_in / 2 * 2.0 ** -24) * size + 2.0 ** -140
+    assert bool(((y.double() - ref).abs() <= bound).all()), ((y.double() - ref).abs() / bound).max().item()
+    if values == "x rows":                     # ... and not on the rows that share its tile
+        grown = x * 2.0 ** 20
+        grown[3] = x[3]
+        z = torch.full_like(y, math.inf)
+        ab.astraea_sparse_linear(grown, w, None, None, k, z, x_is_compact=True, y_is_compact=True, N=k)
+        torch.cuda.synchronize()
+        assert torch.equal(z[3], y[3])
 
 
 # bf16 attention: 256 queries per workgroup, 32 per wave (rows pass through LDS whole, four at a time), 64 keys per tile; the
