@@ -22,8 +22,8 @@ if str(ROOT) not in sys.path:
     sys.path.insert(0, str(ROOT))
 
 METRIC = "selected-token attn TFLOP/s (% MFMA peak) + ms/layer, N=118800 H=24 D=128"
-# MI355X dense MFMA peaks; fp32 products are three products of fp16 halves, which the matrix unit takes at the bf16 rate
-PEAK_TFLOPS = {"bf16": 2500.0, "f32": 2500.0 / 3}
+# MI355X dense MFMA peaks; an fp32 product is six products of bf16 parts
+PEAK_TFLOPS = {"bf16": 2500.0, "f32": 2500.0 / 6}
 PEAK_HBM_GBS = 8000.0
 TRAFFIC_PROFILE = ROOT / "profiles" / "hot_path_cfg3_hbm_traffic_and_mfma.txt"
 _CSRC = ROOT / "paper_2506_05096_amd" / "csrc"

@@ -439,8 +439,8 @@ def test_attn_bf16_non_finite_values_stay_in_their_head_dims(k):
     assert torch.isfinite(o).all()
 
 
-# fp32 attention: tiles of 64 (d = 64) or 32 (d = 128) keys whose operands are split into fp16 halves, scaled by tile or query row
-# where their largest magnitude asks for it; out of that range the workgroup takes the fp32 products.  Edges of tiles and query blocks,
+# fp32 attention: tiles of 64 (d = 64) or 32 (d = 128) keys whose operands are split into bf16 parts; where a sum is not finite or K is
+# too large the workgroup takes the fp32 products.  Edges of tiles and query blocks,
 # then magnitudes: in K (its queries the other way, so that logits stay), in V, from tile to tile, zeros, an infinity.
 # fp64 on the device.  Bound: a logit is off by a few 2^-23 of |q| |k| scale, a result by that, relative, and a few 2^-23 of |V|.
 @pytest.mark.parametrize("n,h,d,k", [(1, 1, 64, 1), (63, 2, 64, 31), (64, 1, 64, 128), (65, 3, 64, 129), (257, 2, 64, 300),
@@ -479,6 +479,61 @@ def test_attn_f32_split_range(n, h, d, k, values):
     bound = 8 * 2.0 ** -23 * (1.0 + size.T[:, :, None]) * spread + 2.0 ** -140
     assert bool(((o.double() - exp).abs() <= bound).all()), ((o.double() - exp).abs() / bound).max().item()
     assert bool(((lse.double() - torch.logsumexp(logits, 2).T).abs() <= 8 * 2.0 ** -23 * (1.0 + size.T + lse.double().abs())).all())
+
+
+# fp32 attention, magnitudes that differ between keys, head-dims and tiles: V's head-dims, opposed head-dims of q and K, a huge key
+# that half the queries turn away from, huge values behind negligible weights, an outlier of V in another head-dim.
+# Bound, to first order: with s_n = scale sum_d |q_d k_nd|, a logit is off by a few 2^-23 s_n and its exponential's argument by a few 2^-23 of
+# itself; a result is off by that, weighted, and a few 2^-23 of the weighted |V|.
+@pytest.mark.parametrize("n,h,d,k", [(65, 2, 64, 129), (700, 8, 64, 60), (225, 2, 128, 130), (97, 1, 128, 300)])
+@pytest.mark.parametrize("values", ["v head-dims", "opposed", "huge key", "hidden values", "v outlier", "q rows", "k past range", "tiny scale", "nan"])
+def test_attn_f32_spread_magnitudes(n, h, d, k, values):
+    g = torch.Generator(device=DEV).manual_seed(n + h + d + k)
+    q, kc, vc = (torch.randn(m, h, d, device=DEV, generator=g) for m in (k, n, n))
+    fall = 2.0 ** -(torch.arange(d, device=DEV) % 24).float()
+    scale = 1.0 / math.sqrt(d)
+    if values == "v head-dims":
+        vc *= fall
+    elif values == "opposed":
+        q, kc = q * fall, kc / fall
+    elif values == "huge key":
+        kc[n // 3] *= 2.0 ** 40
+        q[:, :, :] = torch.where(((q * kc[n // 3]).sum(2, keepdim=True) > 0), -q, q)
+        q[0] = 0.0
+    elif values == "hidden values":
+        q[:, :, 0] = 16.0
+        kc[:32, :, 0] = -8.0 / scale            # weights of e^-128 before the other logits, and 2^20 in V
+        vc[:32] *= 2.0 ** 20
+    elif values == "v outlier":
+        vc[n // 2, 0, 5] = 2.0 ** 40
+    elif values == "q rows":
+        q *= 2.0 ** -(torch.arange(k, device=DEV) % 24).float()[:, None, None]
+    elif values == "k past range":             # of the split: the fp32 products serve
+        q, kc = q * 2.0 ** -60, kc * 2.0 ** 60
+    elif values == "tiny scale":
+        q, kc, scale = q * 2.0 ** 35, kc * 2.0 ** 35, scale * 2.0 ** -70
+    elif values == "nan":
+        q[k // 2] = math.nan
+    ws = torch.empty(max(1, ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d)), dtype=torch.uint8, device=DEV)
+    o, lse = torch.full((k, h, d), math.inf, device=DEV), torch.full((k, h), math.inf, device=DEV)
+    ab.astraea_sparse_attn_fwd(q, kc, vc, None, k, o, scale, q_is_compact=True, lse_sel=lse, workspace=ws)
+    torch.cuda.synchronize()
+    if values == "nan":
+        assert bool(o[k // 2].isnan().all()) and bool(lse[k // 2].isnan().all())
+        q[k // 2] = 0.0
+    for i in range(h):
+        qd, kd, vd = q[:, i].double(), kc[:, i].double(), vc[:, i].double()
+        logits, s = qd @ kd.T.contiguous() * scale, qd.abs() @ kd.abs().T.contiguous() * scale
+        lse_ref = torch.logsumexp(logits, 1)
+        p = torch.softmax(logits, 1)
+        off = p * (1.0 + s + (lse_ref[:, None] - logits))                      # [k, n]
+        ref = p @ vd
+        bound = 8 * 2.0 ** -23 * (off @ vd.abs() + off.sum(1, keepdim=True) * ref.abs()) + 2.0 ** -140
+        err, lse_err, lse_bound = (o[:, i].double() - ref).abs(), (lse[:, i].double() - lse_ref).abs(), 8 * 2.0 ** -23 * (off.sum(1) + lse_ref.abs())
+        if values == "nan":
+            err[k // 2], lse_err[k // 2] = 0.0, 0.0
+        assert bool((err <= bound).all()), (err / bound).max().item()
+        assert bool((lse_err <= lse_bound).all()), (lse_err / lse_bound).max().item()
 
 
 # ... and of 128 features x 128 tokens where larger ones would leave most CUs without one: edges of the tile on both sides, ragged
