@@ -536,6 +536,21 @@ def test_attn_f32_spread_magnitudes(n, h, d, k, values):
         assert bool((lse_err <= lse_bound).all()), (lse_err / lse_bound).max().item()
 
 
+@pytest.mark.parametrize("n,h,d,k", [(1, 1, 64, 1), (65, 2, 64, 10), (700, 8, 64, 60), (33, 1, 128, 128), (97, 2, 128, 300)])
+def test_attn_f32_infinity_in_the_last_key(n, h, d, k):
+    """Rows past the last key fill its tile with weight 0: nothing of it may reach them."""
+    g = torch.Generator(device=DEV).manual_seed(n + d)
+    q, kc, vc = (torch.randn(m, h, d, device=DEV, generator=g) for m in (k, n, n))
+    vc[n - 1, 0, 3] = math.inf
+    ws = torch.empty(max(1, ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d)), dtype=torch.uint8, device=DEV)
+    o = torch.full((k, h, d), math.nan, device=DEV)
+    ab.astraea_sparse_attn_fwd(q, kc, vc, None, k, o, 1.0 / math.sqrt(d), q_is_compact=True, workspace=ws)
+    torch.cuda.synchronize()
+    assert bool((o[:, 0, 3] == math.inf).all())
+    o[:, 0, 3] = 0.0
+    assert bool(o.isfinite().all())
+
+
 # ... and of 128 features x 128 tokens where larger ones would leave most CUs without one: edges of the tile on both sides, ragged
 # features, one tile, and contractions that end anywhere in the ring of four stages.
 @pytest.mark.parametrize("n,k,c_in,c_out,gather,scatter,bias,act", [
