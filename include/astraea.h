@@ -150,7 +150,7 @@ int astraea_select_topk_static(const float *score, int64_t N, int64_t k, int32_t
  * a row's offset when a logit passes it by 6 powers of two.
  * Supported: (BF16, D = 128) on bf16 MFMA with fp32 softmax and accumulation;
  * (F32, D = 64 or 128) on bf16 MFMA, fp32 accumulation: every fp32 operand and probability is held whole as three
- * bf16 parts, and six products of parts are summed for one of numbers, off by less than 2^-23 of it.  Queries whose key range
+ * bf16 parts, and six products of parts are summed for one of numbers, off by at most 2^-24 of it.  Queries whose key range
  * holds infinities, NaN or sums that overflow, magnitudes of 2^44 and more in q or K, and scales below 2^-60 are computed on
  * fp32 MFMA.  k_sel == 0 enqueues nothing.
  * Pointers must be 16-byte aligned and strides multiples of 8 elements.
@@ -222,8 +222,8 @@ int astraea_kv_refresh(void *k_cache, void *v_cache, const void *k_new, const vo
  *   act      ASTRAEA_ACT_NONE, or ASTRAEA_ACT_GELU_TANH: 0.5 t (1 + tanh(sqrt(2/pi) (t + 0.044715 t^3))).
  * BF16: bf16 MFMA, fp32 accumulation, bias and activation in fp32, one rounding to bf16; x and w must
  * each span less than 4 GiB.  F32: fp32 in, out and accumulated; products on fp32 MFMA or, in
- * larger tiles, of the operands' three bf16 parts, which hold every fp32 number below 2^112 whole: six products of parts for
- * one of numbers, off by less than 2^-23 of it.  A tile with a sum that is not finite there (infinities, NaN, results from 2^96)
+ * larger tiles, of the operands' three bf16 parts, which hold every fp32 number below 2^111 whole: six products of parts for
+ * one of numbers, off by at most 2^-24 of it.  A tile with a sum that is not finite there (infinities, NaN, results from 2^96)
  * is done again on fp32 MFMA.  Beyond rounding a row depends on no other row.  Both: c_in a multiple of 64, c_out a
  * multiple of 8, strides multiples of 8 elements, pointers 16-byte aligned.
  * idx_sel (distinct, in [0, N)) is required unless both sides are compact.  No workspace.

@@ -1,8 +1,8 @@
 // fp32 products on the bf16 matrix instruction: an operand x is held as the sum of three bf16 numbers, b0 + b1 + b2, each the rest rounded
-// to nearest.  3 x 8 bits and bf16's exponents, which are fp32's, hold x 2^16 exactly for every |x| below 2^112, subnormal ones included;
+// to nearest.  3 x 8 bits and bf16's exponents, which are fp32's, hold x 2^16 exactly for every |x| below 2^111, subnormal ones included;
 // there is no scale that x would have to share with its neighbours.  A product is the sum of six of the nine products of parts,
-// b2 b0' + b1 b1' + b1 b0' + b0 b2' + b0 b1' + b0 b0', in fp32: with |b1| <= 2^-8 |x| and |b2| <= 2^-16 |x| the three left out come to
-// less than 2^-23 |x x'|, 2^-26 in the mean.  (The method: Henry, Tang and Heinecke, "Leveraging the bfloat16 artificial
+// b2 b0' + b1 b1' + b1 b0' + b0 b2' + b0 b1' + b0 b0', in fp32: with |b1| <= 2^-8 |x| and |b2| <= 2^-17 |x| the three left out come to
+// 2^-24 |x x'| at most (half a unit in the last place), 2^-27 in the mean.  (The method: Henry, Tang and Heinecke, "Leveraging the bfloat16 artificial
 // intelligence datatype for higher-precision computations", 2019.)
 // Larger numbers, infinities and NaN have parts whose sums are not finite: a tile with such a sum is done again with fp32 products.
 // (The matrix instruction takes subnormal parts and leaves subnormal sums as they are: checked on the card.)  Error of a dot product
