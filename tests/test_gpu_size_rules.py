@@ -38,7 +38,7 @@ def test_score_sizes(n, c, stride, dtype, mode):
 
 
 # fp32 linear: 128-, 64- or 32-wide tiles by an estimate of the rounds they leave (32: the four waves split the contraction, and
-# a 64-wide contraction leaves two of them without a stage); stages of 32 indices in a ring of four.  `tile` is what the
+# a 64-wide contraction leaves two of them without a stage); stages of 32 indices in a ring of four, 128: of 16 in pairs.  `tile` is what the
 # launch says it takes; each tile meets ragged rows and features and contractions that end inside the ring.  Bound: sums of c_in
 # products of size ~1/sqrt(c_in) in fp32, error below c_in * 2^-24 / sqrt(c_in) * 4 <= 1e-4 absolute at c_in <= 4096.
 @pytest.mark.parametrize("n,k,c_in,c_out,gather,scatter,bias,act,tile", [
@@ -460,7 +460,7 @@ def test_attn_f32_split_range(n, h, d, k, values):
         kc[: n // 2] = 0.0
         vc[n // 2:] = 0.0
         q[0] = 0.0
-    elif values == "inf" and n > 1:                    # not in the last key, which rows past it in a tile repeat with weight 0
+    elif values == "inf" and n > 1:                    # the last key has a test of its own
         vc[n // 2 - 1, 0, 3] = math.inf
     scale = 1.0 / math.sqrt(d)
     ws = torch.empty(max(1, ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d)), dtype=torch.uint8, device=DEV)
