@@ -151,7 +151,7 @@ int astraea_select_topk_static(const float *score, int64_t N, int64_t k, int32_t
  * Supported: (BF16, D = 128) on bf16 MFMA with fp32 softmax and accumulation;
  * (F32, D = 64 or 128) on bf16 MFMA, fp32 accumulation: every fp32 operand and probability is held whole as three
  * bf16 parts, and six products of parts are summed for one of numbers, off by at most 2^-24 of it.  Queries whose key range
- * holds infinities, NaN or sums that overflow, magnitudes of 2^44 and more in q or K, and scales below 2^-60 are computed on
+ * holds infinities, NaN or sums that overflow, magnitudes of 2^44 and more in q or K, and scales below 2^-94 are computed on
  * fp32 MFMA.  k_sel == 0 enqueues nothing.
  * Pointers must be 16-byte aligned and strides multiples of 8 elements.
  */

@@ -486,7 +486,7 @@ def test_attn_f32_split_range(n, h, d, k, values):
 # Bound, to first order: with s_n = scale sum_d |q_d k_nd|, a logit is off by a few 2^-23 s_n and its exponential's argument by a few 2^-23 of
 # itself; a result is off by that, weighted, and a few 2^-23 of the weighted |V|.
 @pytest.mark.parametrize("n,h,d,k", [(65, 2, 64, 129), (700, 8, 64, 60), (225, 2, 128, 130), (97, 1, 128, 300)])
-@pytest.mark.parametrize("values", ["v head-dims", "opposed", "huge key", "hidden values", "v outlier", "q rows", "k past range", "tiny scale", "nan"])
+@pytest.mark.parametrize("values", ["v head-dims", "opposed", "huge key", "hidden values", "v outlier", "q rows", "k past range", "tiny scale", "scale past range", "nan"])
 def test_attn_f32_spread_magnitudes(n, h, d, k, values):
     g = torch.Generator(device=DEV).manual_seed(n + h + d + k)
     q, kc, vc = (torch.randn(m, h, d, device=DEV, generator=g) for m in (k, n, n))
@@ -512,6 +512,8 @@ def test_attn_f32_spread_magnitudes(n, h, d, k, values):
         q, kc = q * 2.0 ** -60, kc * 2.0 ** 60
     elif values == "tiny scale":
         q, kc, scale = q * 2.0 ** 35, kc * 2.0 ** 35, scale * 2.0 ** -70
+    elif values == "scale past range":
+        q, kc, scale = q * 2.0 ** 50, kc * 2.0 ** 50, scale * 2.0 ** -100
     elif values == "nan":
         q[k // 2] = math.nan
     ws = torch.empty(max(1, ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d)), dtype=torch.uint8, device=DEV)
