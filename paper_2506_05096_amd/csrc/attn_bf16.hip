@@ -38,6 +38,8 @@
 //    sweep the keys together; K/V tiles are then served from that XCD's L2.
 //  * the two waves that share a SIMD alternate: while one runs the MFMAs of a tile the other runs
 //    the exponentials of its own tile, so the matrix pipe and the VALU work at the same time.
+//  * few or short work items run in workgroups of four waves instead of eight: halves of an item each on a CU of its own, or two
+//    on one CU, one of which stores or loads while the other sweeps.
 #include <type_traits>
 
 #include "gfx950.h"
@@ -47,8 +49,8 @@ namespace {
 
 
 constexpr int D = 128;
-constexpr int kWaves = 8;
-constexpr int kBq = 32 * kWaves;        // queries per workgroup
+constexpr int kGroupWaves = 4;          // one wave per SIMD
+constexpr int kBq = 256;                // queries per work item
 constexpr int kBk = 64;                 // keys per LDS tile
 constexpr int kRowBytes = D * 2;        // 256 B per key row, unpadded
 constexpr int kTileBytes = kBk * kRowBytes;          // 16 KiB
@@ -58,6 +60,7 @@ constexpr float kTau = 8.0f;            // exact form: lazy-rescale threshold, l
 constexpr float kRose = 0x1p8f;         // 2^kTau
 constexpr float kBig = 0x1p80f;         // fast form: after a final row sum above this the workgroup repeats its sweep in the exact form
 constexpr int kNumXcd = 8;
+constexpr int kCuPerXcd = 32;
 // The pre-pass costs a read and a write of V whatever the selection, direct V tiles half as many LDS reads again per key and
 // query.  Retiled against direct, same results, us: 608 queries x 2025 keys 38.5 / 32.2; 7020 x 512 64.5 / 60.0; 1755 x 17550
 // 376 / 344; 7020 x 17550 1323 / 1301; 17550 x 17550 3159 / 3151; 11880 x 118800 14315 / 14225; 35640 x 118800 41688 / 41906.
@@ -152,16 +155,16 @@ __device__ __forceinline__ bf16x4 lds_read_tr(uint32_t addr)
 // round) are each cut into `splits` key ranges of `tiles_per_split` tiles, run by as many workgroups,
 // whose unnormalised partial results are combined by merge_partials_kernel.  Execution time then
 // follows the number of selected tokens instead of the number of rounds.
+// All of it fits 32 bits (plan_attn refuses grids past 2^31), which spares a workgroup its 64-bit divisions.
 struct AttnSchedule {
-    int64_t items_per_xcd;
-    int64_t full_items;
-    int64_t tiles_per_split;
-    int32_t q_tiles;
-    int32_t splits;
+    uint32_t items_per_xcd;
+    uint32_t full_items;
+    uint32_t tiles_per_split;
+    uint32_t q_tiles;
+    uint32_t splits;
 };
 constexpr int kPartialFloats = kBq * D + 2 * kBq;    // O^T accumulators, then running max, then row sum
 constexpr int kMaxSharesPerXcd = 64;
-constexpr int kCuPerXcd = 32;
 
 constexpr int MFMA = 0x008, DSR = 0x100;
 #define SGB(mask, n) __builtin_amdgcn_sched_group_barrier(mask, n, 0)
@@ -176,40 +179,47 @@ constexpr int MFMA = 0x008, DSR = 0x100;
 
 // RETILED: V comes from the pre-pass's V^T tiles.  Otherwise its rows are copied as they lie, in the K tile's shape, and the
 // fragments are read through the transposing LDS read.
-template <bool RETILED>
-__global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
+// GROUPS: groups of four waves in a workgroup (half_workgroups).  2: an item's 256 queries, the groups taking turns at the matrix pipe.  1: half
+// an item's queries; two such workgroups share a CU.
+template <bool RETILED, int GROUPS>
+__global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_bf16_kernel(
     const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const void *__restrict__ v, int64_t N, int32_t H,
     int64_t q_stride_n, int64_t q_stride_h, int64_t kv_stride_n, int64_t kv_stride_h,
     const int32_t *__restrict__ idx_sel, int64_t k_sel, int q_is_compact, float scale_log2e,
     __bf16 *__restrict__ o_sel, int64_t o_stride_n, int o_scatter, float *__restrict__ lse_sel, AttnSchedule sch,
     float *__restrict__ partial)
 {
-    // [parity][K tile | V^T tile], 64 KiB, then 8 KiB per wave for its query rows and later its output rows; one
-    // 8-wave workgroup per CU (two waves per SIMD)
-    __shared__ __attribute__((aligned(1024))) char lds[2 * kBufBytes + kWaves * kRowsBytes];
-    __shared__ uint32_t wave_outgrew[kWaves];
+    constexpr int kWaves = GROUPS * kGroupWaves;
+    // [parity][K tile | V^T tile], 64 KiB, and 8 KiB per wave for its query rows and later its output rows: behind the tiles for one
+    // 8-wave workgroup per CU; from the second V tile's place on for two 4-wave ones, whose 160 KiB are the CU's whole LDS
+    constexpr uint32_t kRowsAt = GROUPS == 2 ? 2 * kBufBytes : kBufBytes + kTileBytes;
+    __shared__ __attribute__((aligned(1024))) char lds[kRowsAt + kWaves * kRowsBytes + (GROUPS == 2 ? 64 : 0)];
+    // one word per wave; the first K tile's place is free when they are used
+    uint32_t *const wave_outgrew = reinterpret_cast<uint32_t *>(lds + (GROUPS == 2 ? sizeof(lds) - 64 : 0));
 
     const int64_t ntiles = (N + kBk - 1) / kBk;
-    const int64_t total_items = (int64_t)H * sch.q_tiles;
-    const int64_t xcd = blockIdx.x % kNumXcd, slot = blockIdx.x / kNumXcd;
-    int64_t item, tile_begin = 0, tile_end = ntiles, pslot = -1;
-    if (slot < sch.full_items) {
-        item = xcd * sch.items_per_xcd + slot;
-    } else {
-        const int64_t p = slot - sch.full_items, li = p / sch.splits, sp = p % sch.splits;
+    const uint32_t total_items = (uint32_t)H * sch.q_tiles;
+    const uint32_t xcd = blockIdx.x % kNumXcd, slot = blockIdx.x / (kNumXcd * (2 / GROUPS));
+    uint32_t item = xcd * sch.items_per_xcd + slot;
+    int64_t tile_begin = 0, tile_end = ntiles, pslot = -1;
+    if (slot >= sch.full_items) {
+        const uint32_t p = slot - sch.full_items, li = p / sch.splits, sp = p - li * sch.splits;
         item = xcd * sch.items_per_xcd + sch.full_items + li;
-        tile_begin = sp * sch.tiles_per_split;
+        tile_begin = (int64_t)sp * sch.tiles_per_split;
         tile_end = tile_begin + sch.tiles_per_split < ntiles ? tile_begin + sch.tiles_per_split : ntiles;
-        pslot = (xcd * (sch.items_per_xcd - sch.full_items) + li) * sch.splits + sp;
+        pslot = (int64_t)(xcd * (sch.items_per_xcd - sch.full_items) + li) * sch.splits + sp;
     }
     if (item >= (xcd + 1) * sch.items_per_xcd || item >= total_items) return;
     const int head = (int)(item / sch.q_tiles);
-    const int64_t qt = item % sch.q_tiles;
+    const int64_t qt = item - (uint32_t)head * sch.q_tiles;
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int qc = lane & 31, hf = lane >> 5;
-    const int64_t r0 = qt * kBq + wave * 32;
+    // the wave's place among the item's eight: a 4-wave workgroup takes one half of them
+    const int iwave = GROUPS == 2 ? wave : wave + (blockIdx.x / kNumXcd & 1) * kGroupWaves;
+    const int64_t r0 = qt * kBq + iwave * 32;
+    if (GROUPS == 1 && r0 - wave * 32 >= k_sel) return;
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
 
     floatx16 oacc[4];
@@ -270,11 +280,11 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
 
     const int grp = wave >> 2, wig = wave & 3;
     using W4 = std::integral_constant<int, 4>;
-    using W8 = std::integral_constant<int, 8>;
+    using WAll = std::integral_constant<int, kWaves>;
     auto first_tiles = [&]() __attribute__((always_inline)) {
-        dma_k_tile(tile_begin, 0, wave, W8{});
-        dma_v_tile(tile_begin, 0, wave, W8{});
-        if (tile_begin + 1 < tile_end) dma_k_tile(tile_begin + 1, 1, wave, W8{});
+        dma_k_tile(tile_begin, 0, wave, WAll{});
+        dma_v_tile(tile_begin, 0, wave, WAll{});
+        if (tile_begin + 1 < tile_end) dma_k_tile(tile_begin + 1, 1, wave, WAll{});
     };
     first_tiles();
 
@@ -285,7 +295,7 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
     auto lane_row = [&](int n) { return (int64_t)n < row_n ? r0 + n : k_sel - 1; };    // ragged tile: a valid row, never stored
     // an index outside [0, N) reads a valid row instead
     const int32_t q_row = q_is_compact ? 0 : clamp_row(idx_sel[lane_row(qc)], (int32_t)N);
-    const uint32_t rows_lds = lds0 + 2 * kBufBytes + wave * kRowsBytes;
+    const uint32_t rows_lds = lds0 + kRowsAt + wave * kRowsBytes;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int n = 4 * i + d_row;
@@ -296,6 +306,7 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
     bf16x8 qf[D / 16];
 #pragma unroll
     for (int s = 0; s < D / 16; ++s) qf[s] = lds_read_b128(rows_lds + qc * kRowBytes + (((2 * s + hf) ^ (qc & 15)) << 4));
+    if (GROUPS == 1) __builtin_amdgcn_s_waitcnt(0xc07f);         // lgkmcnt(0): past the next barrier a V tile may lie there
 
     // ---- LDS read offsets relative to a buffer pair; the buffer parity and the array's base are added where
     // the offsets are used (the tile loop is unrolled by two, so the parity is a compile-time constant there
@@ -476,29 +487,33 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
         if (!EXACT) m_c = tile_row_max();
         PHASE_BARRIER();
 
+        auto between_phases = [&]() __attribute__((always_inline)) {
+            if (GROUPS == 2) PHASE_BARRIER();
+            else __builtin_amdgcn_sched_barrier(0);
+        };
         // One tile that has a successor: VALU phase of tile j, then the MFMA phase (second product of tile j from
         // V buffer PAR, first product of tile j+1 from K buffer PAR ^ 1).
         auto tile_step = [&](int64_t j, auto par_tag) __attribute__((always_inline)) {
             constexpr int PAR = decltype(par_tag)::value;
-            if (grp == 1) {
+            if (GROUPS == 1 || grp == 1) {
                 dma_v_tile(j + 1, PAR ^ 1, wig, W4{});
                 if (j + 2 < tile_end) dma_k_tile(j + 2, PAR, wig, W4{});
             }
             softmax_tile(j, exact_tag);
-            PHASE_BARRIER();
+            between_phases();
             // The wave in its MFMA phase gets issue priority over its SIMD neighbour, which is in its VALU phase.
             __builtin_amdgcn_s_setprio(3);
             mfma_phase(std::true_type{}, par_tag);
             __builtin_amdgcn_s_setprio(0);
-            if (grp == 1) wait_dma();
+            if (GROUPS == 1 || grp == 1) wait_dma();
             PHASE_BARRIER();
         };
         // last tile: no next tile to prefetch or to start
         auto last_step = [&](int64_t j, auto par_tag) __attribute__((always_inline)) {
             softmax_tile(j, exact_tag);
-            PHASE_BARRIER();
+            between_phases();
             mfma_phase(std::false_type{}, par_tag);
-            PHASE_BARRIER();
+            if (GROUPS == 2) PHASE_BARRIER();
         };
         // the loop is unrolled by two so that the buffer parity is a constant in each copy
         int64_t j = tile_begin;
@@ -512,7 +527,7 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
         } else {
             last_step(j, P0{});
         }
-        if (grp == 0) PHASE_BARRIER();
+        if (GROUPS == 2 && grp == 0) PHASE_BARRIER();
     };
     sweep(std::false_type{});
     float l_tot = xhalf_sum(l_run);
@@ -536,6 +551,7 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) any |= wave_outgrew[w];
     if (__builtin_amdgcn_readfirstlane(any) != 0) {
+        if (GROUPS == 1) __syncthreads();            // every wave has read the words that the first tile is about to replace
         first_tiles();
         wait_dma();
         sweep(std::true_type{});
@@ -546,12 +562,12 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void attn_bf16_kernel(
         // merge_partials_kernel combines the shares.  The accumulators are stored as they lie, [wave][b][g][lane][4]:
         // whole lines, where rows of head-dim would put 16 bytes on each of 64 lines.
         float *pp = partial + pslot * kPartialFloats;
-        const int row = wave * 32 + qc;
+        const int row = iwave * 32 + qc;
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
             for (int g = 0; g < 4; ++g)
-                *reinterpret_cast<float4 *>(pp + (((wave * 4 + b) * 4 + g) * kWave + lane) * 4) =
+                *reinterpret_cast<float4 *>(pp + (((iwave * 4 + b) * 4 + g) * kWave + lane) * 4) =
                     make_float4(oacc[b][4 * g], oacc[b][4 * g + 1], oacc[b][4 * g + 2], oacc[b][4 * g + 3]);
         if (hf == 0) {
             pp[kBq * D + row] = m_c;
@@ -601,24 +617,24 @@ __global__ __launch_bounds__(256) void merge_partials_kernel(const float *__rest
                                                              float *__restrict__ lse_sel)
 {
     __shared__ __attribute__((aligned(1024))) char rows[kRowsBytes];
-    const int64_t left = sch.items_per_xcd - sch.full_items;
-    const int64_t xcd = blockIdx.x / left, li = blockIdx.x % left;
-    const int64_t item = xcd * sch.items_per_xcd + sch.full_items + li;
-    if (item >= (xcd + 1) * sch.items_per_xcd || item >= (int64_t)H * sch.q_tiles) return;
+    const uint32_t left = sch.items_per_xcd - sch.full_items;
+    const uint32_t xcd = blockIdx.x / left;
+    const uint32_t item = xcd * sch.items_per_xcd + sch.full_items + (blockIdx.x - xcd * left);
+    if (item >= (xcd + 1) * sch.items_per_xcd || item >= (uint32_t)H * sch.q_tiles) return;
     const int head = (int)(item / sch.q_tiles);
-    const int64_t r0 = (item % sch.q_tiles) * kBq + 32 * blockIdx.y;
+    const int64_t r0 = (int64_t)(item - (uint32_t)head * sch.q_tiles) * kBq + 32 * blockIdx.y;
     if (r0 >= k_sel) return;
-    const float *base = partial + (xcd * left + li) * sch.splits * (int64_t)kPartialFloats;
+    const float *base = partial + blockIdx.x * sch.splits * (int64_t)kPartialFloats;
     const int lane = threadIdx.x & (kWave - 1), b = threadIdx.x / kWave;
     const int row = 32 * blockIdx.y + (lane & 31);
     float m_star = -INFINITY;
-    for (int s = 0; s < sch.splits; ++s) m_star = fmaxf(m_star, base[s * (int64_t)kPartialFloats + kBq * D + row]);
+    for (uint32_t s = 0; s < sch.splits; ++s) m_star = fmaxf(m_star, base[s * (int64_t)kPartialFloats + kBq * D + row]);
     floatx4 acc[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) acc[g] = floatx4{0.f, 0.f, 0.f, 0.f};
     float l = 0.0f;
 #pragma unroll 2
-    for (int s = 0; s < sch.splits; ++s) {
+    for (uint32_t s = 0; s < sch.splits; ++s) {
         const float *ps = base + s * (int64_t)kPartialFloats;
         const float w = exp2f(ps[kBq * D + row] - m_star);
         l += w * ps[kBq * D + kBq + row];
@@ -675,12 +691,10 @@ static double tail_us(int64_t left, int64_t s, int64_t ntiles)
 static bool plan_attn(int64_t N, int32_t H, int64_t k_sel, AttnSchedule &sch, int64_t &slots)
 {
     const int64_t ntiles = (N + kBk - 1) / kBk;
-    sch.q_tiles = (int32_t)((k_sel + kBq - 1) / kBq);
-    const int64_t total = (int64_t)sch.q_tiles * H;
-    sch.items_per_xcd = (total + kNumXcd - 1) / kNumXcd;
+    const int64_t q_tiles = (k_sel + kBq - 1) / kBq, items = (q_tiles * H + kNumXcd - 1) / kNumXcd;
     // Items that would run in a last, partly filled round are cut along the keys into `splits` shares each (up to 8
     // per item, 64 per XCD) where that is cheaper by the estimate below.
-    int64_t left = sch.items_per_xcd % kCuPerXcd;
+    int64_t left = items % kCuPerXcd;
     int64_t splits = 1;
     if (left > 0) {
         double best = tail_us(left, 1, ntiles);
@@ -697,11 +711,34 @@ static bool plan_attn(int64_t N, int32_t H, int64_t k_sel, AttnSchedule &sch, in
         left = 0;
         splits = 1;
     }
-    sch.full_items = sch.items_per_xcd - left;
-    sch.splits = (int32_t)splits;
-    sch.tiles_per_split = (ntiles + splits - 1) / splits;
-    slots = sch.full_items + left * splits;
+    slots = items - left + left * splits;
+    sch.q_tiles = (uint32_t)q_tiles;
+    sch.items_per_xcd = (uint32_t)items;
+    sch.full_items = (uint32_t)(items - left);
+    sch.splits = (uint32_t)splits;
+    sch.tiles_per_split = (uint32_t)((ntiles + splits - 1) / splits);
     return slots * kNumXcd <= 2147483647LL && ntiles <= 2147483647LL;
+}
+
+// Whether the plan's workgroups run as two of four waves each.  A 4-wave workgroup copies its own key tiles, so a CU with two of them
+// copies twice what one of eight waves does, and two waves on a SIMD meet as they come instead of taking turns: 3 - 5 % slower where the
+// sweep is most of the time and every CU has work.  It is the faster one
+//  * where every half gets a CU of its own (at most 32 per XCD): four waves with a CU to themselves sweep 8 tiles in 8.8 us, eight in 11;
+//  * in short sweeps of more than one round, where rows and results of one half move under the other's sweep, provided that the halves
+//    fill fewer rounds, that they are at most one to a CU in the last round, or that there are enough rounds for it not to matter.
+// Eight waves / four, us: 450 queries x 900 keys x 24 heads 23.5 / 20.2, 433 x 439 x 16 14.5 / 12.5, 1564 x 966 x 12 24.9 / 22.1, 1094 x 301 x 24
+// 13.0 / 11.4; two rounds and more: 36000 x 77 x 24 137 / 121, 8712 x 476 x 8 34.8 / 31.9, 2595 x 205 x 24 23.2 / 21.2, 12941 x 1227 x 16 144.5 /
+// 138.8; past the lines: 3060 x 390 x 12 15.8 / 16.4 (36 halves per XCD), 6382 x 2188 x 24 164 / 169 (35 tiles), 4234 x 445 x 24 33.5 / 34.5 and
+// 7020 x 512 x 24 56.6 / 57.0 (last rounds of 38 halves).
+static bool half_workgroups(int32_t H, int64_t k_sel, int64_t slots, const AttnSchedule &sch)
+{
+    constexpr int64_t kShort = 24;                 // key tiles
+    constexpr int64_t kRound = 2 * kCuPerXcd;      // halves of an XCD's round
+    const int64_t items = (k_sel + kBq / 2 - 1) / (kBq / 2) * H, all = items * (sch.full_items ? 1 : sch.splits);
+    if (slots <= kCuPerXcd) return all <= kNumXcd * kCuPerXcd;
+    const int64_t halves = (items + kNumXcd - 1) / kNumXcd, rounds = (halves + kRound - 1) / kRound;
+    return sch.splits == 1 && sch.tiles_per_split <= kShort && slots < (1 << 26) /* a grid of 2^30 at most */ &&
+           (rounds > 3 || rounds < (slots + kCuPerXcd - 1) / kCuPerXcd || (halves - 1) % kRound < kCuPerXcd);
 }
 
 int attn_bf16_plan(int64_t N, int32_t H, int64_t k_sel, int64_t plan[8])
@@ -754,7 +791,9 @@ int launch_attn_bf16_d128(const void *q, const void *k, const void *v, int64_t N
     char *vt = (char *)workspace;
     float *partial = (float *)(vt + vt_bytes(N, H));
     const bool retile = k_sel > kRetileRows;
-    dim3 grid((unsigned)(slots * kNumXcd)), block(kWaves * kWave);
+    const bool narrow = half_workgroups(H, k_sel, slots, sch);
+    const int groups = narrow ? 1 : 2;
+    dim3 grid((unsigned)(slots * kNumXcd * (2 / groups))), block(groups * kGroupWaves * kWave);
     const float c = scale * 1.44269504088896340736f;
     if (retile)
         hipLaunchKernelGGL(transpose_v_kernel, dim3((unsigned)ntiles, (unsigned)H), dim3(256), 0, stream, (const __bf16 *)v, N,
@@ -765,8 +804,10 @@ int launch_attn_bf16_d128(const void *q, const void *k, const void *v, int64_t N
                            o_stride_n, o_scatter, lse_sel, sch, partial);
     };
     kernel_timer_begin(stream);
-    if (retile) go(attn_bf16_kernel<true>, vt);
-    else go(attn_bf16_kernel<false>, v);
+    if (retile && narrow) go(attn_bf16_kernel<true, 1>, vt);
+    else if (narrow) go(attn_bf16_kernel<false, 1>, v);
+    else if (retile) go(attn_bf16_kernel<true, 2>, vt);
+    else go(attn_bf16_kernel<false, 2>, v);
     kernel_timer_end(stream);
     if (left > 0)
         hipLaunchKernelGGL(merge_partials_kernel, dim3((unsigned)(left * kNumXcd), kBq / 32), dim3(256), 0, stream, partial, sch,

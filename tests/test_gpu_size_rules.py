@@ -215,6 +215,17 @@ def test_attn_bf16_tiles(n, h, k, hot, scatter, splits):
         assert torch.equal(out[keep], before[keep])
 
 
+# Workgroups of four waves, 128 queries: where every half of an item gets a CU of its own (up to 256 halves), and in sweeps of up to 24 key
+# tiles of more than 32 items per XCD.  Both sides of both lines, with rows that send a workgroup through its sweep again, a second
+# half without queries, and one key tile.
+@pytest.mark.parametrize("n,h,k,hot,scatter", [
+    (2048, 16, 2048, True, True), (2100, 16, 2049, True, True), (1536, 8, 8300, True, False), (1537, 8, 8300, True, False),
+    (60, 24, 3000, False, False), (65, 24, 2900, True, False), (500, 8, 128, True, True), (500, 8, 129, True, True), (64, 40, 1800, True, False),
+])
+def test_attn_bf16_half_workgroups(n, h, k, hot, scatter):
+    test_attn_bf16_tiles(n, h, k, hot, scatter, None)
+
+
 def _attn_rise_case(n, h, k, d, rise_nats, dtype, first_tile):
     """Logits near zero, except that those of the first key tile lie `rise_nats` lower."""
     g = torch.Generator(device=DEV).manual_seed(n + k + d)
