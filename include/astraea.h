@@ -181,6 +181,23 @@ int astraea_sparse_attn_update_fwd(const void *q, const void *k, const void *v, 
                                    void *workspace, size_t workspace_bytes, void *stream);
 
 /*
+ * astraea_sparse_attn_scatter_fwd - astraea_sparse_attn_fwd and, of its result, astraea_scatter_update(src_is_full = 0) as
+ * one operation: row r goes to o_sel[r] and to out_cache[idx_sel[r]], with the same bits, and no launch reads the compact
+ * rows again.
+ *   out_cache         [cache_rows, cache_row_stride] elements of dtype `dt`, rows not in idx_sel untouched; any alignment and
+ *                     stride that astraea_scatter_update takes, and it may share memory with q, k or v (the rows are then
+ *                     moved by a launch of their own).
+ *   idx_sel           required (distinct, in [0, cache_rows)), also when q_is_compact == 1; k_sel <= cache_rows.
+ * All other arguments, limits and the workspace are those of astraea_sparse_attn_fwd.
+ */
+int astraea_sparse_attn_scatter_fwd(const void *q, const void *k, const void *v, astraea_dtype dt, int64_t N, int32_t H,
+                                    int32_t D, int64_t q_stride_n, int64_t q_stride_h, int64_t kv_stride_n,
+                                    int64_t kv_stride_h, const int32_t *idx_sel, int64_t k_sel, int q_is_compact,
+                                    float softmax_scale, void *o_sel, void *out_cache, int64_t cache_rows,
+                                    int64_t cache_row_stride, float *lse_sel, void *workspace, size_t workspace_bytes,
+                                    void *stream);
+
+/*
  * astraea_scatter_update - cache merge (Algorithm 1 steps 6-7): rows listed in idx_sel
  * are overwritten, every other row keeps what it held (the reuse of cached results).
  *   src_is_full == 0: cache[idx_sel[r], :] = src[r, :]            (src is [k_sel, row_elems])

@@ -26,7 +26,7 @@ CROSSOVER_UNIFORM, CROSSOVER_BLOCK = 0, 1
 
 EXPORTS = (
     "astraea_score", "astraea_select_topk", "astraea_select_topk_static", "astraea_sparse_attn_fwd", "astraea_sparse_attn_update_fwd",
-    "astraea_scatter_update", "astraea_kv_refresh", "astraea_gather_rows", "astraea_sparse_linear", "astraea_workspace_bytes", "astraea_budget_to_k", "astraea_attn_flops",
+    "astraea_sparse_attn_scatter_fwd", "astraea_scatter_update", "astraea_kv_refresh", "astraea_gather_rows", "astraea_sparse_linear", "astraea_workspace_bytes", "astraea_budget_to_k", "astraea_attn_flops",
     "astraea_probe_mfma_bf16", "astraea_probe_copy", "astraea_probe_kernel_timer", "astraea_probe_kernel_count",
     "astraea_probe_kernel_ms", "astraea_lse_weight_update", "astraea_attn_plan", "astraea_linear_plan", "astraea_check_indices",
     "astraea_budget_search", "astraea_search_crossover", "astraea_search_mutate", "astraea_search_repair",
@@ -70,6 +70,9 @@ def lib() -> C.CDLL:
                                               C.c_int, f32, vp, vp, vp, sz, vp]
         L.astraea_sparse_attn_update_fwd.argtypes = [vp, vp, vp, C.c_int, i64, i32, i32, i64, i64, i64, i64, vp, i64,
                                                      C.c_int, f32, vp, i64, vp, vp, sz, vp]
+        L.astraea_sparse_attn_scatter_fwd.argtypes = [vp, vp, vp, C.c_int, i64, i32, i32, i64, i64, i64, i64, vp, i64,
+                                                      C.c_int, f32, vp, vp, i64, i64, vp, vp, sz, vp]
+        L.astraea_sparse_attn_scatter_fwd.restype = C.c_int
         L.astraea_scatter_update.argtypes = [vp, vp, C.c_int, i64, i64, i64, i64, vp, i64, C.c_int, vp]
         L.astraea_gather_rows.argtypes = [vp, vp, C.c_int, i64, i64, i64, i64, vp, i64, vp]
         L.astraea_kv_refresh.argtypes = [vp, vp, vp, vp, C.c_int, i64, i64, i64, i64, vp, i64, vp]
@@ -204,6 +207,21 @@ def astraea_sparse_attn_update_fwd(q: torch.Tensor, k: torch.Tensor, v: torch.Te
                                                 k.stride(0), k.stride(1), _p(idx_sel), k_sel, 1 if q_is_compact else 0,
                                                 softmax_scale, _p(out_cache), out_cache.stride(0), _p(lse_sel),
                                                 _p(workspace), wsb, _stream()))
+
+
+def astraea_sparse_attn_scatter_fwd(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, idx_sel: torch.Tensor, k_sel: int,
+                                    o_sel: torch.Tensor, out_cache: torch.Tensor, softmax_scale: float,
+                                    q_is_compact: bool = False, lse_sel: Optional[torch.Tensor] = None,
+                                    workspace: Optional[torch.Tensor] = None) -> None:
+    N, H, D = k.shape
+    assert v.shape == k.shape and v.stride() == k.stride() and q.stride(2) == 1 and k.stride(2) == 1
+    assert q.dtype == k.dtype == v.dtype == o_sel.dtype == out_cache.dtype and o_sel.is_contiguous()
+    assert out_cache.dim() == 2 and out_cache.shape[1] == H * D and out_cache.stride(1) == 1
+    wsb = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    _check(lib().astraea_sparse_attn_scatter_fwd(_p(q), _p(k), _p(v), _dt(k), N, H, D, q.stride(0), q.stride(1),
+                                                 k.stride(0), k.stride(1), _p(idx_sel), k_sel, 1 if q_is_compact else 0,
+                                                 softmax_scale, _p(o_sel), _p(out_cache), out_cache.shape[0],
+                                                 out_cache.stride(0), _p(lse_sel), _p(workspace), wsb, _stream()))
 
 
 def astraea_scatter_update(cache: torch.Tensor, src: torch.Tensor, idx_sel: torch.Tensor, k_sel: int,

@@ -99,31 +99,30 @@ int astraea_select_topk_static(const float *score, int64_t N, int64_t k, int32_t
     return launch_select_topk(score, N, k, idx_sel, idx_remain, sel_mask, skip_count, scratch_ptr, (hipStream_t)stream);
 }
 
-// Shared body of the two attention entry points: `out` is either the compact [k_sel, H, D] result
-// (scatter == 0, row stride H*D) or the cached per-token buffer [N, out_stride_n] whose rows idx_sel
-// names are overwritten (scatter == 1).
+// Shared body of the attention entry points: out.rows is the compact [k_sel, H, D] result, out.cache the cached per-token buffer whose
+// rows idx_sel names are overwritten; one of them or both (update: only the cached one, and it has a row per key).
 static int sparse_attn_common(const char *fn, const void *q, const void *k, const void *v, astraea_dtype dt, int64_t N,
                               int32_t H, int32_t D, int64_t q_stride_n, int64_t q_stride_h, int64_t kv_stride_n,
                               int64_t kv_stride_h, const int32_t *idx_sel, int64_t k_sel, int q_is_compact,
-                              float softmax_scale, void *out, int64_t out_stride_n, int scatter, float *lse_sel,
-                              void *workspace, size_t workspace_bytes, void *stream)
+                              float softmax_scale, const AttnOut &out, bool update, float *lse_sel, void *workspace,
+                              size_t workspace_bytes, void *stream)
 {
     if (!dtype_ok(dt)) return fail(ASTRAEA_ERR_UNSUPPORTED, "%s: unknown dtype %d", fn, (int)dt);
     if (N <= 0 || N > kMaxTokens) return fail(ASTRAEA_ERR_INVALID, "%s: N=%lld out of range", fn, (long long)N);
     if (H <= 0 || H > 65535) return fail(ASTRAEA_ERR_INVALID, "%s: H=%d out of range", fn, (int)H);
-    if (k_sel < 0 || k_sel > kMaxTokens || ((!q_is_compact || scatter) && k_sel > N))
+    if (k_sel < 0 || k_sel > kMaxTokens || ((!q_is_compact || update) && k_sel > N))
         return fail(ASTRAEA_ERR_INVALID, "%s: k_sel=%lld out of range", fn, (long long)k_sel);
     if (!(dt == ASTRAEA_BF16 && D == 128) && !(dt == ASTRAEA_F32 && (D == 64 || D == 128)))
         return fail(ASTRAEA_ERR_UNSUPPORTED, "%s: no kernel for dtype %d with head_dim %d", fn, (int)dt, (int)D);
     if (!(softmax_scale > 0.0f) || !std::isfinite(softmax_scale))
         return fail(ASTRAEA_ERR_INVALID, "%s: softmax_scale must be positive and finite", fn);
-    if (scatter && (out_stride_n < (int64_t)H * D || out_stride_n % 8 != 0))
+    if (update && (out.cache_stride < (int64_t)H * D || out.cache_stride % 8 != 0))
         return fail(ASTRAEA_ERR_INVALID, "%s: cache_row_stride must be a multiple of 8 and at least H*D", fn);
     if (k_sel == 0) return ASTRAEA_OK;
-    if (!q || !k || !v || !out) return fail(ASTRAEA_ERR_INVALID, "%s: NULL tensor", fn);
-    if ((!q_is_compact || scatter) && !idx_sel)
+    if (!q || !k || !v || !(out.rows || out.cache)) return fail(ASTRAEA_ERR_INVALID, "%s: NULL tensor", fn);
+    if ((!q_is_compact || out.cache) && !idx_sel)
         return fail(ASTRAEA_ERR_INVALID, "%s: idx_sel is required to gather queries or to place rows", fn);
-    if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out) % 16 != 0)
+    if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out.rows | (uintptr_t)out.cache) % 16 != 0)
         return fail(ASTRAEA_ERR_INVALID, "%s: q, k, v and the output must be 16-byte aligned", fn);
     if (((uintptr_t)idx_sel | (uintptr_t)lse_sel) % 4 != 0)
         return fail(ASTRAEA_ERR_INVALID, "%s: idx_sel / lse_sel must be 4-byte aligned", fn);
@@ -136,10 +135,9 @@ static int sparse_attn_common(const char *fn, const void *q, const void *k, cons
         return fail(ASTRAEA_ERR_WORKSPACE, "%s: workspace must be 256-byte aligned and >= %zu bytes", fn, need);
     if (dt == ASTRAEA_BF16)
         return launch_attn_bf16_d128(q, k, v, N, H, q_stride_n, q_stride_h, kv_stride_n, kv_stride_h, idx_sel, k_sel,
-                                     q_is_compact, softmax_scale, out, out_stride_n, scatter, lse_sel, workspace,
-                                     (hipStream_t)stream);
+                                     q_is_compact, softmax_scale, out, lse_sel, workspace, (hipStream_t)stream);
     return launch_attn_f32(q, k, v, N, H, D, q_stride_n, q_stride_h, kv_stride_n, kv_stride_h, idx_sel, k_sel,
-                           q_is_compact, softmax_scale, out, out_stride_n, scatter, lse_sel,
+                           q_is_compact, softmax_scale, out, lse_sel,
                            (uintptr_t)workspace % 256 == 0 ? workspace : nullptr, workspace_bytes, (hipStream_t)stream);
 }
 
@@ -150,7 +148,7 @@ int astraea_sparse_attn_fwd(const void *q, const void *k, const void *v, astraea
                             size_t workspace_bytes, void *stream)
 {
     return sparse_attn_common("astraea_sparse_attn_fwd", q, k, v, dt, N, H, D, q_stride_n, q_stride_h, kv_stride_n,
-                              kv_stride_h, idx_sel, k_sel, q_is_compact, softmax_scale, o_sel, (int64_t)H * D, 0,
+                              kv_stride_h, idx_sel, k_sel, q_is_compact, softmax_scale, AttnOut{o_sel, nullptr, 0, 0}, false,
                               lse_sel, workspace, workspace_bytes, stream);
 }
 
@@ -160,9 +158,9 @@ int astraea_sparse_attn_update_fwd(const void *q, const void *k, const void *v, 
                                    float softmax_scale, void *out_cache, int64_t cache_row_stride, float *lse_sel,
                                    void *workspace, size_t workspace_bytes, void *stream)
 {
-    return sparse_attn_common("astraea_sparse_attn_update_fwd", q, k, v, dt, N, H, D, q_stride_n, q_stride_h,
-                              kv_stride_n, kv_stride_h, idx_sel, k_sel, q_is_compact, softmax_scale, out_cache,
-                              cache_row_stride, 1, lse_sel, workspace, workspace_bytes, stream);
+    return sparse_attn_common("astraea_sparse_attn_update_fwd", q, k, v, dt, N, H, D, q_stride_n, q_stride_h, kv_stride_n,
+                              kv_stride_h, idx_sel, k_sel, q_is_compact, softmax_scale,
+                              AttnOut{nullptr, out_cache, cache_row_stride, N}, true, lse_sel, workspace, workspace_bytes, stream);
 }
 
 int astraea_sparse_linear(const void *x, const void *w, const void *bias, astraea_dtype dt, int64_t N, int64_t c_in,
@@ -242,6 +240,39 @@ int astraea_kv_refresh(void *k_cache, void *v_cache, const void *k_new, const vo
     const int64_t es = (int64_t)esize(dt);
     return launch_move_rows(k_cache, k_new, row_elems * es, cache_row_stride * es, src_row_stride * es, idx_sel, k_sel, N,
                             true, true, (hipStream_t)stream, v_cache, v_new);
+}
+
+// Whether [a, a + a_elems) and [b, b + b_elems), counted in elements of es bytes, share a byte.
+static bool overlap(const void *a, int64_t a_elems, const void *b, int64_t b_elems, int64_t es)
+{
+    return (uintptr_t)a < (uintptr_t)b + (uint64_t)(b_elems * es) && (uintptr_t)b < (uintptr_t)a + (uint64_t)(a_elems * es);
+}
+
+int astraea_sparse_attn_scatter_fwd(const void *q, const void *k, const void *v, astraea_dtype dt, int64_t N, int32_t H,
+                                    int32_t D, int64_t q_stride_n, int64_t q_stride_h, int64_t kv_stride_n,
+                                    int64_t kv_stride_h, const int32_t *idx_sel, int64_t k_sel, int q_is_compact,
+                                    float softmax_scale, void *o_sel, void *out_cache, int64_t cache_rows,
+                                    int64_t cache_row_stride, float *lse_sel, void *workspace, size_t workspace_bytes,
+                                    void *stream)
+{
+    const char *fn = "astraea_sparse_attn_scatter_fwd";
+    const int64_t row = (int64_t)H * D;
+    int rc = check_rows(fn, out_cache, o_sel, dt, cache_rows, row, cache_row_stride, row, idx_sel, k_sel);
+    if (rc != ASTRAEA_OK) return rc;
+    if (k_sel > 0 && !o_sel) return fail(ASTRAEA_ERR_INVALID, "%s: NULL tensor", fn);
+    // The kernel stores both in 16-byte pieces while other workgroups still read q, K and V: a cached buffer that is not aligned
+    // for that, or may share memory with one of them, gets its rows by a launch of its own.
+    const int64_t es = (int64_t)esize(dt), kv_elems = (N - 1) * kv_stride_n + (H - 1) * kv_stride_h + D;
+    const int64_t q_elems = ((q_is_compact ? k_sel : N) - 1) * q_stride_n + (H - 1) * q_stride_h + D;
+    const int64_t c_elems = (cache_rows - 1) * cache_row_stride + row;
+    const bool apart = (uintptr_t)out_cache % 16 != 0 || cache_row_stride % 8 != 0 || overlap(out_cache, c_elems, q, q_elems, es) ||
+                       overlap(out_cache, c_elems, k, kv_elems, es) || overlap(out_cache, c_elems, v, kv_elems, es);
+    rc = sparse_attn_common(fn, q, k, v, dt, N, H, D, q_stride_n, q_stride_h, kv_stride_n, kv_stride_h, idx_sel, k_sel, q_is_compact,
+                            softmax_scale, AttnOut{o_sel, apart ? nullptr : out_cache, cache_row_stride, cache_rows}, false, lse_sel,
+                            workspace, workspace_bytes, stream);
+    if (rc != ASTRAEA_OK || k_sel == 0 || !apart) return rc;
+    return launch_move_rows(out_cache, o_sel, row * es, cache_row_stride * es, row * es, idx_sel, k_sel, cache_rows, true, false,
+                            (hipStream_t)stream);
 }
 
 int astraea_gather_rows(const void *src, void *dst, astraea_dtype dt, int64_t N, int64_t row_elems,

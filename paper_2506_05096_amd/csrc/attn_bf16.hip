@@ -138,6 +138,15 @@ __device__ __forceinline__ uint4v rows_get(uint32_t rows_lds, int row, int chunk
     return __builtin_bit_cast(uint4v, lds_read_b128(rows_lds + row * kRowBytes + ((chunk ^ (row & 15)) << 4)));
 }
 
+// 16 bytes of result row r, which belongs to `token`: to wherever the caller asked for.
+__device__ __forceinline__ void store_row(const AttnOut &out, int32_t H, int head, int64_t r, int64_t token, int chunk, uint4v val, bool valid)
+{
+    const int64_t at = (int64_t)head * D + 8 * chunk;
+    if (out.rows && valid) *reinterpret_cast<uint4v *>(reinterpret_cast<__bf16 *>(out.rows) + r * H * D + at) = val;
+    if (out.cache && valid && (uint64_t)token < (uint64_t)out.cache_rows)
+        *reinterpret_cast<uint4v *>(reinterpret_cast<__bf16 *>(out.cache) + token * out.cache_stride + at) = val;
+}
+
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 // The transposing LDS read: of each 16 lanes, lane 4 r + c supplies elements 4 c .. 4 c + 3 of row r, and lane i gets element i of
 // the four rows.
@@ -186,8 +195,7 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
     const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const void *__restrict__ v, int64_t N, int32_t H,
     int64_t q_stride_n, int64_t q_stride_h, int64_t kv_stride_n, int64_t kv_stride_h,
     const int32_t *__restrict__ idx_sel, int64_t k_sel, int q_is_compact, float scale_log2e,
-    __bf16 *__restrict__ o_sel, int64_t o_stride_n, int o_scatter, float *__restrict__ lse_sel, AttnSchedule sch,
-    float *__restrict__ partial)
+    AttnOut out, float *__restrict__ lse_sel, AttnSchedule sch, float *__restrict__ partial)
 {
     constexpr int kWaves = GROUPS * kGroupWaves;
     // [parity][K tile | V^T tile], 64 KiB, and 8 KiB per wave for its query rows and later its output rows: behind the tiles for one
@@ -591,16 +599,12 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
             rows_put(rows_lds, b, g, el, o4);
         }
     __builtin_amdgcn_s_waitcnt(0xc07f);              // lgkmcnt(0): this wave's rows are in LDS; no other wave reads them
-    // compact output row r0 + n, or straight into the cached buffer's row of that token
-    const int32_t o_row = o_scatter ? idx_sel[lane_row(el & 31)] : 0;
+    const int32_t o_row = out.cache ? idx_sel[lane_row(el & 31)] : 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int n = 4 * i + (el >> 4);
-        const int64_t orow = o_scatter ? (int64_t)__shfl(o_row, n) : r0 + n;
-        const uint4v val = rows_get(rows_lds, n, (el & 15));
-        // a row index outside the cached buffer writes nothing
-        if ((int64_t)n < row_n && (!o_scatter || (uint64_t)orow < (uint64_t)N))
-            *reinterpret_cast<uint4v *>(o_sel + orow * o_stride_n + (int64_t)head * D + 8 * (el & 15)) = val;
+        const int64_t token = __shfl(o_row, n);
+        store_row(out, H, head, r0 + n, token, el & 15, rows_get(rows_lds, n, (el & 15)), (int64_t)n < row_n);
     }
     if (lse_sel && el < 32 && (int64_t)el < row_n)
         lse_sel[(r0 + el) * H + head] = (m_c + log2f(l_tot)) * 0.69314718055994530942f;
@@ -611,10 +615,8 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
 // O = sum_s w_s O_s / sum_s w_s l_s.  Workgroup (x, y) handles rows 32*y .. 32*y+31 of split item x, i.e. what wave y of
 // each share stored; its wave b takes head-dim 32*b .. 32*b+31.  Bound by reading the shares (4 KiB per wave and share).
 __global__ __launch_bounds__(256) void merge_partials_kernel(const float *__restrict__ partial, AttnSchedule sch,
-                                                             int32_t H, int64_t k_sel, int64_t n_rows,
-                                                             const int32_t *__restrict__ idx_sel, __bf16 *__restrict__ o_sel,
-                                                             int64_t o_stride_n, int o_scatter,
-                                                             float *__restrict__ lse_sel)
+                                                             int32_t H, int64_t k_sel, const int32_t *__restrict__ idx_sel,
+                                                             AttnOut out, float *__restrict__ lse_sel)
 {
     __shared__ __attribute__((aligned(1024))) char rows[kRowsBytes];
     const uint32_t left = sch.items_per_xcd - sch.full_items;
@@ -657,9 +659,7 @@ __global__ __launch_bounds__(256) void merge_partials_kernel(const float *__rest
         const int n = 16 * i + (threadIdx.x >> 4), c = threadIdx.x & 15;
         const int64_t rr = r0 + n;
         if (rr >= k_sel) break;
-        const int64_t orow = o_scatter ? (int64_t)idx_sel[rr] : rr;
-        if (!o_scatter || (uint64_t)orow < (uint64_t)n_rows)
-            *reinterpret_cast<uint4v *>(o_sel + orow * o_stride_n + (int64_t)head * D + 8 * c) = rows_get(rows_lds, n, c);
+        store_row(out, H, head, rr, out.cache ? idx_sel[rr] : 0, c, rows_get(rows_lds, n, c), true);
     }
     if (lse_sel && threadIdx.x < 32 && r0 + lane < k_sel)
         lse_sel[(r0 + lane) * H + head] = (m_star + log2f(l)) * 0.69314718055994530942f;
@@ -774,8 +774,7 @@ size_t attn_bf16_workspace_bytes(int64_t N, int32_t H)
 
 int launch_attn_bf16_d128(const void *q, const void *k, const void *v, int64_t N, int32_t H, int64_t q_stride_n,
                           int64_t q_stride_h, int64_t kv_stride_n, int64_t kv_stride_h, const int32_t *idx_sel,
-                          int64_t k_sel, int q_is_compact, float scale, void *o_sel, int64_t o_stride_n, int o_scatter,
-                          float *lse_sel, void *workspace,
+                          int64_t k_sel, int q_is_compact, float scale, const AttnOut &out, float *lse_sel, void *workspace,
                           hipStream_t stream)
 {
     if (k_sel == 0) return ASTRAEA_OK;
@@ -800,8 +799,8 @@ int launch_attn_bf16_d128(const void *q, const void *k, const void *v, int64_t N
                            kv_stride_n, kv_stride_h, ntiles, vt);
     auto go = [&](auto kernel, const void *vsrc) {
         hipLaunchKernelGGL(kernel, grid, block, 0, stream, (const __bf16 *)q, (const __bf16 *)k, vsrc, N, H, q_stride_n,
-                           q_stride_h, kv_stride_n, kv_stride_h, idx_sel, k_sel, q_is_compact, c, (__bf16 *)o_sel,
-                           o_stride_n, o_scatter, lse_sel, sch, partial);
+                           q_stride_h, kv_stride_n, kv_stride_h, idx_sel, k_sel, q_is_compact, c, out, lse_sel, sch,
+                           partial);
     };
     kernel_timer_begin(stream);
     if (retile && narrow) go(attn_bf16_kernel<true, 1>, vt);
@@ -811,7 +810,7 @@ int launch_attn_bf16_d128(const void *q, const void *k, const void *v, int64_t N
     kernel_timer_end(stream);
     if (left > 0)
         hipLaunchKernelGGL(merge_partials_kernel, dim3((unsigned)(left * kNumXcd), kBq / 32), dim3(256), 0, stream, partial, sch,
-                           H, k_sel, N, idx_sel, (__bf16 *)o_sel, o_stride_n, o_scatter, lse_sel);
+                           H, k_sel, idx_sel, out, lse_sel);
     return check_launch("astraea_sparse_attn_fwd(bf16)");
 }
 

@@ -57,17 +57,23 @@ struct LinearTile {
 LinearTile linear_bf16_tile(int64_t k_sel, int32_t c_in, int64_t c_out);
 int linear_f32_tile(int64_t k_sel, int64_t c_in, int64_t c_out);
 
+// Where the attention puts row r: rows[r] of a compact [k_sel, H * D] result, and row idx_sel[r] of a cached buffer of cache_rows rows.
+// Either may be null; an index outside the cached buffer writes nothing.
+struct AttnOut {
+    void *rows;
+    void *cache;
+    int64_t cache_stride, cache_rows;
+};
 size_t attn_bf16_workspace_bytes(int64_t N, int32_t H);
 int attn_bf16_plan(int64_t N, int32_t H, int64_t k_sel, int64_t plan[8]);
 int launch_attn_bf16_d128(const void *q, const void *k, const void *v, int64_t N, int32_t H, int64_t q_stride_n,
                           int64_t q_stride_h, int64_t kv_stride_n, int64_t kv_stride_h, const int32_t *idx_sel,
-                          int64_t k_sel, int q_is_compact, float scale, void *o_sel, int64_t o_stride_n, int o_scatter,
-                          float *lse_sel, void *workspace,
+                          int64_t k_sel, int q_is_compact, float scale, const AttnOut &out, float *lse_sel, void *workspace,
                           hipStream_t stream);
 int launch_attn_f32(const void *q, const void *k, const void *v, int64_t N, int32_t H, int32_t D, int64_t q_stride_n,
                     int64_t q_stride_h, int64_t kv_stride_n, int64_t kv_stride_h, const int32_t *idx_sel,
-                    int64_t k_sel, int q_is_compact, float scale, void *o_sel, int64_t o_stride_n, int o_scatter,
-                    float *lse_sel, void *workspace, size_t workspace_bytes, hipStream_t stream);
+                    int64_t k_sel, int q_is_compact, float scale, const AttnOut &out, float *lse_sel, void *workspace,
+                    size_t workspace_bytes, hipStream_t stream);
 size_t attn_f32_workspace_bytes(int64_t N, int32_t H, int32_t D, int64_t k_sel);
 
 }  // namespace astraea

@@ -3,7 +3,7 @@
 Order of the calls (paper, supplementary Algorithm 1; Sec. 3.2 execution flow):
 score -> select top-k -> refresh the cached K/V rows of the selected tokens ->
 attention of the selected queries over the full-length K/V (queries gathered
-in-kernel) -> scatter of the fresh outputs into the cached output buffer.
+in-kernel), whose fresh outputs also go into the cached output buffer.
 
 Host logic only: buffers are allocated once, k comes from the budget on the
 host, nothing is read back from the device between calls.
@@ -61,6 +61,17 @@ class LayerStep:
         E = self.H * self.D
         ab.astraea_scatter_update(t["out_cache"], self.o_sel.view(self.N, E), self.idx_sel, k, src_is_full=False)
 
+    def step_attn_scatter(self, t: Dict[str, torch.Tensor], k: int, lse: Optional[torch.Tensor] = None) -> None:
+        """step_attn and step_scatter: one call where neither is a subclass's own."""
+        cls = type(self)
+        if cls.step_attn is not LayerStep.step_attn or cls.step_scatter is not LayerStep.step_scatter:
+            self.step_attn(t, k) if lse is None else self.step_attn(t, k, lse=lse)
+            self.step_scatter(t, k)
+            return
+        ab.astraea_sparse_attn_scatter_fwd(t["q"], t["k_cache"], t["v_cache"], self.idx_sel, k, self.o_sel[:max(k, 1)],
+                                           t["out_cache"], self.scale, q_is_compact=False, lse_sel=lse,
+                                           workspace=self.attn_ws)
+
     def run(self, t: Dict[str, torch.Tensor], k: int) -> None:
         """The whole hot path for one batch of inputs; updates k_cache, v_cache and out_cache in place."""
         self.step_score(t)
@@ -69,8 +80,7 @@ class LayerStep:
         if self.fused_update:
             self.step_attn_update(t, k)
         else:
-            self.step_attn(t, k)
-            self.step_scatter(t, k)
+            self.step_attn_scatter(t, k)
 
 
 class StatefulLayer(LayerStep):
@@ -108,11 +118,9 @@ class StatefulLayer(LayerStep):
         self.step_kv_refresh(t, k)
         if self.fused_update:
             self.step_attn_update(t, k, lse=self.lse_sel[:max(k, 1)])
-            self.step_state(t, k)
         else:
-            self.step_attn(t, k, lse=self.lse_sel[:max(k, 1)])
-            self.step_state(t, k)
-            self.step_scatter(t, k)
+            self.step_attn_scatter(t, k, lse=self.lse_sel[:max(k, 1)])
+        self.step_state(t, k)
 
 
 class TokenSparseBlock(LayerStep):

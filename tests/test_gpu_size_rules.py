@@ -226,6 +226,39 @@ def test_attn_bf16_half_workgroups(n, h, k, hot, scatter):
     test_attn_bf16_tiles(n, h, k, hot, scatter, None)
 
 
+# The compact result and the cached rows from one call, against the two calls it stands for: whole and cut work items, both workgroup
+# sizes, cached buffers that the kernel writes itself and those that get a launch of their own (stride, alignment, memory shared with q).
+@pytest.mark.parametrize("dtype,n,h,d,k", [
+    (torch.bfloat16, 2025, 24, 128, 608), (torch.bfloat16, 300, 3, 128, 77), (torch.bfloat16, 300, 30, 128, 300),
+    (torch.float32, 700, 8, 64, 60), (torch.float32, 97, 2, 128, 97),
+])
+@pytest.mark.parametrize("cache", ["plain", "padded", "odd stride", "misaligned", "shares q"])
+def test_attn_result_and_cached_rows(dtype, n, h, d, k, cache):
+    g = torch.Generator(device=DEV).manual_seed(n + k)
+    e = h * d
+    both = torch.randn(n, 2, e, device=DEV, generator=g).to(dtype)
+    q = both[:, 0].view(n, h, d)
+    kc, vc = (torch.randn(n, h, d, device=DEV, generator=g).to(dtype) for _ in range(2))
+    base = both if cache == "shares q" else torch.randn((n + 3) * (e + 16), device=DEV, generator=g).to(dtype)
+
+    def view(b):
+        return {"plain": lambda: b[:n * e].view(n, e), "padded": lambda: b.view(n + 3, e + 16)[:, 8:8 + e],
+                "odd stride": lambda: b[:n * (e + 3)].view(n, e + 3)[:, :e], "misaligned": lambda: b[1:1 + n * e].view(n, e),
+                "shares q": lambda: b[:, 1]}[cache]()
+    idx = torch.randperm(n, device=DEV, generator=g)[:k].sort().values.to(torch.int32)
+    if cache == "padded":
+        idx[-1] = n + 7                                      # outside the keys and the cached buffer: writes nothing there
+    ws = torch.empty(max(ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d), 256), dtype=torch.uint8, device=DEV)
+    o0, lse0 = torch.empty(k, h, d, dtype=dtype, device=DEV), torch.empty(k, h, device=DEV)
+    o1, lse1 = torch.empty_like(o0), torch.empty_like(lse0)
+    want = base.clone()
+    ab.astraea_sparse_attn_fwd(q, kc, vc, idx, k, o0, d ** -0.5, lse_sel=lse0, workspace=ws)
+    ab.astraea_scatter_update(view(want), o0.view(k, e), idx, k)
+    ab.astraea_sparse_attn_scatter_fwd(q, kc, vc, idx, k, o1, view(base), d ** -0.5, lse_sel=lse1, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(o0, o1) and torch.equal(lse0, lse1) and torch.equal(base, want)
+
+
 def _attn_rise_case(n, h, k, d, rise_nats, dtype, first_tile):
     """Logits near zero, except that those of the first key tile lie `rise_nats` lower."""
     g = torch.Generator(device=DEV).manual_seed(n + k + d)
