@@ -357,6 +357,28 @@ def test_attn_f32_tiles(n, h, k, d, hot, scatter, pitch):
         assert torch.equal(out[keep], before[keep])
 
 
+# Workgroups of eight waves (256 queries, tiles staged a whole tile ahead): items whole, all cut along the keys, and cut only past the last whole
+# round (24 heads x 11 tiles of queries are 33 items per XCD); one to three key tiles, ragged last tiles of keys and queries, a workgroup
+# whose last four waves have no queries.  A workspace of the size named is not written past, and without one the result is the
+# same up to the order of the sums: 1e-5 as above.
+@pytest.mark.parametrize("n,h,k,d,hot,scatter", [
+    (4097, 8, 2047, 64, True, False), (600, 24, 2700, 64, True, False), (600, 24, 2699, 128, True, False), (257, 8, 6000, 64, False, False),
+    (33, 24, 2700, 64, True, False), (65, 24, 2690, 128, False, False), (1100, 16, 900, 128, True, True), (2100, 24, 1401, 64, False, True),
+    (150, 24, 5500, 64, True, False),
+])
+def test_attn_f32_eight_waves(n, h, k, d, hot, scatter):
+    test_attn_f32_tiles(n, h, k, d, hot, scatter, None)
+    g = torch.Generator(device=DEV).manual_seed(n)
+    q, kc, vc = (torch.randn(m, h, d, device=DEV, generator=g) for m in (k, n, n))
+    need = ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d)
+    ws = torch.full((need + 65536,), 170, dtype=torch.uint8, device=DEV)
+    a, b = torch.empty_like(q), torch.empty_like(q)
+    ab.astraea_sparse_attn_fwd(q, kc, vc, None, k, a, d ** -0.5, q_is_compact=True, workspace=ws[:need] if need else None)
+    ab.astraea_sparse_attn_fwd(q, kc, vc, None, k, b, d ** -0.5, q_is_compact=True)
+    torch.cuda.synchronize()
+    assert (a - b).abs().max().item() <= 1e-5 and bool((ws[need:] == 170).all())
+
+
 # Rows whose first key tile lies 45 nats below the rest: a fixed exponent offset would leave arguments of 65 to the
 # exponential (rounded by 2^-18: 1.5e-6 of a probability in the mean square) and 2^65 in the accumulators, which
 # values of 2^64 then overflow.  Values of 2^110 leave the accumulators seven bits above the largest sum of 1300.  Expected
