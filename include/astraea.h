@@ -252,6 +252,22 @@ int astraea_sparse_linear(const void *x, const void *w, const void *bias, astrae
                           void *stream);
 
 /*
+ * astraea_sparse_linear_group - up to three layers of the same input, sizes and activation (the Q, K and V projections) in one
+ * launch: the same as one astraea_sparse_linear call per entry of `parts`, in their order.  Their weights and results are separate
+ * buffers; a result that shares memory with x, a weight or another result is computed by a launch of its own.
+ */
+typedef struct {
+    const void *w;          /* [c_out, c_in] */
+    const void *bias;       /* [c_out] or NULL */
+    void *y;
+    int64_t y_row_stride;
+    int y_is_compact;
+} astraea_linear_part;
+int astraea_sparse_linear_group(const void *x, astraea_dtype dt, int64_t N, int64_t c_in, int64_t c_out, int64_t x_row_stride,
+                                const int32_t *idx_sel, int64_t k_sel, int x_is_compact, astraea_activation act,
+                                const astraea_linear_part *parts, int32_t n_parts, void *stream);
+
+/*
  * Token-budget search (Sec. 3.3 "Algorithm"; supplementary algorithm "Evolutionary Search for Token
  * Scheduling").  Host-only: no GPU work, every pointer is host memory.  A schedule is T int32 levels in
  * tenths, theta_i in 0..10 for 0 %..100 % of the tokens at timestep i; budget_tenths is the target sum and

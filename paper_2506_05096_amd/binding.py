@@ -26,7 +26,7 @@ CROSSOVER_UNIFORM, CROSSOVER_BLOCK = 0, 1
 
 EXPORTS = (
     "astraea_score", "astraea_select_topk", "astraea_select_topk_static", "astraea_sparse_attn_fwd", "astraea_sparse_attn_update_fwd",
-    "astraea_sparse_attn_scatter_fwd", "astraea_scatter_update", "astraea_kv_refresh", "astraea_gather_rows", "astraea_sparse_linear", "astraea_workspace_bytes", "astraea_budget_to_k", "astraea_attn_flops",
+    "astraea_sparse_attn_scatter_fwd", "astraea_scatter_update", "astraea_kv_refresh", "astraea_gather_rows", "astraea_sparse_linear", "astraea_sparse_linear_group", "astraea_workspace_bytes", "astraea_budget_to_k", "astraea_attn_flops",
     "astraea_probe_mfma_bf16", "astraea_probe_copy", "astraea_probe_kernel_timer", "astraea_probe_kernel_count",
     "astraea_probe_kernel_ms", "astraea_lse_weight_update", "astraea_attn_plan", "astraea_linear_plan", "astraea_check_indices",
     "astraea_budget_search", "astraea_search_crossover", "astraea_search_mutate", "astraea_search_repair",
@@ -39,6 +39,12 @@ class SearchConfig(C.Structure):
     _fields_ = [("T", C.c_int32), ("population", C.c_int32), ("children", C.c_int32), ("generations", C.c_int32),
                 ("budget_tenths", C.c_int64), ("p_mutation_start", C.c_double), ("p_mutation_final", C.c_double),
                 ("seed", C.c_uint64)]
+
+
+class LinearPart(C.Structure):
+    """astraea_linear_part"""
+    _fields_ = [("w", C.c_void_p), ("bias", C.c_void_p), ("y", C.c_void_p), ("y_row_stride", C.c_int64),
+                ("y_is_compact", C.c_int)]
 
 
 FITNESS_FN = C.CFUNCTYPE(C.c_double, C.POINTER(C.c_int32), C.c_int32, C.c_void_p)
@@ -80,6 +86,9 @@ def lib() -> C.CDLL:
         L.astraea_sparse_linear.argtypes = [vp, vp, vp, C.c_int, i64, i64, i64, i64, vp, i64, C.c_int, C.c_int, vp, i64,
                                             C.c_int, vp]
         L.astraea_sparse_linear.restype = C.c_int
+        L.astraea_sparse_linear_group.argtypes = [vp, C.c_int, i64, i64, i64, i64, vp, i64, C.c_int, C.c_int,
+                                                  C.POINTER(LinearPart), i32, vp]
+        L.astraea_sparse_linear_group.restype = C.c_int
         L.astraea_workspace_bytes.argtypes = [C.c_int, i64, i64, i32, i32]
         L.astraea_workspace_bytes.restype = sz
         L.astraea_budget_to_k.argtypes = [i64, i32]
@@ -263,6 +272,22 @@ def astraea_sparse_linear(x: torch.Tensor, w: torch.Tensor, bias: Optional[torch
     _check(lib().astraea_sparse_linear(_p(x), _p(w), _p(bias), _dt(x), N, w.shape[1], w.shape[0], x.stride(0),
                                        _p(idx_sel), k_sel, 1 if x_is_compact else 0, act, _p(y), y.stride(0),
                                        1 if y_is_compact else 0, _stream()))
+
+
+def astraea_sparse_linear_group(x: torch.Tensor, layers, idx_sel: Optional[torch.Tensor], k_sel: int, act: int = ACT_NONE,
+                                x_is_compact: bool = False, N: Optional[int] = None) -> None:
+    """astraea_sparse_linear of the same x for up to three layers (w, bias or None, y, y_is_compact) of one shape."""
+    c_out, c_in = layers[0][0].shape
+    assert x.dim() == 2 and x.stride(1) == 1 and x.shape[1] == c_in
+    for w, _, y, _ in layers:
+        assert w.shape == (c_out, c_in) and w.is_contiguous() and y.dim() == 2 and y.shape[1] == c_out and y.stride(1) == 1
+        assert x.dtype == w.dtype == y.dtype
+    if N is None:
+        N = x.shape[0] if not x_is_compact else next((y.shape[0] for _, _, y, compact in layers if not compact), max(k_sel, 1))
+    parts = (LinearPart * len(layers))(*[LinearPart(_p(w), _p(b), _p(y), y.stride(0), 1 if compact else 0)
+                                         for w, b, y, compact in layers])
+    _check(lib().astraea_sparse_linear_group(_p(x), _dt(x), N, c_in, c_out, x.stride(0), _p(idx_sel), k_sel,
+                                             1 if x_is_compact else 0, act, parts, len(layers), _stream()))
 
 
 def astraea_lse_weight_update(lse_sel: torch.Tensor, idx_sel: torch.Tensor, k_sel: int, lse_weight: torch.Tensor) -> None:

@@ -163,40 +163,85 @@ int astraea_sparse_attn_update_fwd(const void *q, const void *k, const void *v, 
                               AttnOut{nullptr, out_cache, cache_row_stride, N}, true, lse_sel, workspace, workspace_bytes, stream);
 }
 
-int astraea_sparse_linear(const void *x, const void *w, const void *bias, astraea_dtype dt, int64_t N, int64_t c_in,
-                          int64_t c_out, int64_t x_row_stride, const int32_t *idx_sel, int64_t k_sel,
-                          int x_is_compact, astraea_activation act, void *y, int64_t y_row_stride, int y_is_compact,
-                          void *stream)
+// Whether [a, a + a_bytes) and [b, b + b_bytes) share a byte.
+static bool overlap(const void *a, int64_t a_bytes, const void *b, int64_t b_bytes)
 {
-    const char *fn = "astraea_sparse_linear";
+    return (uintptr_t)a < (uintptr_t)b + (uint64_t)b_bytes && (uintptr_t)b < (uintptr_t)a + (uint64_t)a_bytes;
+}
+
+static int sparse_linear_common(const char *fn, const void *x, astraea_dtype dt, int64_t N, int64_t c_in, int64_t c_out,
+                                int64_t x_row_stride, const int32_t *idx_sel, int64_t k_sel, int x_is_compact,
+                                astraea_activation act, const astraea_linear_part *parts, int n_parts, void *stream)
+{
     if (!dtype_ok(dt)) return fail(ASTRAEA_ERR_UNSUPPORTED, "%s: unknown dtype %d", fn, (int)dt);
     if (act != ASTRAEA_ACT_NONE && act != ASTRAEA_ACT_GELU_TANH)
         return fail(ASTRAEA_ERR_UNSUPPORTED, "%s: unknown activation %d", fn, (int)act);
     if (N <= 0 || N > kMaxTokens) return fail(ASTRAEA_ERR_INVALID, "%s: N=%lld out of range", fn, (long long)N);
-    const bool indexed = !x_is_compact || !y_is_compact;
+    bool indexed = !x_is_compact;
+    for (int i = 0; i < n_parts; ++i) indexed = indexed || !parts[i].y_is_compact;
     if (k_sel < 0 || k_sel > kMaxTokens || (indexed && k_sel > N))
         return fail(ASTRAEA_ERR_INVALID, "%s: k_sel=%lld out of range", fn, (long long)k_sel);
     if (c_in <= 0 || c_out <= 0 || c_in > (1 << 24) || c_out > (1 << 24))
         return fail(ASTRAEA_ERR_INVALID, "%s: c_in=%lld, c_out=%lld out of range", fn, (long long)c_in, (long long)c_out);
     if (c_in % 64 != 0 || c_out % 8 != 0)
         return fail(ASTRAEA_ERR_UNSUPPORTED, "%s: c_in must be a multiple of 64 and c_out of 8", fn);
-    if (x_row_stride < c_in || y_row_stride < c_out || x_row_stride % 8 != 0 || y_row_stride % 8 != 0)
-        return fail(ASTRAEA_ERR_INVALID, "%s: row strides must cover a row and be multiples of 8 elements", fn);
+    bool strides = x_row_stride >= c_in && x_row_stride % 8 == 0;
+    for (int i = 0; i < n_parts; ++i) strides = strides && parts[i].y_row_stride >= c_out && parts[i].y_row_stride % 8 == 0;
+    if (!strides) return fail(ASTRAEA_ERR_INVALID, "%s: row strides must cover a row and be multiples of 8 elements", fn);
     // the bf16 kernel's tile copies address x and w with 32-bit byte offsets
     const int64_t x_rows = x_is_compact ? k_sel : N;
     if (dt == ASTRAEA_BF16 && (x_rows * x_row_stride * 2 >= ((int64_t)1 << 32) || c_out * c_in * 2 >= ((int64_t)1 << 32)))
         return fail(ASTRAEA_ERR_UNSUPPORTED, "%s: x and w must each span less than 4 GiB", fn);
     if (k_sel == 0) return ASTRAEA_OK;
-    if (!x || !w || !y) return fail(ASTRAEA_ERR_INVALID, "%s: NULL tensor", fn);
+    bool tensors = x != nullptr;
+    uintptr_t bits = (uintptr_t)x;
+    LinearPart part[kMaxLinearParts];
+    for (int i = 0; i < n_parts; ++i) {
+        tensors = tensors && parts[i].w && parts[i].y;
+        bits |= (uintptr_t)parts[i].w | (uintptr_t)parts[i].y | (uintptr_t)parts[i].bias;
+        part[i] = LinearPart{parts[i].w, parts[i].bias, parts[i].y, parts[i].y_row_stride, parts[i].y_is_compact ? 0 : 1};
+    }
+    if (!tensors) return fail(ASTRAEA_ERR_INVALID, "%s: NULL tensor", fn);
     if (indexed && !idx_sel) return fail(ASTRAEA_ERR_INVALID, "%s: idx_sel is required to gather or place rows", fn);
-    if (((uintptr_t)x | (uintptr_t)w | (uintptr_t)y | (uintptr_t)bias) % 16 != 0)
-        return fail(ASTRAEA_ERR_INVALID, "%s: x, w, bias and y must be 16-byte aligned", fn);
+    if (bits % 16 != 0) return fail(ASTRAEA_ERR_INVALID, "%s: x, w, bias and y must be 16-byte aligned", fn);
     if ((uintptr_t)idx_sel % 4 != 0) return fail(ASTRAEA_ERR_INVALID, "%s: idx_sel must be 4-byte aligned", fn);
-    if (dt == ASTRAEA_F32)
-        return launch_linear_f32(x, w, bias, y, idx_sel, k_sel, N, (int32_t)c_in, (int32_t)c_out, x_row_stride,
-                                 y_row_stride, x_is_compact ? 0 : 1, y_is_compact ? 0 : 1, (int)act, (hipStream_t)stream);
-    return launch_linear_bf16(x, w, bias, y, idx_sel, k_sel, N, (int32_t)c_in, (int32_t)c_out, x_row_stride, y_row_stride,
-                              x_is_compact ? 0 : 1, y_is_compact ? 0 : 1, (int)act, (hipStream_t)stream);
+    const auto launch = dt == ASTRAEA_F32 ? launch_linear_f32 : launch_linear_bf16;
+    // Layers whose results lie where another one reads or writes keep their order.
+    const int64_t es = (int64_t)esize(dt);
+    auto y_bytes = [&](int i) { return (((parts[i].y_is_compact ? k_sel : N) - 1) * parts[i].y_row_stride + c_out) * es; };
+    bool apart = false;
+    for (int i = 0; n_parts > 1 && i < n_parts; ++i) {
+        apart = apart || overlap(parts[i].y, y_bytes(i), x, ((x_rows - 1) * x_row_stride + c_in) * es);
+        for (int j = 0; j < n_parts; ++j)
+            apart = apart || overlap(parts[i].y, y_bytes(i), parts[j].w, c_in * c_out * es) ||
+                    (parts[j].bias && overlap(parts[i].y, y_bytes(i), parts[j].bias, c_out * es)) ||
+                    (j > i && overlap(parts[i].y, y_bytes(i), parts[j].y, y_bytes(j)));
+    }
+    int rc = ASTRAEA_OK;
+    for (int i = 0; rc == ASTRAEA_OK && i < n_parts; i += apart ? 1 : n_parts)
+        rc = launch(x, part + i, apart ? 1 : n_parts, idx_sel, k_sel, N, (int32_t)c_in, (int32_t)c_out, x_row_stride, x_is_compact ? 0 : 1,
+                    (int)act, (hipStream_t)stream);
+    return rc;
+}
+
+int astraea_sparse_linear(const void *x, const void *w, const void *bias, astraea_dtype dt, int64_t N, int64_t c_in,
+                          int64_t c_out, int64_t x_row_stride, const int32_t *idx_sel, int64_t k_sel,
+                          int x_is_compact, astraea_activation act, void *y, int64_t y_row_stride, int y_is_compact,
+                          void *stream)
+{
+    const astraea_linear_part part = {w, bias, y, y_row_stride, y_is_compact};
+    return sparse_linear_common("astraea_sparse_linear", x, dt, N, c_in, c_out, x_row_stride, idx_sel, k_sel, x_is_compact, act, &part,
+                                1, stream);
+}
+
+int astraea_sparse_linear_group(const void *x, astraea_dtype dt, int64_t N, int64_t c_in, int64_t c_out, int64_t x_row_stride,
+                                const int32_t *idx_sel, int64_t k_sel, int x_is_compact, astraea_activation act,
+                                const astraea_linear_part *parts, int32_t n_parts, void *stream)
+{
+    const char *fn = "astraea_sparse_linear_group";
+    if (n_parts < 1 || n_parts > kMaxLinearParts || !parts)
+        return fail(ASTRAEA_ERR_INVALID, "%s: 1 to %d layers, n_parts=%d", fn, kMaxLinearParts, (int)n_parts);
+    return sparse_linear_common(fn, x, dt, N, c_in, c_out, x_row_stride, idx_sel, k_sel, x_is_compact, act, parts, n_parts, stream);
 }
 
 static int check_rows(const char *fn, const void *a, const void *b, astraea_dtype dt, int64_t N, int64_t row_elems,
@@ -242,12 +287,6 @@ int astraea_kv_refresh(void *k_cache, void *v_cache, const void *k_new, const vo
                             true, true, (hipStream_t)stream, v_cache, v_new);
 }
 
-// Whether [a, a + a_elems) and [b, b + b_elems), counted in elements of es bytes, share a byte.
-static bool overlap(const void *a, int64_t a_elems, const void *b, int64_t b_elems, int64_t es)
-{
-    return (uintptr_t)a < (uintptr_t)b + (uint64_t)(b_elems * es) && (uintptr_t)b < (uintptr_t)a + (uint64_t)(a_elems * es);
-}
-
 int astraea_sparse_attn_scatter_fwd(const void *q, const void *k, const void *v, astraea_dtype dt, int64_t N, int32_t H,
                                     int32_t D, int64_t q_stride_n, int64_t q_stride_h, int64_t kv_stride_n,
                                     int64_t kv_stride_h, const int32_t *idx_sel, int64_t k_sel, int q_is_compact,
@@ -262,11 +301,11 @@ int astraea_sparse_attn_scatter_fwd(const void *q, const void *k, const void *v,
     if (k_sel > 0 && !o_sel) return fail(ASTRAEA_ERR_INVALID, "%s: NULL tensor", fn);
     // The kernel stores both in 16-byte pieces while other workgroups still read q, K and V: a cached buffer that is not aligned
     // for that, or may share memory with one of them, gets its rows by a launch of its own.
-    const int64_t es = (int64_t)esize(dt), kv_elems = (N - 1) * kv_stride_n + (H - 1) * kv_stride_h + D;
-    const int64_t q_elems = ((q_is_compact ? k_sel : N) - 1) * q_stride_n + (H - 1) * q_stride_h + D;
-    const int64_t c_elems = (cache_rows - 1) * cache_row_stride + row;
-    const bool apart = (uintptr_t)out_cache % 16 != 0 || cache_row_stride % 8 != 0 || overlap(out_cache, c_elems, q, q_elems, es) ||
-                       overlap(out_cache, c_elems, k, kv_elems, es) || overlap(out_cache, c_elems, v, kv_elems, es);
+    const int64_t es = (int64_t)esize(dt), kv_bytes = ((N - 1) * kv_stride_n + (H - 1) * kv_stride_h + D) * es;
+    const int64_t q_bytes = (((q_is_compact ? k_sel : N) - 1) * q_stride_n + (H - 1) * q_stride_h + D) * es;
+    const int64_t c_bytes = ((cache_rows - 1) * cache_row_stride + row) * es;
+    const bool apart = (uintptr_t)out_cache % 16 != 0 || cache_row_stride % 8 != 0 || overlap(out_cache, c_bytes, q, q_bytes) ||
+                       overlap(out_cache, c_bytes, k, kv_bytes) || overlap(out_cache, c_bytes, v, kv_bytes);
     rc = sparse_attn_common(fn, q, k, v, dt, N, H, D, q_stride_n, q_stride_h, kv_stride_n, kv_stride_h, idx_sel, k_sel, q_is_compact,
                             softmax_scale, AttnOut{o_sel, apart ? nullptr : out_cache, cache_row_stride, cache_rows}, false, lse_sel,
                             workspace, workspace_bytes, stream);
@@ -354,8 +393,8 @@ int astraea_linear_plan(astraea_dtype dt, int64_t k_sel, int64_t c_in, int64_t c
     if (k_sel <= 0 || k_sel > kMaxTokens || c_in <= 0 || c_out <= 0 || c_in > (1 << 24) || c_out > (1 << 24))
         return fail(ASTRAEA_ERR_INVALID, "astraea_linear_plan: k_sel=%lld, c_in=%lld, c_out=%lld out of range",
                     (long long)k_sel, (long long)c_in, (long long)c_out);
-    const int square = dt == ASTRAEA_F32 ? linear_f32_tile(k_sel, c_in, c_out) : 0;
-    const LinearTile tile = dt == ASTRAEA_F32 ? LinearTile{square, square} : linear_bf16_tile(k_sel, (int32_t)c_in, c_out);
+    const int square = dt == ASTRAEA_F32 ? linear_f32_tile(k_sel, c_in, c_out, 1) : 0;
+    const LinearTile tile = dt == ASTRAEA_F32 ? LinearTile{square, square} : linear_bf16_tile(k_sel, (int32_t)c_in, c_out, 1);
     const int tokens = tile.tokens;
     plan_out[0] = tile.features;
     plan_out[1] = tokens;

@@ -42,20 +42,40 @@ int launch_check_indices(const int32_t *idx_sel, int64_t k_sel, int64_t N, int32
 int launch_lse_weight_update(const float *lse_sel, int32_t H, int64_t N, const int32_t *idx_sel, int64_t k_sel,
                              float *lse_weight, hipStream_t stream);
 
-int launch_linear_bf16(const void *x, const void *w, const void *bias, void *y, const int32_t *idx_sel, int64_t k_sel,
-                       int64_t n_rows, int32_t c_in, int32_t c_out, int64_t ldx, int64_t ldy, int x_indexed,
-                       int y_indexed, int act, hipStream_t stream);
+// What a linear layer multiplies by and where its rows go.  Up to kMaxLinearParts layers of the same input and sizes run as one launch,
+// their feature tiles one after another.
+struct LinearPart {
+    const void *w, *bias;      // bias or null
+    void *y;
+    int64_t ldy;               // row stride in elements
+    int32_t y_indexed;
+};
+constexpr int kMaxLinearParts = 3;
+struct LinearParts {
+    LinearPart part[kMaxLinearParts];
+    int32_t n_tiles_each;      // feature tiles of a layer
+    // The layer that feature tile nt belongs to; nt becomes its own tile number.  (Chosen by selections: an index would put the parts into memory.)
+    __device__ __forceinline__ LinearPart of(int &nt) const
+    {
+        LinearPart p = part[0];
+        if (nt >= n_tiles_each) p = nt >= 2 * n_tiles_each ? part[2] : part[1];
+        nt -= nt >= 2 * n_tiles_each ? 2 * n_tiles_each : nt >= n_tiles_each ? n_tiles_each : 0;
+        return p;
+    }
+};
 
-int launch_linear_f32(const void *x, const void *w, const void *bias, void *y, const int32_t *idx_sel, int64_t k_sel,
-                      int64_t n_rows, int32_t c_in, int32_t c_out, int64_t ldx, int64_t ldy, int x_indexed,
-                      int y_indexed, int act, hipStream_t stream);
+int launch_linear_bf16(const void *x, const LinearPart *parts, int n_parts, const int32_t *idx_sel, int64_t k_sel, int64_t n_rows,
+                       int32_t c_in, int32_t c_out, int64_t ldx, int x_indexed, int act, hipStream_t stream);
+
+int launch_linear_f32(const void *x, const LinearPart *parts, int n_parts, const int32_t *idx_sel, int64_t k_sel, int64_t n_rows,
+                      int32_t c_in, int32_t c_out, int64_t ldx, int x_indexed, int act, hipStream_t stream);
 
 // The tile a bf16 linear launch takes, and the tokens (and as many features) of an fp32 one.
 struct LinearTile {
     int features, tokens;
 };
-LinearTile linear_bf16_tile(int64_t k_sel, int32_t c_in, int64_t c_out);
-int linear_f32_tile(int64_t k_sel, int64_t c_in, int64_t c_out);
+LinearTile linear_bf16_tile(int64_t k_sel, int32_t c_in, int64_t c_out, int parts);
+int linear_f32_tile(int64_t k_sel, int64_t c_in, int64_t c_out, int parts);
 
 // Where the attention puts row r: rows[r] of a compact [k_sel, H * D] result, and row idx_sel[r] of a cached buffer of cache_rows rows.
 // Either may be null; an index outside the cached buffer writes nothing.

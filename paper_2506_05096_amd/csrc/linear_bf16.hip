@@ -70,15 +70,13 @@ __device__ __forceinline__ void touch_line(const void *gbase, uint32_t goff, uin
 
 struct LinearArgs {
     const __bf16 *x;
-    const __bf16 *w;
-    const __bf16 *bias;        // or null
-    __bf16 *y;
+    LinearParts parts;
     const int32_t *idx_sel;    // or null when neither side is indexed
-    int64_t ldx, ldy;          // row strides in elements
+    int64_t ldx;               // row stride in elements
     int32_t k_sel, c_in, c_out;
     int32_t n_rows;            // rows of the indexed buffer(s): indices outside [0, n_rows) read a valid row, write none
-    int32_t x_indexed, y_indexed, act;
-    int32_t m_tiles, n_tiles;  // token and feature tiles
+    int32_t x_indexed, act;
+    int32_t m_tiles, n_tiles;  // token tiles, and feature tiles of all parts
 };
 
 // A wave has NB x TB MFMA blocks of 32 features x 32 tokens, a tile kBn features: <4, 2, 256> makes tiles of 256 tokens, <2, 3, 256> of
@@ -122,7 +120,9 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
     const int sb_h = a.m_tiles - sb_row * kSbM < kSbM ? a.m_tiles - sb_row * kSbM : kSbM;
     const int sb_col = in_row / (kSbN * sb_h), inner = in_row % (kSbN * sb_h);
     const int mt = sb_row * kSbM + inner % sb_h, nt = sb_col * kSbN + inner / sb_h;
-    const int m0 = mt * kBm, n0 = nt * kBn;
+    int part_nt = nt;
+    const LinearPart part = a.parts.of(part_nt);
+    const int m0 = mt * kBm, n0 = part_nt * kBn;
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -136,13 +136,13 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
         const int m = m0 + tid;
         if (tid < kBm && m < a.k_sel) {
             my_row = m;
-            if (a.y_indexed) {
+            if (part.y_indexed) {
                 const int32_t ix = a.idx_sel[m];
                 my_row = (uint32_t)ix < (uint32_t)a.n_rows ? ix : -1;
             }
         }
         const int n = n0 + tid;
-        if (a.bias && n < a.c_out) my_bias = reinterpret_cast<const uint16_t *>(a.bias)[n];
+        if (part.bias && n < a.c_out) my_bias = reinterpret_cast<const uint16_t *>(part.bias)[n];
     }
 
     // ---- tile copies.  The memory pipe accepts a 1 KiB copy instruction only every ~16 clocks per CU
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
 #pragma unroll
     for (int t = 0; t < kCopiesX; ++t) asm volatile("" ::"v"(xoff[t]));
 
-    const char *wg = reinterpret_cast<const char *>(a.w);
+    const char *wg = reinterpret_cast<const char *>(part.w);
     const char *xg = reinterpret_cast<const char *>(a.x);
     // L2 warm-up: a step's 128 bytes of one row are one cache line, and this wave copies up to 64 rows of
     // each tile, so one lane per row touches all of them (lane l: the l/8-th copy's row l%8).
@@ -378,7 +378,7 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
             (uintptr_t)(ebase + tl * kPitch + o_chunk * 16));
         // written once: streaming stores leave the tiles other workgroups still read in L2 (+1-3 %)
         if (n < a.c_out && orow >= 0)
-            __builtin_nontemporal_store(val, reinterpret_cast<uint4v *>(a.y + orow * a.ldy + n));
+            __builtin_nontemporal_store(val, reinterpret_cast<uint4v *>(reinterpret_cast<__bf16 *>(part.y) + orow * part.ldy + n));
     }
 }
 
@@ -394,7 +394,7 @@ static double layer_us(int64_t tiles, int nk, double fixed, double base, double 
     return (double)(tiles / kCus) * round(1.0) + (last ? round((double)last / kCus) : 0.0);
 }
 
-int64_t tiles_of(int64_t k_sel, int64_t c_out, int64_t bm, int64_t bn = 256) { return (k_sel + bm - 1) / bm * ((c_out + bn - 1) / bn); }
+int64_t tiles_of(int64_t k_sel, int64_t c_out, int parts, int64_t bm, int64_t bn = 256) { return (k_sel + bm - 1) / bm * ((c_out + bn - 1) / bn) * parts; }
 
 }  // namespace
 
@@ -404,43 +404,39 @@ int64_t tiles_of(int64_t k_sel, int64_t c_out, int64_t bm, int64_t bn = 256) { r
 // 6144 -> 1536 62 / 45, 90 rows 3072 -> 12288 47 / 32; where the larger tiles fill a round they stay, 608 rows 3072 -> 9216 48 / 59.
 // Contractions below kDeep are all start and end in either tile (608 rows 128 -> 3072 9.7 / 9.8).
 constexpr int32_t kDeep = 512;
-LinearTile linear_bf16_tile(int64_t k_sel, int32_t c_in, int64_t c_out)
+LinearTile linear_bf16_tile(int64_t k_sel, int32_t c_in, int64_t c_out, int parts)
 {
     const int nk = c_in / kBk;
-    const double us256 = layer_us(tiles_of(k_sel, c_out, 256), nk, 9.0, 1.05, 0.4, 0.78),
-                 us192 = layer_us(tiles_of(k_sel, c_out, 192), nk, 7.5, 0.93, 0.6, 0.65),
-                 us128 = layer_us(tiles_of(k_sel, c_out, 128), nk, 6.0, 0.56, 0.6, 0.7),
-                 small = layer_us(tiles_of(k_sel, c_out, 128, 128), nk, 5.0, 0.36, 0.4, 0.3);
+    const double us256 = layer_us(tiles_of(k_sel, c_out, parts, 256), nk, 9.0, 1.05, 0.4, 0.78),
+                 us192 = layer_us(tiles_of(k_sel, c_out, parts, 192), nk, 7.5, 0.93, 0.6, 0.65),
+                 us128 = layer_us(tiles_of(k_sel, c_out, parts, 128), nk, 6.0, 0.56, 0.6, 0.7),
+                 small = layer_us(tiles_of(k_sel, c_out, parts, 128, 128), nk, 5.0, 0.36, 0.4, 0.3);
     if (c_in >= kDeep && small < us128 && small < us192 && small < us256) return {128, 128};
     if (us256 <= us192 && us256 <= us128) return {256, 256};
     return {256, us192 < us128 ? 192 : 128};
 }
 
-int launch_linear_bf16(const void *x, const void *w, const void *bias, void *y, const int32_t *idx_sel, int64_t k_sel,
-                       int64_t n_rows, int32_t c_in, int32_t c_out, int64_t ldx, int64_t ldy, int x_indexed, int y_indexed, int act,
-                       hipStream_t stream)
+int launch_linear_bf16(const void *x, const LinearPart *parts, int n_parts, const int32_t *idx_sel, int64_t k_sel, int64_t n_rows,
+                       int32_t c_in, int32_t c_out, int64_t ldx, int x_indexed, int act, hipStream_t stream)
 {
     if (k_sel == 0) return ASTRAEA_OK;
     LinearArgs a;
     a.x = (const __bf16 *)x;
-    a.w = (const __bf16 *)w;
-    a.bias = (const __bf16 *)bias;
-    a.y = (__bf16 *)y;
+    for (int i = 0; i < kMaxLinearParts; ++i) a.parts.part[i] = parts[i < n_parts ? i : 0];
     a.idx_sel = idx_sel;
     a.ldx = ldx;
-    a.ldy = ldy;
     a.k_sel = (int32_t)k_sel;
     a.n_rows = (int32_t)n_rows;
     a.c_in = c_in;
     a.c_out = c_out;
     a.x_indexed = x_indexed;
-    a.y_indexed = y_indexed;
     a.act = act;
-    if (tiles_of(k_sel, c_out, 128, 128) > 2147483647LL / 16) return fail(ASTRAEA_ERR_INVALID, "astraea_sparse_linear: grid too large");
-    const LinearTile tile = linear_bf16_tile(k_sel, c_in, c_out);
+    if (tiles_of(k_sel, c_out, n_parts, 128, 128) > 2147483647LL / 16) return fail(ASTRAEA_ERR_INVALID, "astraea_sparse_linear: grid too large");
+    const LinearTile tile = linear_bf16_tile(k_sel, c_in, c_out, n_parts);
     auto go = [&](auto kernel) {
         a.m_tiles = (int32_t)((k_sel + tile.tokens - 1) / tile.tokens);
-        a.n_tiles = (c_out + tile.features - 1) / tile.features;
+        a.parts.n_tiles_each = (c_out + tile.features - 1) / tile.features;
+        a.n_tiles = a.parts.n_tiles_each * n_parts;
         const int64_t t = (int64_t)a.m_tiles * a.n_tiles;
         const int64_t grid = t / kCus * kCus + (t % kCus + kNumXcd - 1) / kNumXcd * kNumXcd;
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kWaves * kWave), 0, stream, a);

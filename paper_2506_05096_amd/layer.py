@@ -171,9 +171,9 @@ class TokenSparseBlock(LayerStep):
             ab.astraea_sparse_linear(x, self.w["wqkv"], self._b("bqkv"), idx, k, t["qkv_cache"].view(N, 3 * E),
                                      y_is_compact=False)
             return
-        ab.astraea_sparse_linear(x, self.w["wq"], self._b("bq"), idx, k, self.q_sel.view(N, E)[:max(k, 1)])
-        ab.astraea_sparse_linear(x, self.w["wk"], self._b("bk"), idx, k, t["k_cache"].view(N, E), y_is_compact=False)
-        ab.astraea_sparse_linear(x, self.w["wv"], self._b("bv"), idx, k, t["v_cache"].view(N, E), y_is_compact=False)
+        ab.astraea_sparse_linear_group(x, ((self.w["wq"], self._b("bq"), self.q_sel.view(N, E)[:max(k, 1)], True),
+                                           (self.w["wk"], self._b("bk"), t["k_cache"].view(N, E), False),
+                                           (self.w["wv"], self._b("bv"), t["v_cache"].view(N, E), False)), idx, k)
 
     def step_attn(self, t: Dict[str, torch.Tensor], k: int, lse: Optional[torch.Tensor] = None) -> None:
         if "qkv_cache" in t:

@@ -629,3 +629,44 @@ def test_attn_f32_infinity_in_the_last_key(n, h, d, k):
 ])
 def test_linear_bf16_small_tile(n, k, c_in, c_out, gather, scatter, bias, act):
     test_linear_bf16_tiles(n, k, c_in, c_out, gather, scatter, bias, act, 128, features=128)
+
+
+# Layers of one input in one launch, against a call each: one to three parts, widths that end inside a tile of features, every tile kind
+# (few rows, many rows, deep and shallow contractions), a part without a bias, compact and placed results.  bf16 sums a contraction in one
+# order whatever the tile, so its bits are the same; fp32 results are held to the bound of their products (test_linear_f32_split_range).
+# "chained": a layer whose weight is the result before it gets its turn after it.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("n,k,c_in,c_out,parts,chained", [
+    (700, 300, 128, 264, 3, False), (2100, 2049, 512, 512, 3, False), (1300, 1000, 1024, 1096, 2, False), (90, 33, 64, 8, 3, False),
+    (4000, 3900, 320, 776, 3, False), (500, 499, 192, 192, 1, False), (500, 192, 192, 192, 3, True),
+])
+def test_linear_group(dtype, n, k, c_in, c_out, parts, chained):
+    g = torch.Generator(device=DEV).manual_seed(n + k)
+    x = torch.randn(n, c_in, device=DEV, generator=g).to(dtype)
+    ws = [torch.randn(c_out, c_in, device=DEV, generator=g).div(math.sqrt(c_in)).to(dtype) for _ in range(parts)]
+    bs = [None if i == 1 else torch.randn(c_out, device=DEV, generator=g).to(dtype) for i in range(parts)]
+    idx = torch.randperm(n, device=DEV, generator=g)[:k].sort().values.to(torch.int32)
+
+    def layers():
+        ys = [torch.zeros(k if i == 0 else n, c_out + 8, dtype=dtype, device=DEV)[:, :c_out] for i in range(parts)]
+        w = list(ws)
+        if chained:
+            w[1] = ys[0] = torch.zeros(k, c_out, dtype=dtype, device=DEV)
+        return [(w[i], bs[i], ys[i], i == 0) for i in range(parts)]
+    la, lb = layers(), layers()
+    for w, b, y, compact in la:
+        ab.astraea_sparse_linear(x, w, b, idx, k, y, act=ab.ACT_GELU_TANH, y_is_compact=compact)
+    ab.astraea_sparse_linear_group(x, lb, idx, k, act=ab.ACT_GELU_TANH)
+    torch.cuda.synchronize()
+    for (w, _, ya, _), (_, _, yb, _) in zip(la, lb):
+        if dtype == torch.bfloat16 or chained:               # a launch each, of the same tiles, where chained
+            assert torch.equal(ya, yb)
+        else:
+            # either is off by (2^-22 + c_in / 2 2^-24) of the sum of |x w|, and GELU (slope at most 1.13) by 2^-21 of its result
+            size = x.double().abs()[idx.long()] @ w.double().abs().T
+            a, b = (t.double() if t.shape[0] == k else t[idx.long()].double() for t in (ya, yb))
+            bound = 2 * 1.13 * (2.0 ** -22 + c_in / 2 * 2.0 ** -24) * size + 2.0 ** -20 * (1 + a.abs())
+            assert bool(((a - b).abs() <= bound).all())
+            rest = torch.ones(n, dtype=torch.bool, device=DEV)
+            rest[idx.long()] = False
+            assert ya.shape[0] == k or not yb[rest].any()
