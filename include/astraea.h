@@ -95,9 +95,9 @@ int astraea_score(const void *x_cur, const void *x_prev, astraea_dtype dt, int64
  *   sel_mask    [N] uint8 out (1 = selected), or NULL.
  *   skip_count  [N] int32 in/out, or NULL: set to 0 for selected tokens and
  *               incremented for the others (the n_i of the penalty term).
- *   workspace   at least astraea_workspace_bytes(ASTRAEA_OP_SELECT_TOPK, N, k, 0, 0)
- *               bytes, 256-byte aligned; contents need not be initialised and are
- *               clobbered.  Calls sharing a workspace must not overlap in time.
+ *   workspace   astraea_workspace_bytes(ASTRAEA_OP_SELECT_TOPK, N, k, 0, 0) bytes, 256-byte aligned;
+ *               contents need not be initialised and are clobbered.  (From 8448 + 8 * ceil(N / 2048) bytes,
+ *               rounded up to 256, the call also works, with two more launches.)  Calls sharing a workspace must not overlap in time.
  * k == 0 and k == N are valid.
  */
 int astraea_select_topk(const float *score, int64_t N, int64_t k, int32_t *idx_sel, int32_t *idx_remain,
@@ -108,8 +108,8 @@ int astraea_select_topk(const float *score, int64_t N, int64_t k, int32_t *idx_s
  * astraea_select_topk_static - astraea_select_topk for callers that cannot allocate device memory or
  * hand over a workspace: code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments without the workspace, same result to the bit.  The selection state, the
- * digit histogram and the per-workgroup counts live in a device array built into the library
- * (24.25 KiB per GPU, held until the process ends); the call allocates and frees nothing.
+ * digits' histograms and the per-workgroup counts live in a device array built into the library
+ * (385 KiB per GPU, held until the process ends); the call allocates and frees nothing.
  *   N           at most 4194304 (2^22) scores; more returns ASTRAEA_ERR_UNSUPPORTED and enqueues nothing.
  * The GPU that `stream` belongs to must be the current device.  The array's address on that device is
  * looked up at the first call made with it current (hipGetSymbolAddress; make that first call outside

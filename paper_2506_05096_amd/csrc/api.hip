@@ -77,11 +77,12 @@ int astraea_select_topk(const float *score, int64_t N, int64_t k, int32_t *idx_s
 {
     const int rc = check_topk("astraea_select_topk", score, N, k, idx_sel, idx_remain, skip_count);
     if (rc != ASTRAEA_OK || N == 0) return rc;
-    const size_t need = topk_workspace_bytes(N);
+    const size_t need = topk_min_workspace_bytes(N);
     if (!workspace || (uintptr_t)workspace % 256 != 0 || workspace_bytes < need)
         return fail(ASTRAEA_ERR_WORKSPACE, "astraea_select_topk: workspace must be 256-byte aligned and >= %zu bytes",
                     need);
-    return launch_select_topk(score, N, k, idx_sel, idx_remain, sel_mask, skip_count, workspace, (hipStream_t)stream);
+    return launch_select_topk(score, N, k, idx_sel, idx_remain, sel_mask, skip_count, workspace, workspace_bytes,
+                              (hipStream_t)stream);
 }
 
 int astraea_select_topk_static(const float *score, int64_t N, int64_t k, int32_t *idx_sel, int32_t *idx_remain,
@@ -96,7 +97,8 @@ int astraea_select_topk_static(const float *score, int64_t N, int64_t k, int32_t
     void *scratch_ptr = nullptr;
     const int rs = topk_static_scratch(&scratch_ptr);
     if (rs != ASTRAEA_OK) return rs;
-    return launch_select_topk(score, N, k, idx_sel, idx_remain, sel_mask, skip_count, scratch_ptr, (hipStream_t)stream);
+    return launch_select_topk(score, N, k, idx_sel, idx_remain, sel_mask, skip_count, scratch_ptr, topk_static_bytes(),
+                              (hipStream_t)stream);
 }
 
 // Shared body of the attention entry points: out.rows is the compact [k_sel, H, D] result, out.cache the cached per-token buffer whose

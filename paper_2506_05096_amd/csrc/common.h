@@ -26,11 +26,13 @@ int launch_score(const void *x_cur, const void *x_prev, astraea_dtype dt, int64_
                  const float *penalty_table, int32_t table_len, float w_alpha, float w_beta, float *score_out,
                  hipStream_t stream);
 
-size_t topk_workspace_bytes(int64_t N);
+size_t topk_workspace_bytes(int64_t N);       // for the fewest launches; with topk_min_workspace_bytes the selection takes two more
+size_t topk_min_workspace_bytes(int64_t N);
 int64_t topk_static_max_n();
+size_t topk_static_bytes();
 int topk_static_scratch(void **ptr_out);      // the library's own per-device scratch array, for astraea_select_topk_static
-int launch_select_topk(const float *score, int64_t N, int64_t k, int32_t *idx_sel, int32_t *idx_remain,
-                       uint8_t *sel_mask, int32_t *skip_count, void *workspace, hipStream_t stream);
+int launch_select_topk(const float *score, int64_t N, int64_t k, int32_t *idx_sel, int32_t *idx_remain, uint8_t *sel_mask,
+                       int32_t *skip_count, void *workspace, size_t workspace_bytes, hipStream_t stream);
 
 // dst_b / src_b: an optional second buffer pair of the same shape and strides, moved by the same launch
 int launch_move_rows(void *dst, const void *src, int64_t row_bytes, int64_t dst_stride_bytes,

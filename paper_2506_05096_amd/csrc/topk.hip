@@ -2,19 +2,20 @@
 //
 // Exact, deterministic selection of the k largest fp32 scores with lowest-index tie-break:
 //   1. scores map to order-preserving 32-bit keys (-0 -> +0, NaN -> lowest key);
-//   2. a 3-pass radix select (11 + 11 + 10 bits, most significant first) finds the key T of the
-//      k-th largest element and `need`, the number of elements equal to T that are still selected;
-//      each pass is a histogram over the elements that match the prefix found so far, built with
-//      wavefront match-free LDS atomics and merged by integer global atomics (order-independent);
-//      the workgroup that finishes last (atomic ticket) resolves the digit, so no host round trip
-//      and no spinning is involved;
-//   3. a count kernel + an emit kernel compact the selected indices in ascending index order:
-//      an element is selected iff key > T, or key == T and fewer than `need` equal elements
-//      precede it.  Ranks come from wavefront ballots and prefix popcounts.
-// The score array (4N bytes) stays in L2 across the five small launches; the step is latency-bound.
-// Up to 32768 scores take a single-workgroup kernel instead (one launch, keys held in registers).  (A single
-// workgroup that streams more scores than LDS holds from L2 in every pass was measured too: one launch, but
-// one compute unit's loads are latency-bound, 129 us against 43 us at 118800 scores.)
+//   2. radix passes, most significant digit first, find the key T of the k-th largest element and `need`, the number
+//      of elements equal to T that are still selected;
+//   3. the selected indices are compacted in ascending index order: an element is selected iff key > T, or
+//      key == T and fewer than `need` equal elements precede it.  Ranks come from wavefront ballots and counts.
+// The score array (4N bytes) stays in the caches; the step is latency-bound.  By the number of scores:
+//   * up to 32768: one workgroup, one launch, keys in registers.  (A single workgroup that streams more scores than
+//     it holds from L2 in every pass was measured too: one CU's loads are latency-bound, 129 us at 118800 scores.)
+//   * up to 786432, if the workspace holds a slot per workgroup: a launch per digit and one for the outputs.  us, indices
+//     alone / every output, by this and by the next form: 32769 scores 24 / 25 and 34 / 36, 118800 25 / 25 and 42 / 44, 262144
+//     30 / 30 and 56 / 58, 786432 40 / 41 and 107 / 111 (scores of one magnitude; others 1 - 2 us less).  The limit bounds
+//     the slots: every workgroup reads all of them in every launch.
+//   * more, or a smaller workspace: three histogram launches (11 + 11 + 10 bits) whose counts are merged by integer
+//     global atomics (order-independent) and whose last workgroup (atomic ticket) resolves the digit, a count and an emit
+//     launch, and one before them that clears the state.
 #include <mutex>
 
 #include "common.h"
@@ -315,6 +316,60 @@ constexpr int kSmallMax = 32768;
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / kWave;
 constexpr int kCopyPitch = kBins + 16;       // of the histogram's copies: their counters lie in different banks
+constexpr uint32_t kPad = 0xffffffffu;      // stands for no element; above every key (the largest is +inf's, 0xff800000)
+
+// Writes the outputs of a workgroup whose wave w owns ITEMS * 64 consecutive elements, element first + 64 j in register j: ranks in
+// index order come from ballots.  g_before and e_before count the keys above / equal to T in front of the workgroup's elements.
+template <int ITEMS>
+__device__ __forceinline__ void emit_in_order(const uint32_t (&key)[ITEMS], const int32_t (&skip)[ITEMS], int first, int wave, int lane,
+                                              uint32_t T, uint32_t need, uint32_t g_before, uint32_t e_before, uint32_t *wt_a,
+                                              uint32_t *wt_b, int32_t *__restrict__ idx_sel, int32_t *__restrict__ idx_remain,
+                                              uint8_t *__restrict__ sel_mask, int32_t *__restrict__ skip_count)
+{
+    auto above = [&](uint32_t kk) { return kk - (T + 1) < kPad - (T + 1); };       // kk > T and an element
+    uint32_t mg = 0, me = 0;
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        mg += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(above(key[j])));
+        me += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(key[j] == T));
+    }
+    if (lane == 0) {
+        wt_a[wave] = mg;
+        wt_b[wave] = me;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) {
+        g_before += w < wave ? wt_a[w] : 0u;
+        e_before += w < wave ? wt_b[w] : 0u;
+    }
+    g_before = __builtin_amdgcn_readfirstlane(g_before);      // in front of the wave's present 64 elements from here on
+    e_before = __builtin_amdgcn_readfirstlane(e_before);
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const int i = first + j * kWave;
+        bool sel = above(key[j]);
+        const uint64_t gm = __builtin_amdgcn_ballot_w64(sel), em = __builtin_amdgcn_ballot_w64(key[j] == T);
+        uint32_t sel_before = g_before + lanes_below(gm);
+        if (em == 0) {
+            sel_before += e_before < need ? e_before : need;
+        } else {
+            const uint32_t eb = e_before + lanes_below(em);
+            sel_before += eb < need ? eb : need;
+            sel = sel || (key[j] == T && eb < need);
+        }
+        if (sel)
+            idx_sel[sel_before] = i;
+        else if (idx_remain && key[j] != kPad)
+            idx_remain[(uint32_t)i - sel_before] = i;
+        if (key[j] != kPad) {
+            if (sel_mask) sel_mask[i] = sel ? 1 : 0;
+            if (skip_count) skip_count[i] = sel ? 0 : skip[j] + 1;
+        }
+        g_before += (uint32_t)__popcll(gm);
+        e_before += (uint32_t)__popcll(em);
+    }
+}
 
 template <int ITEMS>
 __global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(const float *__restrict__ score, int32_t N, uint32_t k,
@@ -329,7 +384,6 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(const float *
     __shared__ __attribute__((aligned(16))) uint32_t hist[kCopyPitch * kCopies];
     __shared__ uint32_t wt_a[kSmallWaves], wt_b[kSmallWaves];
     __shared__ uint32_t s_base, s_krem;
-    constexpr uint32_t kPad = 0xffffffffu;      // stands for no element; above every key (the largest is +inf's, 0xff800000)
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int first = wave * ITEMS * kWave + lane;                      // element j of this thread: first + 64 j
@@ -422,61 +476,188 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(const float *
         T = base;
         need = k_rem;
     }
-    // ordered emit, as in topk_emit_kernel
-    auto above = [&](uint32_t kk) { return kk - (T + 1) < kPad - (T + 1); };       // kk > T and an element
-    uint32_t mg = 0, me = 0;
+    // last read of wt_a before the barriers above (k == 0: for the key range, unused then)
+    emit_in_order(key, skip, first, wave, lane, T, need, 0u, 0u, wt_a, wt_b, idx_sel, idx_remain, sel_mask, skip_count);
+}
+
+// ---- more scores than one workgroup takes: a launch for each of three digits and one for the outputs.  A workgroup owns 12288
+// elements, laid out as in the kernel above.  Its part of a pass is a slot of its own in the workspace, for every bin the number of
+// its candidates in that bin or a higher one, 16 bits each.  The next launch adds up the slots: the digit is the highest bin whose sum
+// reaches what is left to be taken, and the sum over the slots in front of a workgroup's own says how many larger keys precede its
+// elements.  Every workgroup does that for itself, so nothing is cleared, counted by tickets or merged by atomics, and no launch ends with
+// one workgroup at work alone.  Passes 0 and 2 use the same slots: pass 2 writes them after pass 1 has read them.
+// Bound by the start of four launches and, in each, the chain of load, histogram, scan and store (6 us apiece at 118800 scores).
+constexpr int kSlotItems = 12;
+constexpr int kSlotChunk = kSlotItems * kSmallThreads;
+constexpr int64_t kSlotMax = 64 * (int64_t)kSlotChunk;
+constexpr int kSlotBits[3] = {11, 10, 11};
+constexpr int kSlotShift[3] = {21, 11, 0};
+constexpr int kSlotWordsA = 1 << (kSlotBits[0] - 1), kSlotWordsB = 1 << (kSlotBits[1] - 1);        // of 32 bits, a slot of passes 0 and 2 / pass 1
+
+// What a workgroup knows after a pass: the threshold's digits so far, how many elements are still to be taken among those that share
+// them, how many larger keys lie in front of its elements.
+struct SlotRecord {
+    uint32_t prefix, k_rem, above, pad;
+};
+
+// workspace layout: [slots of passes 0 and 2][slots of pass 1][records], one of each per workgroup
+constexpr size_t slot_bytes(int64_t N)
+{
+    const size_t n_wg = (size_t)((N + kSlotChunk - 1) / kSlotChunk);
+    return n_wg * ((kSlotWordsA + kSlotWordsB) * sizeof(uint32_t) + sizeof(SlotRecord));
+}
+
+struct SlotShared {
+    uint32_t tot[kSlotWordsA + 1], pre[kSlotWordsA + 1];
+    uint32_t digit, k_rem, above, equal;
+};
+
+// The digit of a pass from its slots.  equal counts the keys with that digit in front of workgroup `me`.
+template <int WORDS>
+__device__ __forceinline__ void resolve_digit(const uint32_t *__restrict__ slots, int n_wg, int me, uint32_t k_rem, SlotShared &sh)
+{
+    const int t = threadIdx.x;
+    uint32_t lo = 0, hi = 0, pre_lo = 0, pre_hi = 0;       // bins 2t and 2t + 1: over all workgroups, over those in front
+    if (t < WORDS) {
+        constexpr int kBatch = 10;
+        for (int w0 = 0; w0 < n_wg; w0 += kBatch) {
+            uint32_t v[kBatch];
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        mg += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(above(key[j])));
-        me += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(key[j] == T));
+            for (int j = 0; j < kBatch; ++j) v[j] = slots[(w0 + j < n_wg ? w0 + j : n_wg - 1) * WORDS + t];
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                const uint32_t u = w0 + j < n_wg ? v[j] : 0u;
+                pre_lo += w0 + j < me ? u & 0xffffu : 0u;
+                pre_hi += w0 + j < me ? u >> 16 : 0u;
+                lo += u & 0xffffu;
+                hi += u >> 16;
+            }
+        }
+        sh.tot[t] = lo;
+        sh.pre[t] = pre_lo;
     }
-    if (lane == 0) {
-        wt_a[wave] = mg;                         // last read before the barriers above (k == 0: for the key range, unused then)
-        wt_b[wave] = me;
+    if (t == 0) sh.tot[WORDS] = sh.pre[WORDS] = 0;
+    __syncthreads();
+    if (t < WORDS) {
+        const uint32_t next = sh.tot[t + 1], pre_next = sh.pre[t + 1];
+        // sums fall from bin to bin, bin 0 has all the candidates: true for exactly one bin
+        if (lo >= k_rem && next < k_rem) {
+            const bool upper = hi >= k_rem;
+            sh.digit = 2 * t + (upper ? 1 : 0);
+            sh.k_rem = k_rem - (upper ? next : hi);
+            sh.above = upper ? pre_next : pre_hi;
+            sh.equal = upper ? pre_hi - pre_next : pre_lo - pre_hi;
+        }
     }
     __syncthreads();
-    uint32_t g_before = 0, e_before = 0;         // keys above / equal to T in front of the wave's present 64 elements
+}
+
+template <int PASS>
+__global__ __launch_bounds__(kSmallThreads) void topk_slot_kernel(const float *__restrict__ score, int32_t N, uint32_t k,
+                                                                  const uint32_t *__restrict__ slots_in, uint32_t *__restrict__ slots_out,
+                                                                  SlotRecord *__restrict__ records)
+{
+    constexpr int kCopies = 4;
+    constexpr int BINS = 1 << kSlotBits[PASS], SHIFT = kSlotShift[PASS];
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kCopyPitch * kCopies];
+    __shared__ SlotShared sh;
+    __shared__ uint32_t wt[kSmallWaves];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int first = (int)blockIdx.x * kSlotChunk + wave * kSlotItems * kWave + lane;
+    uint32_t key[kSlotItems];
 #pragma unroll
-    for (int w = 0; w < kSmallWaves; ++w) {
-        g_before += w < wave ? wt_a[w] : 0u;
-        e_before += w < wave ? wt_b[w] : 0u;
+    for (int j = 0; j < kSlotItems; ++j)
+        key[j] = __float_as_uint(score[first + j * kWave < N ? first + j * kWave : N - 1]);
+    for (int i = tid; i < kCopyPitch * kCopies / 4; i += kSmallThreads) reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0, 0, 0, 0);
+    SlotRecord rec = {0u, k, 0u, 0u};
+    if (PASS > 0) {
+        constexpr int P = PASS > 0 ? PASS - 1 : 0;
+        if (PASS > 1) rec = records[blockIdx.x];
+        resolve_digit<(1 << kSlotBits[P]) / 2>(slots_in, gridDim.x, blockIdx.x, rec.k_rem, sh);
+        rec = SlotRecord{rec.prefix | (sh.digit << kSlotShift[P]), sh.k_rem, rec.above + sh.above, 0u};
+        if (tid == 0) records[blockIdx.x] = rec;
+    } else {
+        __syncthreads();
     }
-    g_before = __builtin_amdgcn_readfirstlane(g_before);
-    e_before = __builtin_amdgcn_readfirstlane(e_before);
+    uint32_t *mine = hist + (lane & (kCopies - 1)) * kCopyPitch;
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        const int i = first + j * kWave;
-        bool sel = above(key[j]);
-        const uint64_t gm = __builtin_amdgcn_ballot_w64(sel), em = __builtin_amdgcn_ballot_w64(key[j] == T);
-        uint32_t sel_before = g_before + lanes_below(gm);
-        if (em == 0) {
-            sel_before += e_before < need ? e_before : need;
-        } else {
-            const uint32_t eb = e_before + lanes_below(em);
-            sel_before += eb < need ? eb : need;
-            sel = sel || (key[j] == T && eb < need);
-        }
-        if (sel)
-            idx_sel[sel_before] = i;
-        else if (idx_remain && key[j] != kPad)
-            idx_remain[(uint32_t)i - sel_before] = i;
-        if (key[j] != kPad) {
-            if (sel_mask) sel_mask[i] = sel ? 1 : 0;
-            if (skip_count) skip_count[i] = sel ? 0 : skip[j] + 1;
-        }
-        g_before += (uint32_t)__popcll(gm);
-        e_before += (uint32_t)__popcll(em);
+    for (int j = 0; j < kSlotItems; ++j) {
+        const uint32_t kk = score_key(__uint_as_float(key[j]));
+        constexpr int TOP = PASS > 0 ? kSlotShift[PASS > 0 ? PASS - 1 : 0] : 0;
+        const bool candidate = PASS == 0 || (kk ^ rec.prefix) >> TOP == 0;
+        if (candidate && first + j * kWave < N) atomicAdd(&mine[(kk >> SHIFT) & (BINS - 1)], 1u);
     }
+    __syncthreads();
+    // thread t owns bins BINS - 1 - 2t and BINS - 2 - 2t
+    uint32_t c0 = 0, c1 = 0;
+    if (tid < BINS / 2) {
+        const uint2 *cells = reinterpret_cast<const uint2 *>(hist + BINS - 2 - 2 * tid);
+#pragma unroll
+        for (int c = 0; c < kCopies; ++c) {
+            const uint2 u = cells[c * (kCopyPitch / 2)];
+            c1 += u.x;
+            c0 += u.y;
+        }
+    }
+    uint32_t incl = c0 + c1;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t o = __shfl_up(incl, d);
+        if (lane >= d) incl += o;
+    }
+    if (lane == kWave - 1) wt[wave] = incl;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) incl += w < wave ? wt[w] : 0u;
+    if (tid < BINS / 2) slots_out[(int)blockIdx.x * (BINS / 2) + BINS / 2 - 1 - tid] = incl | (incl - c1) << 16;
+}
+
+// k == 0: a threshold no key reaches.
+__global__ __launch_bounds__(kSmallThreads) void topk_slot_emit_kernel(const float *__restrict__ score, int32_t N, uint32_t k,
+                                                                       const uint32_t *__restrict__ slots,
+                                                                       const SlotRecord *__restrict__ records,
+                                                                       int32_t *__restrict__ idx_sel, int32_t *__restrict__ idx_remain,
+                                                                       uint8_t *__restrict__ sel_mask, int32_t *__restrict__ skip_count)
+{
+    __shared__ SlotShared sh;
+    __shared__ uint32_t wt_a[kSmallWaves], wt_b[kSmallWaves];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int first = (int)blockIdx.x * kSlotChunk + wave * kSlotItems * kWave + lane;
+    uint32_t key[kSlotItems];
+    int32_t skip[kSlotItems];
+#pragma unroll
+    for (int j = 0; j < kSlotItems; ++j) {
+        const int i = first + j * kWave < N ? first + j * kWave : N - 1;
+        key[j] = __float_as_uint(score[i]);
+        if (skip_count) skip[j] = skip_count[i];
+    }
+    uint32_t T = kPad - 1, need = 0, above = 0, equal = 0;
+    if (k > 0) {
+        const SlotRecord rec = records[blockIdx.x];
+        resolve_digit<kSlotWordsA>(slots, gridDim.x, blockIdx.x, rec.k_rem, sh);
+        T = __builtin_amdgcn_readfirstlane(rec.prefix | sh.digit);
+        need = __builtin_amdgcn_readfirstlane(sh.k_rem);
+        above = rec.above + sh.above;
+        equal = sh.equal;
+    }
+#pragma unroll
+    for (int j = 0; j < kSlotItems; ++j)
+        key[j] = first + j * kWave < N ? score_key(__uint_as_float(key[j])) : kPad;
+    emit_in_order(key, skip, first, wave, lane, T, need, above, equal, wt_a, wt_b, idx_sel, idx_remain, sel_mask, skip_count);
 }
 
 // ---- astraea_select_topk_static: the same selection for callers that cannot allocate.  The selection state,
 // the histogram and the per-workgroup counts live in this file-scope device array instead of a caller's
-// workspace: 256 B of state + 8 KiB of histogram + 8 B per 2048 scores, 24.25 KiB for the largest input
-// the entry point takes.  Every GPU the library runs on holds its own copy, at its own address, until the
+// workspace: 256 B of state + 8 KiB of histogram + 8 B per 2048 scores, or the slots, 6160 B per 12288 scores: 385 KiB
+// for the largest input that uses them.  Every GPU the library runs on holds its own copy, at its own address, until the
 // process ends.  In host code the array's name only stands for the symbol: the address kernels are given is
 // the one hipGetSymbolAddress returns for the device that is current, looked up once per device.
 constexpr int64_t kStaticMaxN = (int64_t)1 << 22;
-constexpr size_t kStaticBytes = sizeof(SelectState) + kBins * sizeof(uint32_t) + 2 * (size_t)(kStaticMaxN / kChunk) * sizeof(uint32_t);
+constexpr size_t kStaticSlotBytes = slot_bytes(kSlotMax);
+constexpr size_t kStaticCountBytes = sizeof(SelectState) + kBins * sizeof(uint32_t) + 2 * (size_t)(kStaticMaxN / kChunk) * sizeof(uint32_t);
+constexpr size_t kStaticBytes = kStaticSlotBytes > kStaticCountBytes ? kStaticSlotBytes : kStaticCountBytes;
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 
 constexpr int kMaxDevices = 64;
@@ -508,15 +689,23 @@ int topk_static_scratch(void **ptr_out)
     return ASTRAEA_OK;
 }
 
-size_t topk_workspace_bytes(int64_t N)
+size_t topk_static_bytes() { return kStaticBytes; }
+
+size_t topk_min_workspace_bytes(int64_t N)
 {
     const int64_t nblk = (N + kChunk - 1) / kChunk;
     size_t b = ws_cnt_off() + 2 * (size_t)(nblk > 0 ? nblk : 1) * sizeof(uint32_t);
     return (b + 255) & ~(size_t)255;
 }
 
+size_t topk_workspace_bytes(int64_t N)
+{
+    const size_t least = topk_min_workspace_bytes(N), slots = (slot_bytes(N) + 255) & ~(size_t)255;
+    return N > kSmallMax && N <= kSlotMax && slots > least ? slots : least;
+}
+
 int launch_select_topk(const float *score, int64_t N, int64_t k, int32_t *idx_sel, int32_t *idx_remain,
-                       uint8_t *sel_mask, int32_t *skip_count, void *workspace, hipStream_t stream)
+                       uint8_t *sel_mask, int32_t *skip_count, void *workspace, size_t workspace_bytes, hipStream_t stream)
 {
     if (N == 0) return ASTRAEA_OK;
     if (N <= kSmallMax) {
@@ -544,6 +733,22 @@ int launch_select_topk(const float *score, int64_t N, int64_t k, int32_t *idx_se
         case 15: go(topk_small_kernel<30>); break;
         default: go(topk_small_kernel<32>); break;
         }
+        return check_launch("astraea_select_topk");
+    }
+    if (N <= kSlotMax && workspace_bytes >= slot_bytes(N)) {
+        const unsigned n_wg = (unsigned)((N + kSlotChunk - 1) / kSlotChunk);
+        uint32_t *slots_a = reinterpret_cast<uint32_t *>(workspace), *slots_b = slots_a + (size_t)n_wg * kSlotWordsA;
+        SlotRecord *records = reinterpret_cast<SlotRecord *>(slots_b + (size_t)n_wg * kSlotWordsB);
+        auto pass = [&](auto kernel, const uint32_t *in, uint32_t *out) {
+            hipLaunchKernelGGL(kernel, dim3(n_wg), dim3(kSmallThreads), 0, stream, score, (int32_t)N, (uint32_t)k, in, out, records);
+        };
+        if (k > 0) {
+            pass(topk_slot_kernel<0>, slots_b, slots_a);
+            pass(topk_slot_kernel<1>, slots_a, slots_b);
+            pass(topk_slot_kernel<2>, slots_b, slots_a);
+        }
+        hipLaunchKernelGGL(topk_slot_emit_kernel, dim3(n_wg), dim3(kSmallThreads), 0, stream, score, (int32_t)N, (uint32_t)k, slots_a,
+                           records, idx_sel, idx_remain, sel_mask, skip_count);
         return check_launch("astraea_select_topk");
     }
     const unsigned nblk = (unsigned)((N + kChunk - 1) / kChunk);

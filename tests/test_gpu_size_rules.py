@@ -453,6 +453,37 @@ def test_topk_sizes(n, kind):
         assert np.array_equal(skip[:n].cpu().numpy(), e_skip) and skip[n].item() == -7
 
 
+# Selection by a launch per digit (12288 scores a workgroup, 32769 to 786432 of them, workspaces that hold its slots) and by
+# histograms in one place (more scores, smaller workspaces): edges of the workgroups' runs and of both ranges, against the oracle.
+@pytest.mark.parametrize("kind", ["narrow", "ties", "extremes"])
+@pytest.mark.parametrize("n,small", [(32769, False), (36863, False), (36864, False), (36865, False), (36865, True), (118800, True),
+                                     (135169, False), (786432, False), (786433, False)])
+def test_topk_of_several_workgroups(n, small, kind):
+    g = torch.Generator().manual_seed(n)
+    s = 5.54 + 0.1 * torch.randn(n, generator=g)
+    if kind == "ties":
+        s = torch.randint(-1, 2, (n,), generator=g).float() * 0.5
+    elif kind == "extremes":
+        special = torch.tensor([math.inf, -math.inf, math.nan, 3.4e38, -3.4e38, 1e-45, -1e-45, 0.0, -0.0])
+        s = special[torch.randint(0, 9, (n,), generator=g)]
+    size = ab.workspace_bytes(ab.OP_SELECT_TOPK, n)
+    if small:
+        assert size > 64 + 8448 + 8 * ((n + 2047) // 2048)
+        size = -(-(8448 + 8 * ((n + 2047) // 2048)) // 256) * 256
+    for k in (0, 1, n // 3, n - 1, n):
+        e_idx, e_rest, e_mask = oracle.topk(s.numpy(), k)
+        idx, rest, skip = (torch.full((n + 1,), -7, dtype=torch.int32, device=DEV) for _ in range(3))
+        mask = torch.full((n + 1,), 9, dtype=torch.uint8, device=DEV)
+        ws = torch.full((size + 256,), 255, dtype=torch.uint8, device=DEV)
+        ab.astraea_select_topk(s.to(DEV), k, idx, ws[:size], idx_remain=rest, sel_mask=mask, skip_count=skip)
+        torch.cuda.synchronize()
+        assert (ws[size:] == 255).all()
+        assert np.array_equal(idx[:k].cpu().numpy(), e_idx) and (idx[k:] == -7).all()
+        assert np.array_equal(rest[:n - k].cpu().numpy(), e_rest) and (rest[n - k:] == -7).all()
+        assert np.array_equal(mask[:n].cpu().numpy(), e_mask) and mask[n].item() == 9
+        assert np.array_equal(skip[:n].cpu().numpy(), np.where(e_mask != 0, 0, -6)) and skip[n].item() == -7
+
+
 # bf16 linear: tiles of 256 features x 256, 192 or 128 tokens by the launch's estimate (the sizes below take each of them), edges
 # of the token tiles, ragged features, more and fewer tiles than CUs, one to many contraction steps.  Reference: fp64; bar:
 # relative L2 1e-2 per row (bf16 inputs and result).
