@@ -38,7 +38,7 @@ def test_score_sizes(n, c, stride, dtype, mode):
 
 
 # fp32 linear: 128-, 64- or 32-wide tiles by an estimate of the rounds they leave (32: the four waves split the contraction, and
-# a 64-wide contraction leaves two of them without a stage); stages of 32 indices in a ring of four, 128: of 16 in pairs.  `tile` is what the
+# a 64-wide contraction leaves two of them without a stage); stages of 32 indices, four in flight, 128: of 16 in pairs.  `tile` is what the
 # launch says it takes; each tile meets ragged rows and features and contractions that end inside the ring.  Bound: sums of c_in
 # products of size ~1/sqrt(c_in) in fp32, error below c_in * 2^-24 / sqrt(c_in) * 4 <= 1e-4 absolute at c_in <= 4096.
 @pytest.mark.parametrize("n,k,c_in,c_out,gather,scatter,bias,act,tile", [
@@ -95,7 +95,7 @@ def test_linear_f32_operand_past_4_gib(k, c_out, tile):
 
 
 # fp32 linear, magnitudes of a whole operand or of part of the contraction: zeros at its start, growth and fall along it, the ends of the
-# range, infinities, in tiles that form products of bf16 parts (128) and of fp32 numbers (64).  Bound, of the sum of magnitudes: 2^-21 for
+# range, infinities, in the tiles that form products of bf16 parts.  Bound, of the sum of magnitudes: 2^-21 for
 # the products and 2^-24 for each rounding of the sum, of which three per 16 indices are allowed here; either form stays below.
 @pytest.mark.parametrize("k,c_in,c_out,tile", [(705, 1088, 1096, 64), (2049, 128, 512, 64), (1000, 64, 4096, 128), (1001, 320, 3976, 128)])
 @pytest.mark.parametrize("values", ["plain", "w tiny", "x huge", "x grows", "x falls", "w starts at 0", "x is 0", "x inf"])
@@ -126,6 +126,31 @@ def test_linear_f32_split_range(k, c_in, c_out, tile, values):
     ref, size = x.double() @ w.double().T, x.double().abs() @ w.double().abs().T
     bound = (2.0 ** -21 + c_in * 3 / 16 * 2.0 ** -24) * size + 2.0 ** -140
     assert bool(((y.double() - ref).abs() <= bound).all()), ((y.double() - ref).abs() / bound).max().item()
+
+
+# fp32 linear in 64-wide tiles, whose waves hold half of every 32 contraction indices each: infinities that one half or both halves meet, and
+# halves that cancel, of the smallest and of ragged contractions.  Bound as above: cancelling halves are exact to the sum of magnitudes.
+@pytest.mark.parametrize("k,c_in,c_out", [(4095, 64, 1032), (2049, 128, 512), (2000, 320, 504)])
+@pytest.mark.parametrize("channels,cancel", [((), True), ((3,), False), ((17,), False), ((0, 31), False), ((-1,), False)])
+def test_linear_f32_halves_of_the_contraction(k, c_in, c_out, channels, cancel):
+    assert ab.astraea_linear_plan(ab.F32, k, c_in, c_out)["tile_tokens"] == 64
+    g = torch.Generator(device=DEV).manual_seed(k + c_in)
+    x, w = torch.randn(k, c_in, device=DEV, generator=g), torch.randn(c_out, c_in, device=DEV, generator=g).abs() + 0.5
+    if cancel:
+        x = x.view(k, c_in // 32, 2, 16)
+        x[:, :, 1] = -x[:, :, 0]
+        x = x.reshape(k, c_in)
+        w = w.view(c_out, c_in // 32, 2, 16)[:, :, :1].expand(-1, -1, 2, -1).reshape(c_out, c_in).contiguous()
+    for c in channels:
+        x[k // 2, c] = math.inf
+    y = torch.full((k, c_out), math.nan, device=DEV)
+    ab.astraea_sparse_linear(x, w, None, None, k, y, x_is_compact=True)
+    torch.cuda.synchronize()
+    if channels:
+        assert bool((y[k // 2] == math.inf).all())
+        x[k // 2], y[k // 2] = 0.0, 0.0
+    bound = (2.0 ** -21 + c_in * 3 / 16 * 2.0 ** -24) * (x.double().abs() @ w.double().abs().T) + 2.0 ** -140
+    assert bool(((y.double() - x.double() @ w.double().T).abs() <= bound).all())
 
 
 # fp32 linear, magnitudes that differ between rows, between channels and inside a row: each result stands on its own row and feature
