@@ -613,7 +613,10 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
 
 // Combines the key-range shares of the split items: with m* = max_s m_s and w_s = 2^(m_s - m*),
 // O = sum_s w_s O_s / sum_s w_s l_s.  Workgroup (x, y) handles rows 32*y .. 32*y+31 of split item x, i.e. what wave y of
-// each share stored; its wave b takes head-dim 32*b .. 32*b+31.  Bound by reading the shares (4 KiB per wave and share).
+// each share stored; its wave b takes head-dim 32*b .. 32*b+31.  Bound by reading the shares (4 KiB per wave and share), which is why
+// their number S is a constant: all loads of a wave go out at once, one round trip instead of one per share for the offsets and one
+// per two for the sums.
+template <int S>
 __global__ __launch_bounds__(256) void merge_partials_kernel(const float *__restrict__ partial, AttnSchedule sch,
                                                              int32_t H, int64_t k_sel, const int32_t *__restrict__ idx_sel,
                                                              AttnOut out, float *__restrict__ lse_sel)
@@ -626,23 +629,42 @@ __global__ __launch_bounds__(256) void merge_partials_kernel(const float *__rest
     const int head = (int)(item / sch.q_tiles);
     const int64_t r0 = (int64_t)(item - (uint32_t)head * sch.q_tiles) * kBq + 32 * blockIdx.y;
     if (r0 >= k_sel) return;
-    const float *base = partial + blockIdx.x * sch.splits * (int64_t)kPartialFloats;
+    const float *base = partial + blockIdx.x * S * (int64_t)kPartialFloats;
     const int lane = threadIdx.x & (kWave - 1), b = threadIdx.x / kWave;
     const int row = 32 * blockIdx.y + (lane & 31);
+    float ms[S], ls[S];
+    floatx4 os[S][4];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const float *ps = base + s * (int64_t)kPartialFloats;
+        ms[s] = ps[kBq * D + row];
+        ls[s] = ps[kBq * D + kBq + row];
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            os[s][g] = *reinterpret_cast<const floatx4 *>(base + s * (int64_t)kPartialFloats + (((blockIdx.y * 4 + b) * 4 + g) * kWave + lane) * 4);
+    int32_t token[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int64_t rr = r0 + 16 * i + (threadIdx.x >> 4);
+        token[i] = out.cache ? idx_sel[rr < k_sel ? rr : k_sel - 1] : 0;
+    }
+    __builtin_amdgcn_sched_barrier(0);
     float m_star = -INFINITY;
-    for (uint32_t s = 0; s < sch.splits; ++s) m_star = fmaxf(m_star, base[s * (int64_t)kPartialFloats + kBq * D + row]);
+#pragma unroll
+    for (int s = 0; s < S; ++s) m_star = fmaxf(m_star, ms[s]);
     floatx4 acc[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) acc[g] = floatx4{0.f, 0.f, 0.f, 0.f};
     float l = 0.0f;
-#pragma unroll 2
-    for (uint32_t s = 0; s < sch.splits; ++s) {
-        const float *ps = base + s * (int64_t)kPartialFloats;
-        const float w = exp2f(ps[kBq * D + row] - m_star);
-        l += w * ps[kBq * D + kBq + row];
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-            acc[g] += w * *reinterpret_cast<const floatx4 *>(ps + (((blockIdx.y * 4 + b) * 4 + g) * kWave + lane) * 4);
+    for (int s = 0; s < S; ++s) {
+        const float w = exp2f(ms[s] - m_star);
+        l += w * ls[s];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) acc[g] += w * os[s][g];
     }
     const float inv = 1.0f / l;
     const uint32_t rows_lds = (uint32_t)(uintptr_t)rows;
@@ -659,7 +681,7 @@ __global__ __launch_bounds__(256) void merge_partials_kernel(const float *__rest
         const int n = 16 * i + (threadIdx.x >> 4), c = threadIdx.x & 15;
         const int64_t rr = r0 + n;
         if (rr >= k_sel) break;
-        store_row(out, H, head, rr, out.cache ? idx_sel[rr] : 0, c, rows_get(rows_lds, n, c), true);
+        store_row(out, H, head, rr, token[i], c, rows_get(rows_lds, n, c), true);
     }
     if (lse_sel && threadIdx.x < 32 && r0 + lane < k_sel)
         lse_sel[(r0 + lane) * H + head] = (m_star + log2f(l)) * 0.69314718055994530942f;
@@ -809,8 +831,10 @@ int launch_attn_bf16_d128(const void *q, const void *k, const void *v, int64_t N
     else go(attn_bf16_kernel<false, 2>, v);
     kernel_timer_end(stream);
     if (left > 0)
-        hipLaunchKernelGGL(merge_partials_kernel, dim3((unsigned)(left * kNumXcd), kBq / 32), dim3(256), 0, stream, partial, sch,
-                           H, k_sel, idx_sel, out, lse_sel);
+        with_shares((int)sch.splits, [&](auto shares) {
+            hipLaunchKernelGGL(merge_partials_kernel<decltype(shares)::value>, dim3((unsigned)(left * kNumXcd), kBq / 32), dim3(256), 0, stream,
+                               partial, sch, H, k_sel, idx_sel, out, lse_sel);
+        });
     return check_launch("astraea_sparse_attn_fwd(bf16)");
 }
 

@@ -1,5 +1,7 @@
 // Internal declarations shared by the HIP translation units of libastraea (gfx950 only).
 #pragma once
+#include <type_traits>
+
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
@@ -97,5 +99,19 @@ int launch_attn_f32(const void *q, const void *k, const void *v, int64_t N, int3
                     int64_t k_sel, int q_is_compact, float scale, const AttnOut &out, float *lse_sel, void *workspace,
                     size_t workspace_bytes, hipStream_t stream);
 size_t attn_f32_workspace_bytes(int64_t N, int32_t H, int32_t D, int64_t k_sel);
+
+// Calls f with the number of key-range shares of an item, 2 to 8, as a constant.
+template <class F> void with_shares(int shares, F &&f)
+{
+    switch (shares) {
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 5: f(std::integral_constant<int, 5>{}); break;
+    case 6: f(std::integral_constant<int, 6>{}); break;
+    case 7: f(std::integral_constant<int, 7>{}); break;
+    default: f(std::integral_constant<int, 8>{}); break;
+    }
+}
 
 }  // namespace astraea
