@@ -320,12 +320,14 @@ constexpr uint32_t kPad = 0xffffffffu;      // stands for no element; above ever
 
 // Writes the outputs of a workgroup whose wave w owns ITEMS * 64 consecutive elements, element first + 64 j in register j: ranks in
 // index order come from ballots.  g_before and e_before count the keys above / equal to T in front of the workgroup's elements.
-template <int ITEMS>
+// PARTS workgroups may share the elements: all count, and each writes the outputs of its part of a wave's registers.
+template <int ITEMS, int PARTS>
 __device__ __forceinline__ void emit_in_order(const uint32_t (&key)[ITEMS], const int32_t (&skip)[ITEMS], int first, int wave, int lane,
                                               uint32_t T, uint32_t need, uint32_t g_before, uint32_t e_before, uint32_t *wt_a,
                                               uint32_t *wt_b, int32_t *__restrict__ idx_sel, int32_t *__restrict__ idx_remain,
-                                              uint8_t *__restrict__ sel_mask, int32_t *__restrict__ skip_count)
+                                              uint8_t *__restrict__ sel_mask, int32_t *__restrict__ skip_count, int part)
 {
+    static_assert(ITEMS % PARTS == 0, "whole registers");
     auto above = [&](uint32_t kk) { return kk - (T + 1) < kPad - (T + 1); };       // kk > T and an element
     uint32_t mg = 0, me = 0;
 #pragma unroll
@@ -358,13 +360,15 @@ __device__ __forceinline__ void emit_in_order(const uint32_t (&key)[ITEMS], cons
             sel_before += eb < need ? eb : need;
             sel = sel || (key[j] == T && eb < need);
         }
-        if (sel)
-            idx_sel[sel_before] = i;
-        else if (idx_remain && key[j] != kPad)
-            idx_remain[(uint32_t)i - sel_before] = i;
-        if (key[j] != kPad) {
-            if (sel_mask) sel_mask[i] = sel ? 1 : 0;
-            if (skip_count) skip_count[i] = sel ? 0 : skip[j] + 1;
+        if (PARTS == 1 || j / (ITEMS / PARTS) == part) {
+            if (sel)
+                idx_sel[sel_before] = i;
+            else if (idx_remain && key[j] != kPad)
+                idx_remain[(uint32_t)i - sel_before] = i;
+            if (key[j] != kPad) {
+                if (sel_mask) sel_mask[i] = sel ? 1 : 0;
+                if (skip_count) skip_count[i] = sel ? 0 : skip[j] + 1;
+            }
         }
         g_before += (uint32_t)__popcll(gm);
         e_before += (uint32_t)__popcll(em);
@@ -477,7 +481,7 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(const float *
         need = k_rem;
     }
     // last read of wt_a before the barriers above (k == 0: for the key range, unused then)
-    emit_in_order(key, skip, first, wave, lane, T, need, 0u, 0u, wt_a, wt_b, idx_sel, idx_remain, sel_mask, skip_count);
+    emit_in_order<ITEMS, 1>(key, skip, first, wave, lane, T, need, 0u, 0u, wt_a, wt_b, idx_sel, idx_remain, sel_mask, skip_count, 0);
 }
 
 // ---- more scores than one workgroup takes: a launch for each of three digits and one for the outputs.  A workgroup owns 12288
@@ -489,6 +493,7 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(const float *
 // Bound by the start of four launches and, in each, the chain of load, histogram, scan and store (6 us apiece at 118800 scores).
 constexpr int kSlotItems = 12;
 constexpr int kSlotChunk = kSlotItems * kSmallThreads;
+constexpr int kEmitParts = 4;        // workgroups that share the writing of a chunk's outputs (one: 1.2 us slower at 118800 scores, every output)
 constexpr int64_t kSlotMax = 64 * (int64_t)kSlotChunk;
 constexpr int kSlotBits[3] = {11, 10, 11};
 constexpr int kSlotShift[3] = {21, 11, 0};
@@ -645,7 +650,8 @@ __global__ __launch_bounds__(kSmallThreads) void topk_slot_emit_kernel(const flo
 #pragma unroll
     for (int j = 0; j < kSlotItems; ++j)
         key[j] = first + j * kWave < N ? score_key(__uint_as_float(key[j])) : kPad;
-    emit_in_order(key, skip, first, wave, lane, T, need, above, equal, wt_a, wt_b, idx_sel, idx_remain, sel_mask, skip_count);
+    emit_in_order<kSlotItems, kEmitParts>(key, skip, first, wave, lane, T, need, above, equal, wt_a, wt_b, idx_sel, idx_remain, sel_mask,
+                                          skip_count, (int)blockIdx.y);
 }
 
 // ---- astraea_select_topk_static: the same selection for callers that cannot allocate.  The selection state,
@@ -747,7 +753,7 @@ int launch_select_topk(const float *score, int64_t N, int64_t k, int32_t *idx_se
             pass(topk_slot_kernel<1>, slots_a, slots_b);
             pass(topk_slot_kernel<2>, slots_b, slots_a);
         }
-        hipLaunchKernelGGL(topk_slot_emit_kernel, dim3(n_wg), dim3(kSmallThreads), 0, stream, score, (int32_t)N, (uint32_t)k, slots_a,
+        hipLaunchKernelGGL(topk_slot_emit_kernel, dim3(n_wg, kEmitParts), dim3(kSmallThreads), 0, stream, score, (int32_t)N, (uint32_t)k, slots_a,
                            records, idx_sel, idx_remain, sel_mask, skip_count);
         return check_launch("astraea_select_topk");
     }
