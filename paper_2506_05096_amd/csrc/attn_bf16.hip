@@ -199,7 +199,9 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
 {
     constexpr int kWaves = GROUPS * kGroupWaves;
     // [parity][K tile | V^T tile], 64 KiB, and 8 KiB per wave for its query rows and later its output rows: behind the tiles for one
-    // 8-wave workgroup per CU; from the second V tile's place on for two 4-wave ones, whose 160 KiB are the CU's whole LDS
+    // 8-wave workgroup per CU; from the second V tile's place on for two 4-wave ones, whose 160 KiB are the CU's whole LDS.  There the rows of
+    // waves 0 and 1 lie over the whole second V buffer: query rows are read before the barrier in front of the first tile, output
+    // rows are written past a barrier behind the last one (the vote's, or its own after a repeated sweep)
     constexpr uint32_t kRowsAt = GROUPS == 2 ? 2 * kBufBytes : kBufBytes + kTileBytes;
     __shared__ __attribute__((aligned(1024))) char lds[kRowsAt + kWaves * kRowsBytes + (GROUPS == 2 ? 64 : 0)];
     // one word per wave; the first K tile's place is free when they are used
@@ -563,6 +565,7 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
         first_tiles();
         wait_dma();
         sweep(std::true_type{});
+        if (GROUPS == 1) __syncthreads();            // every wave is past its last V tile, over which output rows are about to lie
         l_tot = xhalf_sum(l_run);
     }
     if (pslot >= 0) {

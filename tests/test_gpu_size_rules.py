@@ -251,6 +251,26 @@ def test_attn_bf16_half_workgroups(n, h, k, hot, scatter):
     test_attn_bf16_tiles(n, h, k, hot, scatter, None)
 
 
+# Four-wave workgroups whose output rows lie over the second V buffer, all of them sweeping again (logits 90 nats above the first key tile's) with
+# their last key tile in that buffer (even numbers of tiles) or in the first: values 2^10 times larger in the last tile show a wave
+# that read anything else there.  V direct and retiled.  Bars as above.
+@pytest.mark.parametrize("n,h,k", [(128, 8, 1024), (192, 8, 1000), (2048, 16, 2048), (1536, 8, 10000), (128, 4, 16500), (192, 4, 16500)])
+def test_attn_bf16_half_workgroups_that_sweep_again(n, h, k):
+    q, kc, vc = _attn_rise_case(n, h, k, 128, 90.0, torch.bfloat16, 64)
+    vc[n - 64:] *= 2.0 ** 10
+    lse = torch.full((k, h), math.nan, device=DEV)
+    out = torch.empty(k, h, 128, dtype=torch.bfloat16, device=DEV)
+    ws = torch.full((ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, 128),), 255, dtype=torch.uint8, device=DEV)
+    ab.astraea_sparse_attn_fwd(q, kc, vc, None, k, out, 1.0 / math.sqrt(128), q_is_compact=True, lse_sel=lse, workspace=ws)
+    torch.cuda.synchronize()
+    for i in range(h):
+        logits = q[:, i].double() @ kc[:, i].double().T.contiguous() / math.sqrt(128)
+        ref = torch.softmax(logits, 1) @ vc[:, i].double()
+        assert_rel_l2(out[:, i].double().cpu().numpy(), ref.cpu().numpy(), tag=f"head {i}")
+        want = torch.logsumexp(logits, 1)
+        assert ((lse[:, i].double() - want).abs() / want.abs().clamp(min=1.0)).max().item() <= 2.0 ** -9
+
+
 # The compact result and the cached rows from one call, against the two calls it stands for: whole and cut work items, both workgroup
 # sizes, cached buffers that the kernel writes itself and those that get a launch of their own (stride, alignment, memory shared with q).
 @pytest.mark.parametrize("dtype,n,h,d,k", [
