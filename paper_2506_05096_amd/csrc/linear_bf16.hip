@@ -123,6 +123,12 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
     int part_nt = nt;
     const LinearPart part = a.parts.of(part_nt);
     const int m0 = mt * kBm, n0 = part_nt * kBn;
+    // Every argument that is used from here on is loaded here, in one round trip.  The compiler would otherwise load each next to its first
+    // use, x inside the copying waves' branch: LDS reads and scalar loads share a counter and scalar loads come out of order, so with one
+    // pending at the loop header each step waits for all of its fragments in front of its first MFMA instead of for three at a time.
+    // 35640 rows 3072 -> 9216 / 3072 -> 3072 / 3072 -> 12288 / 12288 -> 3072, us: 1586 / 537 / 2198 / 2057 so, 1572 / 534 / 2189 / 2039 now
+    asm volatile("" ::"s"(part.w), "s"(part.bias), "s"(part.y), "s"(part.ldy), "s"(part.y_indexed), "s"(a.x), "s"(a.idx_sel), "s"(a.ldx),
+                 "s"(a.k_sel), "s"(a.c_in), "s"(a.c_out), "s"(a.n_rows), "s"(a.x_indexed), "s"(a.act));
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
