@@ -211,12 +211,13 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
     const uint32_t total_items = (uint32_t)H * sch.q_tiles;
     const uint32_t xcd = blockIdx.x % kNumXcd, slot = blockIdx.x / (kNumXcd * (2 / GROUPS));
     uint32_t item = xcd * sch.items_per_xcd + slot;
-    int64_t tile_begin = 0, tile_end = ntiles, pslot = -1;
+    int tile_begin = 0, tile_end = (int)ntiles;      // at most 2^25 tiles
+    int64_t pslot = -1;
     if (slot >= sch.full_items) {
         const uint32_t p = slot - sch.full_items, li = p / sch.splits, sp = p - li * sch.splits;
         item = xcd * sch.items_per_xcd + sch.full_items + li;
-        tile_begin = (int64_t)sp * sch.tiles_per_split;
-        tile_end = tile_begin + sch.tiles_per_split < ntiles ? tile_begin + sch.tiles_per_split : ntiles;
+        tile_begin = (int)(sp * sch.tiles_per_split);
+        tile_end = tile_begin + (int64_t)sch.tiles_per_split < ntiles ? tile_begin + (int)sch.tiles_per_split : (int)ntiles;
         pslot = (int64_t)(xcd * (sch.items_per_xcd - sch.full_items) + li) * sch.splits + sp;
     }
     if (item >= (xcd + 1) * sch.items_per_xcd || item >= total_items) return;
@@ -503,7 +504,7 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
         };
         // One tile that has a successor: VALU phase of tile j, then the MFMA phase (second product of tile j from
         // V buffer PAR, first product of tile j+1 from K buffer PAR ^ 1).
-        auto tile_step = [&](int64_t j, auto par_tag) __attribute__((always_inline)) {
+        auto tile_step = [&](int j, auto par_tag) __attribute__((always_inline)) {
             constexpr int PAR = decltype(par_tag)::value;
             if (GROUPS == 1 || grp == 1) {
                 dma_v_tile(j + 1, PAR ^ 1, wig, W4{});
@@ -519,15 +520,18 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
             PHASE_BARRIER();
         };
         // last tile: no next tile to prefetch or to start
-        auto last_step = [&](int64_t j, auto par_tag) __attribute__((always_inline)) {
+        auto last_step = [&](int j, auto par_tag) __attribute__((always_inline)) {
             softmax_tile(j, exact_tag);
             between_phases();
             mfma_phase(std::false_type{}, par_tag);
             if (GROUPS == 2) PHASE_BARRIER();
         };
-        // the loop is unrolled by two so that the buffer parity is a constant in each copy
-        int64_t j = tile_begin;
-        for (; j + 2 < tile_end; j += 2) {
+        // The loop is unrolled by two so that the buffer parity is a constant in each copy.  Tiles are counted in 32 bits: with 64-bit ones, whose
+        // comparisons take vector instructions, and the work split in 32, the two groups' ways through the loop are laid out worse: us 64-bit
+        // / 32-bit, code aligned as the build says: 35640 queries x 118800 keys x 24 heads 38648 / 38278, 11880 x 118800 13036 / 13006,
+        // 7020 x 17550 1177.5 / 1173.3, 7020 x 512 52.1 / 51.1, 36000 x 77 119 / 114
+        int j = tile_begin;
+        for (; j < tile_end - 2; j += 2) {
             tile_step(j, P0{});
             tile_step(j + 1, P1{});
         }
