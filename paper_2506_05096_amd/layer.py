@@ -62,15 +62,18 @@ class LayerStep:
         ab.astraea_scatter_update(t["out_cache"], self.o_sel.view(self.N, E), self.idx_sel, k, src_is_full=False)
 
     def step_attn_scatter(self, t: Dict[str, torch.Tensor], k: int, lse: Optional[torch.Tensor] = None) -> None:
-        """step_attn and step_scatter: one call where neither is a subclass's own."""
-        cls = type(self)
-        if cls.step_attn is not LayerStep.step_attn or cls.step_scatter is not LayerStep.step_scatter:
+        """step_attn and step_scatter: one call where both are the class's own."""
+        if not self._plain("step_attn", "step_scatter"):
             self.step_attn(t, k) if lse is None else self.step_attn(t, k, lse=lse)
             self.step_scatter(t, k)
             return
         ab.astraea_sparse_attn_scatter_fwd(t["q"], t["k_cache"], t["v_cache"], self.idx_sel, k, self.o_sel[:max(k, 1)],
                                            t["out_cache"], self.scale, q_is_compact=False, lse_sel=lse,
                                            workspace=self.attn_ws)
+
+    def _plain(self, *names: str) -> bool:
+        """Whether these steps are the ones defined in this module, not a subclass's, an instance's or a patched class's."""
+        return all(getattr(getattr(self, n), "__func__", None) is _STEPS[n] for n in names)
 
     def run(self, t: Dict[str, torch.Tensor], k: int) -> None:
         """The whole hot path for one batch of inputs; updates k_cache, v_cache and out_cache in place."""
@@ -118,9 +121,17 @@ class StatefulLayer(LayerStep):
         self.step_kv_refresh(t, k)
         if self.fused_update:
             self.step_attn_update(t, k, lse=self.lse_sel[:max(k, 1)])
-        else:
+            self.step_state(t, k)
+        elif self._plain("step_attn", "step_state", "step_scatter"):
             self.step_attn_scatter(t, k, lse=self.lse_sel[:max(k, 1)])
-        self.step_state(t, k)
+            self.step_state(t, k)
+        else:
+            self.step_attn(t, k, lse=self.lse_sel[:max(k, 1)])
+            self.step_state(t, k)            # sees the cached outputs of the step before
+            self.step_scatter(t, k)
+
+
+_STEPS = {"step_attn": LayerStep.step_attn, "step_scatter": LayerStep.step_scatter, "step_state": StatefulLayer.step_state}
 
 
 class TokenSparseBlock(LayerStep):
