@@ -636,7 +636,8 @@ __global__ __launch_bounds__(kSmallThreads) void topk_slot_emit_kernel(const flo
     for (int j = 0; j < kSlotItems; ++j) {
         const int i = first + j * kWave < N ? first + j * kWave : N - 1;
         key[j] = __float_as_uint(score[i]);
-        if (skip_count) skip[j] = skip_count[i];
+        // the counters that this workgroup writes, and no others: the chunk's other workgroups write theirs at the same time
+        if (skip_count && j / (kSlotItems / kEmitParts) == (int)blockIdx.y && first + j * kWave < N) skip[j] = skip_count[i];
     }
     uint32_t T = kPad - 1, need = 0, above = 0, equal = 0;
     if (k > 0) {
