@@ -320,9 +320,10 @@ constexpr uint32_t kPad = 0xffffffffu;      // stands for no element; above ever
 
 // Writes the outputs of a workgroup whose wave w owns ITEMS * 64 consecutive elements, element first + 64 j in register j: ranks in
 // index order come from ballots.  g_before and e_before count the keys above / equal to T in front of the workgroup's elements.
-// PARTS workgroups may share the elements: all count, and each writes the outputs of its part of a wave's registers.
+// PARTS workgroups may share the elements: all count, and each writes the outputs of its part of a wave's registers, whose counters
+// `skip` holds.
 template <int ITEMS, int PARTS>
-__device__ __forceinline__ void emit_in_order(const uint32_t (&key)[ITEMS], const int32_t (&skip)[ITEMS], int first, int wave, int lane,
+__device__ __forceinline__ void emit_in_order(const uint32_t (&key)[ITEMS], const int32_t (&skip)[ITEMS / PARTS], int first, int wave, int lane,
                                               uint32_t T, uint32_t need, uint32_t g_before, uint32_t e_before, uint32_t *wt_a,
                                               uint32_t *wt_b, int32_t *__restrict__ idx_sel, int32_t *__restrict__ idx_remain,
                                               uint8_t *__restrict__ sel_mask, int32_t *__restrict__ skip_count, int part)
@@ -367,7 +368,7 @@ __device__ __forceinline__ void emit_in_order(const uint32_t (&key)[ITEMS], cons
                 idx_remain[(uint32_t)i - sel_before] = i;
             if (key[j] != kPad) {
                 if (sel_mask) sel_mask[i] = sel ? 1 : 0;
-                if (skip_count) skip_count[i] = sel ? 0 : skip[j] + 1;
+                if (skip_count) skip_count[i] = sel ? 0 : skip[j % (ITEMS / PARTS)] + 1;
             }
         }
         g_before += (uint32_t)__popcll(gm);
@@ -631,13 +632,16 @@ __global__ __launch_bounds__(kSmallThreads) void topk_slot_emit_kernel(const flo
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int first = (int)blockIdx.x * kSlotChunk + wave * kSlotItems * kWave + lane;
     uint32_t key[kSlotItems];
-    int32_t skip[kSlotItems];
 #pragma unroll
-    for (int j = 0; j < kSlotItems; ++j) {
-        const int i = first + j * kWave < N ? first + j * kWave : N - 1;
-        key[j] = __float_as_uint(score[i]);
-        // the counters that this workgroup writes, and no others: the chunk's other workgroups write theirs at the same time
-        if (skip_count && j / (kSlotItems / kEmitParts) == (int)blockIdx.y && first + j * kWave < N) skip[j] = skip_count[i];
+    for (int j = 0; j < kSlotItems; ++j)
+        key[j] = __float_as_uint(score[first + j * kWave < N ? first + j * kWave : N - 1]);
+    // the counters that this workgroup writes, and no others: the chunk's other workgroups write theirs at the same time
+    constexpr int kMine = kSlotItems / kEmitParts;
+    int32_t skip[kMine];
+#pragma unroll
+    for (int j = 0; j < kMine; ++j) {
+        const int i = first + ((int)blockIdx.y * kMine + j) * kWave;
+        if (skip_count && i < N) skip[j] = skip_count[i];
     }
     uint32_t T = kPad - 1, need = 0, above = 0, equal = 0;
     if (k > 0) {
