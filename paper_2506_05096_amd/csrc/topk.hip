@@ -10,8 +10,8 @@
 //   * up to 32768: one workgroup, one launch, keys in registers.  (A single workgroup that streams more scores than
 //     it holds from L2 in every pass was measured too: one CU's loads are latency-bound, 129 us at 118800 scores.)
 //   * up to 786432, if the workspace holds a slot per workgroup: a launch per digit and one for the outputs.  us, indices
-//     alone / every output, by this and by the next form: 32769 scores 24 / 25 and 34 / 36, 118800 25 / 25 and 42 / 44, 262144
-//     30 / 30 and 56 / 58, 786432 40 / 41 and 107 / 111 (scores of one magnitude; others 1 - 2 us less).  The limit bounds
+//     alone / every output, by this and by the next form: 33000 scores 23 / 23 and 34 / 36, 118800 24 / 24 and 43 / 45, 262144
+//     27 / 28 and 57 / 59, 786432 36 / 37 and 111 / 115 (scores of one magnitude; others 1 - 2 us less).  The limit bounds
 //     the slots: every workgroup reads all of them in every launch.
 //   * more, or a smaller workspace: three histogram launches (11 + 11 + 10 bits) whose counts are merged by integer
 //     global atomics (order-independent) and whose last workgroup (atomic ticket) resolves the digit, a count and an emit
@@ -494,7 +494,14 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(const float *
 // Bound by the start of four launches and, in each, the chain of load, histogram, scan and store (6 us apiece at 118800 scores).
 constexpr int kSlotItems = 12;
 constexpr int kSlotChunk = kSlotItems * kSmallThreads;
-constexpr int kEmitParts = 4;        // workgroups that share the writing of a chunk's outputs (one: 1.2 us slower at 118800 scores, every output)
+// Workgroups that share the writing of a chunk's outputs.  Each repeats the sums over the slots, which only pays while every one of them has a
+// CU of its own: four, 256 at the most scores that come here.  us, every output, with 1 / 2 / 4 / 6 / 12: 33000 scores 25.2 / 24.4 / 23.8 /
+// 23.6 / 23.3, 118800 25.8 / 24.9 / 24.3 / 24.2 / 23.9, 262144 30.7 / 29.9 / 29.4 / 29.4 / 36.1, 786432 40.8 / 40.4 / 40.0 / 49.9 / 60.9
+constexpr int kEmitParts = 4;
+// Slots that a thread has in flight.  3 to 64 of them are added up: more in flight save round trips, but the branches around those that are
+// not there are passed.  us, indices alone, with 10 / 16 / 22 / 32: 33000 scores 22.5 / 23.0 / 23.7 / 25.8, 118800 23.8 / 24.0 / 24.6 / 26.7, 262144
+// 27.9 / 27.4 / 26.3 / 27.9, 786432 38.6 / 36.3 / 36.0 / 36.7; 16 is best over the range
+constexpr int kSlotBatch = 16;
 constexpr int64_t kSlotMax = 64 * (int64_t)kSlotChunk;
 constexpr int kSlotBits[3] = {11, 10, 11};
 constexpr int kSlotShift[3] = {21, 11, 0};
@@ -525,19 +532,20 @@ __device__ __forceinline__ void resolve_digit(const uint32_t *__restrict__ slots
     const int t = threadIdx.x;
     uint32_t lo = 0, hi = 0, pre_lo = 0, pre_hi = 0;       // bins 2t and 2t + 1: over all workgroups, over those in front
     if (t < WORDS) {
-        constexpr int kBatch = 10;
-        for (int w0 = 0; w0 < n_wg; w0 += kBatch) {
-            uint32_t v[kBatch];
+        for (int w0 = 0; w0 < n_wg; w0 += kSlotBatch) {
+            uint32_t v[kSlotBatch];
 #pragma unroll
-            for (int j = 0; j < kBatch; ++j) v[j] = slots[(w0 + j < n_wg ? w0 + j : n_wg - 1) * WORDS + t];
+            for (int j = 0; j < kSlotBatch; ++j)
+                if (w0 + j < n_wg) v[j] = slots[(w0 + j) * WORDS + t];
 #pragma unroll
-            for (int j = 0; j < kBatch; ++j) {
-                const uint32_t u = w0 + j < n_wg ? v[j] : 0u;
-                pre_lo += w0 + j < me ? u & 0xffffu : 0u;
-                pre_hi += w0 + j < me ? u >> 16 : 0u;
-                lo += u & 0xffffu;
-                hi += u >> 16;
-            }
+            for (int j = 0; j < kSlotBatch; ++j)
+                if (w0 + j < n_wg) {
+                    const uint32_t u = v[j];
+                    pre_lo += w0 + j < me ? u & 0xffffu : 0u;
+                    pre_hi += w0 + j < me ? u >> 16 : 0u;
+                    lo += u & 0xffffu;
+                    hi += u >> 16;
+                }
         }
         sh.tot[t] = lo;
         sh.pre[t] = pre_lo;

@@ -502,7 +502,7 @@ def test_topk_sizes(n, kind):
 # histograms in one place (more scores, smaller workspaces): edges of the workgroups' runs and of both ranges, against the oracle.
 @pytest.mark.parametrize("kind", ["narrow", "ties", "extremes"])
 @pytest.mark.parametrize("n,small", [(32769, False), (36863, False), (36864, False), (36865, False), (36865, True), (118800, True),
-                                     (135169, False), (786432, False), (786433, False)])
+                                     (135169, False), (196608, False), (196609, False), (786432, False), (786433, False)])
 def test_topk_of_several_workgroups(n, small, kind):
     g = torch.Generator().manual_seed(n)
     s = 5.54 + 0.1 * torch.randn(n, generator=g)
