@@ -372,6 +372,15 @@ int astraea_check_indices(const int32_t *idx_sel, int64_t k_sel, int64_t N, int3
 int astraea_attn_plan(int64_t N, int32_t H, int64_t k_sel, int64_t plan_out[8]);
 
 /*
+ * The same of the fp32 attention with a workspace of workspace_bytes (0: none) and keys less than 4 GiB apart per 64.  A work item
+ * is one head times one tile of 256 or 128 selected queries, spread over the XCDs as above; either all items are cut along the
+ * keys, or those past full_items, or none, as far as the workspace holds their partial results.
+ * plan_out (host, 8 entries): queries per workgroup, q_tiles, items_per_xcd, full_items, splits, tiles_per_split (64 keys
+ * each), workgroups launched, bytes of partial results.
+ */
+int astraea_attn_plan_f32(int64_t N, int32_t H, int32_t D, int64_t k_sel, size_t workspace_bytes, int64_t plan_out[8]);
+
+/*
  * The tile astraea_sparse_linear would give a workgroup for k_sel rows, c_in -> c_out.  Host only, nothing is
  * enqueued; for inspection and tests.  plan_out (host, 3 entries): output features per tile, tokens per
  * tile, tiles.

@@ -388,6 +388,16 @@ int astraea_attn_plan(int64_t N, int32_t H, int64_t k_sel, int64_t plan_out[8])
     return attn_bf16_plan(N, H, k_sel, plan_out);
 }
 
+int astraea_attn_plan_f32(int64_t N, int32_t H, int32_t D, int64_t k_sel, size_t workspace_bytes, int64_t plan_out[8])
+{
+    if (!plan_out) return fail(ASTRAEA_ERR_INVALID, "astraea_attn_plan_f32: NULL output");
+    if (N <= 0 || N > kMaxTokens || H <= 0 || H > 65535 || k_sel <= 0 || k_sel > kMaxTokens)
+        return fail(ASTRAEA_ERR_INVALID, "astraea_attn_plan_f32: N=%lld, H=%d, k_sel=%lld out of range", (long long)N, (int)H,
+                    (long long)k_sel);
+    if (D != 64 && D != 128) return fail(ASTRAEA_ERR_UNSUPPORTED, "astraea_attn_plan_f32: no kernel for head_dim %d", (int)D);
+    return attn_f32_plan(N, H, D, k_sel, workspace_bytes, plan_out);
+}
+
 int astraea_linear_plan(astraea_dtype dt, int64_t k_sel, int64_t c_in, int64_t c_out, int64_t plan_out[3])
 {
     if (!plan_out) return fail(ASTRAEA_ERR_INVALID, "astraea_linear_plan: NULL output");

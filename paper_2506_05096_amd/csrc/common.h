@@ -99,6 +99,7 @@ int launch_attn_f32(const void *q, const void *k, const void *v, int64_t N, int3
                     int64_t k_sel, int q_is_compact, float scale, const AttnOut &out, float *lse_sel, void *workspace,
                     size_t workspace_bytes, hipStream_t stream);
 size_t attn_f32_workspace_bytes(int64_t N, int32_t H, int32_t D, int64_t k_sel);
+int attn_f32_plan(int64_t N, int32_t H, int32_t D, int64_t k_sel, size_t workspace_bytes, int64_t plan[8]);
 
 // Calls f with the number of key-range shares of an item, 2 to 8, as a constant.
 template <class F> void with_shares(int shares, F &&f)

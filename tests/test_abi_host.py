@@ -299,6 +299,47 @@ def test_attention_plan_work_follows_the_budget():
     assert all(abs(cost[pct] / (unit * pct) - 1) < 0.10 for pct in cost), cost
 
 
+def test_fp32_attention_plan_counts():
+    """Every (head, query tile) has a place, shares cover the key tiles and none is empty, partial rows fit the bytes named and those the
+    workspace; all items, those past the last whole round and none are cut, in workgroups of either size."""
+    import random
+    rnd = random.Random(0)
+    cases = [(4096, 8, 64, 2048), (6016, 24, 64, 5461), (600, 24, 64, 2700), (8192, 8, 64, 33), (33, 8, 64, 8192), (1, 1, 128, 1)]
+    cases += [(rnd.randint(1, 7000), rnd.randint(1, 24), rnd.choice((64, 128)), rnd.randint(1, 9000)) for _ in range(300)]
+    seen = set()
+    for N, H, D, k in cases:
+        for room in (0, ab.workspace_bytes(ab.OP_SPARSE_ATTN, N, k, H, D), 1 << 40):
+            p = ab.astraea_attn_plan_f32(N, H, D, k, room)
+            bq, ipx, full, s, tps = (p[n] for n in ("queries_per_workgroup", "items_per_xcd", "full_items", "splits", "tiles_per_split"))
+            tiles, left = -(-N // 64), ipx - full
+            assert bq in (128, 256) and p["q_tiles"] == -(-k // bq) and ipx == -(-p["q_tiles"] * H // 8)
+            assert p["workgroups"] == 8 * (full + left * s) and p["workgroups"] * 2 * bq < 1 << 32
+            assert p["partial_bytes"] <= room and (s > 1) == (left > 0) == (p["partial_bytes"] > 0)
+            assert 1 <= s <= 8 and (s - 1) * tps < tiles <= s * tps                       # no empty share
+            rows = s * (k * H if full == 0 else left * 8 * bq)
+            assert s == 1 or p["partial_bytes"] == rows * (D + 4) * 4
+            seen.add((bq, "none" if s == 1 else "all" if full == 0 else "tail"))
+    assert seen == {(b, c) for b in (128, 256) for c in ("none", "all", "tail")}, seen
+
+
+def test_fp32_attention_grid_limits():
+    """2^24 - 8 items of 128 queries are accepted, in a grid of fewer than 2^32 threads, and more are refused; the head count is at
+    most 65535."""
+    assert ab.astraea_attn_plan_f32(1, 65279, 64, 257 * 128, 0)["queries_per_workgroup"] == 128      # 129 x 65279 items of 256 do not fit
+    assert ab.astraea_attn_plan_f32(1, 65535, 64, 256 * 128, 0)["workgroups"] * 256 < 1 << 32
+    with pytest.raises(Exception, match="grid too large"):
+        ab.astraea_attn_plan_f32(1, 65535, 64, 257 * 128, 0)
+
+
+def test_fp32_attention_plan_rejects_bad_arguments(L):
+    out = (C.c_int64 * 8)()
+    f = L.astraea_attn_plan_f32
+    assert f(0, 1, 64, 1, 0, out) == ab.ERR_INVALID and f(10, 0, 64, 1, 0, out) == ab.ERR_INVALID
+    assert f(10, 65536, 64, 1, 0, out) == ab.ERR_INVALID and f(10, 1, 64, 0, 0, out) == ab.ERR_INVALID
+    assert f(10, 1, 96, 1, 0, out) == ab.ERR_UNSUPPORTED and f(10, 1, 64, 1, 0, None) == ab.ERR_INVALID
+    assert f(10, 1, 64, 1, 0, out) == ab.OK
+
+
 def test_check_indices_rejects_bad_arguments(L):
     f = L.astraea_check_indices
     assert f(FAKE, 5, 0, FAKE, None) == ab.ERR_INVALID
