@@ -365,9 +365,11 @@ int astraea_check_indices(const int32_t *idx_sel, int64_t k_sel, int64_t N, int3
  * times one tile of 256 selected queries, head-major; XCD x (of 8) owns items
  * [x*items_per_xcd, (x+1)*items_per_xcd).  The first full_items of each XCD sweep all key tiles
  * (64 keys each); every later item is cut into `splits` consecutive key ranges of tiles_per_split
- * tiles, each run by its own workgroup, whose partial results a second kernel combines.
+ * tiles, whose partial results a second kernel combines.  So an XCD has full_items + (items_per_xcd - full_items) * splits
+ * pieces of work.  Either one workgroup runs a piece (workgroup x + 8 p piece p of XCD x), or, where few items or short sweeps
+ * make that faster, two do, with half of the queries each (workgroups x + 16 p and x + 16 p + 8 its first and second 128).
  * plan_out (host, 8 entries): q_tiles, items_per_xcd, full_items, splits, tiles_per_split,
- * workgroups launched, key tiles, partial-result slots the workspace holds.
+ * workgroups launched (8 or 16 per piece of an XCD), key tiles, partial-result slots the workspace holds.
  */
 int astraea_attn_plan(int64_t N, int32_t H, int64_t k_sel, int64_t plan_out[8]);
 

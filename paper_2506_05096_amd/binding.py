@@ -323,7 +323,10 @@ def astraea_attn_plan(N: int, H: int, k_sel: int) -> dict:
     _check(lib().astraea_attn_plan(N, H, k_sel, out))
     names = ("q_tiles", "items_per_xcd", "full_items", "splits", "tiles_per_split", "workgroups", "key_tiles",
              "partial_slots")
-    return dict(zip(names, (int(v) for v in out)))
+    plan = dict(zip(names, (int(v) for v in out)))
+    pieces = plan["full_items"] + (plan["items_per_xcd"] - plan["full_items"]) * plan["splits"]
+    plan["queries_per_workgroup"] = 256 * 8 * pieces // plan["workgroups"]
+    return plan
 
 
 def astraea_attn_plan_f32(N: int, H: int, D: int, k_sel: int, workspace_bytes: int) -> dict:

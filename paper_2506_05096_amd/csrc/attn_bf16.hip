@@ -780,7 +780,7 @@ int attn_bf16_plan(int64_t N, int32_t H, int64_t k_sel, int64_t plan[8])
     plan[2] = sch.full_items;
     plan[3] = sch.splits;
     plan[4] = sch.tiles_per_split;
-    plan[5] = slots * kNumXcd;
+    plan[5] = slots * kNumXcd * (half_workgroups(H, k_sel, slots, sch) ? 2 : 1);
     plan[6] = (N + kBk - 1) / kBk;
     plan[7] = (int64_t)kNumXcd * kMaxSharesPerXcd;
     return ASTRAEA_OK;

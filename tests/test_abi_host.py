@@ -234,16 +234,20 @@ def test_synthetic_workloads_have_the_configured_shapes():
 
 # ------------------------------------------------------ budget-aware launch plan --
 
-def _covered(plan, H):
+def _covered(plan, H, k):
     """Walks every workgroup of the plan the way the header describes it and returns, per work item, the list of
-    key-tile ranges its workgroups take, plus the partial-result slots used."""
+    key-tile ranges its workgroups take, plus the partial-result slots used.  Where two workgroups share a piece, every half with
+    queries is taken once, with the same ranges and slots: one half stands for both in what is returned."""
     q_tiles, ipx, full, splits, tps, wgs, key_tiles, _ = (plan[n] for n in (
         "q_tiles", "items_per_xcd", "full_items", "splits", "tiles_per_split", "workgroups", "key_tiles",
         "partial_slots"))
     total = q_tiles * H
+    parts = 256 // plan["queries_per_workgroup"]
+    assert parts in (1, 2) and wgs == 8 * parts * (full + (ipx - full) * splits)
     ranges, slots = {}, []
+    halves = {}
     for wg in range(wgs):
-        xcd, slot = wg % 8, wg // 8
+        xcd, slot, half = wg % 8, wg // (8 * parts), wg // 8 % parts
         if slot < full:
             item, lo, hi, ps = xcd * ipx + slot, 0, key_tiles, None
         else:
@@ -254,9 +258,15 @@ def _covered(plan, H):
             ps = (xcd * (ipx - full) + li) * splits + sp
         if item >= (xcd + 1) * ipx or item >= total:
             continue
+        if item % q_tiles * 256 + half * 128 < k:
+            halves.setdefault((item, lo, hi, ps), []).append(half)
+        if half:
+            continue
         ranges.setdefault(item, []).append((lo, hi))
         if ps is not None:
             slots.append(ps)
+    for (item, *_), taken in halves.items():
+        assert taken == list(range(min(parts, -(-(k - item % q_tiles * 256) // 128)))), (item, taken)
     return ranges, slots
 
 
@@ -266,10 +276,13 @@ def test_attention_plan_covers_every_item_and_key_tile_once():
     cases = [(118800, 24, k) for k in (1, 255, 256, 257, 11880, 35640, 118800)]
     cases += [(17550, 24, 7020), (16384, 24, 4096), (1, 1, 1), (63, 2, 63), (77, 3, 1000), (64, 65535, 1)]
     cases += [(rnd.randint(1, 5000), rnd.randint(1, 40), rnd.randint(1, 60000)) for _ in range(300)]
+    cases += [(4000, 1, 30), (4000, 2, 300)]                       # shares of halves
+    sizes = set()
     for N, H, k in cases:
         plan = ab.astraea_attn_plan(N, H, k)
         assert plan["q_tiles"] == -(-k // 256) and plan["key_tiles"] == -(-N // 64), (N, H, k)
-        ranges, slots = _covered(plan, H)
+        ranges, slots = _covered(plan, H, k)
+        sizes.add((plan["queries_per_workgroup"], plan["splits"] > 1))
         total = plan["q_tiles"] * H
         assert sorted(ranges) == list(range(total)), (N, H, k)                 # every (head, query tile) is taken
         for item, rs in ranges.items():
@@ -283,6 +296,7 @@ def test_attention_plan_covers_every_item_and_key_tile_once():
         left = plan["items_per_xcd"] - plan["full_items"]
         assert 0 <= left < 32 and left * plan["splits"] <= 64 and 1 <= plan["splits"] <= 8
         assert plan["full_items"] % 32 == 0 or left == 0
+    assert sizes == {(128, False), (128, True), (256, False), (256, True)}
 
 
 def test_attention_plan_work_follows_the_budget():
