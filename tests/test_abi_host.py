@@ -178,6 +178,52 @@ def test_sparse_linear_rejects_bad_arguments(L):
     assert call(k_sel=0, x=None, w=None, y=None, idx=None) == ab.OK
 
 
+def test_sparse_attn_scatter_rejects_bad_arguments(L):
+    f = L.astraea_sparse_attn_scatter_fwd
+
+    def call(dt=ab.BF16, N=100, H=2, D=128, idx=FAKE, k_sel=10, compact=0, scale=0.1, q=FAKE, o=FAKE, cache=FAKE, rows=100, stride=256):
+        return f(q, FAKE, FAKE, dt, N, H, D, 256, 128, 256, 128, idx, k_sel, compact, scale, o, cache, rows, stride, None, None, 0, None)
+
+    assert call(dt=7) == ab.ERR_UNSUPPORTED and call(dt=ab.F32, D=96) == ab.ERR_UNSUPPORTED
+    assert call(stride=248) == ab.ERR_INVALID                   # narrower than H*D
+    assert call(rows=9) == ab.ERR_INVALID                       # fewer cached rows than selected ones
+    assert call(rows=-1) == ab.ERR_INVALID and call(k_sel=-1) == ab.ERR_INVALID
+    assert call(k_sel=101, rows=200) == ab.ERR_INVALID          # more gathered queries than tokens
+    assert call(idx=None, compact=1) == ab.ERR_INVALID          # the index list also says where rows go
+    assert call(idx=FAKE + 2) == ab.ERR_INVALID
+    assert call(o=None) == ab.ERR_INVALID and call(o=FAKE + 8) == ab.ERR_INVALID
+    assert call(cache=None) == ab.ERR_INVALID and call(cache=FAKE + 1) == ab.ERR_INVALID
+    assert call(q=None) == ab.ERR_INVALID and call(scale=0.0) == ab.ERR_INVALID
+    assert call() == ab.ERR_WORKSPACE                           # everything else valid: the bf16 path wants its workspace
+    assert call(k_sel=0, q=None, o=None, cache=None, idx=None) == ab.OK
+
+
+def test_sparse_linear_group_rejects_bad_arguments(L):
+    f = L.astraea_sparse_linear_group
+    good = dict(w=FAKE, bias=None, y=FAKE, y_row_stride=64, y_is_compact=1)
+
+    def call(*changes, n_parts=None, parts=True, dt=ab.BF16, N=100, cin=128, cout=64, xs=128, idx=FAKE, k_sel=10, xc=0, act=0, x=FAKE):
+        arr = (ab.LinearPart * max(len(changes), 1))(*[ab.LinearPart(*{**good, **c}.values()) for c in changes])
+        return f(x, dt, N, cin, cout, xs, idx, k_sel, xc, act, arr if parts else None, len(changes) if n_parts is None else n_parts, None)
+
+    assert call({}, n_parts=0) == ab.ERR_INVALID and call({}, {}, {}, {}) == ab.ERR_INVALID and call({}, n_parts=-1) == ab.ERR_INVALID
+    assert call({}, parts=False) == ab.ERR_INVALID
+    for i in range(3):                                          # the same mistakes in each of three layers
+        def one(**c):
+            return [c if j == i else {} for j in range(3)]
+        assert call(*one(w=None)) == ab.ERR_INVALID and call(*one(y=None)) == ab.ERR_INVALID
+        assert call(*one(w=FAKE + 8)) == ab.ERR_INVALID and call(*one(y=FAKE + 8)) == ab.ERR_INVALID
+        assert call(*one(bias=FAKE + 4)) == ab.ERR_INVALID
+        assert call(*one(y_row_stride=56)) == ab.ERR_INVALID and call(*one(y_row_stride=68)) == ab.ERR_INVALID
+        assert call(*one(y_is_compact=0), idx=None, xc=1) == ab.ERR_INVALID          # its rows must be placed
+    three = ({}, {}, {})
+    assert call(*three, dt=9) == ab.ERR_UNSUPPORTED and call(*three, act=2) == ab.ERR_UNSUPPORTED
+    assert call(*three, cin=96, xs=96) == ab.ERR_UNSUPPORTED and call(*three, cout=60) == ab.ERR_UNSUPPORTED
+    assert call(*three, xs=64) == ab.ERR_INVALID and call(*three, idx=None) == ab.ERR_INVALID
+    assert call(*three, k_sel=101) == ab.ERR_INVALID and call(*three, x=None) == ab.ERR_INVALID
+    assert call(*three, k_sel=0, x=None, idx=None) == ab.OK
+
+
 def test_row_movers_reject_bad_arguments(L):
     sc, ga = L.astraea_scatter_update, L.astraea_gather_rows
     assert sc(FAKE, FAKE, 5, 10, 8, 8, 8, FAKE, 3, 0, None) == ab.ERR_UNSUPPORTED

@@ -163,6 +163,61 @@ def test_sparse_linear_reads_and_writes_stay_inside_the_buffers():
     assert close(got[idx[good]])
 
 
+# The compact rows and the cached ones from one call, against the two calls it stands for: cached buffers with fewer, as many and more rows
+# than there are keys, whose rows past the keys an index may name, written by the attention itself and (stride) by a launch of their own.
+@pytest.mark.parametrize("dtype,d,h,k", [(torch.bfloat16, 128, 2, 300), (torch.bfloat16, 128, 40, 690), (torch.float32, 64, 2, 300), (torch.float32, 128, 24, 690)])
+@pytest.mark.parametrize("extra_rows", [-2, 0, 2])
+@pytest.mark.parametrize("pad", [0, 3])
+def test_attention_with_cached_rows_stays_inside_the_buffers(dtype, d, h, k, extra_rows, pad):
+    n, e = 700, h * d
+    g = torch.Generator().manual_seed(d + k)
+    idx, good = _indices(n, k, seed=d)
+    didx = torch.from_numpy(idx).to(DEV)
+    _, _, q = _guarded(n, e, dtype, g)
+    kk, vv = (torch.randn(n, h, d, generator=g).to(dtype).to(DEV) for _ in range(2))
+    rows = n + extra_rows
+    big = torch.randn(n + 2 * G, e + pad, generator=g).to(dtype).to(DEV)
+    want = big.clone()
+    wsb = ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d)
+    ws = torch.empty(max(wsb, 256), dtype=torch.uint8, device=DEV)
+    o0, o1 = (torch.full((k, h, d), math.nan, dtype=dtype, device=DEV) for _ in range(2))
+    ab.astraea_sparse_attn_fwd(q.view(n, h, d), kk, vv, didx, k, o0, d ** -0.5, workspace=ws)
+    ab.astraea_scatter_update(want[G:G + rows, :e], o0.view(k, e), didx, k)
+    ab.astraea_sparse_attn_scatter_fwd(q.view(n, h, d), kk, vv, didx, k, o1, big[G:G + rows, :e], d ** -0.5, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(o0, o1) and bool(o0.isfinite().all()) and torch.equal(big, want)
+
+
+# Three layers of one input, placed and compact results: rows of bad indices are written nowhere, whichever part they belong to.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("k,c_in,c_out", [(300, 128, 264), (490, 512, 1032)])
+def test_linear_group_stays_inside_the_buffers(dtype, k, c_in, c_out):
+    n = 500
+    g = torch.Generator().manual_seed(c_out)
+    idx, good = _indices(n, k, seed=c_out)
+    didx = torch.from_numpy(idx).to(DEV)
+    _, xhost, x = _guarded(n, c_in, dtype, g)
+    ws = [(torch.randn(c_out, c_in, generator=g) / math.sqrt(c_in)).to(dtype) for _ in range(3)]
+    bufs = [_guarded(n, c_out, dtype, g) for _ in range(3)]
+    compact = torch.zeros(k, c_out, dtype=dtype, device=DEV)
+    for placed in ((0, 1, 2), (1,)):
+        for big, host, _ in bufs:
+            big.copy_(torch.from_numpy(host.view(np.int16)).view(dtype) if dtype == torch.bfloat16 else torch.from_numpy(host))
+        ab.astraea_sparse_linear_group(x, [(w.to(DEV), None, bufs[i][2] if i in placed else compact, i not in placed)
+                                           for i, w in enumerate(ws[:len(placed) if len(placed) == 3 else 2])], didx, k)
+        torch.cuda.synchronize()
+        for i, (big, host, y) in enumerate(bufs):
+            got = to_np(y)
+            if i not in placed:
+                assert np.array_equal(to_np(big), host)
+                continue
+            want = oracle.sparse_linear(xhost[G:G + n], to_np(ws[i]), idx[good])
+            assert _guards_untouched(big, host, n)
+            rest = np.setdiff1d(np.arange(n), idx[good])
+            assert np.array_equal(got[rest], host[G:G + n][rest])
+            assert_rel_l2(_f64(got[idx[good]]), want, tol=1e-2 if dtype == torch.bfloat16 else 1e-5, tag=f"part {i}")
+
+
 def test_check_indices_counts_what_breaks_the_contract():
     n = 5000
     counts = torch.full((2,), -7, dtype=torch.int32, device=DEV)

@@ -241,14 +241,18 @@ def test_attn_bf16_tiles(n, h, k, hot, scatter, splits):
 
 
 # Workgroups of four waves, 128 queries: where every half of an item gets a CU of its own (up to 256 halves), and in sweeps of up to 24 key
-# tiles of more than 32 items per XCD.  Both sides of both lines, with rows that send a workgroup through its sweep again, a second
-# half without queries, and one key tile.
-@pytest.mark.parametrize("n,h,k,hot,scatter", [
-    (2048, 16, 2048, True, True), (2100, 16, 2049, True, True), (1536, 8, 8300, True, False), (1537, 8, 8300, True, False),
-    (60, 24, 3000, False, False), (65, 24, 2900, True, False), (500, 8, 128, True, True), (500, 8, 129, True, True), (64, 40, 1800, True, False),
+# tiles of more than 32 items per XCD, none of them cut.  Both sides of each line (`queries` is what the launch says), with rows that send a
+# workgroup through its sweep again, a second half without queries, shares of halves, and one key tile; V direct and retiled.
+@pytest.mark.parametrize("n,h,k,hot,scatter,queries,splits", [
+    (2048, 16, 2048, True, True, 128, 1), (2100, 16, 2049, True, True, 256, 1),
+    (1536, 8, 10000, True, False, 128, 1), (1537, 8, 10000, True, False, 256, 1), (1536, 8, 8300, True, False, 256, 8),
+    (60, 24, 3000, False, False, 128, 1), (65, 24, 2900, True, False, 128, 1), (64, 40, 1800, True, False, 128, 1),
+    (500, 8, 128, True, True, 128, 1), (500, 8, 129, True, True, 128, 1), (4000, 2, 300, True, True, 128, 8), (4200, 4, 4200, True, True, 256, 3),
+    (1536, 4, 20000, True, False, 128, 1), (1537, 4, 20000, True, False, 256, 1), (77, 8, 17000, True, False, 128, 1),
 ])
-def test_attn_bf16_half_workgroups(n, h, k, hot, scatter):
-    test_attn_bf16_tiles(n, h, k, hot, scatter, None)
+def test_attn_bf16_half_workgroups(n, h, k, hot, scatter, queries, splits):
+    assert ab.astraea_attn_plan(n, h, k)["queries_per_workgroup"] == queries
+    test_attn_bf16_tiles(n, h, k, hot, scatter, splits)
 
 
 # Four-wave workgroups whose output rows lie over the second V buffer, all of them sweeping again (logits 90 nats above the first key tile's) with
@@ -256,6 +260,8 @@ def test_attn_bf16_half_workgroups(n, h, k, hot, scatter):
 # that read anything else there.  V direct and retiled.  Bars as above.
 @pytest.mark.parametrize("n,h,k", [(128, 8, 1024), (192, 8, 1000), (2048, 16, 2048), (1536, 8, 10000), (128, 4, 16500), (192, 4, 16500)])
 def test_attn_bf16_half_workgroups_that_sweep_again(n, h, k):
+    plan = ab.astraea_attn_plan(n, h, k)
+    assert plan["queries_per_workgroup"] == 128 and plan["splits"] == 1
     q, kc, vc = _attn_rise_case(n, h, k, 128, 90.0, torch.bfloat16, 64)
     vc[n - 64:] *= 2.0 ** 10
     lse = torch.full((k, h), math.nan, device=DEV)
@@ -273,12 +279,17 @@ def test_attn_bf16_half_workgroups_that_sweep_again(n, h, k):
 
 # The compact result and the cached rows from one call, against the two calls it stands for: whole and cut work items, both workgroup
 # sizes, cached buffers that the kernel writes itself and those that get a launch of their own (stride, alignment, memory shared with q).
-@pytest.mark.parametrize("dtype,n,h,d,k", [
-    (torch.bfloat16, 2025, 24, 128, 608), (torch.bfloat16, 300, 3, 128, 77), (torch.bfloat16, 300, 30, 128, 300),
-    (torch.float32, 700, 8, 64, 60), (torch.float32, 97, 2, 128, 97),
+@pytest.mark.parametrize("dtype,n,h,d,k,queries,splits", [
+    (torch.bfloat16, 2025, 24, 128, 608, 256, 3), (torch.bfloat16, 2100, 16, 128, 2049, 256, 1), (torch.bfloat16, 300, 3, 128, 77, 128, 1),
+    (torch.bfloat16, 300, 30, 128, 300, 128, 1), (torch.bfloat16, 4000, 2, 128, 300, 128, 8),
+    (torch.float32, 700, 8, 64, 60, 128, 2), (torch.float32, 97, 2, 128, 97, 128, 1), (torch.float32, 2500, 8, 128, 2500, 256, 3),
+    (torch.float32, 2700, 24, 64, 2700, 256, 8),
 ])
 @pytest.mark.parametrize("cache", ["plain", "padded", "odd stride", "misaligned", "shares q"])
-def test_attn_result_and_cached_rows(dtype, n, h, d, k, cache):
+def test_attn_result_and_cached_rows(dtype, n, h, d, k, queries, splits, cache):
+    room = max(ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d), 256)
+    plan = ab.astraea_attn_plan(n, h, k) if dtype == torch.bfloat16 else ab.astraea_attn_plan_f32(n, h, d, k, room)
+    assert (plan["queries_per_workgroup"], plan["splits"]) == (queries, splits)
     g = torch.Generator(device=DEV).manual_seed(n + k)
     e = h * d
     both = torch.randn(n, 2, e, device=DEV, generator=g).to(dtype)
@@ -293,7 +304,7 @@ def test_attn_result_and_cached_rows(dtype, n, h, d, k, cache):
     idx = torch.randperm(n, device=DEV, generator=g)[:k].sort().values.to(torch.int32)
     if cache == "padded":
         idx[-1] = n + 7                                      # outside the keys and the cached buffer: writes nothing there
-    ws = torch.empty(max(ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d), 256), dtype=torch.uint8, device=DEV)
+    ws = torch.empty(room, dtype=torch.uint8, device=DEV)
     o0, lse0 = torch.empty(k, h, d, dtype=dtype, device=DEV), torch.empty(k, h, device=DEV)
     o1, lse1 = torch.empty_like(o0), torch.empty_like(lse0)
     want = base.clone()
@@ -402,26 +413,43 @@ def test_attn_f32_tiles(n, h, k, d, hot, scatter, pitch):
         assert torch.equal(out[keep], before[keep])
 
 
-# Workgroups of eight waves (256 queries, tiles staged a whole tile ahead): items whole, all cut along the keys, and cut only past the last whole
-# round (24 heads x 11 tiles of queries are 33 items per XCD); one to three key tiles, ragged last tiles of keys and queries, a workgroup
-# whose last four waves have no queries.  A workspace of the size named is not written past, and without one the result is the
-# same up to the order of the sums: 1e-5 as above.
-@pytest.mark.parametrize("n,h,k,d,hot,scatter", [
-    (4097, 8, 2047, 64, True, False), (600, 24, 2700, 64, True, False), (600, 24, 2699, 128, True, False), (257, 8, 6000, 64, False, False),
-    (33, 24, 2700, 64, True, False), (65, 24, 2690, 128, False, False), (1100, 16, 900, 128, True, True), (2100, 24, 1401, 64, False, True),
-    (150, 24, 5500, 64, True, False),
+# Workgroups of eight waves (256 queries, tiles staged a whole tile ahead) and of four: items whole, all cut along the keys, and cut only past the
+# last whole round (24 heads x 11 tiles of queries are 33 items per XCD); one to three key tiles, ragged last tiles of keys and queries, a
+# workgroup whose last four waves have no queries.  `queries`, `cut`: what the launch says.  A workspace of the size named is not written
+# past, and without one the result is the same up to the order of the sums: 1e-5 as above.
+@pytest.mark.parametrize("n,h,k,d,hot,scatter,queries,cut", [
+    (4097, 8, 2047, 64, True, False, 256, "all"), (600, 24, 2700, 64, True, False, 256, "tail"), (600, 24, 2699, 128, True, False, 256, "tail"),
+    (257, 8, 6000, 64, False, False, 256, "none"), (2100, 24, 1401, 64, False, True, 256, "none"), (2500, 8, 2500, 128, True, True, 256, "all"),
+    (33, 8, 8192, 64, True, False, 256, "none"), (33, 8, 8065, 64, True, False, 256, "none"), (150, 8, 8192, 64, True, False, 256, "none"),
+    (97, 4, 16300, 128, False, False, 256, "none"), (130, 8, 8100, 128, True, False, 256, "none"),
+    (33, 24, 2700, 64, True, False, 128, "none"), (65, 24, 2690, 128, False, False, 128, "none"), (150, 24, 5500, 64, True, False, 128, "none"),
+    (1100, 16, 900, 128, True, True, 128, "all"), (2100, 2, 2100, 64, True, True, 128, "all"),
 ])
-def test_attn_f32_eight_waves(n, h, k, d, hot, scatter):
+def test_attn_f32_eight_waves(n, h, k, d, hot, scatter, queries, cut):
+    need = ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d)
+    plan = ab.astraea_attn_plan_f32(n, h, d, k, need)
+    assert plan["queries_per_workgroup"] == queries
+    assert cut == ("none" if plan["splits"] == 1 else "all" if plan["full_items"] == 0 else "tail")
     test_attn_f32_tiles(n, h, k, d, hot, scatter, None)
     g = torch.Generator(device=DEV).manual_seed(n)
     q, kc, vc = (torch.randn(m, h, d, device=DEV, generator=g) for m in (k, n, n))
-    need = ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d)
     ws = torch.full((need + 65536,), 170, dtype=torch.uint8, device=DEV)
     a, b = torch.empty_like(q), torch.empty_like(q)
     ab.astraea_sparse_attn_fwd(q, kc, vc, None, k, a, d ** -0.5, q_is_compact=True, workspace=ws[:need] if need else None)
     ab.astraea_sparse_attn_fwd(q, kc, vc, None, k, b, d ** -0.5, q_is_compact=True)
     torch.cuda.synchronize()
     assert (a - b).abs().max().item() <= 1e-5 and bool((ws[need:] == 170).all())
+
+
+def _f32_queries(n, h, d, k):
+    return ab.astraea_attn_plan_f32(n, h, d, k, max(256, ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d)))["queries_per_workgroup"]
+
+
+F32_EIGHT_WAVES = [(33, 8, 64, 8192), (150, 8, 64, 8192), (97, 4, 128, 16300)]       # one and three key tiles, four of 32 keys
+
+
+def test_f32_eight_wave_sizes():
+    assert all(_f32_queries(*s) == 256 for s in F32_EIGHT_WAVES)
 
 
 # Rows whose first key tile lies 45 nats below the rest: a fixed exponent offset would leave arguments of 65 to the
@@ -445,10 +473,10 @@ def test_attn_f32_rows_that_rise_from_a_low_first_tile(h, k, d, rise_nats, size)
         assert ((out[:, i].double() - ref).norm() / ref.norm()).item() <= 9e-7
 
 
-@pytest.mark.parametrize("d", [64, 128])
-def test_attn_f32_non_finite_inputs_stay_in_their_rows_and_head_dims(d):
+@pytest.mark.parametrize("d,n,h,k,queries", [(64, 300, 2, 140, 128), (128, 300, 2, 140, 128), (64, 300, 8, 8100, 256), (128, 97, 4, 16300, 256)])
+def test_attn_f32_non_finite_inputs_stay_in_their_rows_and_head_dims(d, n, h, k, queries):
     """A NaN or an infinity in a row of Q spoils that row alone, one in V its head-dim alone."""
-    n, h, k = 300, 2, 140
+    assert _f32_queries(n, h, d, k) == queries
     g = torch.Generator(device=DEV).manual_seed(d)
     q, kc, vc = (torch.randn(m, h, d, device=DEV, generator=g) for m in (k, n, n))
     ref = torch.softmax((q[:, 1].double() @ kc[:, 1].double().T.contiguous()) / math.sqrt(d), 1) @ vc[:, 1].double()
@@ -586,7 +614,7 @@ def test_attn_bf16_non_finite_values_stay_in_their_head_dims(k):
 # then magnitudes: in K (its queries the other way, so that logits stay), in V, from tile to tile, zeros, an infinity.
 # fp64 on the device.  Bound: a logit is off by a few 2^-23 of |q| |k| scale, a result by that, relative, and a few 2^-23 of |V|.
 @pytest.mark.parametrize("n,h,d,k", [(1, 1, 64, 1), (63, 2, 64, 31), (64, 1, 64, 128), (65, 3, 64, 129), (257, 2, 64, 300),
-                                     (31, 1, 128, 5), (32, 2, 128, 32), (33, 1, 128, 128), (225, 2, 128, 130), (700, 8, 64, 60)])
+                                     (31, 1, 128, 5), (32, 2, 128, 32), (33, 1, 128, 128), (225, 2, 128, 130), (700, 8, 64, 60)] + F32_EIGHT_WAVES)
 @pytest.mark.parametrize("values", ["plain", "k tiny", "k huge", "v tiny", "v huge", "v grows", "v falls", "v falls far", "zeros", "inf"])
 def test_attn_f32_split_range(n, h, d, k, values):
     g = torch.Generator(device=DEV).manual_seed(n + h + d + k)
@@ -627,7 +655,7 @@ def test_attn_f32_split_range(n, h, d, k, values):
 # that half the queries turn away from, huge values behind negligible weights, an outlier of V in another head-dim.
 # Bound, to first order: with s_n = scale sum_d |q_d k_nd|, a logit is off by a few 2^-23 s_n and its exponential's argument by a few 2^-23 of
 # itself; a result is off by that, weighted, and a few 2^-23 of the weighted |V|.
-@pytest.mark.parametrize("n,h,d,k", [(65, 2, 64, 129), (700, 8, 64, 60), (225, 2, 128, 130), (97, 1, 128, 300)])
+@pytest.mark.parametrize("n,h,d,k", [(65, 2, 64, 129), (700, 8, 64, 60), (225, 2, 128, 130), (97, 1, 128, 300)] + F32_EIGHT_WAVES)
 @pytest.mark.parametrize("values", ["v head-dims", "opposed", "huge key", "hidden values", "v outlier", "q rows", "k past range", "tiny scale", "scale past range", "nan"])
 def test_attn_f32_spread_magnitudes(n, h, d, k, values):
     g = torch.Generator(device=DEV).manual_seed(n + h + d + k)
@@ -680,7 +708,7 @@ def test_attn_f32_spread_magnitudes(n, h, d, k, values):
         assert bool((lse_err <= lse_bound).all()), (lse_err / lse_bound).max().item()
 
 
-@pytest.mark.parametrize("n,h,d,k", [(1, 1, 64, 1), (65, 2, 64, 10), (700, 8, 64, 60), (33, 1, 128, 128), (97, 2, 128, 300)])
+@pytest.mark.parametrize("n,h,d,k", [(1, 1, 64, 1), (65, 2, 64, 10), (700, 8, 64, 60), (33, 1, 128, 128), (97, 2, 128, 300)] + F32_EIGHT_WAVES)
 def test_attn_f32_infinity_in_the_last_key(n, h, d, k):
     """Rows past the last key fill its tile with weight 0: nothing of it may reach them."""
     g = torch.Generator(device=DEV).manual_seed(n + d)
