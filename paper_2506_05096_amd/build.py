@@ -22,7 +22,7 @@ FLAGS = [
 
 # The attention's sweep: the time of a loop whose waves meet at a barrier every 200 instructions depends on where its branch targets lie in an
 # instruction cache line.  All of them at the start of a line, same code otherwise, us: 35640 queries x 118800 keys x 24 heads 38440 ->
-# 38278, 7020 x 17550 x 24 1175.4 -> 1173.3. 
+# 38278, 7020 x 17550 x 24 1175.4 -> 1173.3.
 FILE_FLAGS = {"attn_bf16": ["-mllvm", "-align-all-nofallthru-blocks=6"]}
 
 
