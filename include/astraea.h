@@ -114,8 +114,8 @@ int astraea_select_topk(const float *score, int64_t N, int64_t k, int32_t *idx_s
  * The GPU that `stream` belongs to must be the current device.  The array's address on that device is
  * looked up at the first call made with it current (hipGetSymbolAddress; make that first call outside
  * a graph capture).  All calls on one GPU share the one array, whatever their stream: two calls
- * that overlap in time on the same GPU race, so order them on one stream or with events.  Every
- * call clears what it needs at its start, with a kernel, so calls of any sizes may follow each other.
+ * that overlap in time on the same GPU race, so order them on one stream or with events.  No call
+ * reads what it has not written or cleared itself (with a kernel), so calls of any sizes may follow each other.
  */
 int astraea_select_topk_static(const float *score, int64_t N, int64_t k, int32_t *idx_sel, int32_t *idx_remain,
                                uint8_t *sel_mask, int32_t *skip_count, void *stream);
@@ -137,11 +137,14 @@ int astraea_select_topk_static(const float *score, int64_t N, int64_t k, int32_t
  *               256-byte aligned (may be NULL when that is 0).  The bf16 path stages a re-tiled
  *               copy of V there (N rounded up to 64, times H*D*2 bytes; large selections) and up to
  *               68 MB of partial results; contents need not be initialised and are clobbered.
- *               The fp32 path uses it only for a selection too small to fill the chip, which
- *               it then cuts into key ranges (up to 8 x k_sel x H x (D + 4) floats of partial
- *               results); there the workspace is optional: with NULL, or fewer bytes than
- *               named, every work item sweeps all keys itself and the result is the same up
- *               to summation order.
+ *               The fp32 path cuts the keys into up to 8 ranges where a selection does not fill
+ *               the chip, and those of the last round of work items where they do not, as far as
+ *               workspace_bytes hold the partial results ((D + 4) floats per range, row and head).
+ *               There the workspace is optional: with NULL, or fewer bytes than named, every work
+ *               item sweeps all keys itself.  More bytes than named may be used too, so results
+ *               for buffers of different sizes are the same up to summation order
+ *               (astraea_attn_plan_f32 says what is cut).
+ *               Calls sharing a workspace must not overlap in time, in either dtype and at any size.
  * The bf16 path runs its main kernel with each row's exponent offset fixed at the row max over the
  * first key tile, which is exact as long as no later logit exceeds that max by more than 80 powers of
  * two and the unnormalised sums stay finite; a workgroup with a row where that fails, or with a NaN or an
@@ -238,9 +241,11 @@ int astraea_kv_refresh(void *k_cache, void *v_cache, const void *k_new, const vo
  *            with the cache refresh.
  *   act      ASTRAEA_ACT_NONE, or ASTRAEA_ACT_GELU_TANH: 0.5 t (1 + tanh(sqrt(2/pi) (t + 0.044715 t^3))).
  * BF16: bf16 MFMA, fp32 accumulation, bias and activation in fp32, one rounding to bf16; x and w must
- * each span less than 4 GiB.  F32: fp32 in, out and accumulated; products on fp32 MFMA or, in
- * larger tiles, of the operands' three bf16 parts, which hold every fp32 number below 2^111 whole: six products of parts for
- * one of numbers, off by at most 2^-24 of it.  A tile with a sum that is not finite there (infinities, NaN, results from 2^96)
+ * each span less than 4 GiB.  F32: fp32 in, out and accumulated; products on fp32 MFMA in tiles of 32 (astraea_linear_plan) or, in
+ * tiles of 64 and 128, of the operands' three bf16 parts, which hold every fp32 number below 2^111 whole: six products of parts for
+ * one of numbers, off by at most 2^-24 of it, whose sum is rounded in turn.  Sums of many products are closer to 64 bits that way (512 to
+ * 3072 N(0, 1) terms: 0.6 to 0.7 of the fp32 MFMA's error); a sum with one product that is not zero, which fp32 MFMA rounds
+ * correctly, was off by up to 2.8 x 2^-24 of it in 17 million.  A tile with a sum that is not finite there (infinities, NaN, results from 2^96)
  * is done again on fp32 MFMA.  Beyond rounding a row depends on no other row.  Both: c_in a multiple of 64, c_out a
  * multiple of 8, strides multiples of 8 elements, pointers 16-byte aligned.
  * idx_sel (distinct, in [0, N)) is required unless both sides are compact.  No workspace.
@@ -253,8 +258,9 @@ int astraea_sparse_linear(const void *x, const void *w, const void *bias, astrae
 
 /*
  * astraea_sparse_linear_group - up to three layers of the same input, sizes and activation (the Q, K and V projections) in one
- * launch: the same as one astraea_sparse_linear call per entry of `parts`, in their order.  Their weights and results are separate
- * buffers; a result that shares memory with x, a weight or another result is computed by a launch of its own.
+ * launch: the same as one astraea_sparse_linear call per entry of `parts`, in their order (to the bit in bf16; in fp32 up to rounding and
+ * summation order, since the tile is chosen for the launch as a whole).  Their weights and results are separate
+ * buffers; where a result shares memory with x, a weight, a bias or another result, each layer has a launch of its own.
  */
 typedef struct {
     const void *w;          /* [c_out, c_in] */
