@@ -59,11 +59,11 @@ struct LinearParts {
     LinearPart part[kMaxLinearParts];
     int32_t n_tiles_each;      // feature tiles of a layer
     // The layer that feature tile nt belongs to; nt becomes its own tile number.  (Chosen by selections: an index would put the parts into memory.)
-    // EARLY: the first layer's part is loaded with the kernel's other arguments instead of from an address that is chosen first.
-    template <bool EARLY = false> __device__ __forceinline__ LinearPart of(int &nt) const
+    // GROUP: there may be more than one.  A launch of one does not choose: it loads the part with the kernel's other arguments, in one round trip.
+    template <bool GROUP> __device__ __forceinline__ LinearPart of(int &nt) const
     {
         LinearPart p = part[0];
-        if (EARLY) asm volatile("" : "+s"(p.w), "+s"(p.bias), "+s"(p.y), "+s"(p.ldy), "+s"(p.y_indexed));
+        if (!GROUP) return p;
         if (nt >= n_tiles_each) p = nt >= 2 * n_tiles_each ? part[2] : part[1];
         nt -= nt >= 2 * n_tiles_each ? 2 * n_tiles_each : nt >= n_tiles_each ? n_tiles_each : 0;
         return p;

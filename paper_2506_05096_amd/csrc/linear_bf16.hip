@@ -70,18 +70,18 @@ __device__ __forceinline__ void touch_line(const void *gbase, uint32_t goff, uin
 
 struct LinearArgs {
     const __bf16 *x;
-    LinearParts parts;
     const int32_t *idx_sel;    // or null when neither side is indexed
     int64_t ldx;               // row stride in elements
     int32_t k_sel, c_in, c_out;
     int32_t n_rows;            // rows of the indexed buffer(s): indices outside [0, n_rows) read a valid row, write none
     int32_t x_indexed, act;
     int32_t m_tiles, n_tiles;  // token tiles, and feature tiles of all parts
+    LinearParts parts;         // last: what a launch of one layer loads lies together
 };
 
 // A wave has NB x TB MFMA blocks of 32 features x 32 tokens, a tile kBn features: <4, 2, 256> makes tiles of 256 tokens, <2, 3, 256> of
 // 192, <2, 2, 256> and <2, 1, 128> of 128.
-template <int NB, int TB, int kBn>
+template <int NB, int TB, int kBn, bool GROUP>
 __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArgs a)
 {
     constexpr int kTileBytes = kBn * kRowBytes;                   // the w tile of a stage
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
     const int sb_col = in_row / (kSbN * sb_h), inner = in_row % (kSbN * sb_h);
     const int mt = sb_row * kSbM + inner % sb_h, nt = sb_col * kSbN + inner / sb_h;
     int part_nt = nt;
-    const LinearPart part = a.parts.of(part_nt);
+    const LinearPart part = a.parts.of<GROUP>(part_nt);
     const int m0 = mt * kBm, n0 = part_nt * kBn;
     // Every argument that is used from here on is loaded here, in one round trip.  The compiler would otherwise load each next to its first
     // use, x inside the copying waves' branch: LDS reads and scalar loads share a counter and scalar loads come out of order, so with one
@@ -447,10 +447,15 @@ int launch_linear_bf16(const void *x, const LinearPart *parts, int n_parts, cons
         const int64_t grid = t / kCus * kCus + (t % kCus + kNumXcd - 1) / kNumXcd * kNumXcd;
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kWaves * kWave), 0, stream, a);
     };
-    if (tile.tokens == 256) go(linear_bf16_kernel<4, 2, 256>);
-    else if (tile.tokens == 192) go(linear_bf16_kernel<2, 3, 256>);
-    else if (tile.features == 256) go(linear_bf16_kernel<2, 2, 256>);
-    else go(linear_bf16_kernel<2, 1, 128>);
+    auto choose = [&](auto group) {
+        constexpr bool G = decltype(group)::value;
+        if (tile.tokens == 256) go(linear_bf16_kernel<4, 2, 256, G>);
+        else if (tile.tokens == 192) go(linear_bf16_kernel<2, 3, 256, G>);
+        else if (tile.features == 256) go(linear_bf16_kernel<2, 2, 256, G>);
+        else go(linear_bf16_kernel<2, 1, 128, G>);
+    };
+    if (n_parts > 1) choose(std::true_type{});
+    else choose(std::false_type{});
     return check_launch("astraea_sparse_linear(bf16)");
 }
 

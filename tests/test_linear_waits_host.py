@@ -17,7 +17,7 @@ def kernels(tmp_path_factory):
     return {m[1]: p for p in parts if (m := re.match(r"_ZN\S*linear_bf16_kernelILi(\w+?)EEEv", p))}
 
 
-@pytest.mark.parametrize("shape", ["4ELi2ELi256", "2ELi3ELi256", "2ELi2ELi256", "2ELi1ELi128"])
+@pytest.mark.parametrize("shape", [s + g for s in ("4ELi2ELi256", "2ELi3ELi256", "2ELi2ELi256", "2ELi1ELi128") for g in ("ELb0", "ELb1")])
 def test_first_mfma_of_a_step_waits_for_its_own_fragments_only(kernels, shape):
     body = kernels[shape]
     loop = body[body.index("Loop Header"):]
