@@ -414,14 +414,15 @@ def test_attn_f32_tiles(n, h, k, d, hot, scatter, pitch):
 
 
 # Workgroups of eight waves (256 queries, tiles staged a whole tile ahead) and of four: items whole, all cut along the keys, and cut only past the
-# last whole round (24 heads x 11 tiles of queries are 33 items per XCD); one to three key tiles, ragged last tiles of keys and queries, a
-# workgroup whose last four waves have no queries.  `queries`, `cut`: what the launch says.  A workspace of the size named is not written
+# last whole round (24 heads x 11 tiles of queries are 33 items per XCD); both sides of four key tiles, from which eight waves are taken, shares of one tile,
+# ragged last tiles of keys and queries, a workgroup whose last four waves have no queries.  `queries`, `cut`: what the launch says.  A workspace of the size named is not written
 # past, and without one the result is the same up to the order of the sums: 1e-5 as above.
 @pytest.mark.parametrize("n,h,k,d,hot,scatter,queries,cut", [
     (4097, 8, 2047, 64, True, False, 256, "all"), (600, 24, 2700, 64, True, False, 256, "tail"), (600, 24, 2699, 128, True, False, 256, "tail"),
     (257, 8, 6000, 64, False, False, 256, "none"), (2100, 24, 1401, 64, False, True, 256, "none"), (2500, 8, 2500, 128, True, True, 256, "all"),
-    (33, 8, 8192, 64, True, False, 256, "none"), (33, 8, 8065, 64, True, False, 256, "none"), (150, 8, 8192, 64, True, False, 256, "none"),
-    (97, 4, 16300, 128, False, False, 256, "none"), (130, 8, 8100, 128, True, False, 256, "none"),
+    (193, 8, 8192, 64, True, False, 256, "none"), (256, 8, 8065, 64, True, False, 256, "none"), (500, 24, 2700, 64, True, False, 256, "tail"),
+    (200, 4, 16300, 128, False, False, 256, "none"), (193, 8, 8100, 128, True, False, 256, "none"),
+    (192, 8, 8192, 64, True, False, 128, "none"), (33, 8, 8192, 64, True, False, 128, "none"), (97, 4, 16300, 128, False, False, 128, "none"),
     (33, 24, 2700, 64, True, False, 128, "none"), (65, 24, 2690, 128, False, False, 128, "none"), (150, 24, 5500, 64, True, False, 128, "none"),
     (1100, 16, 900, 128, True, True, 128, "all"), (2100, 2, 2100, 64, True, True, 128, "all"),
 ])
@@ -445,7 +446,7 @@ def _f32_queries(n, h, d, k):
     return ab.astraea_attn_plan_f32(n, h, d, k, max(256, ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d)))["queries_per_workgroup"]
 
 
-F32_EIGHT_WAVES = [(33, 8, 64, 8192), (150, 8, 64, 8192), (97, 4, 128, 16300)]       # one and three key tiles, four of 32 keys
+F32_EIGHT_WAVES = [(193, 8, 64, 8192), (500, 24, 64, 2700), (200, 4, 128, 16300)]    # four key tiles; eight, and shares of one; seven of 32 keys
 
 
 def test_f32_eight_wave_sizes():
@@ -473,7 +474,7 @@ def test_attn_f32_rows_that_rise_from_a_low_first_tile(h, k, d, rise_nats, size)
         assert ((out[:, i].double() - ref).norm() / ref.norm()).item() <= 9e-7
 
 
-@pytest.mark.parametrize("d,n,h,k,queries", [(64, 300, 2, 140, 128), (128, 300, 2, 140, 128), (64, 300, 8, 8100, 256), (128, 97, 4, 16300, 256)])
+@pytest.mark.parametrize("d,n,h,k,queries", [(64, 300, 2, 140, 128), (128, 300, 2, 140, 128), (64, 300, 8, 8100, 256), (128, 200, 4, 16300, 256)])
 def test_attn_f32_non_finite_inputs_stay_in_their_rows_and_head_dims(d, n, h, k, queries):
     """A NaN or an infinity in a row of Q spoils that row alone, one in V its head-dim alone."""
     assert _f32_queries(n, h, d, k) == queries
