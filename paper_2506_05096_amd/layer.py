@@ -63,7 +63,7 @@ class LayerStep:
 
     def step_attn_scatter(self, t: Dict[str, torch.Tensor], k: int, lse: Optional[torch.Tensor] = None) -> None:
         """step_attn and step_scatter: one call where both are the class's own."""
-        if not self._plain("step_attn", "step_scatter"):
+        if not self._plain_attn_scatter():
             self.step_attn(t, k) if lse is None else self.step_attn(t, k, lse=lse)
             self.step_scatter(t, k)
             return
@@ -71,9 +71,9 @@ class LayerStep:
                                            t["out_cache"], self.scale, q_is_compact=False, lse_sel=lse,
                                            workspace=self.attn_ws)
 
-    def _plain(self, *names: str) -> bool:
-        """Whether these steps are the ones defined in this module, not a subclass's, an instance's or a patched class's."""
-        return all(getattr(getattr(self, n), "__func__", None) is _STEPS[n] for n in names)
+    def _plain_attn_scatter(self) -> bool:
+        """Whether both steps are the ones defined here, not a subclass's, an instance's or a patched class's."""
+        return getattr(self.step_attn, "__func__", None) is _ATTN and getattr(self.step_scatter, "__func__", None) is _SCATTER
 
     def run(self, t: Dict[str, torch.Tensor], k: int) -> None:
         """The whole hot path for one batch of inputs; updates k_cache, v_cache and out_cache in place."""
@@ -84,6 +84,9 @@ class LayerStep:
             self.step_attn_update(t, k)
         else:
             self.step_attn_scatter(t, k)
+
+
+_ATTN, _SCATTER = LayerStep.step_attn, LayerStep.step_scatter
 
 
 class StatefulLayer(LayerStep):
@@ -122,7 +125,7 @@ class StatefulLayer(LayerStep):
         if self.fused_update:
             self.step_attn_update(t, k, lse=self.lse_sel[:max(k, 1)])
             self.step_state(t, k)
-        elif self._plain("step_attn", "step_state", "step_scatter"):
+        elif getattr(self.step_state, "__func__", None) is _STATE and self._plain_attn_scatter():
             self.step_attn_scatter(t, k, lse=self.lse_sel[:max(k, 1)])
             self.step_state(t, k)
         else:
@@ -131,7 +134,7 @@ class StatefulLayer(LayerStep):
             self.step_scatter(t, k)
 
 
-_STEPS = {"step_attn": LayerStep.step_attn, "step_scatter": LayerStep.step_scatter, "step_state": StatefulLayer.step_state}
+_STATE = StatefulLayer.step_state
 
 
 class TokenSparseBlock(LayerStep):
