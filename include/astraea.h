@@ -140,10 +140,10 @@ int astraea_select_topk_static(const float *score, int64_t N, int64_t k, int32_t
  *               The fp32 path cuts the keys into up to 8 ranges where a selection does not fill
  *               the chip, and those of the last round of work items where they do not, as far as
  *               workspace_bytes hold the partial results ((D + 4) floats per range, row and head).
- *               There the workspace is optional: with NULL, or fewer bytes than named, every work
- *               item sweeps all keys itself.  More bytes than named may be used too, so results
- *               for buffers of different sizes are the same up to summation order
- *               (astraea_attn_plan_f32 says what is cut).
+ *               There the workspace is optional: with NULL every work item sweeps all keys itself,
+ *               with fewer bytes than named items are cut into fewer ranges or not at all, and
+ *               more bytes may be used too, so results for buffers of different sizes are the same
+ *               up to summation order (astraea_attn_plan_f32 says what is cut).
  *               Calls sharing a workspace must not overlap in time, in either dtype and at any size.
  * The bf16 path runs its main kernel with each row's exponent offset fixed at the row max over the
  * first key tile, which is exact as long as no later logit exceeds that max by more than 80 powers of
