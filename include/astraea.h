@@ -380,6 +380,14 @@ int astraea_check_indices(const int32_t *idx_sel, int64_t k_sel, int64_t N, int3
 int astraea_attn_plan(int64_t N, int32_t H, int64_t k_sel, int64_t plan_out[8]);
 
 /*
+ * Whether the bf16 attention of k_sel selected queries runs by that plan (1), or, where few items make it faster, with 2 or 4 key
+ * groups: then a workgroup has 256 / groups selected queries of one head, each group of its waves sweeps one of as many equal shares of the
+ * keys, and the workgroup merges them itself; XCD x owns the items [x*n, (x+1)*n) of all, head-major, n an eighth of them rounded up.  0 for
+ * sizes out of range.  Host only; for inspection and tests.
+ */
+int32_t astraea_attn_key_groups(int64_t N, int32_t H, int64_t k_sel);
+
+/*
  * The same of the fp32 attention with a workspace of workspace_bytes (0: none) and keys less than 4 GiB apart per 64.  A work item
  * is one head times one tile of 256 or 128 selected queries, spread over the XCDs as above; either all items are cut along the
  * keys, or those past full_items, or none, as far as the workspace holds their partial results.

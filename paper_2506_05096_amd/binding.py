@@ -28,7 +28,7 @@ EXPORTS = (
     "astraea_score", "astraea_select_topk", "astraea_select_topk_static", "astraea_sparse_attn_fwd", "astraea_sparse_attn_update_fwd",
     "astraea_sparse_attn_scatter_fwd", "astraea_scatter_update", "astraea_kv_refresh", "astraea_gather_rows", "astraea_sparse_linear", "astraea_sparse_linear_group", "astraea_workspace_bytes", "astraea_budget_to_k", "astraea_attn_flops",
     "astraea_probe_mfma_bf16", "astraea_probe_copy", "astraea_probe_kernel_timer", "astraea_probe_kernel_count",
-    "astraea_probe_kernel_ms", "astraea_lse_weight_update", "astraea_attn_plan", "astraea_attn_plan_f32", "astraea_linear_plan", "astraea_check_indices",
+    "astraea_probe_kernel_ms", "astraea_lse_weight_update", "astraea_attn_plan", "astraea_attn_key_groups", "astraea_attn_plan_f32", "astraea_linear_plan", "astraea_check_indices",
     "astraea_budget_search", "astraea_search_crossover", "astraea_search_mutate", "astraea_search_repair",
     "astraea_status_string", "astraea_last_error",
 )
@@ -106,6 +106,8 @@ def lib() -> C.CDLL:
         L.astraea_check_indices.restype = C.c_int
         L.astraea_attn_plan.argtypes = [i64, i32, i64, C.POINTER(i64)]
         L.astraea_attn_plan.restype = C.c_int
+        L.astraea_attn_key_groups.argtypes = [i64, i32, i64]
+        L.astraea_attn_key_groups.restype = i32
         L.astraea_attn_plan_f32.argtypes = [i64, i32, i32, i64, sz, C.POINTER(i64)]
         L.astraea_attn_plan_f32.restype = C.c_int
         L.astraea_linear_plan.argtypes = [i32, i64, i64, i64, C.POINTER(i64)]
@@ -327,6 +329,10 @@ def astraea_attn_plan(N: int, H: int, k_sel: int) -> dict:
     pieces = plan["full_items"] + (plan["items_per_xcd"] - plan["full_items"]) * plan["splits"]
     plan["queries_per_workgroup"] = 256 * 8 * pieces // plan["workgroups"]
     return plan
+
+
+def astraea_attn_key_groups(N: int, H: int, k_sel: int) -> int:
+    return int(lib().astraea_attn_key_groups(N, H, k_sel))
 
 
 def astraea_attn_plan_f32(N: int, H: int, D: int, k_sel: int, workspace_bytes: int) -> dict:

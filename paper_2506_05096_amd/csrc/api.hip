@@ -388,6 +388,12 @@ int astraea_attn_plan(int64_t N, int32_t H, int64_t k_sel, int64_t plan_out[8])
     return attn_bf16_plan(N, H, k_sel, plan_out);
 }
 
+int32_t astraea_attn_key_groups(int64_t N, int32_t H, int64_t k_sel)
+{
+    if (N <= 0 || N > kMaxTokens || H <= 0 || H > 65535 || k_sel <= 0 || k_sel > kMaxTokens) return 0;
+    return attn_bf16_key_groups(N, H, k_sel);
+}
+
 int astraea_attn_plan_f32(int64_t N, int32_t H, int32_t D, int64_t k_sel, size_t workspace_bytes, int64_t plan_out[8])
 {
     if (!plan_out) return fail(ASTRAEA_ERR_INVALID, "astraea_attn_plan_f32: NULL output");

@@ -39,7 +39,8 @@
 //  * the two waves that share a SIMD alternate: while one runs the MFMAs of a tile the other runs
 //    the exponentials of its own tile, so the matrix pipe and the VALU work at the same time.
 //  * few or short work items run in workgroups of four waves instead of eight: halves of an item each on a CU of its own, or two
-//    on one CU, one of which stores or loads while the other sweeps.
+//    on one CU, one of which stores or loads while the other sweeps.  Fewer still run in workgroups of eight waves that share 128 or 64
+//    queries and split the keys between them.
 #include <type_traits>
 
 #include "gfx950.h"
@@ -54,7 +55,6 @@ constexpr int kBq = 256;                // queries per work item
 constexpr int kBk = 64;                 // keys per LDS tile
 constexpr int kRowBytes = D * 2;        // 256 B per key row, unpadded
 constexpr int kTileBytes = kBk * kRowBytes;          // 16 KiB
-constexpr int kBufBytes = 2 * kTileBytes;            // K tile then V tile
 constexpr int kRowsBytes = 32 * kRowBytes;           // a wave's 32 query or output rows
 constexpr float kTau = 8.0f;            // exact form: lazy-rescale threshold, log2 units
 constexpr float kRose = 0x1p8f;         // 2^kTau
@@ -190,24 +190,32 @@ constexpr int MFMA = 0x008, DSR = 0x100;
 // fragments are read through the transposing LDS read.
 // GROUPS: groups of four waves in a workgroup (half_workgroups).  2: an item's 256 queries, the groups taking turns at the matrix pipe.  1: half
 // an item's queries; two such workgroups share a CU.
-template <bool RETILED, int GROUPS>
+// KEYS: key groups of an eight-wave workgroup (key_groups).  1: its waves have 32 queries each and sweep the same keys.  2 or 4: there are 128
+// or 64 queries, and each group of waves that has them all takes a share of the keys in tiles of its own; the groups' results are merged through LDS.
+template <bool RETILED, int GROUPS, int KEYS>
 __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_bf16_kernel(
     const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const void *__restrict__ v, int64_t N, int32_t H,
     int64_t q_stride_n, int64_t q_stride_h, int64_t kv_stride_n, int64_t kv_stride_h,
     const int32_t *__restrict__ idx_sel, int64_t k_sel, int q_is_compact, float scale_log2e,
     AttnOut out, float *__restrict__ lse_sel, AttnSchedule sch, float *__restrict__ partial)
 {
+    static_assert(KEYS == 1 || (GROUPS == 2 && !RETILED), "key groups are for eight waves and V as it lies");
     constexpr int kWaves = GROUPS * kGroupWaves;
+    constexpr int kKeyWaves = kWaves / KEYS;         // waves of a key group
+    constexpr int KB = KEYS == 4 ? 1 : 2;            // blocks of 32 keys in a tile: four groups' tiles fit LDS twice at 32 keys
+    constexpr int kTk = 32 * KB, kTile = kTk * kRowBytes, kBuf = 2 * kTile;
+    constexpr int kMfmas = 8 * KB;                   // of either product, per tile
     // [parity][K tile | V^T tile], 64 KiB, and 8 KiB per wave for its query rows and later its output rows: behind the tiles for one
     // 8-wave workgroup per CU; from the second V tile's place on for two 4-wave ones, whose 160 KiB are the CU's whole LDS.  There the rows of
     // waves 0 and 1 lie over the whole second V buffer: query rows are read before the barrier in front of the first tile, output
     // rows are written past a barrier behind the last one (the vote's, or its own after a repeated sweep)
-    constexpr uint32_t kRowsAt = GROUPS == 2 ? 2 * kBufBytes : kBufBytes + kTileBytes;
-    __shared__ __attribute__((aligned(1024))) char lds[kRowsAt + kWaves * kRowsBytes + (GROUPS == 2 ? 64 : 0)];
-    // one word per wave; the first K tile's place is free when they are used
-    uint32_t *const wave_outgrew = reinterpret_cast<uint32_t *>(lds + (GROUPS == 2 ? sizeof(lds) - 64 : 0));
+    constexpr uint32_t kRowsAt = GROUPS == 2 ? KEYS * 2 * kBuf : kBuf + kTile;
+    constexpr uint32_t kRowsEnd = kRowsAt + kKeyWaves * kRowsBytes;      // key groups have the same query rows
+    __shared__ __attribute__((aligned(1024))) char lds[kRowsEnd + (GROUPS == 2 && KEYS == 1 ? 64 : 0)];
+    // one word per wave; the first K tile's place, or that of key groups' query rows, is free when they are used
+    uint32_t *const wave_outgrew = reinterpret_cast<uint32_t *>(lds + (KEYS > 1 ? kRowsAt : GROUPS == 2 ? sizeof(lds) - 64 : 0));
 
-    const int64_t ntiles = (N + kBk - 1) / kBk;
+    const int64_t ntiles = (N + kTk - 1) / kTk;
     const uint32_t total_items = (uint32_t)H * sch.q_tiles;
     const uint32_t xcd = blockIdx.x % kNumXcd, slot = blockIdx.x / (kNumXcd * (2 / GROUPS));
     uint32_t item = xcd * sch.items_per_xcd + slot;
@@ -228,10 +236,19 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int qc = lane & 31, hf = lane >> 5;
     // the wave's place among the item's eight: a 4-wave workgroup takes one half of them
-    const int iwave = GROUPS == 2 ? wave : wave + (blockIdx.x / kNumXcd & 1) * kGroupWaves;
-    const int64_t r0 = qt * kBq + iwave * 32;
+    const int iwave = KEYS > 1 ? wave % kKeyWaves : GROUPS == 2 ? wave : wave + (blockIdx.x / kNumXcd & 1) * kGroupWaves;
+    const int64_t r0 = qt * (kBq / KEYS) + iwave * 32;
     if (GROUPS == 1 && r0 - wave * 32 >= k_sel) return;
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+    // The key group, its share of the tiles and where it keeps them.  Shares differ by a tile at most; there are at least KEYS tiles.
+    const int kg = KEYS > 1 ? wave / kKeyWaves : 0;
+    if (KEYS > 1) {
+        tile_begin = (int)(kg * ntiles / KEYS);
+        tile_end = (int)((kg + 1) * ntiles / KEYS);
+    }
+    const uint32_t tiles0 = lds0 + kg * 2 * kBuf;
+    // part of the fragments' addresses where it differs among the waves
+    const uint32_t at0 = KEYS > 1 ? tiles0 : 0, from0 = KEYS > 1 ? 0 : lds0;
 
     floatx16 oacc[4];
     float m_c;                 // running max of scale*log2(e)*logit actually used as exponent offset
@@ -241,31 +258,33 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
     // K: block = 4 key rows; physical chunk p of row r holds logical chunk p ^ (r & 15).
     // V^T: the pre-pass already wrote the tile as its LDS image, so the copy is linear.
     const char *kbase = reinterpret_cast<const char *>(k + (int64_t)head * kv_stride_h);
-    const char *vbase = RETILED ? reinterpret_cast<const char *>(v) + (int64_t)head * ntiles * kTileBytes
+    const char *vbase = RETILED ? reinterpret_cast<const char *>(v) + (int64_t)head * ntiles * kTile
                                 : reinterpret_cast<const char *>(reinterpret_cast<const __bf16 *>(v) + (int64_t)head * kv_stride_h);
     const int64_t row_pitch = kv_stride_n * 2;       // bytes between consecutive keys
     const int d_row = lane >> 4, d_p = lane & 15;
     const uint32_t lin_off = lane * 16;
     // Rows [key0, key0 + 64) of K or V; physical chunk p of row r holds logical chunk p ^ sw(r).
     auto dma_rows = [&](const char *base, int64_t tile, uint32_t buf, int w, auto nw_tag, int swz, bool zero_fill) __attribute__((always_inline)) {
-        constexpr int NW = decltype(nw_tag)::value;  // 4 or 8: a wave's rows advance by 16 or 32 per step,
-        const int64_t key0 = tile * kBk;             // so the swizzle is the same for all of them
+        // a wave's rows advance by 4 NW: with 4 or 8 waves the swizzle is the same for all of them, with 2 it alternates for K
+        constexpr int NW = decltype(nw_tag)::value;
+        const int64_t key0 = tile * kTk;
         const char *src = base + key0 * row_pitch;
         const uint32_t dst = buf + w * 1024;
         const int row0 = 4 * w + d_row;
         const uint32_t sw = (uint32_t)((d_p ^ swz) << 4);
-        if (key0 + kBk <= N) {
-            const uint32_t off = (uint32_t)row0 * (uint32_t)row_pitch + sw;
+        const uint32_t sw_odd = NW == 2 && !zero_fill ? sw ^ 128 : sw;
+        if (key0 + kTk <= N) {
+            const uint32_t off = (uint32_t)row0 * (uint32_t)row_pitch;
 #pragma unroll
-            for (int i = 0; i < 16 / NW; ++i) dma16(src + i * 4 * NW * row_pitch, off, dst + i * NW * 1024);
+            for (int i = 0; i < kTk / 4 / NW; ++i) dma16(src + i * 4 * NW * row_pitch, off + (i & 1 ? sw_odd : sw), dst + i * NW * 1024);
         } else {
             const int64_t last = N - 1 - key0;       // K rows past the last key re-read it (masked later); V rows are zero
 #pragma unroll
-            for (int i = 0; i < 16 / NW; ++i) {
+            for (int i = 0; i < kTk / 4 / NW; ++i) {
                 const int rr = row0 + 4 * NW * i;
                 const int64_t rc = rr < last ? rr : last;
                 if (!zero_fill || rr <= last)
-                    dma16(src, (uint32_t)(rc * row_pitch) + sw, dst + i * NW * 1024);
+                    dma16(src, (uint32_t)(rc * row_pitch) + (i & 1 ? sw_odd : sw), dst + i * NW * 1024);
                 else
                     *reinterpret_cast<uint4v __attribute__((address_space(3))) *>((uintptr_t)(dst + i * NW * 1024 + lane * 16)) = uint4v{0u, 0u, 0u, 0u};
             }
@@ -276,9 +295,9 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
     // tile is copied by wave b % NW.
     auto dma_v_tile = [&](int64_t tile, int par, int w, auto nw_tag) __attribute__((always_inline)) {
         constexpr int NW = decltype(nw_tag)::value;
-        const uint32_t buf = lds0 + par * kBufBytes + kTileBytes;
+        const uint32_t buf = tiles0 + par * kBuf + kTile;
         if (RETILED) {
-            const char *src = vbase + tile * kTileBytes + w * 1024;
+            const char *src = vbase + tile * kTile + w * 1024;
 #pragma unroll
             for (int i = 0; i < 16 / NW; ++i) dma16(src + i * NW * 1024, lin_off, buf + w * 1024 + i * NW * 1024);
         } else {
@@ -286,16 +305,18 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
         }
     };
     auto dma_k_tile = [&](int64_t tile, int par, int w, auto nw_tag) __attribute__((always_inline)) {
-        dma_rows(kbase, tile, lds0 + par * kBufBytes, w, nw_tag, (4 * w + d_row) & 15, false);
+        dma_rows(kbase, tile, tiles0 + par * kBuf, w, nw_tag, (4 * w + d_row) & 15, false);
     };
 
-    const int grp = wave >> 2, wig = wave & 3;
-    using W4 = std::integral_constant<int, 4>;
-    using WAll = std::integral_constant<int, kWaves>;
+    // the waves that copy a tile in the sweep, those of one phase group or of a key group, and this wave's number among them; the first
+    // tiles are copied by all waves that read them
+    const int grp = wave >> 2, wig = KEYS > 1 ? iwave : wave & 3, wkg = KEYS > 1 ? iwave : wave;
+    using WGrp = std::integral_constant<int, (KEYS > 1 ? kKeyWaves : kGroupWaves)>;
+    using WAll = std::integral_constant<int, kKeyWaves>;
     auto first_tiles = [&]() __attribute__((always_inline)) {
-        dma_k_tile(tile_begin, 0, wave, WAll{});
-        dma_v_tile(tile_begin, 0, wave, WAll{});
-        if (tile_begin + 1 < tile_end) dma_k_tile(tile_begin + 1, 1, wave, WAll{});
+        dma_k_tile(tile_begin, 0, wkg, WAll{});
+        dma_v_tile(tile_begin, 0, wkg, WAll{});
+        if (tile_begin + 1 < tile_end) dma_k_tile(tile_begin + 1, 1, wkg, WAll{});
     };
     first_tiles();
 
@@ -306,14 +327,15 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
     auto lane_row = [&](int n) { return (int64_t)n < row_n ? r0 + n : k_sel - 1; };    // ragged tile: a valid row, never stored
     // an index outside [0, N) reads a valid row instead
     const int32_t q_row = q_is_compact ? 0 : clamp_row(idx_sel[lane_row(qc)], (int32_t)N);
-    const uint32_t rows_lds = lds0 + kRowsAt + wave * kRowsBytes;
+    const uint32_t rows_lds = lds0 + kRowsAt + wkg * kRowsBytes;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int n = 4 * i + d_row;
+    for (int ii = 0; ii < 8 / KEYS; ++ii) {          // key groups share the copying
+        const int i = ii * KEYS + kg, n = 4 * i + d_row;
         const int64_t row = q_is_compact ? lane_row(n) : (int64_t)__shfl(q_row, n);
         dma16_far(q + row * q_stride_n + (int64_t)head * q_stride_h + 8 * (d_p ^ (n & 15)), rows_lds + i * 1024);
     }
     wait_dma();
+    if (KEYS > 1) __syncthreads();
     bf16x8 qf[D / 16];
 #pragma unroll
     for (int s = 0; s < D / 16; ++s) qf[s] = lds_read_b128(rows_lds + qc * kRowBytes + (((2 * s + hf) ^ (qc & 15)) << 4));
@@ -325,7 +347,7 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
     // K fragment (kb, s): row 32*kb + qc, logical chunk 2*s + hf; kb is an immediate offset
     uint32_t ka[D / 16];
 #pragma unroll
-    for (int s = 0; s < D / 16; ++s) ka[s] = qc * kRowBytes + (((2 * s + hf) ^ (qc & 15)) << 4);
+    for (int s = 0; s < D / 16; ++s) ka[s] = at0 + qc * kRowBytes + (((2 * s + hf) ^ (qc & 15)) << 4);
     // V^T fragment (tt, b): row d = 32*b + qc (128-byte rows), logical chunk 2*tt + hf; b is an immediate
     // Not retiled: lane 16 g + i of a transposing read supplies 4 head-dims of key 4 (g / 2) + i / 4 and gets head-dim
     // 16 (g % 2) + i of four keys; V fragment (tt, b) is two of them, keys 16 tt + 4 hf + 0..3 and 8 further.  va[b] is
@@ -334,18 +356,18 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
     const int tr_row = qc & 15;
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-        va[u] = RETILED ? kTileBytes + qc * 128 + (((2 * u + hf) ^ ((qc >> 1) & 7)) << 4)
-                        : kTileBytes + (4 * hf + (tr_row >> 2)) * kRowBytes +
+        va[u] = RETILED ? kTile + qc * 128 + (((2 * u + hf) ^ ((qc >> 1) & 7)) << 4)
+                        : at0 + kTile + (4 * hf + (tr_row >> 2)) * kRowBytes +
                               ((((u ^ (tr_row >> 2)) << 2) + 2 * (qc >> 4) + ((tr_row >> 1) & 1)) << 4) + 8 * (tr_row & 1);
     auto read_v = [&](int u, uint32_t at) __attribute__((always_inline)) -> bf16x8 {     // fragment tt = u / 4, b = u % 4 of the buffer pair at `at`
-        if (RETILED) return lds_read_b128(lds0 + va[u >> 2] + (at + (u & 3) * 32 * 128));
-        const uint32_t p = lds0 + va[u & 3] + (at + (u >> 2) * 16 * kRowBytes);
+        if (RETILED) return lds_read_b128(from0 + va[u >> 2] + (at + (u & 3) * 32 * 128));
+        const uint32_t p = from0 + va[u & 3] + (at + (u >> 2) * 16 * kRowBytes);
         const bf16x4 lo = lds_read_tr(p), hi = lds_read_tr(p + 8 * kRowBytes);
         return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     };
 
-    floatx16 sacc[2];          // S^T of the current tile (two blocks of 32 keys)
-    uint32_t pw[16];           // P^T as bf16 pairs: pw[8*kb + i] = registers 2i, 2i+1 of block kb
+    floatx16 sacc[KB];         // S^T of the current tile (blocks of 32 keys)
+    uint32_t pw[8 * KB];       // P^T as bf16 pairs: pw[8*kb + i] = registers 2i, 2i+1 of block kb
 
     // VALU phase for tile j: exponentials -> pw, row sums; in the exact form first the row max: the running
     // max is only raised (and what was accumulated under the old one rescaled) when some row's max moved up by
@@ -354,19 +376,19 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
     auto tile_row_max = [&]() __attribute__((always_inline)) -> float {
         float tm = sacc[0][0];
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
             for (int i = 0; i < 16; ++i) tm = fmaxf(tm, sacc[kb][i]);
         return xhalf_max(tm) * scale_log2e;
     };
     auto softmax_tile = [&](int64_t j, auto exact_tag) __attribute__((always_inline)) {
         constexpr bool EXACT = decltype(exact_tag)::value;
-        if ((j + 1) * kBk > N) {                    // only the last tile can be ragged
+        if ((j + 1) * kTk > N) {                    // only the last tile can be ragged
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+            for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const int key = (int)(j * kBk - N) + 32 * kb + (i >> 2) * 8 + hf * 4 + (i & 3);
+                    const int key = (int)(j * kTk - N) + 32 * kb + (i >> 2) * 8 + hf * 4 + (i & 3);
                     if (key >= 0) sacc[kb][i] = -INFINITY;
                 }
         }
@@ -386,7 +408,7 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
         float ps0 = 0.0f, ps1 = 0.0f;
         const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
+        for (int u = 0; u < 8 * KB; ++u) {
             const int kb = u >> 3, i = 2 * (u & 7);
             const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[kb][i], scale_log2e, -m_c));
             const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[kb][i + 1], scale_log2e, -m_c));
@@ -413,45 +435,44 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
     // from pair PAR ^ 1.
     auto mfma_phase = [&](auto qk_tag, auto par_tag) __attribute__((always_inline)) {
         constexpr bool WITH_QK = decltype(qk_tag)::value;
-        constexpr uint32_t VP = decltype(par_tag)::value * kBufBytes;
-        constexpr uint32_t KP = (decltype(par_tag)::value ^ 1) * kBufBytes;
-        bf16x8 vf[16], kf[16];
+        constexpr uint32_t VP = decltype(par_tag)::value * kBuf;
+        constexpr uint32_t KP = (decltype(par_tag)::value ^ 1) * kBuf;
+        bf16x8 vf[kMfmas], kf[kMfmas];
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) vf[u] = read_v(u, VP);
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
+        for (int u = 0; u < kMfmas; ++u) {
             const int tt = u >> 2, b = u & 3;
             uint4v p4 = {pw[4 * tt], pw[4 * tt + 1], pw[4 * tt + 2], pw[4 * tt + 3]};
             oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[u], __builtin_bit_cast(bf16x8, p4), oacc[b], 0, 0, 0);
             const int n = u + kAhead;
-            if (n < 16)
+            if (n < kMfmas)
                 vf[n] = read_v(n, VP);
             else if (WITH_QK)
-                kf[n - 16] = lds_read_b128(lds0 + ka[(n - 16) >> 1] + (KP + ((n - 16) & 1) * 32 * kRowBytes));
+                kf[n - kMfmas] = lds_read_b128(from0 + ka[(n - kMfmas) / KB] + (KP + (n - kMfmas) % KB * 32 * kRowBytes));
         }
         if (WITH_QK) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                sacc[0][i] = 0.0f;
-                sacc[1][i] = 0.0f;
-            }
+            for (int i = 0; i < 16; ++i)
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                sacc[u & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[u], qf[u >> 1], sacc[u & 1], 0, 0, 0);
+                for (int kb = 0; kb < KB; ++kb) sacc[kb][i] = 0.0f;
+#pragma unroll
+            for (int u = 0; u < kMfmas; ++u) {
+                sacc[u % KB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[u], qf[u / KB], sacc[u % KB], 0, 0, 0);
                 const int n = u + kAhead;
-                if (n < 16) kf[n] = lds_read_b128(lds0 + ka[n >> 1] + (KP + (n & 1) * 32 * kRowBytes));
+                if (n < kMfmas) kf[n] = lds_read_b128(from0 + ka[n / KB] + (KP + n % KB * 32 * kRowBytes));
             }
         }
         constexpr int kVReads = RETILED ? 1 : 2;         // LDS instructions per V fragment
         SGB(DSR, kAhead * kVReads);
 #pragma unroll
-        for (int u = 0; u < 16 - kAhead; ++u) {
+        for (int u = 0; u < kMfmas - kAhead; ++u) {
             SGB(MFMA, 1);
             SGB(DSR, kVReads);
         }
         if (WITH_QK) {
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
+            for (int u = 0; u < kMfmas; ++u) {
                 SGB(MFMA, 1);
                 SGB(DSR, 1);
             }
@@ -461,14 +482,13 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
     // S^T of tile 0 (prologue only)
     auto qk_mfmas = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            sacc[0][i] = 0.0f;
-            sacc[1][i] = 0.0f;
-        }
+        for (int i = 0; i < 16; ++i)
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
+            for (int kb = 0; kb < KB; ++kb) sacc[kb][i] = 0.0f;
+#pragma unroll
+        for (int u = 0; u < kMfmas; ++u)
             sacc[u >> 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                lds_read_b128(lds0 + ka[u & 7] + (u >> 3) * 32 * kRowBytes), qf[u & 7], sacc[u >> 3], 0, 0, 0);
+                lds_read_b128(from0 + ka[u & 7] + (u >> 3) * 32 * kRowBytes), qf[u & 7], sacc[u >> 3], 0, 0, 0);
     };
     // ---- ping-pong schedule.  K tile j lives in K buffer j & 1, V^T tile j in V buffer j & 1.
     // The 8 waves form two groups of 4 (one wave of each group per SIMD).  Each wave alternates a VALU
@@ -506,9 +526,9 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
         // V buffer PAR, first product of tile j+1 from K buffer PAR ^ 1).
         auto tile_step = [&](int j, auto par_tag) __attribute__((always_inline)) {
             constexpr int PAR = decltype(par_tag)::value;
-            if (GROUPS == 1 || grp == 1) {
-                dma_v_tile(j + 1, PAR ^ 1, wig, W4{});
-                if (j + 2 < tile_end) dma_k_tile(j + 2, PAR, wig, W4{});
+            if (GROUPS == 1 || KEYS > 1 || grp == 1) {
+                dma_v_tile(j + 1, PAR ^ 1, wig, WGrp{});
+                if (j + 2 < tile_end) dma_k_tile(j + 2, PAR, wig, WGrp{});
             }
             softmax_tile(j, exact_tag);
             between_phases();
@@ -516,7 +536,7 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
             __builtin_amdgcn_s_setprio(3);
             mfma_phase(std::true_type{}, par_tag);
             __builtin_amdgcn_s_setprio(0);
-            if (GROUPS == 1 || grp == 1) wait_dma();
+            if (GROUPS == 1 || KEYS > 1 || grp == 1) wait_dma();
             PHASE_BARRIER();
         };
         // last tile: no next tile to prefetch or to start
@@ -540,6 +560,10 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
             last_step(j + 1, P1{});
         } else {
             last_step(j, P0{});
+        }
+        if (KEYS > 1 && tile_end - tile_begin < (int)((ntiles + KEYS - 1) / KEYS)) {      // a key group with a tile less than another
+            PHASE_BARRIER();
+            PHASE_BARRIER();
         }
         if (GROUPS == 2 && grp == 0) PHASE_BARRIER();
     };
@@ -571,6 +595,71 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
         sweep(std::true_type{});
         if (GROUPS == 1) __syncthreads();            // every wave is past its last V tile, over which output rows are about to lie
         l_tot = xhalf_sum(l_run);
+    }
+    if (KEYS > 1) {
+        // Merge of the key groups: with m* = max_s m_s and w_s = 2^(m_s - m*), O = sum_s w_s O_s / sum_s w_s l_s.  The tiles' place is
+        // free.  Each wave has 16 KiB of it for its accumulators as they lie, [b][g][lane][4], merges 4 / KEYS of the four blocks of
+        // head-dim for its queries, and keeps its offsets and sums where the blocks that it merges itself would lie.
+        constexpr int kOwn = 4 / KEYS;
+        int el = lane;                               // the lane number under another name, as below
+        asm volatile("" : "+v"(el));
+        const int e_qc = el & 31, e_row = el >> 4, e_p = el & 15;
+        const int32_t o_row = out.cache ? idx_sel[lane_row(e_qc)] : 0;
+        auto place = [&](int s, int b) { return lds0 + ((s * kKeyWaves + iwave) * 4 + b) * 4096; };
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            if (b / kOwn == kg) continue;
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                *reinterpret_cast<floatx4 __attribute__((address_space(3))) *>((uintptr_t)(place(kg, b) + g * 1024 + el * 16)) =
+                    floatx4{oacc[b][4 * g], oacc[b][4 * g + 1], oacc[b][4 * g + 2], oacc[b][4 * g + 3]};
+        }
+        if (el < 32)
+            *reinterpret_cast<floatx2 __attribute__((address_space(3))) *>((uintptr_t)(place(kg, kg * kOwn) + e_qc * 8)) = floatx2{m_c, l_tot};
+        __syncthreads();
+        float ms[KEYS], m_star = -INFINITY, l = 0.0f;
+        float w[KEYS];
+#pragma unroll
+        for (int s = 0; s < KEYS; ++s) {
+            const floatx2 ml = *reinterpret_cast<const floatx2 __attribute__((address_space(3))) *>((uintptr_t)(place(s, s * kOwn) + e_qc * 8));
+            ms[s] = ml[0];
+            w[s] = ml[1];
+            m_star = fmaxf(m_star, ms[s]);
+        }
+#pragma unroll
+        for (int s = 0; s < KEYS; ++s) {
+            ms[s] = exp2f(ms[s] - m_star);
+            l += ms[s] * w[s];
+        }
+        const float inv = 1.0f / l;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            if (b / kOwn != kg) continue;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < KEYS; ++s) {
+                    const floatx4 o = s == kg ? floatx4{oacc[b][4 * g], oacc[b][4 * g + 1], oacc[b][4 * g + 2], oacc[b][4 * g + 3]}
+                                              : lds_read_f32x4(place(s, b) + g * 1024 + el * 16);
+                    acc += ms[s] * o;
+                }
+                uint2v o4;
+                o4[0] = pack_bf16(acc[0] * inv, acc[1] * inv);
+                o4[1] = pack_bf16(acc[2] * inv, acc[3] * inv);
+                rows_put(rows_lds, b, g, el, o4);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 8 / KEYS; ++i) {
+            const int n = 4 * (i * KEYS + kg) + e_row;
+            const int64_t token = __shfl(o_row, n);
+            store_row(out, H, head, r0 + n, token, e_p, rows_get(rows_lds, n, e_p), (int64_t)n < row_n);
+        }
+        if (lse_sel && kg == 0 && el < 32 && (int64_t)el < row_n)
+            lse_sel[(r0 + el) * H + head] = (m_star + log2f(l)) * 0.69314718055994530942f;
+        return;
     }
     if (pslot >= 0) {
         // a key-range share of an item: unnormalised accumulators, running max and row sum go to the workspace;
@@ -770,6 +859,45 @@ static bool half_workgroups(int32_t H, int64_t k_sel, int64_t slots, const AttnS
            (rounds > 3 || rounds < (slots + kCuPerXcd - 1) / kCuPerXcd || (halves - 1) % kRound < kCuPerXcd);
 }
 
+// How many key groups the eight waves of a workgroup form.  With few items, the halves' four waves have a SIMD each to themselves, where nothing
+// runs while one of them is not in its MFMAs, and shares cost a merging launch.  Two key groups on the same 128 queries take turns at the
+// matrix pipe instead, and four on 64 queries give CUs work that would have none; the price is key tiles copied for half or a quarter
+// of the queries.  They are taken where every item gets a CU of its own, by estimates of the microseconds a call takes, fitted to 120 shapes of
+// 2 to 170 key tiles (rms 3 %, and 0.3 % lost on choosing by them): n workgroups on an XCD, a step the key groups' tiles.
+// Before / with them, us: 2025 keys x 608 queries x 24 heads (three shares) 31.0 / 23.2, 1497 x 615 x 24 28.7 / 17.7, 900 x 450 x 24 20.6 / 13.8,
+// 1220 x 1746 x 8 26.1 / 15.6, 512 x 1000 x 8 12.6 / 9.2, 2705 x 1894 x 8 33.3 / 27.6; two groups: 1460 x 1460 x 16 29.5 / 24.7, 2072 x 1450 x 16 41.0 /
+// 31.5, 3836 x 1918 x 16 68.6 / 58.1; not taken: 1992 x 317 x 4 13.4 (eight shares) / 18.5, 274 x 1479 x 16 11.1 / 11.1.
+// What bounds four groups is LDS: their tiles are written for two waves each and V fragments are two reads (10454 x 1045 x 12 86 us, 63 without copies).
+static int key_groups(int64_t N, int32_t H, int64_t k_sel, int64_t slots, const AttnSchedule &sch, bool narrow)
+{
+    const int64_t ntiles = (N + kBk - 1) / kBk, blocks = (N + 31) / 32;
+    auto per_xcd = [&](int64_t queries) { return ((k_sel + queries - 1) / queries * H + kNumXcd - 1) / kNumXcd; };
+    if (slots > 2 * kCuPerXcd || blocks < 4) return 1;
+    const double n1 = (double)(per_xcd(128) * (sch.full_items ? 1 : sch.splits)), n2 = (double)per_xcd(128), n4 = (double)per_xcd(64);
+    double best;
+    if (narrow && slots <= kCuPerXcd) {
+        best = 6.1 + (double)sch.tiles_per_split * (0.87 + 0.008 * n1) + (sch.splits > 1 ? 1.6 + 0.13 * n1 : 0.0);
+    } else {
+        const int64_t left = sch.items_per_xcd - sch.full_items, rounds = sch.full_items / kCuPerXcd, rest = left ? left : sch.full_items % kCuPerXcd;
+        best = 1.042 * ((double)rounds * tail_us(kCuPerXcd, 1, ntiles) + (rest ? tail_us(rest, sch.splits, ntiles) : 0.0)) - 9.2;
+    }
+    int keys = 1;
+    const double two = 7.6 + (double)((ntiles + 1) / 2) * (0.99 + 0.017 * n2), four = 6.2 + (double)((blocks + 3) / 4) * (0.744 + 0.0051 * n4) + 0.03 * n4;
+    if (n2 <= kCuPerXcd && ntiles >= 2 && two < best) {
+        best = two;
+        keys = 2;
+    }
+    return n4 <= kCuPerXcd && four < best ? 4 : keys;
+}
+
+int attn_bf16_key_groups(int64_t N, int32_t H, int64_t k_sel)
+{
+    AttnSchedule sch;
+    int64_t slots = 0;
+    if (k_sel > kRetileRows || !plan_attn(N, H, k_sel, sch, slots)) return 1;
+    return key_groups(N, H, k_sel, slots, sch, half_workgroups(H, k_sel, slots, sch));
+}
+
 int attn_bf16_plan(int64_t N, int32_t H, int64_t k_sel, int64_t plan[8])
 {
     AttnSchedule sch;
@@ -815,12 +943,18 @@ int launch_attn_bf16_d128(const void *q, const void *k, const void *v, int64_t N
     int64_t slots = 0;
     if (!plan_attn(N, H, k_sel, sch, slots))
         return fail(ASTRAEA_ERR_INVALID, "astraea_sparse_attn_fwd: grid too large");
-    const int64_t left = sch.items_per_xcd - sch.full_items;
     char *vt = (char *)workspace;
     float *partial = (float *)(vt + vt_bytes(N, H));
     const bool retile = k_sel > kRetileRows;
     const bool narrow = half_workgroups(H, k_sel, slots, sch);
-    const int groups = narrow ? 1 : 2;
+    const int keys = retile ? 1 : key_groups(N, H, k_sel, slots, sch, narrow);
+    if (keys > 1) {          // every item whole, 256 / keys queries each
+        sch.q_tiles = (uint32_t)((k_sel + kBq / keys - 1) / (kBq / keys));
+        slots = sch.items_per_xcd = sch.full_items = (uint32_t)(((int64_t)sch.q_tiles * H + kNumXcd - 1) / kNumXcd);
+        sch.splits = 1;
+    }
+    const int64_t left = sch.items_per_xcd - sch.full_items;
+    const int groups = narrow && keys == 1 ? 1 : 2;
     dim3 grid((unsigned)(slots * kNumXcd * (2 / groups))), block(groups * kGroupWaves * kWave);
     const float c = scale * 1.44269504088896340736f;
     if (retile)
@@ -832,10 +966,12 @@ int launch_attn_bf16_d128(const void *q, const void *k, const void *v, int64_t N
                            partial);
     };
     kernel_timer_begin(stream);
-    if (retile && narrow) go(attn_bf16_kernel<true, 1>, vt);
-    else if (narrow) go(attn_bf16_kernel<false, 1>, v);
-    else if (retile) go(attn_bf16_kernel<true, 2>, vt);
-    else go(attn_bf16_kernel<false, 2>, v);
+    if (keys == 4) go(attn_bf16_kernel<false, 2, 4>, v);
+    else if (keys == 2) go(attn_bf16_kernel<false, 2, 2>, v);
+    else if (retile && narrow) go(attn_bf16_kernel<true, 1, 1>, vt);
+    else if (narrow) go(attn_bf16_kernel<false, 1, 1>, v);
+    else if (retile) go(attn_bf16_kernel<true, 2, 1>, vt);
+    else go(attn_bf16_kernel<false, 2, 1>, v);
     kernel_timer_end(stream);
     if (left > 0)
         with_shares((int)sch.splits, [&](auto shares) {

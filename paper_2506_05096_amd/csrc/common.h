@@ -92,6 +92,7 @@ struct AttnOut {
 };
 size_t attn_bf16_workspace_bytes(int64_t N, int32_t H);
 int attn_bf16_plan(int64_t N, int32_t H, int64_t k_sel, int64_t plan[8]);
+int attn_bf16_key_groups(int64_t N, int32_t H, int64_t k_sel);
 int launch_attn_bf16_d128(const void *q, const void *k, const void *v, int64_t N, int32_t H, int64_t q_stride_n,
                           int64_t q_stride_h, int64_t kv_stride_n, int64_t kv_stride_h, const int32_t *idx_sel,
                           int64_t k_sel, int q_is_compact, float scale, const AttnOut &out, float *lse_sel, void *workspace,

@@ -277,6 +277,48 @@ def test_attn_bf16_half_workgroups_that_sweep_again(n, h, k):
         assert ((lse[:, i].double() - want).abs() / want.abs().clamp(min=1.0)).max().item() <= 2.0 ** -9
 
 
+# Eight waves as two or four key groups (`groups` is what the launch says): one key block per group, uneven shares of the keys, ragged last tiles of
+# keys and queries, query waves without rows, a full round, and rows that send the workgroup through its sweep again.  Next to them
+# the shares that key groups leave to the merging launch, each number of them.  Bars as above.
+@pytest.mark.parametrize("n,h,k,hot,scatter,groups,splits", [
+    (97, 1, 1, False, True, 4, 1), (128, 3, 40, True, True, 4, 1), (129, 2, 65, True, True, 4, 1), (161, 5, 64, False, False, 4, 1),
+    (223, 24, 255, True, False, 4, 1), (255, 16, 129, True, True, 4, 1), (1500, 24, 610, True, True, 4, None),
+    (1028, 4, 4102, False, False, 2, 1), (1460, 16, 1460, True, True, 2, 1), (1089, 8, 3969, True, False, 2, 1), (1500, 2, 16384, False, False, 2, 1),
+    (130, 16, 2000, True, False, 1, 1), (3716, 12, 1400, True, True, 1, 3), (1762, 2, 2470, False, False, 1, 4), (957, 1, 41, True, True, 1, 5),
+    (762, 1, 167, False, True, 1, 6), (2080, 1, 37, True, True, 1, 7), (1398, 1, 20, False, True, 1, 8),
+])
+def test_attn_bf16_key_groups(n, h, k, hot, scatter, groups, splits):
+    assert ab.astraea_attn_key_groups(n, h, k) == groups
+    test_attn_bf16_tiles(n, h, k, hot, scatter, splits)
+
+
+# Key groups that all sweep again, the first of them with logits 90 nats below the others' and its own later ones, or none but the first one's
+# rows above its offset; queries by index, the compact result and the cached rows written at once.
+@pytest.mark.parametrize("n,h,k", [(700, 8, 600), (161, 4, 161), (1460, 16, 1460), (1411, 16, 1400)])
+@pytest.mark.parametrize("rise_nats", [30.0, 90.0])
+def test_attn_bf16_key_groups_that_sweep_again(n, h, k, rise_nats):
+    assert ab.astraea_attn_key_groups(n, h, k) > 1
+    q, kc, vc = _attn_rise_case(n, h, n, 128, rise_nats, torch.bfloat16, 32)
+    vc[n - 32:] *= 2.0 ** 10
+    g = torch.Generator(device=DEV).manual_seed(k)
+    idx = torch.randperm(n, device=DEV, generator=g)[:k].sort().values.to(torch.int32)
+    lse = torch.full((k, h), math.nan, device=DEV)
+    out = torch.empty(k, h, 128, dtype=torch.bfloat16, device=DEV)
+    cache = torch.randn(n, h * 128, device=DEV, generator=g).bfloat16()
+    want_cache = cache.clone()
+    ws = torch.full((ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, 128),), 255, dtype=torch.uint8, device=DEV)
+    ab.astraea_sparse_attn_scatter_fwd(q, kc, vc, idx, k, out, cache, 1.0 / math.sqrt(128), lse_sel=lse, workspace=ws)
+    torch.cuda.synchronize()
+    want_cache[idx.long()] = out.view(k, -1)
+    assert torch.equal(cache, want_cache)
+    for i in range(h):
+        logits = q[idx.long(), i].double() @ kc[:, i].double().T.contiguous() / math.sqrt(128)
+        ref = torch.softmax(logits, 1) @ vc[:, i].double()
+        assert_rel_l2(out[:, i].double().cpu().numpy(), ref.cpu().numpy(), tag=f"head {i}")
+        want = torch.logsumexp(logits, 1)
+        assert ((lse[:, i].double() - want).abs() / want.abs().clamp(min=1.0)).max().item() <= 2.0 ** -9
+
+
 # The compact result and the cached rows from one call, against the two calls it stands for: whole and cut work items, both workgroup
 # sizes, cached buffers that the kernel writes itself and those that get a launch of their own (stride, alignment, memory shared with q).
 @pytest.mark.parametrize("dtype,n,h,d,k,queries,splits", [
