@@ -4,15 +4,15 @@
 // one accumulator walks the channels in ascending order.  One lane owns a token's accumulator and the
 // rest of the design is about feeding it: both feature arrays are read in 16-byte vectors along the
 // rows, turned into fp32 differences, and handed over through an LDS tile whose row t the lane of
-// token t walks.  A chain step takes ~5 clocks, so 3072 channels are 6.5 us however many tokens there are.
+// token t walks.  A chain step takes 5.4 clocks (2.2 ns), so 3072 channels are 6.9 us however many tokens there are.
 //
 // Two kernels, by the number of tokens:
 //  * score_kernel: a workgroup of two waves owns 16 tokens.  The first wave loads slabs of [16 tokens x 256
 //    bytes] of both arrays, four slabs in flight, and writes the differences; the second runs the chains, one
-//    slab behind, with one barrier per slab.  16 tokens per workgroup instead of 64 per wave is what a
+//    slab behind and reading 64 channels ahead of them, with one barrier per slab.  16 tokens per workgroup instead of 64 per wave is what a
 //    short sequence needs: at 17550 tokens 64 per wave make 275 waves, one per CU, and each slab's
 //    load latency, its conversion and its chain came one after the other.  Cold arrays, 64 per wave -> this
-//    kernel: 2025 x 3072 bf16 63 -> 14.5 us; 17550 x 3072 80 -> 41 us (5.3 TB/s); 16384 x 512 13.1 -> 8.8;
+//    kernel, its chain waiting for each slab's reads: 2025 x 3072 bf16 63 -> 14.5 us; 17550 x 3072 80 -> 41 us (5.3 TB/s); 16384 x 512 13.1 -> 8.8;
 //    4096 x 512 fp32 14.3 -> 8.5; 36000 x 3072 89.8 -> 74.5.  Tried: one wave for both jobs 22 and 49 us at
 //    2025 and 17550 tokens; slabs of 8 x 512 B the same, 32 x 128 B 20 us at 2025.
 //  * score_wide_kernel: a wave owns 64 tokens and does both jobs (a [64 x 128 byte] slab, the next one in flight).
@@ -48,6 +48,7 @@ constexpr int kVecPerRow = kSegBytes / 16;
 constexpr int kRowsPerLoad = kWave / kVecPerRow;
 constexpr int kVecPerLane = kTok / kRowsPerLoad;
 constexpr int kDepth = 4;           // slabs in flight
+constexpr int kTiles = 3;           // LDS tiles: one is written, two are read
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
@@ -127,7 +128,7 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
     constexpr int PLANES = EPV / 4;                    // a vector's floats are kept as 16-byte pieces, piece p in plane p
     constexpr int PLANE = 4 * kVecPerRow;              // floats
     constexpr int PITCH = SEG + 4;                     // floats; the 16 row reads of a piece hit distinct banks
-    __shared__ __attribute__((aligned(16))) float tile[2][kTok * PITCH];
+    __shared__ __attribute__((aligned(16))) float tile[kTiles][kTok * PITCH];
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -161,6 +162,7 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
             }
             __builtin_amdgcn_sched_barrier(0);         // the waits count on this order
         };
+        int wt = 0;                                    // the tile written next
         // differences of slab s -> LDS tile
         auto slab = [&](int32_t s, auto buf_tag) __attribute__((always_inline)) {
             constexpr int B = decltype(buf_tag)::value;
@@ -184,7 +186,7 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
                                        : 0.0f;
                         }
                     }
-                    float *dst = tile[B & 1] + (j * kRowsPerLoad + vrow) * PITCH + vcol * 4;
+                    float *dst = tile[wt] + (j * kRowsPerLoad + vrow) * PITCH + vcol * 4;
 #pragma unroll
                     for (int p = 0; p < PLANES; ++p)
                         *reinterpret_cast<float4 *>(dst + p * PLANE) = make_float4(d[4 * p], d[4 * p + 1], d[4 * p + 2], d[4 * p + 3]);
@@ -207,6 +209,7 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
             slab(s, buf_tag);
             issue(s + kDepth, buf_tag);
             publish();
+            wt = wt == kTiles - 1 ? 0 : wt + 1;
         };
         int32_t s = 0;
         for (; s + kDepth <= nslab; s += kDepth) {
@@ -215,48 +218,75 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
             step(s + 2, B2{});
             step(s + 3, B3{});
         }
-        if (s < nslab) {
-            slab(s, B0{});
+        auto last = [&](int32_t at, auto buf_tag) __attribute__((always_inline)) {
+            if (at >= nslab) return;
+            slab(at, buf_tag);
             publish();
-        }
-        if (s + 1 < nslab) {
-            slab(s + 1, B1{});
-            publish();
-        }
-        if (s + 2 < nslab) {
-            slab(s + 2, B2{});
-            publish();
-        }
+            wt = wt == kTiles - 1 ? 0 : wt + 1;
+        };
+        last(s, B0{});
+        last(s + 1, B1{});
+        last(s + 2, B2{});
+        publish();                       // the chains are a slab behind
         return;
     }
 
+    // The chains.  A dependent instruction per channel is their time, so little else may stand among them: pieces are read 64 channels ahead, in
+    // the first half of the instructions of the 64 channels before their own, and waited for once.  Nine reads at the head of a slab waited
+    // for there, and a wait for each later one, took 3.9 ns a channel; this takes 2.4: 2025 x 3072 bf16 hot / cold 14.8 / 18.0 -> 12.2 / 15.5 us,
+    // 17550 x 3072 39.7 / 43.3 -> 38.1 / 41.8, 45000 x 3072 87.8 -> 85.9; against it 28000 x 512 12.3 -> 12.9 hot.  Two loading waves: 13.1 and
+    // 39.3 us at the first two sizes; four, with six slabs in flight, 12.4 and 55.9.
     float acc = 0.0f;
-    for (int32_t s = 0; s < nslab; ++s) {
-        publish();
-        if (lane < kTok) {
-            const float *row = tile[s & 1] + lane * PITCH;
-            auto piece = [&](int e) { return *reinterpret_cast<const float4 *>(row + (e % PLANES) * PLANE + (e / PLANES) * 4); };
-            constexpr int A = 8;             // pieces read ahead of the chain
-            float4 v[A];
+    constexpr int UNIT = 16, UNITS = SEG / 4 / UNIT;   // pieces that are read at a time, and such units of a slab: two, in fp32 one
+    float4 v[2][UNIT];
+    const int t = lane % kTok;           // the other lanes do what the first kTok do
+    auto read = [&](int tl, int unit, int buf, int e) __attribute__((always_inline)) {
+        const int p = unit * UNIT + e;
+        v[buf][e] = *reinterpret_cast<const float4 *>(tile[tl] + t * PITCH + (p % PLANES) * PLANE + (p / PLANES) * 4);
+    };
+    auto channel = [&](float x) __attribute__((always_inline)) {
+        if (MODE == ASTRAEA_DELTA_MEAN_ABS)
+            acc = acc + fabsf(x);
+        else
+            acc = __builtin_fmaf(x, x, acc);
+    };
+    // the chain through the unit in buffer B, and the reads of the next, unit `next` of tile tl, into the other buffer
+    auto chain = [&](auto buf_tag, int tl, int next) __attribute__((always_inline)) {
+        constexpr int B = decltype(buf_tag)::value;
 #pragma unroll
-            for (int e = 0; e < A; ++e) v[e] = piece(e);
-#pragma unroll
-            for (int e = 0; e < SEG / 4; ++e) {
-                const float4 u = v[e % A];
-                if (e + A < SEG / 4) v[e % A] = piece(e + A);
-                if (MODE == ASTRAEA_DELTA_MEAN_ABS) {
-                    acc = acc + fabsf(u.x);
-                    acc = acc + fabsf(u.y);
-                    acc = acc + fabsf(u.z);
-                    acc = acc + fabsf(u.w);
-                } else {
-                    acc = __builtin_fmaf(u.x, u.x, acc);
-                    acc = __builtin_fmaf(u.y, u.y, acc);
-                    acc = __builtin_fmaf(u.z, u.z, acc);
-                    acc = __builtin_fmaf(u.w, u.w, acc);
-                }
-                __builtin_amdgcn_sched_barrier(0);
+        for (int e = 0; e < UNIT; ++e) {
+            const float4 u = v[B][e];
+            if (e < UNIT / 2) {
+                read(tl, next, B ^ 1, 2 * e);
+                read(tl, next, B ^ 1, 2 * e + 1);
             }
+            channel(u.x);
+            channel(u.y);
+            channel(u.z);
+            channel(u.w);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __builtin_amdgcn_s_waitcnt(0xc07f);            // lgkmcnt(0)
+    };
+    using V0 = std::integral_constant<int, 0>;
+    using V1 = std::integral_constant<int, 1>;
+    publish();                           // slab 0 is in its tile
+#pragma unroll
+    for (int e = 0; e < UNIT; ++e) read(0, 0, 0, e);
+    int tl = 0;
+    auto next_tile = [&]() { tl = tl == kTiles - 1 ? 0 : tl + 1; };
+    for (int32_t s = 0; s < nslab; ++s) {
+        publish();                       // slab s + 1 is, if there is one: past the last slab what lies there is read and not used
+        if (UNITS == 2) chain(V0{}, tl, 1);
+        next_tile();
+        if (UNITS == 2) {
+            chain(V1{}, tl, 0);
+        } else {
+            chain(V0{}, tl, 0);
+            if (++s == nslab) break;
+            publish();
+            next_tile();
+            chain(V1{}, tl, 0);
         }
     }
     if (lane >= kTok) return;

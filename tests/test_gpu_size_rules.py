@@ -37,6 +37,14 @@ def test_score_sizes(n, c, stride, dtype, mode):
     assert np.array_equal(out.cpu().numpy().view(np.uint32), exp.view(np.uint32))
 
 
+# The chains run one slab behind a ring of three tiles and of four slabs in flight: every pair of remainders, and a ragged last slab.
+@pytest.mark.parametrize("slabs", range(6, 18))
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_score_ring(slabs, dtype):
+    per_slab = 256 // dtype.itemsize
+    test_score_sizes(35, slabs * per_slab - 5 * (slabs % 2), slabs * per_slab, dtype, ab.DELTA_L2)
+
+
 # fp32 linear: 128-, 64- or 32-wide tiles by an estimate of the rounds they leave (32: the four waves split the contraction, and
 # a 64-wide contraction leaves two of them without a stage); stages of 32 indices, four in flight, 128: of 16 in pairs.  `tile` is what the
 # launch says it takes; each tile meets ragged rows and features and contractions that end inside the ring.  Bound: sums of c_in
