@@ -863,7 +863,8 @@ static bool half_workgroups(int32_t H, int64_t k_sel, int64_t slots, const AttnS
 // runs while one of them is not in its MFMAs, and shares cost a merging launch.  Two key groups on the same 128 queries take turns at the
 // matrix pipe instead, and four on 64 queries give CUs work that would have none; the price is key tiles copied for half or a quarter
 // of the queries.  They are taken where every item gets a CU of its own, by estimates of the microseconds a call takes, fitted to 120 shapes of
-// 2 to 170 key tiles (rms 3 %, and 0.3 % lost on choosing by them): n workgroups on an XCD, a step the key groups' tiles.
+// 2 to 170 key tiles (rms 3 %, and 0.3 % lost on choosing by them): n workgroups on an XCD, a step the key groups' tiles.  A step of four groups takes
+// 0.74 us and not 0.82 in calls that repeat with their keys cached; by that, layer-steps of 6088 x 608 x 16 took 72.6 us for 62.3, 4837 x 967 x 12 65.6 for 58.8.
 // Before / with them, us: 2025 keys x 608 queries x 24 heads (three shares) 31.0 / 23.2, 1497 x 615 x 24 28.7 / 17.7, 900 x 450 x 24 20.6 / 13.8,
 // 1220 x 1746 x 8 26.1 / 15.6, 512 x 1000 x 8 12.6 / 9.2, 2705 x 1894 x 8 33.3 / 27.6; two groups: 1460 x 1460 x 16 29.5 / 24.7, 2072 x 1450 x 16 41.0 /
 // 31.5, 3836 x 1918 x 16 68.6 / 58.1; not taken: 1992 x 317 x 4 13.4 (eight shares) / 18.5, 274 x 1479 x 16 11.1 / 11.1.
@@ -882,7 +883,7 @@ static int key_groups(int64_t N, int32_t H, int64_t k_sel, int64_t slots, const 
         best = 1.042 * ((double)rounds * tail_us(kCuPerXcd, 1, ntiles) + (rest ? tail_us(rest, sch.splits, ntiles) : 0.0)) - 9.2;
     }
     int keys = 1;
-    const double two = 7.6 + (double)((ntiles + 1) / 2) * (0.99 + 0.017 * n2), four = 6.2 + (double)((blocks + 3) / 4) * (0.744 + 0.0051 * n4) + 0.03 * n4;
+    const double two = 7.6 + (double)((ntiles + 1) / 2) * (0.99 + 0.017 * n2), four = 6.2 + (double)((blocks + 3) / 4) * (0.82 + 0.0051 * n4) + 0.03 * n4;
     if (n2 <= kCuPerXcd && ntiles >= 2 && two < best) {
         best = two;
         keys = 2;
