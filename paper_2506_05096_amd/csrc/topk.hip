@@ -7,7 +7,7 @@
 //   3. the selected indices are compacted in ascending index order: an element is selected iff key > T, or
 //      key == T and fewer than `need` equal elements precede it.  Ranks come from wavefront ballots and counts.
 // The score array (4N bytes) stays in the caches; the step is latency-bound.  By the number of scores:
-//   * up to 32768: one workgroup, one launch, keys in registers.  (A single workgroup that streams more scores than
+//   * up to 32768: one launch, every workgroup with all keys in registers, sharing the outputs.  (A single workgroup that streams more scores than
 //     it holds from L2 in every pass was measured too: one CU's loads are latency-bound, 129 us at 118800 scores.)
 //   * up to 786432, if the workspace holds a slot per workgroup: a launch per digit and one for the outputs.  us, indices
 //     alone / every output, by this and by the next form: 33000 scores 23 / 23 and 34 / 36, 118800 24 / 24 and 43 / 45, 262144
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(const float *__rest
     }
 }
 
-// ---- small inputs: the whole selection in one workgroup and one launch, the keys in registers.  Wave w owns the elements
+// ---- small inputs: the whole selection in one launch of workgroups that each do all of it, the keys in registers, and share the outputs.  Wave w owns the elements
 // [w*items*64, (w+1)*items*64), element (w*items + j)*64 + lane in register j, so that loads and stores are coalesced and
 // ranks in index order come from ballots.  The keys' range is found first and the passes look at its bits only: digit 1 is
 // (key - lowest) >> shift, up to 2048 bins, digit 2 the next 11 bits of the keys that share it, and so on until the shift
@@ -311,8 +311,13 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(const float *__rest
 // 20.0 / 40.2 -> 12.8 / 15.5, 32768 30.1 / 77.7 -> 21.4 / 26.3; 17550 scores, 70 % of them 0, 22.7 / 42.3 -> 15.0 / 17.4 (with the
 // lowest counted 20.8 / 23.2), 25000, nearly all 0, 28.3 / 58.2 -> 19.7 / 23.4 (32.5 / 36.1), 17550 half 1 and half -1 24.4 / 44.6 ->
 // 19.5 / 22.0.  A run-time count of elements per thread took 18.1 / 20.5 at 17550, eight copies of the histogram side by side
-// 20.5 / 23.5; a digit that many lanes share counted by ballot cost all other distributions 0.5 us.
+// 20.5 / 23.5; a digit that many lanes share counted by ballot cost all other distributions 0.5 us; a first digit of 8 bits with 32 copies cost
+// most distributions 0.3 - 0.9 us (17550 half 1 and half -1 21.8 -> 19.0).
+// The outputs are a store of 4 bytes and more per element from one CU, and their order takes ballots.  So ITEMS / 2 workgroups do the same
+// selection, each on a CU, and a thread of each writes the outputs of two elements.  One workgroup / now, us, indices alone and every output:
+// 4096 scores 6.9 / 7.1 -> 6.5 / 6.7, 17550 13.2 / 15.7 -> 11.6 / 11.7, 32768 21.7 / 26.7 -> 18.4 / 18.6; two workgroups 12.2 / 13.0 at 17550.
 constexpr int kSmallMax = 32768;
+constexpr int kOutItems = 2;                // elements of a thread whose outputs a workgroup writes
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / kWave;
 constexpr int kCopyPitch = kBins + 16;       // of the histogram's copies: their counters lie in different banks
@@ -393,12 +398,20 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(const float *
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int first = wave * ITEMS * kWave + lane;                      // element j of this thread: first + 64 j
     uint32_t key[ITEMS];
-    int32_t skip[ITEMS];
+    constexpr int PARTS = ITEMS / kOutItems;
+    const int part = PARTS == 1 ? 0 : blockIdx.x;                       // the elements whose outputs, and counters, are this workgroup's
+    int32_t skip[kOutItems];
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
         const int i = first + j * kWave < N ? first + j * kWave : N - 1;     // unconditional loads stay in flight together
         key[j] = __float_as_uint(score[i]);
-        if (skip_count) skip[j] = skip_count[i];
+    }
+    if (skip_count) {
+#pragma unroll
+        for (int j = 0; j < kOutItems; ++j) {
+            const int i = first + (part * kOutItems + j) * kWave;
+            skip[j] = skip_count[i < N ? i : N - 1];
+        }
     }
     for (int i = tid; i < kCopyPitch * kCopies / 4; i += kSmallThreads) reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0, 0, 0, 0);
     uint32_t *mine = hist + (lane & (kCopies - 1)) * kCopyPitch;
@@ -482,7 +495,7 @@ __global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(const float *
         need = k_rem;
     }
     // last read of wt_a before the barriers above (k == 0: for the key range, unused then)
-    emit_in_order<ITEMS, 1>(key, skip, first, wave, lane, T, need, 0u, 0u, wt_a, wt_b, idx_sel, idx_remain, sel_mask, skip_count, 0);
+    emit_in_order<ITEMS, PARTS>(key, skip, first, wave, lane, T, need, 0u, 0u, wt_a, wt_b, idx_sel, idx_remain, sel_mask, skip_count, part);
 }
 
 // ---- more scores than one workgroup takes: a launch for each of three digits and one for the outputs.  A workgroup owns 12288
@@ -728,29 +741,29 @@ int launch_select_topk(const float *score, int64_t N, int64_t k, int32_t *idx_se
 {
     if (N == 0) return ASTRAEA_OK;
     if (N <= kSmallMax) {
-        auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3(1), dim3(kSmallThreads), 0, stream, score, (int32_t)N, (uint32_t)k, idx_sel,
+        auto go = [&](auto kernel, int items) {
+            hipLaunchKernelGGL(kernel, dim3(items / kOutItems), dim3(kSmallThreads), 0, stream, score, (int32_t)N, (uint32_t)k, idx_sel,
                                idx_remain, sel_mask, skip_count);
         };
         // elements per thread, rounded up to an even number: a constant, so that nothing is tested per element and
         // all loads go out together
         switch ((N + 2 * kSmallThreads - 1) / (2 * kSmallThreads)) {
-        case 1: go(topk_small_kernel<2>); break;
-        case 2: go(topk_small_kernel<4>); break;
-        case 3: go(topk_small_kernel<6>); break;
-        case 4: go(topk_small_kernel<8>); break;
-        case 5: go(topk_small_kernel<10>); break;
-        case 6: go(topk_small_kernel<12>); break;
-        case 7: go(topk_small_kernel<14>); break;
-        case 8: go(topk_small_kernel<16>); break;
-        case 9: go(topk_small_kernel<18>); break;
-        case 10: go(topk_small_kernel<20>); break;
-        case 11: go(topk_small_kernel<22>); break;
-        case 12: go(topk_small_kernel<24>); break;
-        case 13: go(topk_small_kernel<26>); break;
-        case 14: go(topk_small_kernel<28>); break;
-        case 15: go(topk_small_kernel<30>); break;
-        default: go(topk_small_kernel<32>); break;
+        case 1: go(topk_small_kernel<2>, 2); break;
+        case 2: go(topk_small_kernel<4>, 4); break;
+        case 3: go(topk_small_kernel<6>, 6); break;
+        case 4: go(topk_small_kernel<8>, 8); break;
+        case 5: go(topk_small_kernel<10>, 10); break;
+        case 6: go(topk_small_kernel<12>, 12); break;
+        case 7: go(topk_small_kernel<14>, 14); break;
+        case 8: go(topk_small_kernel<16>, 16); break;
+        case 9: go(topk_small_kernel<18>, 18); break;
+        case 10: go(topk_small_kernel<20>, 20); break;
+        case 11: go(topk_small_kernel<22>, 22); break;
+        case 12: go(topk_small_kernel<24>, 24); break;
+        case 13: go(topk_small_kernel<26>, 26); break;
+        case 14: go(topk_small_kernel<28>, 28); break;
+        case 15: go(topk_small_kernel<30>, 30); break;
+        default: go(topk_small_kernel<32>, 32); break;
         }
         return check_launch("astraea_select_topk");
     }
