@@ -17,6 +17,9 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
     # packed fp32 VALU forms are kept off for all device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the first 16 dwords of a kernel's arguments come in registers, set up with the wave, instead of by a load that it waits for: 0.2 - 0.3 us of a
+    # launch; us a layer-step without / with: 2025 tokens at 30 % 49.8 / 48.4, 1055 x 211 x 16 32.5 / 30.0, block 1199 x 600 x 24 265.1 / 262.6
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-I", str(ROOT / "include"), "-I", str(CSRC),
 ]
 
