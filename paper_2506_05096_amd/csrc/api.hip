@@ -411,8 +411,7 @@ int astraea_linear_plan(astraea_dtype dt, int64_t k_sel, int64_t c_in, int64_t c
     if (k_sel <= 0 || k_sel > kMaxTokens || c_in <= 0 || c_out <= 0 || c_in > (1 << 24) || c_out > (1 << 24))
         return fail(ASTRAEA_ERR_INVALID, "astraea_linear_plan: k_sel=%lld, c_in=%lld, c_out=%lld out of range",
                     (long long)k_sel, (long long)c_in, (long long)c_out);
-    const int square = dt == ASTRAEA_F32 ? linear_f32_tile(k_sel, c_in, c_out, 1) : 0;
-    const LinearTile tile = dt == ASTRAEA_F32 ? LinearTile{square, square} : linear_bf16_tile(k_sel, (int32_t)c_in, c_out, 1);
+    const LinearTile tile = dt == ASTRAEA_F32 ? linear_f32_tile(k_sel, c_in, c_out, 1) : linear_bf16_tile(k_sel, (int32_t)c_in, c_out, 1);
     const int tokens = tile.tokens;
     plan_out[0] = tile.features;
     plan_out[1] = tokens;

@@ -76,12 +76,12 @@ int launch_linear_bf16(const void *x, const LinearPart *parts, int n_parts, cons
 int launch_linear_f32(const void *x, const LinearPart *parts, int n_parts, const int32_t *idx_sel, int64_t k_sel, int64_t n_rows,
                       int32_t c_in, int32_t c_out, int64_t ldx, int x_indexed, int act, hipStream_t stream);
 
-// The tile a bf16 linear launch takes, and the tokens (and as many features) of an fp32 one.
+// The tile a linear launch takes.
 struct LinearTile {
     int features, tokens;
 };
 LinearTile linear_bf16_tile(int64_t k_sel, int32_t c_in, int64_t c_out, int parts);
-int linear_f32_tile(int64_t k_sel, int64_t c_in, int64_t c_out, int parts);
+LinearTile linear_f32_tile(int64_t k_sel, int64_t c_in, int64_t c_out, int parts);
 
 // Where the attention puts row r: rows[r] of a compact [k_sel, H * D] result, and row idx_sel[r] of a cached buffer of cache_rows rows.
 // Either may be null; an index outside the cached buffer writes nothing.

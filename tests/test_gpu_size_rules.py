@@ -86,6 +86,19 @@ def test_linear_f32_tiles(n, k, c_in, c_out, gather, scatter, bias, act, tile):
     assert torch.equal(y[keep].double(), exp[keep])
 
 
+# Eight waves on 128 x 128 tiles (one round of them) and on 64 features x 128 tokens: ragged rows and features, a feature tile of eight, a row
+# in the last tile, stages that are no multiple of the register sets; the values that send a workgroup to fp32 products.  Bounds as above and below.
+@pytest.mark.parametrize("n,k,c_in,c_out,gather,scatter,bias,act,features", [
+    (3100, 3001, 512, 648, True, True, True, ab.ACT_GELU_TANH, 128), (3100, 2945, 576, 776, False, True, True, ab.ACT_NONE, 128),
+    (3100, 3072, 1088, 768, True, False, False, ab.ACT_NONE, 128),
+    (1300, 1250, 512, 776, True, True, True, ab.ACT_NONE, 64), (1300, 1281, 576, 776, True, False, True, ab.ACT_GELU_TANH, 64),
+    (1300, 1250, 640, 776, False, True, False, ab.ACT_NONE, 64), (3100, 3001, 512, 1288, True, True, True, ab.ACT_NONE, 64),
+])
+def test_linear_f32_halves(n, k, c_in, c_out, gather, scatter, bias, act, features):
+    assert ab.astraea_linear_plan(ab.F32, k, c_in, c_out)["tile_features"] == features
+    test_linear_f32_tiles(n, k, c_in, c_out, gather, scatter, bias, act, 128)
+
+
 @pytest.mark.parametrize("k,c_out,tile", [(100, 72, 32), (2000, 504, 64), (4000, 1000, 128)])
 def test_linear_f32_operand_past_4_gib(k, c_out, tile):
     """Rows beyond the reach of a 32-bit byte offset: 4110 rows of 2 MiB pitch."""
@@ -134,6 +147,12 @@ def test_linear_f32_split_range(k, c_in, c_out, tile, values):
     ref, size = x.double() @ w.double().T, x.double().abs() @ w.double().abs().T
     bound = (2.0 ** -21 + c_in * 3 / 16 * 2.0 ** -24) * size + 2.0 ** -140
     assert bool(((y.double() - ref).abs() <= bound).all()), ((y.double() - ref).abs() / bound).max().item()
+
+
+@pytest.mark.parametrize("k,c_in,c_out", [(3001, 512, 648), (1281, 576, 776)])
+@pytest.mark.parametrize("values", ["plain", "w tiny", "x huge", "x grows", "x falls", "w starts at 0", "x is 0", "x inf"])
+def test_linear_f32_halves_range(k, c_in, c_out, values):
+    test_linear_f32_split_range(k, c_in, c_out, 128, values)
 
 
 # fp32 linear in 64-wide tiles, whose waves hold half of every 32 contraction indices each: infinities that one half or both halves meet, and
@@ -200,6 +219,12 @@ def test_linear_f32_spread_magnitudes(k, c_in, c_out, tile, values):
         ab.astraea_sparse_linear(grown, w, None, None, k, z, x_is_compact=True, y_is_compact=True, N=k)
         torch.cuda.synchronize()
         assert torch.equal(z[3], y[3])
+
+
+@pytest.mark.parametrize("k,c_in,c_out", [(3001, 512, 648), (1281, 576, 776)])
+@pytest.mark.parametrize("values", ["x rows", "w rows", "opposed", "outlier", "tiny x huge", "nan"])
+def test_linear_f32_halves_magnitudes(k, c_in, c_out, values):
+    test_linear_f32_spread_magnitudes(k, c_in, c_out, 128, values)
 
 
 # bf16 attention: 256 queries per workgroup, 32 per wave (rows pass through LDS whole, four at a time), 64 keys per tile; the
