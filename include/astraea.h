@@ -404,6 +404,12 @@ int astraea_attn_plan_f32(int64_t N, int32_t H, int32_t D, int64_t k_sel, size_t
 int astraea_linear_plan(astraea_dtype dt, int64_t k_sel, int64_t c_in, int64_t c_out, int64_t plan_out[3]);
 
 /*
+ * Whether a bf16 layer of few rows takes smaller tiles than astraea_linear_plan names: plan_out as there, or three zeros.  Host only; for
+ * inspection and tests.
+ */
+int astraea_linear_few_rows(int64_t k_sel, int64_t c_in, int64_t c_out, int64_t plan_out[3]);
+
+/*
  * Measurement aids for the benchmark; neither is a step of the method.
  *
  * astraea_probe_mfma_bf16 runs a register-resident loop of v_mfma_f32_32x32x16_bf16

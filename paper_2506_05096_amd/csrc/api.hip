@@ -419,6 +419,19 @@ int astraea_linear_plan(astraea_dtype dt, int64_t k_sel, int64_t c_in, int64_t c
     return ASTRAEA_OK;
 }
 
+int astraea_linear_few_rows(int64_t k_sel, int64_t c_in, int64_t c_out, int64_t plan_out[3])
+{
+    if (!plan_out) return fail(ASTRAEA_ERR_INVALID, "astraea_linear_few_rows: NULL output");
+    if (k_sel <= 0 || k_sel > kMaxTokens || c_in <= 0 || c_out <= 0 || c_in > (1 << 24) || c_out > (1 << 24))
+        return fail(ASTRAEA_ERR_INVALID, "astraea_linear_few_rows: k_sel=%lld, c_in=%lld, c_out=%lld out of range",
+                    (long long)k_sel, (long long)c_in, (long long)c_out);
+    const LinearTile tile = linear_bf16_few(k_sel, (int32_t)c_in, c_out, 1);
+    plan_out[0] = tile.features;
+    plan_out[1] = tile.tokens;
+    plan_out[2] = tile.tokens ? ((c_out + tile.features - 1) / tile.features) * ((k_sel + tile.tokens - 1) / tile.tokens) : 0;
+    return ASTRAEA_OK;
+}
+
 const char *astraea_status_string(int status)
 {
     switch (status) {

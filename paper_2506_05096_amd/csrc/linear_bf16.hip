@@ -30,6 +30,7 @@
 //    workgroups that use the row, touches the lines of two steps ahead so that the copies hit in L2.  The 128-token tile has
 //    three stages, copied two ahead (128 x 128: four, three ahead), and no touches: its steps are shorter than a copy takes (all linear layers of a
 //    block, 608 rows: 387 us with two stages' touches, 316 shared, 308 without).
+//  * layers with fewer tiles than CUs take tiles of 64 features x 64 or 128 tokens (linear_bf16_few_kernel).
 //  * workgroup ids are mapped so that the 32 workgroups resident on one XCD form an 8 x 4 block of
 //    tiles: they stream 8 row tiles and 4 weight tiles through that XCD's L2 instead of 32 + 32.  The tiles
 //    left after whole rounds go to all XCDs evenly.
@@ -79,6 +80,26 @@ struct LinearArgs {
     LinearParts parts;         // last: what a launch of one layer loads lies together
 };
 
+// Which tile a workgroup has: workgroup ids reach the XCDs round-robin.  The tiles are listed super-block by super-block (8 token
+// tiles x 4 feature tiles, fewer at the edges); while whole rounds of 256 are left, each XCD takes 32 of the list at
+// a time, and what is left after them is dealt evenly.
+__device__ __forceinline__ bool find_tile(const LinearArgs &a, int &mt, int &nt)
+{
+    const int xcd = blockIdx.x % kNumXcd, seq = blockIdx.x / kNumXcd;
+    const int tiles = a.m_tiles * a.n_tiles, whole = tiles / kCus * kCuPerXcd;
+    int tile = (seq / kCuPerXcd * kNumXcd + xcd) * kCuPerXcd + seq % kCuPerXcd;
+    if (seq >= whole) {
+        const int left = tiles - whole * kNumXcd, per_xcd = (left + kNumXcd - 1) / kNumXcd, at = xcd * per_xcd + seq - whole;
+        if (at >= left) return false;
+        tile = whole * kNumXcd + at;
+    }
+    const int sb_row = tile / (kSbM * a.n_tiles), in_row = tile % (kSbM * a.n_tiles);
+    const int sb_h = a.m_tiles - sb_row * kSbM < kSbM ? a.m_tiles - sb_row * kSbM : kSbM;
+    const int sb_col = in_row / (kSbN * sb_h), inner = in_row % (kSbN * sb_h);
+    mt = sb_row * kSbM + inner % sb_h, nt = sb_col * kSbN + inner / sb_h;
+    return true;
+}
+
 // A wave has NB x TB MFMA blocks of 32 features x 32 tokens, a tile kBn features: <4, 2, 256> makes tiles of 256 tokens, <2, 3, 256> of
 // 192, <2, 2, 256> and <2, 1, 128> of 128.
 template <int NB, int TB, int kBn, bool GROUP>
@@ -105,21 +126,8 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
     __shared__ int32_t tile_rows[kBm];
     __shared__ __attribute__((aligned(16))) uint16_t tile_bias[kBn];
 
-    // ---- which tile: workgroup ids reach the XCDs round-robin.  The tiles are listed super-block by super-block (8 token
-    // tiles x 4 feature tiles, fewer at the edges); while whole rounds of 256 are left, each XCD takes 32 of the list at
-    // a time, and what is left after them is dealt evenly.
-    const int xcd = blockIdx.x % kNumXcd, seq = blockIdx.x / kNumXcd;
-    const int tiles = a.m_tiles * a.n_tiles, whole = tiles / kCus * kCuPerXcd;
-    int tile = (seq / kCuPerXcd * kNumXcd + xcd) * kCuPerXcd + seq % kCuPerXcd;
-    if (seq >= whole) {
-        const int left = tiles - whole * kNumXcd, per_xcd = (left + kNumXcd - 1) / kNumXcd, at = xcd * per_xcd + seq - whole;
-        if (at >= left) return;
-        tile = whole * kNumXcd + at;
-    }
-    const int sb_row = tile / (kSbM * a.n_tiles), in_row = tile % (kSbM * a.n_tiles);
-    const int sb_h = a.m_tiles - sb_row * kSbM < kSbM ? a.m_tiles - sb_row * kSbM : kSbM;
-    const int sb_col = in_row / (kSbN * sb_h), inner = in_row % (kSbN * sb_h);
-    const int mt = sb_row * kSbM + inner % sb_h, nt = sb_col * kSbN + inner / sb_h;
+    int mt, nt;
+    if (!find_tile(a, mt, nt)) return;
     int part_nt = nt;
     const LinearPart part = a.parts.of<GROUP>(part_nt);
     const int m0 = mt * kBm, n0 = part_nt * kBn;
@@ -389,6 +397,167 @@ __global__ __launch_bounds__(kWaves *kWave, 1) void linear_bf16_kernel(LinearArg
 }
 
 
+// ---- Few rows: tiles of 32 WN features x 32 WM tokens, a wave a block of 32 x 32.  A wave reads all of its fragments of a step while the
+// MFMAs of the step before run, from a ring whose copies, shared by all waves, are published a step early: with four MFMAs of a wave in a
+// step, fragments that are read between them leave the matrix pipe waiting for LDS.  Sums are formed in the order of the kernel above.
+template <int WN, int WM, bool GROUP>
+__global__ __launch_bounds__(WN *WM *kWave, 1) void linear_bf16_few_kernel(LinearArgs a)
+{
+    constexpr int NW = WN * WM, kWRows = 32 * WN, kXRows = 32 * WM, kWBytes = kWRows * kRowBytes, kStageBytes = kWBytes + kXRows * kRowBytes;
+    constexpr int kStages = 6, kAhead = kStages - 1, kCopiesW = kWRows / 8 / NW, kCopies = kCopiesW + kXRows / 8 / NW;
+    constexpr int kPitch = kWRows * 2 + 16;                  // of a token's features on their way out
+    static_assert(kStages * kStageBytes <= 144 * 1024 && kXRows * kPitch <= kStages * kStageBytes && kXRows <= NW * kWave, "fits");
+    static_assert(kCopies <= 4, "a copy behind each of a step's MFMAs");
+    __shared__ __attribute__((aligned(1024))) char lds[kStages * kStageBytes];
+    __shared__ int32_t tile_rows[kXRows];
+    __shared__ __attribute__((aligned(16))) uint16_t tile_bias[kWRows];
+
+    int mt, nt;
+    if (!find_tile(a, mt, nt)) return;
+    int part_nt = nt;
+    const LinearPart part = a.parts.of<GROUP>(part_nt);
+    const int m0 = mt * kXRows, n0 = part_nt * kWRows;
+    // the arguments in one round trip, as above
+    asm volatile("" ::"s"(part.w), "s"(part.bias), "s"(part.y), "s"(part.ldy), "s"(part.y_indexed), "s"(a.x), "s"(a.idx_sel), "s"(a.ldx),
+                 "s"(a.k_sel), "s"(a.c_in), "s"(a.c_out), "s"(a.n_rows), "s"(a.x_indexed), "s"(a.act));
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int qc = lane & 31, hf = lane >> 5, wn = wave % WN, wm = wave / WN;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+
+    // ---- copies: instruction t of wave w fills rows 8 (w + NW t) .. of an operand's tile, physical chunk p of row r with logical p ^ (r / 2 % 8)
+    const int d_row = lane >> 3, lchunk = (lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7);
+    uint32_t off[kCopies];               // byte offsets of this lane's rows from w and x
+#pragma unroll
+    for (int t = 0; t < kCopies; ++t) {
+        const int r = 8 * (wave + NW * (t < kCopiesW ? t : t - kCopiesW)) + d_row;
+        if (t < kCopiesW) {
+            const int n = n0 + r;        // rows past the end re-read the last one; they are never stored
+            off[t] = (uint32_t)(n < a.c_out ? n : a.c_out - 1) * (uint32_t)a.c_in * 2u;
+        } else {
+            const int m = m0 + r < a.k_sel ? m0 + r : a.k_sel - 1;
+            const int64_t row = a.x_indexed ? (int64_t)clamp_row(a.idx_sel[m], a.n_rows) : (int64_t)m;
+            off[t] = (uint32_t)(row * a.ldx * 2);
+        }
+        off[t] += (uint32_t)lchunk * 16u;
+    }
+    // thread t: destination row of the tile's token t (-1: not stored) and bias of its feature t
+    int32_t my_row = -1;
+    uint16_t my_bias = 0;
+    if (tid < kXRows && m0 + tid < a.k_sel) {
+        my_row = m0 + tid;
+        if (part.y_indexed) {
+            const int32_t ix = a.idx_sel[my_row];
+            my_row = (uint32_t)ix < (uint32_t)a.n_rows ? ix : -1;
+        }
+    }
+    if (tid < kWRows && part.bias && n0 + tid < a.c_out) my_bias = reinterpret_cast<const uint16_t *>(part.bias)[n0 + tid];
+    // no load may be pending at the loop, where the counter counts copies
+    asm volatile("" ::"v"(my_row), "v"((uint32_t)my_bias));
+#pragma unroll
+    for (int t = 0; t < kCopies; ++t) asm volatile("" ::"v"(off[t]));
+    const char *wg = reinterpret_cast<const char *>(part.w), *xg = reinterpret_cast<const char *>(a.x);
+    auto copy = [&](int t, int kstep, uint32_t stage) __attribute__((always_inline)) {
+        const uint32_t to = lds0 + stage + (t < kCopiesW ? 0 : kWBytes) + (wave + NW * (t < kCopiesW ? t : t - kCopiesW)) * 1024;
+        dma16((t < kCopiesW ? wg : xg) + (int64_t)kstep * kRowBytes, off[t], to);
+    };
+
+    // ---- fragments: row qc of this wave's part, logical chunk 2 q + hf for quarter q of a step
+    uint32_t wa[4], xa[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t sw = (uint32_t)(((2 * q + hf) ^ ((qc >> 1) & 7)) << 4);
+        wa[q] = lds0 + (wn * 32 + qc) * kRowBytes + sw;
+        xa[q] = lds0 + kWBytes + (wm * 32 + qc) * kRowBytes + sw;
+    }
+    bf16x8 wf[2][4], xf[2][4];           // [step's parity][quarter]
+    auto read = [&](auto par_tag, uint32_t stage) __attribute__((always_inline)) {
+        constexpr int P = decltype(par_tag)::value;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            wf[P][q] = lds_read_b128(wa[q] + stage);
+            xf[P][q] = lds_read_b128(xa[q] + stage);
+        }
+    };
+    floatx16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+
+    const int nk = a.c_in / kBk;
+#pragma unroll
+    for (int p = 0; p < kAhead; ++p)
+#pragma unroll
+        for (int t = 0; t < kCopies; ++t) copy(t, p < nk ? p : nk - 1, p * kStageBytes);
+    wait_dma_but<(kAhead - 1) * kCopies>();
+    if (tid < kXRows) tile_rows[tid] = my_row;
+    if (tid < kWRows) tile_bias[tid] = my_bias;
+    __builtin_amdgcn_s_barrier();
+    using P0 = std::integral_constant<int, 0>;
+    using P1 = std::integral_constant<int, 1>;
+    read(P0{}, 0);
+    uint32_t next = kStageBytes, to = kAhead * kStageBytes;      // where step kk + 1 lies and where the copies of step kk + kAhead go
+    auto step = [&](int kk, auto par_tag) __attribute__((always_inline)) {
+        constexpr int P = decltype(par_tag)::value;
+        // Step kk + 1 is there, for every wave, and every wave has its fragments of step kk - 1, whose place the copies take.  The last steps have
+        // nothing to copy or to read ahead: they copy the last tiles again and read what lies there.
+        wait_dma_but<(kAhead - 2) * kCopies>();
+        SB();
+        __builtin_amdgcn_s_barrier();
+        SB();
+        read(std::integral_constant<int, P ^ 1>{}, next);
+        SB();
+        const int kn = kk + kAhead < nk ? kk + kAhead : nk - 1;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[P][q], xf[P][q], acc, 0, 0, 0);
+            if (q < kCopies) copy(q, kn, to);
+            SB();
+        }
+        next = next == (kStages - 1) * kStageBytes ? 0 : next + kStageBytes;
+        to = to == (kStages - 1) * kStageBytes ? 0 : to + kStageBytes;
+    };
+    int kk = 0;
+    for (; kk + 2 <= nk; kk += 2) {
+        step(kk, P0{});
+        step(kk + 1, P1{});
+    }
+    if (kk < nk) step(kk, P0{});
+    wait_dma();
+    __syncthreads();                     // nobody reads or copies into the ring any more
+
+    // ---- register group g: features 32 wn + 8 g + 4 hf + 0..3, token 32 wm + qc; through LDS to whole rows of the tile
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const int nl = wn * 32 + 8 * g + 4 * hf;
+        const uint2v b2 = *reinterpret_cast<const uint2v *>(&tile_bias[nl]);
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = acc[4 * g + e];
+        v[0] += __uint_as_float(b2[0] << 16);
+        v[1] += __uint_as_float(b2[0] & 0xffff0000u);
+        v[2] += __uint_as_float(b2[1] << 16);
+        v[3] += __uint_as_float(b2[1] & 0xffff0000u);
+        if (a.act == ASTRAEA_ACT_GELU_TANH) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = gelu_tanh(v[e]);
+        }
+        const uint2v o2 = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+        *reinterpret_cast<uint2v __attribute__((address_space(3))) *>((uintptr_t)(lds0 + (wm * 32 + qc) * kPitch + nl * 2)) = o2;
+    }
+    __syncthreads();
+    // whole rows of the tile: 16 bytes per lane
+    constexpr int kRowLanes = kWRows / 8, kRowsPerStore = NW * kWave / kRowLanes;
+    const int o_chunk = tid % kRowLanes;
+#pragma unroll
+    for (int it = 0; it < kXRows / kRowsPerStore; ++it) {
+        const int tl = kRowsPerStore * it + tid / kRowLanes, n = n0 + 8 * o_chunk;       // c_out is a multiple of 8: a chunk is all in or all out
+        const int64_t orow = tile_rows[tl];
+        const uint4v val = *reinterpret_cast<const uint4v __attribute__((address_space(3))) *>((uintptr_t)(lds0 + tl * kPitch + o_chunk * 16));
+        if (n < a.c_out && orow >= 0)
+            *reinterpret_cast<uint4v *>(reinterpret_cast<__bf16 *>(part.y) + orow * part.ldy + n) = val;
+    }
+}
+
 // Estimated microseconds of a layer of `tiles` tiles and nk contraction steps: rounds of 256 workgroups, each `fixed` us besides
 // its steps, a step taking `base` us while few of the CUs are at work and, past a share `from` of them, `slope` more per unit
 // (the chip at its power limit).  Measured per step, 256 / 192 / 128 tokens per tile: 1.03 / 0.93 / 0.56 with a fifth of the CUs
@@ -410,16 +579,48 @@ int64_t tiles_of(int64_t k_sel, int64_t c_out, int parts, int64_t bm, int64_t bn
 // 6144 -> 1536 62 / 45, 90 rows 3072 -> 12288 47 / 32; where the larger tiles fill a round they stay, 608 rows 3072 -> 9216 48 / 59.
 // Contractions below kDeep are all start and end in either tile (608 rows 128 -> 3072 9.7 / 9.8).
 constexpr int32_t kDeep = 512;
-LinearTile linear_bf16_tile(int64_t k_sel, int32_t c_in, int64_t c_out, int parts)
+static LinearTile whole_tile(int64_t k_sel, int32_t c_in, int64_t c_out, int parts, double &us)
 {
     const int nk = c_in / kBk;
     const double us256 = layer_us(tiles_of(k_sel, c_out, parts, 256), nk, 9.0, 1.05, 0.4, 0.78),
                  us192 = layer_us(tiles_of(k_sel, c_out, parts, 192), nk, 7.5, 0.93, 0.6, 0.65),
                  us128 = layer_us(tiles_of(k_sel, c_out, parts, 128), nk, 6.0, 0.56, 0.6, 0.7),
                  small = layer_us(tiles_of(k_sel, c_out, parts, 128, 128), nk, 5.0, 0.36, 0.4, 0.3);
-    if (c_in >= kDeep && small < us128 && small < us192 && small < us256) return {128, 128};
-    if (us256 <= us192 && us256 <= us128) return {256, 256};
-    return {256, us192 < us128 ? 192 : 128};
+    const LinearTile wide = us256 <= us192 && us256 <= us128 ? LinearTile{256, 256} : LinearTile{256, us192 < us128 ? 192 : 128};
+    us = wide.tokens == 256 ? us256 : wide.tokens == 192 ? us192 : us128;
+    if (c_in < kDeep || small >= us128 || small >= us192 || small >= us256) return wide;
+    us = small;
+    return {128, 128};
+}
+
+LinearTile linear_bf16_tile(int64_t k_sel, int32_t c_in, int64_t c_out, int parts)
+{
+    double us;
+    return whole_tile(k_sel, c_in, c_out, parts, us);
+}
+
+// Tiles of 64 features x 64 or 128 tokens, where there are not more of them than CUs; features 0: none.
+// What bounds a layer of few tiles is what a CU takes in, 64 to 75 bytes a nanosecond of copies through LDS: smaller tiles give more CUs some of it, and a
+// step of them is only as long as its copies if no wave waits for fragments.  By estimates fitted to 96 layers of blocks 1024 to 3072 wide,
+// 80 to 3000 rows, weights from memory (0.1 % lost on choosing by them).  Before / with them, us: 600 rows 12288 -> 3072 106 / 77, 300 x 12288 -> 3072
+// 90 / 55, 1045 x 6144 -> 1536 55 / 43, 707 x 4096 -> 1024 26.7 / 14.2, 707 x 1024 -> 1024 9.9 / 6.7, 152 x 1536 -> 4608 13.2 / 7.7, 218 x 8192 -> 2048
+// 62 / 30; left to the other tiles, which win from a round and a bit on: 600 x 3072 -> 9216 49 / 63, 1885 x 1536 -> 1536 15.0 / 20.9.  128 features x 64
+// tokens measured as 64 x 128 do.  Shallow contractions keep the tiles that are all start and end.
+LinearTile linear_bf16_few(int64_t k_sel, int32_t c_in, int64_t c_out, int parts)
+{
+    double best;
+    whole_tile(k_sel, c_in, c_out, parts, best);
+    LinearTile tile{0, 0};
+    if (c_in < kDeep) return tile;
+    const double nk = (double)(c_in / kBk);
+    const int64_t square = tiles_of(k_sel, c_out, parts, 64, 64), tall = tiles_of(k_sel, c_out, parts, 128, 64);
+    const double us64 = 1.9 + nk * (0.191 + 0.093 * (double)square / kCus), us128 = 2.4 + nk * (0.28 + 0.121 * (double)tall / kCus);
+    if (tall <= kCus && us128 < best) {
+        tile = {64, 128};
+        best = us128;
+    }
+    if (square <= kCus && us64 < best) tile = {64, 64};
+    return tile;
 }
 
 int launch_linear_bf16(const void *x, const LinearPart *parts, int n_parts, const int32_t *idx_sel, int64_t k_sel, int64_t n_rows,
@@ -438,18 +639,21 @@ int launch_linear_bf16(const void *x, const LinearPart *parts, int n_parts, cons
     a.x_indexed = x_indexed;
     a.act = act;
     if (tiles_of(k_sel, c_out, n_parts, 128, 128) > 2147483647LL / 16) return fail(ASTRAEA_ERR_INVALID, "astraea_sparse_linear: grid too large");
-    const LinearTile tile = linear_bf16_tile(k_sel, c_in, c_out, n_parts);
-    auto go = [&](auto kernel) {
+    const LinearTile few = linear_bf16_few(k_sel, c_in, c_out, n_parts);
+    const LinearTile tile = few.tokens ? few : linear_bf16_tile(k_sel, c_in, c_out, n_parts);
+    auto go = [&](auto kernel, int waves = kWaves) {
         a.m_tiles = (int32_t)((k_sel + tile.tokens - 1) / tile.tokens);
         a.parts.n_tiles_each = (c_out + tile.features - 1) / tile.features;
         a.n_tiles = a.parts.n_tiles_each * n_parts;
         const int64_t t = (int64_t)a.m_tiles * a.n_tiles;
         const int64_t grid = t / kCus * kCus + (t % kCus + kNumXcd - 1) / kNumXcd * kNumXcd;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kWaves * kWave), 0, stream, a);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(waves * kWave), 0, stream, a);
     };
     auto choose = [&](auto group) {
         constexpr bool G = decltype(group)::value;
-        if (tile.tokens == 256) go(linear_bf16_kernel<4, 2, 256, G>);
+        if (few.tokens == 128) go(linear_bf16_few_kernel<2, 4, G>, 8);
+        else if (few.tokens == 64) go(linear_bf16_few_kernel<2, 2, G>, 4);
+        else if (tile.tokens == 256) go(linear_bf16_kernel<4, 2, 256, G>);
         else if (tile.tokens == 192) go(linear_bf16_kernel<2, 3, 256, G>);
         else if (tile.features == 256) go(linear_bf16_kernel<2, 2, 256, G>);
         else go(linear_bf16_kernel<2, 1, 128, G>);

@@ -811,6 +811,21 @@ def test_linear_bf16_small_tile(n, k, c_in, c_out, gather, scatter, bias, act):
     test_linear_bf16_tiles(n, k, c_in, c_out, gather, scatter, bias, act, 128, features=128)
 
 
+# ... and of 64 features x 64 or 128 tokens where there are not more of them than CUs: one and many steps past the ring of six stages, odd counts of
+# them, ragged rows and features, one row, a full round.
+@pytest.mark.parametrize("n,k,c_in,c_out,gather,scatter,bias,act,tokens", [
+    (5, 1, 512, 8, True, True, True, ab.ACT_NONE, 64), (300, 65, 576, 72, True, False, True, ab.ACT_GELU_TANH, 64),
+    (300, 64, 640, 64, False, True, False, ab.ACT_NONE, 64), (800, 705, 1088, 1096, True, True, True, ab.ACT_NONE, 64),
+    (800, 707, 4096, 1024, False, True, True, ab.ACT_NONE, 64), (300, 191, 704, 4600, True, True, True, ab.ACT_GELU_TANH, 64),
+    (700, 608, 12288, 3072, True, True, True, ab.ACT_NONE, 128), (1100, 1001, 576, 1544, True, True, True, ab.ACT_GELU_TANH, 128),
+    (1100, 1024, 640, 2048, False, True, False, ab.ACT_NONE, 128), (2100, 2047, 1152, 1000, True, False, True, ab.ACT_NONE, 128),
+])
+def test_linear_bf16_few_rows(n, k, c_in, c_out, gather, scatter, bias, act, tokens):
+    assert ab.astraea_linear_few_rows(k, c_in, c_out) == {"tile_features": 64, "tile_tokens": tokens, "tiles": -(-k // tokens) * -(-c_out // 64)}
+    plan = ab.astraea_linear_plan(ab.BF16, k, c_in, c_out)
+    test_linear_bf16_tiles(n, k, c_in, c_out, gather, scatter, bias, act, plan["tile_tokens"], features=plan["tile_features"])
+
+
 # Layers of one input in one launch, against a call each: one to three parts, widths that end inside a tile of features, every tile kind
 # (few rows, many rows, deep and shallow contractions), a part without a bias, compact and placed results.  bf16 sums a contraction in one
 # order whatever the tile, so its bits are the same; fp32 results are held to the bound of their products (test_linear_f32_split_range).
