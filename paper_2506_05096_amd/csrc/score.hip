@@ -7,8 +7,8 @@
 // token t walks.  A chain step takes 5.4 clocks (2.2 ns), so 3072 channels are 6.9 us however many tokens there are.
 //
 // Two kernels, by the number of tokens:
-//  * score_kernel: a workgroup of two waves owns 16 tokens.  The first wave loads slabs of [16 tokens x 256
-//    bytes] of both arrays, four slabs in flight, and writes the differences; the second runs the chains, one
+//  * score_kernel: a workgroup of two waves owns 16 tokens.  The first wave loads slabs of [16 tokens x 128
+//    channels] of both arrays, 32 KiB in flight, and writes the differences; the second runs the chains, one
 //    slab behind and reading 64 channels ahead of them, with one barrier per slab.  16 tokens per workgroup instead of 64 per wave is what a
 //    short sequence needs: at 17550 tokens 64 per wave make 275 waves, one per CU, and each slab's
 //    load latency, its conversion and its chain came one after the other.  Cold arrays, 64 per wave -> this
@@ -43,11 +43,7 @@ constexpr int64_t kWideMinCachedBf16 = 28672, kWideMinCachedF32 = 20480;
 constexpr int64_t kCacheBytes = (int64_t)256 << 20;
 
 constexpr int kTok = 16;            // tokens per workgroup; lane t < kTok of the second wave reduces token t
-constexpr int kSegBytes = 256;      // bytes of each row handled per slab
-constexpr int kVecPerRow = kSegBytes / 16;
-constexpr int kRowsPerLoad = kWave / kVecPerRow;
-constexpr int kVecPerLane = kTok / kRowsPerLoad;
-constexpr int kDepth = 4;           // slabs in flight
+constexpr int kSlab = 128;          // channels handled per slab
 constexpr int kTiles = 3;           // LDS tiles: one is written, two are read
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -62,7 +58,7 @@ template <bool NT, typename T> __device__ __forceinline__ uint4v load16(const T 
 
 template <typename T> struct Elem;
 template <> struct Elem<float> {
-    static constexpr int kPerVec = 4;
+    static constexpr int kPerVec = 4, kDepth = 2;        // elements of a 16-byte vector; slabs in flight, 32 KiB of both arrays
     __device__ static float load(const float *p) { return *p; }
     __device__ static void diff(const uint4v &a, const uint4v &b, float *d)
     {
@@ -73,7 +69,7 @@ template <> struct Elem<float> {
     }
 };
 template <> struct Elem<uint16_t> {
-    static constexpr int kPerVec = 8;
+    static constexpr int kPerVec = 8, kDepth = 4;
     __device__ static float load(const uint16_t *p) { return __uint_as_float(((uint32_t)*p) << 16); }
     __device__ static void diff(const uint4v &a, const uint4v &b, float *d)
     {
@@ -124,7 +120,8 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
     float *__restrict__ score_out)
 {
     constexpr int EPV = Elem<T>::kPerVec;              // elements per 16-byte vector
-    constexpr int SEG = kSegBytes / (int)sizeof(T);    // channels per slab
+    constexpr int SEG = kSlab, kDepth = Elem<T>::kDepth;
+    constexpr int kVecPerRow = SEG / EPV, kRowsPerLoad = kWave / kVecPerRow, kVecPerLane = kTok / kRowsPerLoad;
     constexpr int PLANES = EPV / 4;                    // a vector's floats are kept as 16-byte pieces, piece p in plane p
     constexpr int PLANE = 4 * kVecPerRow;              // floats
     constexpr int PITCH = SEG + 4;                     // floats; the 16 row reads of a piece hit distinct banks
@@ -203,8 +200,10 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
         using B3 = std::integral_constant<int, 3>;
         issue(0, B0{});
         issue(1, B1{});
-        issue(2, B2{});
-        issue(3, B3{});
+        if constexpr (kDepth == 4) {
+            issue(2, B2{});
+            issue(3, B3{});
+        }
         auto step = [&](int32_t s, auto buf_tag) __attribute__((always_inline)) {
             slab(s, buf_tag);
             issue(s + kDepth, buf_tag);
@@ -215,8 +214,10 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
         for (; s + kDepth <= nslab; s += kDepth) {
             step(s, B0{});
             step(s + 1, B1{});
-            step(s + 2, B2{});
-            step(s + 3, B3{});
+            if constexpr (kDepth == 4) {
+                step(s + 2, B2{});
+                step(s + 3, B3{});
+            }
         }
         auto last = [&](int32_t at, auto buf_tag) __attribute__((always_inline)) {
             if (at >= nslab) return;
@@ -225,8 +226,10 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
             wt = wt == kTiles - 1 ? 0 : wt + 1;
         };
         last(s, B0{});
-        last(s + 1, B1{});
-        last(s + 2, B2{});
+        if constexpr (kDepth == 4) {
+            last(s + 1, B1{});
+            last(s + 2, B2{});
+        }
         publish();                       // the chains are a slab behind
         return;
     }
@@ -234,10 +237,10 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
     // The chains.  A dependent instruction per channel is their time, so little else may stand among them: pieces are read 64 channels ahead, in
     // the first half of the instructions of the 64 channels before their own, and waited for once.  Nine reads at the head of a slab waited
     // for there, and a wait for each later one, took 3.9 ns a channel; this takes 2.4: 2025 x 3072 bf16 hot / cold 14.8 / 18.0 -> 12.2 / 15.5 us,
-    // 17550 x 3072 39.7 / 43.3 -> 38.1 / 41.8, 45000 x 3072 87.8 -> 85.9; against it 28000 x 512 12.3 -> 12.9 hot.  Two loading waves: 13.1 and
-    // 39.3 us at the first two sizes; four, with six slabs in flight, 12.4 and 55.9.
+    // 17550 x 3072 39.7 / 43.3 -> 38.1 / 41.8, 45000 x 3072 87.8 -> 85.9; fp32, also by slabs of 128 channels instead of 64, 1081 x 3072 14.0 -> 11.6
+    // hot, 3446 x 3072 15.5 -> 14.0.  Two loading waves: 13.1 and 39.3 us at the first two sizes; four, with six slabs in flight, 12.4 and 55.9.
     float acc = 0.0f;
-    constexpr int UNIT = 16, UNITS = SEG / 4 / UNIT;   // pieces that are read at a time, and such units of a slab: two, in fp32 one
+    constexpr int UNIT = SEG / 8;        // pieces that are read at a time, half of a slab's
     float4 v[2][UNIT];
     const int t = lane % kTok;           // the other lanes do what the first kTok do
     auto read = [&](int tl, int unit, int buf, int e) __attribute__((always_inline)) {
@@ -274,20 +277,11 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
 #pragma unroll
     for (int e = 0; e < UNIT; ++e) read(0, 0, 0, e);
     int tl = 0;
-    auto next_tile = [&]() { tl = tl == kTiles - 1 ? 0 : tl + 1; };
     for (int32_t s = 0; s < nslab; ++s) {
         publish();                       // slab s + 1 is, if there is one: past the last slab what lies there is read and not used
-        if (UNITS == 2) chain(V0{}, tl, 1);
-        next_tile();
-        if (UNITS == 2) {
-            chain(V1{}, tl, 0);
-        } else {
-            chain(V0{}, tl, 0);
-            if (++s == nslab) break;
-            publish();
-            next_tile();
-            chain(V1{}, tl, 0);
-        }
+        chain(V0{}, tl, 1);
+        tl = tl == kTiles - 1 ? 0 : tl + 1;
+        chain(V1{}, tl, 0);
     }
     if (lane >= kTok) return;
     if (VEC) {
