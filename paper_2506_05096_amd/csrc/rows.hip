@@ -11,7 +11,7 @@
 // than the earlier shape.  Unselected rows are never touched, which is exactly the "reuse the cached result"
 // half of the merge.  HBM-bound: 2 * row_bytes per selected token.
 // A source row is read once, so its loads carry the streaming hint (not kept in L2).  Stores carry it when
-// both sides are rows of full-size buffers (the K/V refresh, the copy of the selected tokens' features): 172 ->
+// both sides are rows of full-size buffers past 128 MB (the K/V refresh, the copy of the selected tokens' features): 172 ->
 // 148 us for the refresh.  Stores of compact rows stay plain (the next kernel reads them), and so do the
 // scatter's: its source was written by the kernel before it and is still in the caches, and with streaming
 // stores that case is slower (64 -> 70 us inside a layer-step).
@@ -114,8 +114,12 @@ int launch_move_rows(void *dst, const void *src, int64_t row_bytes, int64_t dst_
     hipLaunchKernelGGL((move_rows_kernel<V, S>), grid, block, 0, stream, (char *)dst, (const char *)src, (char *)dst_b, \
                        (const char *)src_b, row_bytes, dst_stride_bytes, src_stride_bytes, idx, k_sel, n_rows,         \
                        (int)index_dst, (int)index_src, (int32_t)pieces)
-    // cache rows refreshed from rows of another full-size buffer: both sides come from and go to HBM
-    const bool stream_dst = index_dst && index_src;
+    // Cache rows refreshed from rows of another full-size buffer.  Buffers past half of the 256 MB memory-side cache come from and go to HBM, and what a step
+    // still has there is kept by streaming past it (stateful step of 17550 tokens x 1755 x 24 419 us, 425 with plain stores); smaller ones are read
+    // from that cache by the kernels that follow, where streamed rows are not (layer-step of 2025 x 608 x 24 48.5 us, 45.7 plain, 4000 x 2000 x 24
+    // 120.4 / 118.8; the same from 120 to 150 MB: 9000 x 5400 x 16 396.0 / 395.2).
+    const double reach = (double)n_rows * ((double)dst_stride_bytes + (double)src_stride_bytes) * (dst_b ? 2.0 : 1.0);
+    const bool stream_dst = index_dst && index_src && reach > 128e6;
     if (vec == 16) {
         if (stream_dst) ASTRAEA_MOVE(uint4v, true);
         else ASTRAEA_MOVE(uint4v, false);
