@@ -224,7 +224,7 @@ class GraphedStep:
     Every entry point of the library only enqueues kernels on the caller's stream: it allocates nothing,
     never waits for the device and records no memset, and k is a host number, so a whole layer-step at a fixed
     k can be captured.  That takes the host one launch instead of five to eleven; the device gains nothing, since
-    eager launches keep ahead of it (2025 tokens 48.9 us a step eager, 53.6 replayed, 61.6 and 66.0 when each step is
+    eager launches keep ahead of it (2025 tokens 45.7 us a step eager, 50.1 replayed, 58.7 and 62.3 when each step is
     waited for).  The 50-step schedule of a denoising run needs one graph per distinct budget, at most ten.
 
     `fn` is any callable that makes the calls (e.g. ``lambda: layer.run(t, k)``); the tensors it touches must
