@@ -58,6 +58,9 @@ constexpr int kTileBytes = kBk * kRowBytes;          // 16 KiB
 constexpr int kRowsBytes = 32 * kRowBytes;           // a wave's 32 query or output rows
 constexpr float kTau = 8.0f;            // exact form: lazy-rescale threshold, log2 units
 constexpr float kRose = 0x1p8f;         // 2^kTau
+// Exact form: the offset before the first tile.  From minus infinity, a tile of such logits alone would make NaN of their weights (as it does in the
+// fast form, which the row sums then show); from here they weigh nothing and the first finite logit raises the offset.
+constexpr float kLowest = -3.40282347e38f;
 constexpr float kBig = 0x1p80f;         // fast form: after a final row sum above this the workgroup repeats its sweep in the exact form
 constexpr int kNumXcd = 8;
 constexpr int kCuPerXcd = 32;
@@ -508,7 +511,7 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
         for (int b = 0; b < 4; ++b)
 #pragma unroll
             for (int i = 0; i < 16; ++i) oacc[b][i] = 0.0f;
-        m_c = -INFINITY;
+        m_c = kLowest;
         l_run = 0.0f;
         PHASE_BARRIER();
         if (grp == 1) PHASE_BARRIER();

@@ -352,6 +352,39 @@ def test_attn_bf16_key_groups_that_sweep_again(n, h, k, rise_nats):
         assert ((lse[:, i].double() - want).abs() / want.abs().clamp(min=1.0)).max().item() <= 2.0 ** -9
 
 
+# Keys whose logits are minus infinity for some rows: all of a key group's or a key share's first tile, of the whole of it, of the first tile of all
+# keys, of every key but the last.  They weigh nothing, as in softmax; the other rows see plain logits.  Four key groups, two, shares that a
+# launch merges, four and eight waves on whole items, V retiled (`groups`, `splits`: what the launch says).  Bars as above.
+@pytest.mark.parametrize("n,h,k,groups,splits", [(700, 8, 600, 4, 1), (1460, 16, 1460, 2, 1), (3716, 12, 1400, 1, 3), (130, 16, 2000, 1, 1),
+                                                 (2100, 24, 4100, 1, 1), (300, 2, 16400, 1, 1)])
+@pytest.mark.parametrize("where", ["first tile", "share's first tile", "share", "all but the last"])
+def test_attn_bf16_logits_of_minus_infinity(n, h, k, groups, splits, where):
+    plan = ab.astraea_attn_plan(n, h, k)
+    assert ab.astraea_attn_key_groups(n, h, k) == groups and (groups > 1 or plan["splits"] == splits)
+    unit = 32 if groups == 4 else 64
+    tiles, parts = -(-n // unit), max(groups, splits)
+    begin = tiles // parts * unit if groups > 1 else plan["tiles_per_split"] * unit % (n // 64 * 64)     # of the second group or share
+    lo, hi = {"first tile": (0, 64), "share's first tile": (begin, begin + 64), "share": (begin, begin + max(tiles // parts, 1) * unit + unit),
+              "all but the last": (0, n - 1)}[where]
+    hi = min(hi, n - 1)
+    g = torch.Generator(device=DEV).manual_seed(n + k)
+    q, kc, vc = (torch.randn(m, h, 128, device=DEV, generator=g).bfloat16() for m in (k, n, n))
+    q[:, :, 0], kc[:, :, 0] = 2.0 ** -126, 0.0
+    q[::3, :, 0], kc[lo:hi, :, 0] = 64.0, -3e38
+    lse = torch.full((k, h), math.nan, device=DEV)
+    out = torch.empty(k, h, 128, dtype=torch.bfloat16, device=DEV)
+    ws = torch.full((ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, 128),), 255, dtype=torch.uint8, device=DEV)
+    ab.astraea_sparse_attn_fwd(q, kc, vc, None, k, out, 1.0 / math.sqrt(128), q_is_compact=True, lse_sel=lse, workspace=ws)
+    torch.cuda.synchronize()
+    for i in range(h):
+        logits = q[:, i].double() @ kc[:, i].double().T.contiguous()
+        logits = torch.where(logits < -3.4e38, -math.inf, logits) / math.sqrt(128)
+        ref = torch.softmax(logits, 1) @ vc[:, i].double()
+        assert_rel_l2(out[:, i].double().cpu().numpy(), ref.cpu().numpy(), tag=f"head {i}")
+        want = torch.logsumexp(logits, 1)
+        assert ((lse[:, i].double() - want).abs() / want.abs().clamp(min=1.0)).max().item() <= 2.0 ** -9
+
+
 # The compact result and the cached rows from one call, against the two calls it stands for: whole and cut work items, both workgroup
 # sizes, cached buffers that the kernel writes itself and those that get a launch of their own (stride, alignment, memory shared with q).
 @pytest.mark.parametrize("dtype,n,h,d,k,queries,splits", [
