@@ -115,6 +115,28 @@ def test_linear_f32_operand_past_4_gib(k, c_out, tile):
     assert (y.double() - x[n - k:].double() @ w.double().T).abs().max().item() <= 1e-4
 
 
+# ... and contractions of 512 and more there, which keep the tiles that 32-bit offsets had before they took other kernels: 32 x 32 in four parts of the
+# contraction, stages of 32 indices in turn.  A first product of 2^26 swallows every later one of 1 in its own part: 2^26 has a unit of 8.  So one part
+# loses c_in - 1 and four lose a quarter, and 8 more by the last sums; then random terms, bound as above.
+@pytest.mark.parametrize("k,c_in,c_out", [(1250, 512, 776), (1323, 4096, 1000)])
+def test_linear_f32_parts_past_4_gib(k, c_in, c_out):
+    n = 4110
+    x = torch.empty(n, 1 << 19, device=DEV)[:, :c_in]
+    x.fill_(1.0)
+    x[:, 0] = 2.0 ** 26
+    idx = torch.arange(n - k, n, dtype=torch.int32, device=DEV)
+    y = torch.empty(k, c_out, device=DEV)
+    ab.astraea_sparse_linear(x, torch.ones(c_out, c_in, device=DEV), None, idx, k, y)
+    torch.cuda.synchronize()
+    assert (y.double() - (2.0 ** 26 + c_in - 1)).abs().max().item() <= c_in / 4 + 8
+    g = torch.Generator(device=DEV).manual_seed(k)
+    x.copy_(torch.randn(n, c_in, device=DEV, generator=g))
+    w = torch.randn(c_out, c_in, device=DEV, generator=g) * c_in ** -0.5
+    ab.astraea_sparse_linear(x, w, None, idx, k, y)
+    torch.cuda.synchronize()
+    assert (y.double() - x[n - k:].double() @ w.double().T).abs().max().item() <= 1e-4
+
+
 # fp32 linear, magnitudes of a whole operand or of part of the contraction: zeros at its start, growth and fall along it, the ends of the
 # range, infinities, in the tiles that form products of bf16 parts.  Bound, of the sum of magnitudes: 2^-21 for
 # the products and 2^-24 for each rounding of the sum, of which three per 16 indices are allowed here; either form stays below.
