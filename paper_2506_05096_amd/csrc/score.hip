@@ -8,7 +8,7 @@
 //
 // Two kernels, by the number of tokens:
 //  * score_kernel: a workgroup of two waves owns 16 tokens.  The first wave loads slabs of [16 tokens x 128
-//    channels] of both arrays, 32 KiB in flight, and writes the differences; the second runs the chains, one
+//    channels] of both arrays, 32 KiB in flight, and writes the differences into one of two LDS tiles; the second runs the chains, half a
 //    slab behind and reading 64 channels ahead of them, with one barrier per slab.  16 tokens per workgroup instead of 64 per wave is what a
 //    short sequence needs: at 17550 tokens 64 per wave make 275 waves, one per CU, and each slab's
 //    load latency, its conversion and its chain came one after the other.  Cold arrays, 64 per wave -> this
@@ -43,8 +43,11 @@ constexpr int64_t kWideMinCachedBf16 = 28672, kWideMinCachedF32 = 20480;
 constexpr int64_t kCacheBytes = (int64_t)256 << 20;
 
 constexpr int kTok = 16;            // tokens per workgroup; lane t < kTok of the second wave reduces token t
-constexpr int kSlab = 128;          // channels handled per slab
-constexpr int kTiles = 3;           // LDS tiles: one is written, two are read
+// fp32 slabs have 64 channels above this many tokens, two workgroups per CU: there the arrays' rate is the time, and a workgroup is over sooner that is
+// half a slab behind; below it the chain is, which meets half as many barriers in slabs of 128.  64 / 128 channels, us hot: 2025 x 3072 12.8 / 11.2, 4000 x
+// 1536 8.8 / 8.9, 5000 x 2048 16.0 / 15.6, 9000 x 1024 12.8 / 13.3, 14000 x 512 10.2 / 10.9, 16300 x 1024 22.1 / 23.1.
+constexpr int64_t kShortSlabTokens = 8192;
+constexpr int kInFlight = 32 << 10;  // bytes of both arrays
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
@@ -58,7 +61,7 @@ template <bool NT, typename T> __device__ __forceinline__ uint4v load16(const T 
 
 template <typename T> struct Elem;
 template <> struct Elem<float> {
-    static constexpr int kPerVec = 4, kDepth = 2;        // elements of a 16-byte vector; slabs in flight, 32 KiB of both arrays
+    static constexpr int kPerVec = 4;        // elements of a 16-byte vector
     __device__ static float load(const float *p) { return *p; }
     __device__ static void diff(const uint4v &a, const uint4v &b, float *d)
     {
@@ -69,7 +72,7 @@ template <> struct Elem<float> {
     }
 };
 template <> struct Elem<uint16_t> {
-    static constexpr int kPerVec = 8, kDepth = 4;
+    static constexpr int kPerVec = 8;
     __device__ static float load(const uint16_t *p) { return __uint_as_float(((uint32_t)*p) << 16); }
     __device__ static void diff(const uint4v &a, const uint4v &b, float *d)
     {
@@ -112,7 +115,8 @@ __device__ __forceinline__ void publish()
     asm volatile("" ::: "memory");
 }
 
-template <typename T, int MODE, bool VEC, bool NT>
+// SEG: channels handled per slab.
+template <typename T, int MODE, bool VEC, bool NT, int SEG>
 __global__ __launch_bounds__(2 * kWave) void score_kernel(
     const T *__restrict__ x_cur, const T *__restrict__ x_prev, int64_t N, int64_t C, int64_t row_stride,
     const float *__restrict__ lse_weight, const int32_t *__restrict__ skip_count,
@@ -120,12 +124,12 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
     float *__restrict__ score_out)
 {
     constexpr int EPV = Elem<T>::kPerVec;              // elements per 16-byte vector
-    constexpr int SEG = kSlab, kDepth = Elem<T>::kDepth;
+    constexpr int kDepth = kInFlight / (2 * kTok * SEG * (int)sizeof(T));        // slabs in flight
     constexpr int kVecPerRow = SEG / EPV, kRowsPerLoad = kWave / kVecPerRow, kVecPerLane = kTok / kRowsPerLoad;
     constexpr int PLANES = EPV / 4;                    // a vector's floats are kept as 16-byte pieces, piece p in plane p
     constexpr int PLANE = 4 * kVecPerRow;              // floats
     constexpr int PITCH = SEG + 4;                     // floats; the 16 row reads of a piece hit distinct banks
-    __shared__ __attribute__((aligned(16))) float tile[kTiles][kTok * PITCH];
+    __shared__ __attribute__((aligned(16))) float tile[2][kTok * PITCH];
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -208,7 +212,7 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
             slab(s, buf_tag);
             issue(s + kDepth, buf_tag);
             publish();
-            wt = wt == kTiles - 1 ? 0 : wt + 1;
+            wt ^= 1;
         };
         int32_t s = 0;
         for (; s + kDepth <= nslab; s += kDepth) {
@@ -223,24 +227,28 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
             if (at >= nslab) return;
             slab(at, buf_tag);
             publish();
-            wt = wt == kTiles - 1 ? 0 : wt + 1;
+            wt ^= 1;
         };
         last(s, B0{});
         if constexpr (kDepth == 4) {
             last(s + 1, B1{});
             last(s + 2, B2{});
         }
-        publish();                       // the chains are a slab behind
+        publish();                       // the chains' last one
         return;
     }
 
     // The chains.  A dependent instruction per channel is their time, so little else may stand among them: pieces are read 64 channels ahead, in
     // the first half of the instructions of the 64 channels before their own, and waited for once.  Nine reads at the head of a slab waited
-    // for there, and a wait for each later one, took 3.9 ns a channel; this takes 2.4: 2025 x 3072 bf16 hot / cold 14.8 / 18.0 -> 12.2 / 15.5 us,
-    // 17550 x 3072 39.7 / 43.3 -> 38.1 / 41.8, 45000 x 3072 87.8 -> 85.9; fp32, also by slabs of 128 channels instead of 64, 1081 x 3072 14.0 -> 11.6
-    // hot, 3446 x 3072 15.5 -> 14.0.  Two loading waves: 13.1 and 39.3 us at the first two sizes; four, with six slabs in flight, 12.4 and 55.9.
+    // for there, and a wait for each later one, took 3.9 ns a channel; this takes 2.2: 2025 x 3072 bf16 hot / cold 14.7 / 17.9 -> 11.7 / 15.0 us,
+    // 17550 x 3072 39.6 / 43.7 -> 37.0 / 41.5, 40000 x 3072 77.4 -> 75.5; fp32, slabs of 64 channels then, 900 x 3072 14.1 -> 10.8 hot, 3000 x 3072
+    // 14.4 -> 12.2.  The barrier lies between the halves of a slab: all of it has been read there, so two tiles do, and the first half of a slab waits for
+    // no other.  At the head of the slab, with a third tile: 16384 x 512 fp32 12.6 us for 11.5 and, of rows that are not aligned, whose workgroups
+    // registers and LDS then held to six on a CU, 28000 x 511 bf16 56 for 35.  Two loading waves: 13.1 and 39.3 us at the first two sizes; four, with
+    // six slabs in flight, 12.4 and 55.9.
     float acc = 0.0f;
-    constexpr int UNIT = SEG / 8;        // pieces that are read at a time, half of a slab's
+    // Pieces that are read at a time: half of a slab's, or a quarter where the loads take few registers (68 in all; 132 with half slabs, three waves on a SIMD)
+    constexpr int UNITS = VEC ? 2 : 4, UNIT = SEG / 4 / UNITS;
     float4 v[2][UNIT];
     const int t = lane % kTok;           // the other lanes do what the first kTok do
     auto read = [&](int tl, int unit, int buf, int e) __attribute__((always_inline)) {
@@ -252,6 +260,14 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
             acc = acc + fabsf(x);
         else
             acc = __builtin_fmaf(x, x, acc);
+    };
+    auto unrolled_units = [&](auto f) __attribute__((always_inline)) {
+        f(std::integral_constant<int, 0>{});
+        f(std::integral_constant<int, 1>{});
+        if constexpr (UNITS == 4) {
+            f(std::integral_constant<int, 2>{});
+            f(std::integral_constant<int, 3>{});
+        }
     };
     // the chain through the unit in buffer B, and the reads of the next, unit `next` of tile tl, into the other buffer
     auto chain = [&](auto buf_tag, int tl, int next) __attribute__((always_inline)) {
@@ -271,17 +287,22 @@ __global__ __launch_bounds__(2 * kWave) void score_kernel(
         }
         __builtin_amdgcn_s_waitcnt(0xc07f);            // lgkmcnt(0)
     };
-    using V0 = std::integral_constant<int, 0>;
-    using V1 = std::integral_constant<int, 1>;
     publish();                           // slab 0 is in its tile
 #pragma unroll
     for (int e = 0; e < UNIT; ++e) read(0, 0, 0, e);
+    __builtin_amdgcn_s_waitcnt(0xc07f);                // here and not, for the first slab's sake, in the loop
     int tl = 0;
     for (int32_t s = 0; s < nslab; ++s) {
-        publish();                       // slab s + 1 is, if there is one: past the last slab what lies there is read and not used
-        chain(V0{}, tl, 1);
-        tl = tl == kTiles - 1 ? 0 : tl + 1;
-        chain(V1{}, tl, 0);
+        unrolled_units([&](auto unit_tag) __attribute__((always_inline)) {
+            constexpr int u = decltype(unit_tag)::value;
+            if (u == UNITS - 1) {
+                // All of this slab has been read, so its tile is free, and slab s + 1 is in the other, if there is one: past the last what lies there is
+                // read and not used.
+                publish();
+                tl ^= 1;
+            }
+            chain(std::integral_constant<int, u % 2>{}, tl, (u + 1) % UNITS);
+        });
     }
     if (lane >= kTok) return;
     if (VEC) {
@@ -410,8 +431,10 @@ void launch_mode(astraea_delta_mode mode, bool wide, hipStream_t st, const T *xc
         constexpr int MODE = decltype(mode_tag)::value;
         if (wide)
             go(score_wide_kernel<T, MODE, VEC, NT>);
+        else if (std::is_same<T, float>::value && VEC && N > kShortSlabTokens)
+            go(score_kernel<T, MODE, VEC, NT, 64>);
         else
-            go(score_kernel<T, MODE, VEC, NT>);
+            go(score_kernel<T, MODE, VEC, NT, 128>);
     };
     switch (mode) {
     case ASTRAEA_DELTA_L2: pick(std::integral_constant<int, ASTRAEA_DELTA_L2>{}); break;
@@ -429,22 +452,21 @@ int launch_score(const void *x_cur, const void *x_prev, astraea_dtype dt, int64_
 {
     if (N == 0) return ASTRAEA_OK;
     const int64_t es = dt == ASTRAEA_F32 ? 4 : 2;
-    // Which kernel.  Past the 256 MB of the memory-side cache the line is three wide waves per CU (36000 x 3072 bf16: wide 84.7 us,
-    // 16 tokens 73.7).  Arrays below that are either hot, still in the cache from their producer, or cold.  Cold, 16 tokens
-    // win up to about the same line; hot, they lose it earlier, since the wide kernel then has less latency to cover: bf16 hot /
-    // cold, wide and 16 tokens: 28000 x 512 13.7 / 16.5 and 12.6 / 14.4, 36000 x 512 14.1 / 17.3 and 14.8 / 16.4, 49000 x 256 9.1 /
-    // 11.4 and 10.8 / 11.7; 28000 x 2048 44.6 / 60.5 and 42.2 / 50.4, 32000 x 2048 44.7 / 65.1 and 51.0 / 58.6; fp32: 20000 x 512
-    // 15.3 / 22.6 and 14.1 / 16.0, 28000 x 512 17.9 / 25.3 and 18.7 / 22.2, 24000 x 1024 29.5 / 52.3 and 33.7 / 41.0.  The lines
-    // lie where neither loses hot.  (A 16-token workgroup also addresses its rows with 32-bit byte offsets.)
+    // Which kernel.  Past the 256 MB of the memory-side cache the line is three wide waves per CU (bf16 x 3072, us wide / 16 tokens: 36000 83.7 /
+    // 71.1, 49000 94.2 / 91.1, 52000 97.5 / 100.2).  Arrays below that are either hot, still in the cache from their producer, or cold.  Cold, 16 tokens
+    // win up to about the same line; hot, they lose it earlier, since the wide kernel then has less latency to cover: bf16 28000 x 512 13.0 / 12.0,
+    // 36000 x 512 13.5 / 14.2, 28600 x 2048 43.3 / 44.3, 32000 x 2048 43.5 / 49.4, 32000 x 1536 33.7 / 31.4; fp32 20000 x 512
+    // 14.6 / 13.4, 28000 x 512 17.6 / 18.2, 20400 x 1024 26.6 / 27.3, 24000 x 1024 28.8 / 30.2.  The lines
+    // lie where neither loses hot at the width that loses first.  (A 16-token workgroup also addresses its rows with 32-bit byte offsets.)
     const int64_t bytes = 2 * N * row_stride * es;
     const int64_t line = bytes > kCacheBytes ? kWideMinTokens : dt == ASTRAEA_F32 ? kWideMinCachedF32 : kWideMinCachedBf16;
     const bool wide = N >= line || kTok * row_stride * es > 2147483647LL;
     const bool vec = C * es >= 16 && ((uintptr_t)x_cur % 16 == 0) && ((uintptr_t)x_prev % 16 == 0) && ((row_stride * es) % 16 == 0);
     // The streaming hint (the line is not kept in L2) is for arrays that are not still cached from their producer:
     // above the 256 MB of the memory-side cache, 5.96 -> 6.77 TB/s at 118800 x 3072 (wide).  Up to 24576 tokens the
-    // 16-token kernel takes it from 200 MB on, where it costs little even hot: cold 45.5 -> 41.6 us and hot 39.7 -> 40.8 at
-    // 17550 x 3072 (206 MB); not so below, hot 24.9 -> 32.2 and cold 34.5 -> 32.3 at 17550 x 1024 fp32 (137 MB), nor past
-    // that many tokens, hot 42.2 -> 48.0 and cold 50.4 -> 47.5 at 28000 x 2048 bf16 (219 MB).
+    // 16-token kernel takes it from 200 MB on, where it costs little even hot: 17550 x 3072 (206 MB) cold 45.5 -> 41.6 us (as the chains were before they
+    // read ahead) and hot 37.1 -> 37.8; not so below, hot 25.2 -> 29.7 at 17550 x 1024 fp32 (137 MB), nor past
+    // that many tokens, hot 43.4 -> 46.5 at 28000 x 2048 bf16 (219 MB).
     const bool stream_loads = vec && bytes > (!wide && N <= 24576 ? (int64_t)200 << 20 : kCacheBytes);
 #define ASTRAEA_SCORE_LAUNCH(T, VEC, NT)                                                                                  \
     launch_mode<T, VEC, NT>(mode, wide, stream, (const T *)x_cur, (const T *)x_prev, N, C, row_stride, lse_weight,        \

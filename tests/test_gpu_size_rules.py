@@ -15,7 +15,7 @@ DEV = "cuda"
 
 
 # score: 16 tokens per workgroup below 28672 tokens (fp32 20480; 49152 where the arrays hold more than 256 MB), 64 per wave from
-# there on; streaming loads above 256 MB, up to 24576 tokens above 200; slabs of 128 channels, four in flight, in fp32 two;
+# there on; streaming loads above 256 MB, up to 24576 tokens above 200; slabs of 128 channels, four in flight, in fp32 two, or four of 64;
 # a width that is no multiple of the 16-byte vector ends on single channels.  Bit-exact.
 @pytest.mark.parametrize("n,c,stride,dtype", [
     (15, 128, 128, torch.bfloat16), (16, 256, 256, torch.bfloat16), (17, 384, 384, torch.bfloat16),      # 1 - 3 slabs
@@ -37,12 +37,20 @@ def test_score_sizes(n, c, stride, dtype, mode):
     assert np.array_equal(out.cpu().numpy().view(np.uint32), exp.view(np.uint32))
 
 
-# The chains run one slab of 128 channels behind a ring of three tiles and of four slabs in flight, in fp32 two: every pair of remainders, and a
+# The chains run half a slab of 128 channels behind two tiles and four slabs in flight, in fp32 two: every pair of remainders, and a
 # ragged last slab.
 @pytest.mark.parametrize("slabs", range(6, 18))
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_score_ring(slabs, dtype):
     test_score_sizes(35, slabs * 128 - 5 * (slabs % 2), slabs * 128, dtype, ab.DELTA_L2)
+
+
+# fp32 slabs of 64 channels, four in flight, above 8192 tokens, and of 128 up to there; the element path, whose chains read a quarter of a slab ahead.
+@pytest.mark.parametrize("n,c,stride,dtype", [(8193, slabs * 64 - 4 * (slabs % 2), slabs * 64, torch.float32) for slabs in range(1, 10)] + [
+    (8192, 512, 512, torch.float32), (8195, 321, 324, torch.float32)] + [
+    (n, c, c + 1, dtype) for n, c in ((35, 1), (35, 127), (35, 128), (35, 255), (35, 300), (8193, 449)) for dtype in (torch.bfloat16, torch.float32)])
+def test_score_slabs_by_tokens(n, c, stride, dtype):
+    test_score_sizes(n, c, stride, dtype, ab.DELTA_MEAN_ABS)
 
 
 # fp32 linear: 128-, 64- or 32-wide tiles by an estimate of the rounds they leave (32: the four waves split the contraction, and
