@@ -376,14 +376,16 @@ int astraea_check_indices(const int32_t *idx_sel, int64_t k_sel, int64_t N, int3
  * make that faster, two do, with half of the queries each (workgroups x + 16 p and x + 16 p + 8 its first and second 128).
  * plan_out (host, 8 entries): q_tiles, items_per_xcd, full_items, splits, tiles_per_split,
  * workgroups launched (8 or 16 per piece of an XCD), key tiles, partial-result slots the workspace holds.
+ * This is the launch where astraea_attn_key_groups gives 1.  Where it gives 2 or 4, the call takes the launch described there instead.
  */
 int astraea_attn_plan(int64_t N, int32_t H, int64_t k_sel, int64_t plan_out[8]);
 
 /*
  * Whether the bf16 attention of k_sel selected queries runs by that plan (1), or, where few items make it faster, with 2 or 4 key
- * groups: then a workgroup has 256 / groups selected queries of one head, each group of its waves sweeps one of as many equal shares of the
- * keys, and the workgroup merges them itself; XCD x owns the items [x*n, (x+1)*n) of all, head-major, n an eighth of them rounded up.  0 for
- * sizes out of range.  Host only; for inspection and tests.
+ * groups: then a work item is one head times one tile of 256 / groups selected queries, and one workgroup of eight waves runs it.  The keys' T tiles,
+ * of 64 keys with 2 groups and of 32 with 4, are shared out in order, group g of the waves sweeping [g*T / groups, (g+1)*T / groups) (rounded down), and
+ * the workgroup merges the groups' results itself; XCD x owns the items [x*n, (x+1)*n) of all, head-major, n (at most 32) an eighth of them rounded up,
+ * and workgroup x + 8 p is its item p: 8 n are launched.  0 for sizes out of range.  Host only; for inspection and tests.
  */
 int32_t astraea_attn_key_groups(int64_t N, int32_t H, int64_t k_sel);
 
@@ -397,7 +399,8 @@ int32_t astraea_attn_key_groups(int64_t N, int32_t H, int64_t k_sel);
 int astraea_attn_plan_f32(int64_t N, int32_t H, int32_t D, int64_t k_sel, size_t workspace_bytes, int64_t plan_out[8]);
 
 /*
- * The tile astraea_sparse_linear would give a workgroup for k_sel rows, c_in -> c_out.  Host only, nothing is
+ * The tile astraea_sparse_linear would give a workgroup for k_sel rows, c_in -> c_out: in fp32 where x and w span less than 4 GiB each, in bf16
+ * where astraea_linear_few_rows gives zeros (else its tile is the one).  Host only, nothing is
  * enqueued; for inspection and tests.  plan_out (host, 3 entries): output features per tile, tokens per
  * tile, tiles.
  */
@@ -408,6 +411,12 @@ int astraea_linear_plan(astraea_dtype dt, int64_t k_sel, int64_t c_in, int64_t c
  * inspection and tests.
  */
 int astraea_linear_few_rows(int64_t k_sel, int64_t c_in, int64_t c_out, int64_t plan_out[3]);
+
+/*
+ * Waves of a workgroup of that launch, 4 or 8, which tells fp32 tiles of 128 x 128 apart: eight waves hold halves of the contraction
+ * in pairs, four the whole of it.  0 for an unknown dtype or sizes out of range.  Host only; for inspection and tests.
+ */
+int32_t astraea_linear_waves(astraea_dtype dt, int64_t k_sel, int64_t c_in, int64_t c_out);
 
 /*
  * Measurement aids for the benchmark; neither is a step of the method.

@@ -28,7 +28,7 @@ EXPORTS = (
     "astraea_score", "astraea_select_topk", "astraea_select_topk_static", "astraea_sparse_attn_fwd", "astraea_sparse_attn_update_fwd",
     "astraea_sparse_attn_scatter_fwd", "astraea_scatter_update", "astraea_kv_refresh", "astraea_gather_rows", "astraea_sparse_linear", "astraea_sparse_linear_group", "astraea_workspace_bytes", "astraea_budget_to_k", "astraea_attn_flops",
     "astraea_probe_mfma_bf16", "astraea_probe_copy", "astraea_probe_kernel_timer", "astraea_probe_kernel_count",
-    "astraea_probe_kernel_ms", "astraea_lse_weight_update", "astraea_attn_plan", "astraea_attn_key_groups", "astraea_attn_plan_f32", "astraea_linear_plan", "astraea_linear_few_rows", "astraea_check_indices",
+    "astraea_probe_kernel_ms", "astraea_lse_weight_update", "astraea_attn_plan", "astraea_attn_key_groups", "astraea_attn_plan_f32", "astraea_linear_plan", "astraea_linear_few_rows", "astraea_linear_waves", "astraea_check_indices",
     "astraea_budget_search", "astraea_search_crossover", "astraea_search_mutate", "astraea_search_repair",
     "astraea_status_string", "astraea_last_error",
 )
@@ -114,6 +114,8 @@ def lib() -> C.CDLL:
         L.astraea_linear_plan.restype = C.c_int
         L.astraea_linear_few_rows.argtypes = [i64, i64, i64, C.POINTER(i64)]
         L.astraea_linear_few_rows.restype = C.c_int
+        L.astraea_linear_waves.argtypes = [i32, i64, i64, i64]
+        L.astraea_linear_waves.restype = i32
         L.astraea_probe_kernel_timer.argtypes = [C.c_int]
         L.astraea_probe_kernel_timer.restype = C.c_int
         L.astraea_probe_kernel_count.restype = i32
@@ -359,6 +361,10 @@ def astraea_linear_few_rows(k_sel: int, c_in: int, c_out: int) -> dict:
     out = (C.c_int64 * 3)()
     _check(lib().astraea_linear_few_rows(k_sel, c_in, c_out, out))
     return dict(zip(("tile_features", "tile_tokens", "tiles"), (int(v) for v in out)))
+
+
+def astraea_linear_waves(dtype: int, k_sel: int, c_in: int, c_out: int) -> int:
+    return int(lib().astraea_linear_waves(dtype, k_sel, c_in, c_out))
 
 
 def kernel_timer(enable: bool) -> None:

@@ -432,6 +432,12 @@ int astraea_linear_few_rows(int64_t k_sel, int64_t c_in, int64_t c_out, int64_t 
     return ASTRAEA_OK;
 }
 
+int32_t astraea_linear_waves(astraea_dtype dt, int64_t k_sel, int64_t c_in, int64_t c_out)
+{
+    if (!dtype_ok(dt) || k_sel <= 0 || k_sel > kMaxTokens || c_in <= 0 || c_out <= 0 || c_in > (1 << 24) || c_out > (1 << 24)) return 0;
+    return dt == ASTRAEA_F32 ? linear_f32_waves(k_sel, c_in, c_out, 1) : linear_bf16_few(k_sel, (int32_t)c_in, c_out, 1).tokens == 64 ? 4 : 8;
+}
+
 const char *astraea_status_string(int status)
 {
     switch (status) {

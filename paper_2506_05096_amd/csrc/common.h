@@ -83,6 +83,7 @@ struct LinearTile {
 LinearTile linear_bf16_tile(int64_t k_sel, int32_t c_in, int64_t c_out, int parts);
 LinearTile linear_bf16_few(int64_t k_sel, int32_t c_in, int64_t c_out, int parts);     // features 0: that tile is the one
 LinearTile linear_f32_tile(int64_t k_sel, int64_t c_in, int64_t c_out, int parts);
+int linear_f32_waves(int64_t k_sel, int64_t c_in, int64_t c_out, int parts);
 
 // Where the attention puts row r: rows[r] of a compact [k_sel, H * D] result, and row idx_sel[r] of a cached buffer of cache_rows rows.
 // Either may be null; an index outside the cached buffer writes nothing.

@@ -345,6 +345,52 @@ def test_attention_plan_covers_every_item_and_key_tile_once():
     assert sizes == {(128, False), (128, True), (256, False), (256, True)}
 
 
+def test_attention_key_groups_cover_every_item_and_key_tile_once():
+    """The launch of calls that run as key groups, as the header gives it: every (head, query tile, key tile) has one workgroup and
+    one group of its waves, every workgroup a CU of its own, shares are never empty and differ by one tile at most (a group with one
+    less waits that much longer)."""
+    import random
+    rnd = random.Random(1)
+    cases = [(2025, 24, 608), (97, 1, 1), (128, 3, 40), (129, 2, 65), (1460, 16, 1460), (1500, 2, 16384), (3836, 16, 1918)]
+    cases += [(rnd.randint(1, 9000), rnd.choice((1, 2, 3, 5, 8, 12, 16, 24)), rnd.randint(1, 4000)) for _ in range(600)]
+    seen = set()
+    for N, H, k in cases:
+        groups = ab.astraea_attn_key_groups(N, H, k)
+        seen.add(groups)
+        if groups == 1:
+            continue
+        assert groups in (2, 4) and k <= 16384
+        q_tiles, tiles = -(-k // (256 // groups)), -(-N // (32 if groups == 4 else 64))
+        n = -(-q_tiles * H // 8)
+        assert n <= 32, (N, H, k)
+        items = [xcd * n + p for p in range(n) for xcd in range(8) if xcd * n + p < q_tiles * H]
+        assert sorted(items) == list(range(q_tiles * H)), (N, H, k)
+        shares = [(g * tiles // groups, (g + 1) * tiles // groups) for g in range(groups)]
+        assert shares[0][0] == 0 and shares[-1][1] == tiles and all(a[1] == b[0] for a, b in zip(shares, shares[1:])), (N, H, k)
+        lengths = {hi - lo for lo, hi in shares}
+        assert min(lengths) >= 1 and lengths <= {tiles // groups, -(-tiles // groups)}, (N, H, k)
+    assert seen == {1, 2, 4}
+    assert ab.astraea_attn_key_groups(0, 1, 1) == ab.astraea_attn_key_groups(10, 0, 1) == ab.astraea_attn_key_groups(10, 1, 0) == 0
+    assert ab.astraea_attn_key_groups(10, 65536, 1) == 0
+
+
+def test_linear_waves_and_few_rows():
+    """Which kernel a layer takes where its tile alone does not say: fp32 128 x 128 in eight waves and in four, with more tiles than
+    CUs in either, and the bf16 tiles of few rows, none of them more than CUs."""
+    wide = {(3001, 512, 648): 8, (4099, 6144, 1536): 8, (6000, 1536, 6144): 4, (4000, 64, 1000): 4}
+    for (k, c_in, c_out), waves in wide.items():
+        assert ab.astraea_linear_plan(ab.F32, k, c_in, c_out)["tile_tokens"] == 128
+        assert ab.astraea_linear_plan(ab.F32, k, c_in, c_out)["tile_features"] == 128
+        assert ab.astraea_linear_waves(ab.F32, k, c_in, c_out) == waves, (k, c_in, c_out)
+    assert ab.astraea_linear_plan(ab.F32, 4099, 6144, 1536)["tiles"] > 256
+    assert ab.astraea_linear_waves(ab.F32, 60, 3072, 3072) == 4 and ab.astraea_linear_waves(ab.F32, 1250, 512, 776) == 8
+    for k, c_in, c_out, tokens, waves in ((608, 12288, 3072, 128, 8), (152, 1536, 4608, 64, 4), (35640, 3072, 3072, 0, 8)):
+        few = ab.astraea_linear_few_rows(k, c_in, c_out)
+        assert few["tile_tokens"] == tokens and few["tiles"] <= 256
+        assert ab.astraea_linear_waves(ab.BF16, k, c_in, c_out) == waves
+    assert ab.astraea_linear_waves(7, 1, 64, 8) == 0 and ab.astraea_linear_waves(ab.F32, 0, 64, 8) == 0
+
+
 def test_attention_plan_work_follows_the_budget():
     """Rounds of 32 workgroups per XCD, each weighted by the share of the keys it sweeps: the plan's cost stays
     within 10 % of proportional to k_sel from the 10 % budget up, at the headline shape."""

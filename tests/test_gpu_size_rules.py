@@ -103,7 +103,7 @@ def test_linear_f32_tiles(n, k, c_in, c_out, gather, scatter, bias, act, tile):
     (1300, 1250, 640, 776, False, True, False, ab.ACT_NONE, 64), (3100, 3001, 512, 1288, True, True, True, ab.ACT_NONE, 64),
 ])
 def test_linear_f32_halves(n, k, c_in, c_out, gather, scatter, bias, act, features):
-    assert ab.astraea_linear_plan(ab.F32, k, c_in, c_out)["tile_features"] == features
+    assert ab.astraea_linear_plan(ab.F32, k, c_in, c_out)["tile_features"] == features and ab.astraea_linear_waves(ab.F32, k, c_in, c_out) == 8
     test_linear_f32_tiles(n, k, c_in, c_out, gather, scatter, bias, act, 128)
 
 
