@@ -155,12 +155,17 @@ def _p(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
+# The current device and the number of its current stream; None where this torch does not have them under these names.
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
     """The current stream of the current device.  torch.cuda.current_stream() makes a Python object of it and takes 2.7 us, nearly as long as the
     launch that follows (3.1); the number alone takes 0.3."""
-    if not torch.cuda.is_initialized():
+    if _raw_stream is None or _current_device is None or not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(_current_device())
 
 
 def workspace_bytes(op: int, N: int, k_sel: int = 0, H: int = 0, D: int = 0) -> int:

@@ -491,6 +491,22 @@ def test_block_flop_accounting_is_the_papers_formulas_at_k():
         assert all(abs(part[name] / full[name] - pct / 100) < 1e-12 for name in full)
 
 
+def test_the_current_stream_without_its_number(monkeypatch):
+    """A torch that does not have the stream's number under torch._C still gives the stream."""
+    import importlib.util
+    import types
+
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.delattr(torch._C, "_cuda_getDevice", raising=False)
+    spec = importlib.util.spec_from_file_location("binding_without_numbers", ab.__file__)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    assert mod._stream() == 77
+
+
 def test_header_is_plain_c():
     """The boundary is a C ABI: the header must compile as C99 with nothing but the standard headers, and a C
     program must be able to link against the library by those declarations."""
