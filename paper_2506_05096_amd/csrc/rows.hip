@@ -114,11 +114,12 @@ int launch_move_rows(void *dst, const void *src, int64_t row_bytes, int64_t dst_
     hipLaunchKernelGGL((move_rows_kernel<V, S>), grid, block, 0, stream, (char *)dst, (const char *)src, (char *)dst_b, \
                        (const char *)src_b, row_bytes, dst_stride_bytes, src_stride_bytes, idx, k_sel, n_rows,         \
                        (int)index_dst, (int)index_src, (int32_t)pieces)
-    // Cache rows refreshed from rows of another full-size buffer.  Buffers past half of the 256 MB memory-side cache come from and go to HBM, and what a step
-    // still has there is kept by streaming past it (stateful step of 17550 tokens x 1755 x 24 419 us, 425 with plain stores); smaller ones are read
-    // from that cache by the kernels that follow, where streamed rows are not (layer-step of 2025 x 608 x 24 48.5 us, 45.7 plain, 4000 x 2000 x 24
-    // 120.4 / 118.8; the same from 120 to 150 MB: 9000 x 5400 x 16 396.0 / 395.2).
-    const double reach = (double)n_rows * ((double)dst_stride_bytes + (double)src_stride_bytes) * (dst_b ? 2.0 : 1.0);
+    // Cache rows refreshed from rows of another full-size buffer.  Rows of both sides past half of the 256 MB memory-side cache come from and go to HBM, and
+    // what a step still has there is kept by streaming past it (stateful step of 17550 tokens x 1755 x 24 419 us, 425 with plain stores); fewer are read
+    // from that cache by the kernels that follow, where streamed rows are not.  Layer-steps, us streamed / plain: 2025 x 608 x 24 48.7 / 45.5, 1500 x 700 x
+    // 16 43.4 / 40.0, 4000 x 2000 x 24 120.2 / 119.5; the same from 120 to 150 MB, 9000 x 5400 x 16 383.8 / 383.8.  What lies between the rows (of a packed
+    // cache, the other projections) is not moved and does not count.
+    const double reach = (double)n_rows * (double)row_bytes * (dst_b ? 4.0 : 2.0);
     const bool stream_dst = index_dst && index_src && reach > 128e6;
     if (vec == 16) {
         if (stream_dst) ASTRAEA_MOVE(uint4v, true);
