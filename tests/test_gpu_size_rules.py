@@ -94,11 +94,12 @@ def test_linear_f32_tiles(n, k, c_in, c_out, gather, scatter, bias, act, tile):
     assert torch.equal(y[keep].double(), exp[keep])
 
 
-# Eight waves on 128 x 128 tiles (one round of them) and on 64 features x 128 tokens: ragged rows and features, a feature tile of eight, a row
+# Eight waves on 128 x 128 tiles (one round of them, and more where the contraction is deep) and on 64 features x 128 tokens: ragged rows and features, a feature tile of eight, a row
 # in the last tile, stages that are no multiple of the register sets; the values that send a workgroup to fp32 products.  Bounds as above and below.
 @pytest.mark.parametrize("n,k,c_in,c_out,gather,scatter,bias,act,features", [
     (3100, 3001, 512, 648, True, True, True, ab.ACT_GELU_TANH, 128), (3100, 2945, 576, 776, False, True, True, ab.ACT_NONE, 128),
     (3100, 3072, 1088, 768, True, False, False, ab.ACT_NONE, 128),
+    (2100, 2000, 4160, 4104, True, True, True, ab.ACT_NONE, 128),                  # 528 tiles
     (1300, 1250, 512, 776, True, True, True, ab.ACT_NONE, 64), (1300, 1281, 576, 776, True, False, True, ab.ACT_GELU_TANH, 64),
     (1300, 1250, 640, 776, False, True, False, ab.ACT_NONE, 64), (3100, 3001, 512, 1288, True, True, True, ab.ACT_NONE, 64),
 ])
