@@ -266,7 +266,7 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
     const int64_t row_pitch = kv_stride_n * 2;       // bytes between consecutive keys
     const int d_row = lane >> 4, d_p = lane & 15;
     const uint32_t lin_off = lane * 16;
-    // Rows [key0, key0 + 64) of K or V; physical chunk p of row r holds logical chunk p ^ sw(r).
+    // Rows [key0, key0 + kTk) of K or V; physical chunk p of row r holds logical chunk p ^ sw(r).
     auto dma_rows = [&](const char *base, int64_t tile, uint32_t buf, int w, auto nw_tag, int swz, bool zero_fill) __attribute__((always_inline)) {
         // a wave's rows advance by 4 NW: with 4 or 8 waves the swizzle is the same for all of them, with 2 it alternates for K
         constexpr int NW = decltype(nw_tag)::value;
@@ -375,7 +375,7 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
     // VALU phase for tile j: exponentials -> pw, row sums; in the exact form first the row max: the running
     // max is only raised (and what was accumulated under the old one rescaled) when some row's max moved up by
     // more than 2^kTau, otherwise the stale max stays in use.
-    // register i of sacc[kb]: key = 64*j + 32*kb + (i/4)*8 + hf*4 + i%4, query = qc
+    // register i of sacc[kb]: key = kTk*j + 32*kb + (i/4)*8 + hf*4 + i%4, query = qc
     auto tile_row_max = [&]() __attribute__((always_inline)) -> float {
         float tm = sacc[0][0];
 #pragma unroll
@@ -429,11 +429,11 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
     };
 
     constexpr int kAhead = 4;      // an MFMA's fragment is fetched kAhead MFMAs before it issues
-    // MFMA phase.  O^T += V^T(j) P^T(j): 16 MFMAs; group tt contracts the 16 keys 16*tt + {0..3, 8..11}
+    // MFMA phase.  O^T += V^T(j) P^T(j): kMfmas MFMAs, 8 to a block of 32 keys; group tt contracts the 16 keys 16*tt + {0..3, 8..11}
     // (lanes 0-31) and 16*tt + {4..7, 12..15} (lanes 32-63); V^T(j) is in the parity va[] points at.
-    // Then, if WITH_QK, S^T = K Q^T for the next tile: 16 MFMAs, the two blocks of 32 keys taking turns (two
+    // Then, if WITH_QK, S^T = K Q^T for the next tile: as many, where there are two blocks of 32 keys these taking turns (two
     // consecutive MFMAs share the Q fragment and feed different accumulators).  One LDS read pipeline runs
-    // through all 32 MFMAs.
+    // through all of them.
     // The buffer parity PAR of the phase is a compile-time constant: V^T(j) is read from buffer pair PAR, K(j+1)
     // from pair PAR ^ 1.
     auto mfma_phase = [&](auto qk_tag, auto par_tag) __attribute__((always_inline)) {
@@ -502,6 +502,12 @@ __global__ __launch_bounds__(GROUPS *kGroupWaves *kWave, 2 / GROUPS) void attn_b
     // free (both groups are past the MFMA phase that read them), and the copies are waited for at the
     // end of its following MFMA phase, one phase before group 0 needs them.  Every wave executes the
     // same number of barriers: group 1 one more at the start, group 0 one more at the end.
+    // Key groups (all waves of one are in one of these two groups) have tiles of their own, j counting from their share's first, and copy them
+    // themselves, all waves of a group in the same phase: in the VALU phase for tile j they are past the barrier behind their MFMA phase for tile
+    // j - 1, which read these buffers last, and each waits for its copies in front of the barrier behind the MFMA phase for tile j, the next
+    // phase but one being the first that reads them.  A share that has a tile less than the longest passes two more barriers, one for either phase.
+    // So the last barrier of all, group 1's behind its last tile and group 0's one more, lies behind every wave's last read of a tile: past it
+    // the vote, the repeated sweep's first copies and the merge may use the tiles' place.
     using P0 = std::integral_constant<int, 0>;
     using P1 = std::integral_constant<int, 1>;
     // The whole sweep.  EXACT = false: offset fixed by the first tile, no max in the sweep.  EXACT = true: a max per tile.
