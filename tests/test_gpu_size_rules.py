@@ -891,13 +891,14 @@ def test_linear_bf16_few_rows(n, k, c_in, c_out, gather, scatter, bias, act, tok
 
 
 # Layers of one input in one launch, against a call each: one to three parts, widths that end inside a tile of features, every tile kind
-# (few rows, many rows, deep and shallow contractions), a part without a bias, compact and placed results.  bf16 sums a contraction in one
+# (few rows, in bf16 tiles of 64 and of 128 of them, many rows, deep and shallow contractions), a part without a bias, compact and placed results.  bf16 sums a contraction in one
 # order whatever the tile, so its bits are the same; fp32 results are held to the bound of their products (test_linear_f32_split_range).
 # "chained": a layer whose weight is the result before it gets its turn after it.
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("n,k,c_in,c_out,parts,chained", [
     (700, 300, 128, 264, 3, False), (2100, 2049, 512, 512, 3, False), (1300, 1000, 1024, 1096, 2, False), (90, 33, 64, 8, 3, False),
     (4000, 3900, 320, 776, 3, False), (500, 499, 192, 192, 1, False), (500, 192, 192, 192, 3, True),
+    (300, 131, 576, 264, 3, False), (90, 1, 512, 72, 2, False), (700, 601, 640, 1032, 3, False), (1300, 1001, 1088, 520, 2, False),
 ])
 def test_linear_group(dtype, n, k, c_in, c_out, parts, chained):
     g = torch.Generator(device=DEV).manual_seed(n + k)
