@@ -372,14 +372,16 @@ def test_attn_bf16_rows_that_outgrow_their_first_tile_by_a_tolerated_margin(rise
     assert np.max(np.abs(lse - else_) / np.maximum(1.0, np.abs(else_))) <= 3e-5
 
 
-def test_attn_bf16_only_the_workgroups_that_need_it_are_redone():
+@pytest.mark.parametrize("h,k_sel,groups", [(12, 1400, 1), (24, 1100, 2)])
+def test_attn_bf16_only_the_workgroups_that_need_it_are_redone(h, k_sel, groups):
     """A handful of selected rows meet one key whose logit lies hundreds of nats above everything in their first
     tile (their exponentials overflow under the first tile's offset), all other rows are ordinary.  The
     workgroups holding those rows repeat their sweep in the exact form, the others do not; every row, redone or not,
-    cut into key ranges or not, must match the oracle, and twice the same call the same bits."""
-    n, h, d, k_sel = 4100, 24, 128, 1100
+    of items cut into key ranges or of key groups, must match the oracle, and twice the same call the same bits."""
+    n, d = 4100, 128
+    assert ab.astraea_attn_key_groups(n, h, k_sel) == groups and ab.astraea_attn_plan(n, h, k_sel)["splits"] > 1
     q, k, v, idx = _attn_case(n, h, d, k_sel, torch.bfloat16, seed=404)
-    hot = idx[[3, 300, 1000, 1099]].long()            # rows of the first, second, fourth and last (cut) query tile
+    hot = idx[[3, 300, 1000, k_sel - 1]].long()       # rows of the first, the last and two other query tiles
     q[hot, :, 0] = 64.0
     k[3000, :, 0] = 64.0                              # logit 4096 / sqrt(128) = 362 nats for the hot rows
     k[17, 5, 0] = 48.0                                # and a second, smaller peak inside the first tile of head 5
@@ -405,9 +407,11 @@ def test_attn_bf16_only_the_workgroups_that_need_it_are_redone():
 
 
 @pytest.mark.parametrize("n,h,k_sel", [
-    (4100, 24, 1100),     # 5 query tiles x 24 heads = 15 items per XCD: a partly filled round, cut in 2 key ranges
+    (4100, 24, 1100),     # 9 query tiles of 128 x 24 heads = 27 items per XCD, each in 2 key groups of 33 and 32 tiles
+    (4100, 12, 1400),     # 6 query tiles x 12 heads = 9 items per XCD -> 3 key ranges of the 65 tiles (uneven split)
+    (3000, 24, 2800),     # 33 items per XCD: a whole round, and one cut
     (1500, 8, 256),       # 1 item per XCD, cut into as many key ranges as there are tiles allow
-    (700, 24, 2000 // 3), # 3 tiles x 24 heads = 9 items per XCD -> 3 key ranges of the 11 tiles (uneven split)
+    (700, 24, 2000 // 3), # 6 query tiles of 128 x 24 heads = 18 items per XCD, each in 2 key groups of 6 and 5 tiles
     (200, 3, 190),        # fewer items than XCDs
     (65, 5, 3),           # two tiles, one of them a single key
     (129, 5, 3),          # three tiles, the last a single key
@@ -567,16 +571,17 @@ def test_kernel_timer_counts_attention_launches_and_leaves_results_alone(dtype, 
 
 # ------------------------------------------------------------- determinism --
 
-def test_every_kernel_gives_the_same_bits_on_every_run():
+@pytest.mark.parametrize("n,h,k_sel,groups,splits", [(4100, 12, 1400, 1, 3), (4100, 24, 1100, 2, 2), (2025, 24, 608, 4, 3)])
+def test_every_kernel_gives_the_same_bits_on_every_run(n, h, k_sel, groups, splits):
     """No result depends on the order in which workgroups happen to run: three runs of each call on the same
-    inputs are bit-identical (the split attention items are merged in a fixed order, the top-k compaction is by
-    index, nothing accumulates through atomics)."""
-    n, h, d, c, k_sel = 4100, 24, 128, 520, 1100           # the attention of this shape has split items
+    inputs are bit-identical (the split attention items are merged in a fixed order, and so are key groups, the top-k compaction
+    is by index, nothing accumulates through atomics)."""
+    d, c = 128, 520
     g = torch.Generator().manual_seed(77)
     xc, xp = torch.randn(n, c, generator=g).bfloat16().to(DEV), torch.randn(n, c, generator=g).bfloat16().to(DEV)
     q, k, v = (torch.randn(n, h, d, generator=g).bfloat16().to(DEV) for _ in range(3))
     w = (torch.randn(264, h * d, generator=g) / 55.0).bfloat16().to(DEV)
-    assert ab.astraea_attn_plan(n, h, k_sel)["splits"] > 1
+    assert ab.astraea_attn_plan(n, h, k_sel)["splits"] == splits and ab.astraea_attn_key_groups(n, h, k_sel) == groups
     ws_t = torch.empty(ab.workspace_bytes(ab.OP_SELECT_TOPK, n), dtype=torch.uint8, device=DEV)
     ws_a = torch.empty(ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k_sel, h, d), dtype=torch.uint8, device=DEV)
     runs = []

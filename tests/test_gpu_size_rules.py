@@ -259,16 +259,18 @@ def test_linear_f32_halves_magnitudes(k, c_in, c_out, values):
 
 
 # bf16 attention: 256 queries per workgroup, 32 per wave (rows pass through LDS whole, four at a time), 64 keys per tile; the
-# items of a partly filled round are cut into key shares where the launch's estimate says so (last four cases: 8, 3, 2
-# and 1 shares).  `hot` plants one key whose logit overflows the first tile's offset, so that the workgroup repeats its
+# items of a partly filled round are cut into key shares where the launch's estimate says so, and `groups` is 1 where none of the launches in
+# key groups takes the call.  `hot` plants one key whose logit overflows the first tile's offset, so that the workgroup repeats its
 # sweep; compact queries may outnumber the keys.  Oracle: fp64 softmax; bar: relative L2 1e-2 per row and head.
 @pytest.mark.parametrize("n,h,k,hot,scatter,splits", [
     (1, 1, 1, False, True, 1), (63, 2, 31, False, True, 1), (64, 1, 33, True, False, 1), (65, 3, 65, True, True, 1),
-    (129, 2, 5000, True, False, 1), (300, 1, 255, False, True, 1), (512, 9, 257, True, True, 1),
+    (96, 3, 89, True, True, 1), (129, 4, 5000, True, False, 1), (300, 60, 300, False, True, 1), (512, 24, 2900, True, False, 1),
     (100, 2, 16384, True, False, 1), (100, 2, 16385, True, False, 1), (128, 1, 16385, False, False, 1),      # V direct, retiled
-    (4000, 1, 30, True, True, 8), (2025, 24, 608, True, True, 3), (4100, 24, 1100, False, False, 2), (900, 24, 450, True, True, 1),
+    (4000, 1, 30, True, True, 8), (4000, 3, 3000, True, True, 5), (4100, 24, 4000, False, False, 2), (4000, 12, 1400, True, True, 3),
+    (1500, 8, 8449, True, False, 6), (2025, 12, 5700, True, False, 4), (3000, 24, 2800, True, True, None),                                # whole items and shares
 ])
-def test_attn_bf16_tiles(n, h, k, hot, scatter, splits):
+def test_attn_bf16_tiles(n, h, k, hot, scatter, splits, groups=1):
+    assert ab.astraea_attn_key_groups(n, h, k) == groups
     if splits is not None:
         assert ab.astraea_attn_plan(n, h, k)["splits"] == splits
     g = torch.Generator(device=DEV).manual_seed(n + h + k)
@@ -308,24 +310,24 @@ def test_attn_bf16_tiles(n, h, k, hot, scatter, splits):
 # tiles of more than 32 items per XCD, none of them cut.  Both sides of each line (`queries` is what the launch says), with rows that send a
 # workgroup through its sweep again, a second half without queries, shares of halves, and one key tile; V direct and retiled.
 @pytest.mark.parametrize("n,h,k,hot,scatter,queries,splits", [
-    (2048, 16, 2048, True, True, 128, 1), (2100, 16, 2049, True, True, 256, 1),
+    (300, 16, 2048, True, False, 128, 1), (2100, 16, 2049, True, True, 256, 1),
     (1536, 8, 10000, True, False, 128, 1), (1537, 8, 10000, True, False, 256, 1), (1536, 8, 8300, True, False, 256, 8),
     (60, 24, 3000, False, False, 128, 1), (65, 24, 2900, True, False, 128, 1), (64, 40, 1800, True, False, 128, 1),
-    (500, 8, 128, True, True, 128, 1), (500, 8, 129, True, True, 128, 1), (4000, 2, 300, True, True, 128, 8), (4200, 4, 4200, True, True, 256, 3),
+    (96, 8, 128, True, False, 128, 1), (96, 8, 129, True, False, 128, 1), (300, 24, 1025, True, False, 128, 1), (300, 60, 300, True, True, 128, 1), (4000, 2, 300, True, True, 128, 8), (4200, 4, 4200, True, True, 256, 3),
     (1536, 4, 20000, True, False, 128, 1), (1537, 4, 20000, True, False, 256, 1), (77, 8, 17000, True, False, 128, 1),
 ])
 def test_attn_bf16_half_workgroups(n, h, k, hot, scatter, queries, splits):
     assert ab.astraea_attn_plan(n, h, k)["queries_per_workgroup"] == queries
-    test_attn_bf16_tiles(n, h, k, hot, scatter, splits)
+    test_attn_bf16_tiles(n, h, k, hot, scatter, splits)          # one key group
 
 
 # Four-wave workgroups whose output rows lie over the second V buffer, all of them sweeping again (logits 90 nats above the first key tile's) with
 # their last key tile in that buffer (even numbers of tiles) or in the first: values 2^10 times larger in the last tile show a wave
 # that read anything else there.  V direct and retiled.  Bars as above.
-@pytest.mark.parametrize("n,h,k", [(128, 8, 1024), (192, 8, 1000), (2048, 16, 2048), (1536, 8, 10000), (128, 4, 16500), (192, 4, 16500)])
+@pytest.mark.parametrize("n,h,k", [(128, 8, 2000), (192, 16, 1024), (256, 16, 2048), (300, 24, 1000), (1472, 8, 10000), (1536, 8, 10000), (128, 4, 16500), (192, 4, 16500)])
 def test_attn_bf16_half_workgroups_that_sweep_again(n, h, k):
     plan = ab.astraea_attn_plan(n, h, k)
-    assert plan["queries_per_workgroup"] == 128 and plan["splits"] == 1
+    assert plan["queries_per_workgroup"] == 128 and plan["splits"] == 1 and ab.astraea_attn_key_groups(n, h, k) == 1
     q, kc, vc = _attn_rise_case(n, h, k, 128, 90.0, torch.bfloat16, 64)
     vc[n - 64:] *= 2.0 ** 10
     lse = torch.full((k, h), math.nan, device=DEV)
@@ -348,17 +350,18 @@ def test_attn_bf16_half_workgroups_that_sweep_again(n, h, k):
     (97, 1, 1, False, True, 4, 1), (128, 3, 40, True, True, 4, 1), (129, 2, 65, True, True, 4, 1), (161, 5, 64, False, False, 4, 1),
     (223, 24, 255, True, False, 4, 1), (255, 16, 129, True, True, 4, 1), (1500, 24, 610, True, True, 4, None),
     (1028, 4, 4102, False, False, 2, 1), (1460, 16, 1460, True, True, 2, 1), (1089, 8, 3969, True, False, 2, 1), (1500, 2, 16384, False, False, 2, 1),
+    (129, 2, 5000, True, False, 4, 1), (300, 1, 255, False, True, 4, 1), (512, 9, 257, True, True, 4, 1), (2025, 24, 608, True, True, 4, 3),
+    (4100, 24, 1100, False, False, 2, 2), (900, 24, 450, True, True, 4, 1), (2048, 16, 2048, True, True, 2, 1), (500, 8, 128, True, True, 4, 1), (500, 8, 129, True, True, 4, 1),
     (130, 16, 2000, True, False, 1, 1), (3716, 12, 1400, True, True, 1, 3), (1762, 2, 2470, False, False, 1, 4), (957, 1, 41, True, True, 1, 5),
     (762, 1, 167, False, True, 1, 6), (2080, 1, 37, True, True, 1, 7), (1398, 1, 20, False, True, 1, 8),
 ])
 def test_attn_bf16_key_groups(n, h, k, hot, scatter, groups, splits):
-    assert ab.astraea_attn_key_groups(n, h, k) == groups
-    test_attn_bf16_tiles(n, h, k, hot, scatter, splits)
+    test_attn_bf16_tiles(n, h, k, hot, scatter, splits, groups)
 
 
 # Key groups that all sweep again, the first of them with logits 90 nats below the others' and its own later ones, or none but the first one's
 # rows above its offset; queries by index, the compact result and the cached rows written at once.
-@pytest.mark.parametrize("n,h,k", [(700, 8, 600), (161, 4, 161), (1460, 16, 1460), (1411, 16, 1400)])
+@pytest.mark.parametrize("n,h,k", [(700, 8, 600), (161, 4, 161), (1460, 16, 1460), (1411, 16, 1400), (128, 8, 128), (192, 8, 190), (2048, 16, 2048)])
 @pytest.mark.parametrize("rise_nats", [30.0, 90.0])
 def test_attn_bf16_key_groups_that_sweep_again(n, h, k, rise_nats):
     assert ab.astraea_attn_key_groups(n, h, k) > 1
@@ -417,18 +420,20 @@ def test_attn_bf16_logits_of_minus_infinity(n, h, k, groups, splits, where):
 
 
 # The compact result and the cached rows from one call, against the two calls it stands for: whole and cut work items, both workgroup
-# sizes, cached buffers that the kernel writes itself and those that get a launch of their own (stride, alignment, memory shared with q).
-@pytest.mark.parametrize("dtype,n,h,d,k,queries,splits", [
-    (torch.bfloat16, 2025, 24, 128, 608, 256, 3), (torch.bfloat16, 2100, 16, 128, 2049, 256, 1), (torch.bfloat16, 300, 3, 128, 77, 128, 1),
-    (torch.bfloat16, 300, 30, 128, 300, 128, 1), (torch.bfloat16, 4000, 2, 128, 300, 128, 8),
-    (torch.float32, 700, 8, 64, 60, 128, 2), (torch.float32, 97, 2, 128, 97, 128, 1), (torch.float32, 2500, 8, 128, 2500, 256, 3),
-    (torch.float32, 2700, 24, 64, 2700, 256, 8),
+# sizes, key groups (`groups`), cached buffers that the kernel writes itself and those that get a launch of their own (stride, alignment, memory shared with q).
+@pytest.mark.parametrize("dtype,n,h,d,k,queries,splits,groups", [
+    (torch.bfloat16, 2025, 24, 128, 608, 256, 3, 4), (torch.bfloat16, 2100, 16, 128, 2049, 256, 1, 1), (torch.bfloat16, 300, 3, 128, 77, 128, 1, 4),
+    (torch.bfloat16, 300, 30, 128, 300, 128, 1, 4), (torch.bfloat16, 4000, 2, 128, 300, 128, 8, 1), (torch.bfloat16, 1460, 16, 128, 1460, 128, 1, 2),
+    (torch.bfloat16, 3716, 12, 128, 1400, 256, 3, 1), (torch.bfloat16, 90, 3, 128, 77, 128, 1, 1), (torch.bfloat16, 300, 60, 128, 300, 128, 1, 1),
+    (torch.float32, 700, 8, 64, 60, 128, 2, 0), (torch.float32, 97, 2, 128, 97, 128, 1, 0), (torch.float32, 2500, 8, 128, 2500, 256, 3, 0),
+    (torch.float32, 2700, 24, 64, 2700, 256, 8, 0),
 ])
 @pytest.mark.parametrize("cache", ["plain", "padded", "odd stride", "misaligned", "shares q"])
-def test_attn_result_and_cached_rows(dtype, n, h, d, k, queries, splits, cache):
+def test_attn_result_and_cached_rows(dtype, n, h, d, k, queries, splits, groups, cache):
     room = max(ab.workspace_bytes(ab.OP_SPARSE_ATTN, n, k, h, d), 256)
     plan = ab.astraea_attn_plan(n, h, k) if dtype == torch.bfloat16 else ab.astraea_attn_plan_f32(n, h, d, k, room)
     assert (plan["queries_per_workgroup"], plan["splits"]) == (queries, splits)
+    assert dtype == torch.float32 or ab.astraea_attn_key_groups(n, h, k) == groups
     g = torch.Generator(device=DEV).manual_seed(n + k)
     e = h * d
     both = torch.randn(n, 2, e, device=DEV, generator=g).to(dtype)
@@ -490,10 +495,12 @@ def test_attn_bf16_retiled_layouts_and_rises(layout, rise_nats):
 
 
 # Logits 45 nats above those of the first key tile, inside the margin of the row sums, over values of 2^66: the accumulators
-# of the first sweep overflow.  Compact queries fewer and more than the keys, with and without key shares, V direct and
+# of the first sweep overflow.  Compact queries fewer and more than the keys, in shares of four and of eight waves, in key groups, and whole, V direct and
 # retiled.  Bar: relative L2 1e-2 per row (bf16 probabilities and results).
-@pytest.mark.parametrize("n,h,k", [(1300, 2, 100), (4100, 24, 1100), (1300, 2, 5000), (300, 1, 16385)])
-def test_attn_bf16_large_values_in_rows_that_rise(n, h, k):
+@pytest.mark.parametrize("n,h,k,groups,splits", [(1300, 2, 100, 1, 7), (3716, 12, 1400, 1, 3), (4100, 24, 1100, 2, 2), (1300, 2, 5000, 4, 3), (300, 24, 1000, 1, 1),
+                                                 (300, 1, 16385, 1, 1)])
+def test_attn_bf16_large_values_in_rows_that_rise(n, h, k, groups, splits):
+    assert ab.astraea_attn_key_groups(n, h, k) == groups and ab.astraea_attn_plan(n, h, k)["splits"] == splits
     q, kc, vc = _attn_rise_case(n, h, k, 128, 45.0, torch.bfloat16, 64)
     vc *= 2.0 ** 66
     out = torch.empty(k, h, 128, dtype=torch.bfloat16, device=DEV)
@@ -710,7 +717,8 @@ def test_topk_of_several_workgroups(n, small, kind):
     (9000, 8193, 128, 2048, True, True, True, ab.ACT_NONE, 192), (12100, 12000, 9216, 2048, False, True, True, ab.ACT_NONE, 192),
     (33100, 33000, 3136, 3072, True, True, True, ab.ACT_NONE, 256),
 ])
-def test_linear_bf16_tiles(n, k, c_in, c_out, gather, scatter, bias, act, tile, features=256):
+def test_linear_bf16_tiles(n, k, c_in, c_out, gather, scatter, bias, act, tile, features=256, few=0):
+    assert ab.astraea_linear_few_rows(k, c_in, c_out)["tile_tokens"] == few
     assert ab.astraea_linear_plan(ab.BF16, k, c_in, c_out) == {
         "tile_features": features, "tile_tokens": tile, "tiles": -(-k // tile) * -(-c_out // features)}
     g = torch.Generator(device=DEV).manual_seed(n + k + c_in)
@@ -866,10 +874,11 @@ def test_attn_f32_infinity_in_the_last_key(n, h, d, k):
 # ... and of 128 features x 128 tokens where larger ones would leave most CUs without one: edges of the tile on both sides, ragged
 # features, one tile, and contractions that end anywhere in the ring of four stages.
 @pytest.mark.parametrize("n,k,c_in,c_out,gather,scatter,bias,act", [
-    (5, 1, 512, 8, True, True, True, ab.ACT_NONE), (300, 127, 576, 136, True, False, False, ab.ACT_GELU_TANH),
-    (300, 128, 640, 128, False, True, True, ab.ACT_NONE), (300, 129, 704, 264, True, True, True, ab.ACT_NONE),
-    (700, 608, 512, 3064, True, True, True, ab.ACT_GELU_TANH), (700, 608, 12288, 3072, True, True, True, ab.ACT_NONE),
-    (1100, 1000, 3072, 3072, False, False, True, ab.ACT_NONE),
+    (5, 1, 512, 16392, True, True, True, ab.ACT_NONE), (300, 127, 576, 17000, True, False, False, ab.ACT_GELU_TANH),
+    (300, 128, 640, 17024, False, True, True, ab.ACT_NONE), (300, 129, 704, 8200, True, True, True, ab.ACT_NONE),
+    (700, 608, 512, 3400, True, True, True, ab.ACT_GELU_TANH), (700, 608, 1088, 4104, True, True, True, ab.ACT_NONE),
+    (1100, 1000, 3072, 3072, False, False, True, ab.ACT_NONE), (1100, 1001, 576, 2056, False, True, True, ab.ACT_NONE),
+    (1300, 1153, 640, 3064, True, False, True, ab.ACT_GELU_TANH), (1100, 897, 704, 2568, True, True, False, ab.ACT_NONE),
 ])
 def test_linear_bf16_small_tile(n, k, c_in, c_out, gather, scatter, bias, act):
     test_linear_bf16_tiles(n, k, c_in, c_out, gather, scatter, bias, act, 128, features=128)
@@ -878,6 +887,8 @@ def test_linear_bf16_small_tile(n, k, c_in, c_out, gather, scatter, bias, act):
 # ... and of 64 features x 64 or 128 tokens where there are not more of them than CUs: one and many steps past the ring of six stages, odd counts of
 # them, ragged rows and features, one row, a full round.
 @pytest.mark.parametrize("n,k,c_in,c_out,gather,scatter,bias,act,tokens", [
+    (300, 127, 576, 136, True, False, False, ab.ACT_GELU_TANH, 64), (300, 128, 640, 128, False, True, True, ab.ACT_NONE, 64),
+    (300, 129, 704, 264, True, True, True, ab.ACT_NONE, 64), (700, 608, 512, 3064, True, True, True, ab.ACT_GELU_TANH, 128),
     (5, 1, 512, 8, True, True, True, ab.ACT_NONE, 64), (300, 65, 576, 72, True, False, True, ab.ACT_GELU_TANH, 64),
     (300, 64, 640, 64, False, True, False, ab.ACT_NONE, 64), (800, 705, 1088, 1096, True, True, True, ab.ACT_NONE, 64),
     (800, 707, 4096, 1024, False, True, True, ab.ACT_NONE, 64), (300, 191, 704, 4600, True, True, True, ab.ACT_GELU_TANH, 64),
@@ -887,7 +898,7 @@ def test_linear_bf16_small_tile(n, k, c_in, c_out, gather, scatter, bias, act):
 def test_linear_bf16_few_rows(n, k, c_in, c_out, gather, scatter, bias, act, tokens):
     assert ab.astraea_linear_few_rows(k, c_in, c_out) == {"tile_features": 64, "tile_tokens": tokens, "tiles": -(-k // tokens) * -(-c_out // 64)}
     plan = ab.astraea_linear_plan(ab.BF16, k, c_in, c_out)
-    test_linear_bf16_tiles(n, k, c_in, c_out, gather, scatter, bias, act, plan["tile_tokens"], features=plan["tile_features"])
+    test_linear_bf16_tiles(n, k, c_in, c_out, gather, scatter, bias, act, plan["tile_tokens"], features=plan["tile_features"], few=tokens)
 
 
 # Layers of one input in one launch, against a call each: one to three parts, widths that end inside a tile of features, every tile kind
